@@ -24,6 +24,9 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 constexpr float NEG_BIG = -1.0e30f;
 constexpr int SCORE_THREADS = 256;
+// types the keys of the one-sweep kernel come in: bf16, E4M3 bytes (rows of d bytes: the 8-bit reduced cache; the queries
+// are bf16 then), fp32 (the queries too)
+constexpr int K_BF16 = 0, K_E4M3 = 1, K_F32 = 2;
 
 struct ScoreArgs {
   const void* q_win;   // [heads/H * Hq, W, d]
@@ -38,7 +41,7 @@ struct ScoreArgs {
   // one-sweep kernel: row statistics of the head's chunks as (max, sum) pairs in one 64-bit word each,
   // [heads, fsplit, mpad], all ones = not yet there; status[0] != 0 = a workgroup gave up waiting
   unsigned long long* xchg;
-  int k_fp8;              // keys are E4M3 bytes (rows of d bytes: the 8-bit reduced cache), else bf16
+  int k_kind;             // type of the keys of the one-sweep kernel: K_BF16, K_E4M3 or K_F32
   int xgroups;            // 0: every workgroup reads every chunk's words; else the number of groups of XCHG_GROUP chunks (two levels)
   long long xstride;      // exchange words per head: (fsplit + xgroups) * mpad
   int* status;         // status[0]: workgroups of one-sweep launches that gave up waiting so far (diagnostic counter,
@@ -649,9 +652,10 @@ __global__ __launch_bounds__(256) void score_xchg_init_kernel(unsigned long long
 // Row statistics of a whole head by one workgroup, without matrix cores and without anybody
 // else: wave w takes rows w, w + 4, ...; lanes stride over the keys the row sees.  Q comes from
 // the staged tile.  Leaves offs[r] = max + log2(sum) (log2 domain), +inf for padding rows.
-template <int D, bool F8 = false>
+template <int D, int KIND = K_BF16>
 __device__ __forceinline__ void score_head_stats_alone(const ScoreArgs& a, int Lh, int Mh, int rowbase, const uint16_t* kg, const uint16_t* qs, float* offs) {
-  constexpr int RS = D + 8;
+  constexpr bool F8 = KIND == K_E4M3;
+  constexpr int RS = (KIND == K_F32 ? 2 * D : D) + 8;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int r = wave; r < a.mpad; r += 4) {
     float m = NEG_BIG, l = 0.f;
@@ -659,7 +663,16 @@ __device__ __forceinline__ void score_head_stats_alone(const ScoreArgs& a, int L
       const int pos = Lh - a.W + ((rowbase + r) % a.W);
       for (int key = lane; key <= pos; key += 64) {
         float sdot = 0.f;
-        for (int c = 0; c < D / 8; ++c) {
+        if (KIND == K_F32) {
+          const f32x4_t* kr = reinterpret_cast<const f32x4_t*>(kg + (long long)key * 2 * D);
+          const f32x4_t* qr = reinterpret_cast<const f32x4_t*>(qs + r * RS);
+          for (int c = 0; c < D / 4; ++c) {
+            const f32x4_t kk = kr[c], qq = qr[c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sdot = fmaf(kk[e], qq[e], sdot);
+          }
+        }
+        for (int c = 0; c < (KIND == K_F32 ? 0 : D / 8); ++c) {
           uint4 kk;
           if (F8) {      // 8 of the row's D bytes -> 8 bf16
             const u32x2_t raw = *reinterpret_cast<const u32x2_t*>(reinterpret_cast<const unsigned char*>(kg) + (long long)key * D + c * 8);
@@ -745,7 +758,7 @@ __device__ __forceinline__ void poll_row_words(const ScoreArgs& a, const unsigne
 
 constexpr int XCHG_GROUP = 16;       // chunks per group when the exchange has two levels
 
-template <int D, bool F8 = false>
+template <int D, int KIND = K_BF16>
 __device__ __forceinline__ void collect_row_stats(const ScoreArgs& a, int head, int split, int fs, int Lh, int Mh, int rowbase,
                                                   const uint16_t* kg, const uint16_t* qs, const float* part, float* offs, float* pm, int* s_fail) {
   const int tid = threadIdx.x;
@@ -784,7 +797,7 @@ __device__ __forceinline__ void collect_row_stats(const ScoreArgs& a, int head, 
   __syncthreads();
   if (__builtin_expect(*s_fail, 0)) {         // uniform over the workgroup
     if (tid == 0) atomicAdd(a.status, 1);
-    score_head_stats_alone<D, F8>(a, Lh, Mh, rowbase, kg, qs, offs);
+    score_head_stats_alone<D, KIND>(a, Lh, Mh, rowbase, kg, qs, offs);
   } else if (tid < a.mpad) {
     float mm = NEG_BIG, ll = 0.f;
     for (int q = 0; q < nparts; ++q) merge_ml(mm, ll, pm[(q * a.mpad + tid) * 2], pm[(q * a.mpad + tid) * 2 + 1]);
@@ -792,11 +805,11 @@ __device__ __forceinline__ void collect_row_stats(const ScoreArgs& a, int head, 
   }
 }
 
-template <int D, bool F8 = false>
+template <int D, int KIND = K_BF16>
 __device__ __forceinline__ void exchange_row_stats(const ScoreArgs& a, int head, int split, int fs, int Lh, int Mh, int rowbase,
                                                    const uint16_t* kg, const uint16_t* qs, const float* part, float* offs, float* pm, int* s_fail) {
   post_row_stats(a, head, split, fs, part);
-  collect_row_stats<D, F8>(a, head, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, pm, s_fail);
+  collect_row_stats<D, KIND>(a, head, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, pm, s_fail);
 }
 
 #ifndef MADAKV_FUSED_NS1      // tuning constants of the one-sweep kernel (measured on MI355X)
@@ -808,12 +821,18 @@ __device__ __forceinline__ void exchange_row_stats(const ScoreArgs& a, int head,
 #ifndef MADAKV_FUSED_MAX_SPLIT
 #define MADAKV_FUSED_MAX_SPLIT 64   // most chunks per head the one-sweep kernel is used for
 #endif
-template <int D, int NRB, int NS, bool F8 = false>   // F8: the keys are E4M3 bytes (the 8-bit reduced cache), turned into bf16 when parked in LDS
-__global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(MADAKV_FUSED_WPE, MADAKV_FUSED_WPE))) void score_fused_kernel(ScoreArgs a) {
-  constexpr int PF = MADAKV_FUSED_PF < NS ? MADAKV_FUSED_PF : NS;
-  constexpr int KS = D / 16;                  // MFMA k-steps
-  constexpr int RS = D + 8;                   // bf16 elements per LDS row (16 B pad)
-  constexpr int PPR = D / 8;                  // 16-byte pieces per row
+// KIND: E4M3 keys are turned into bf16 when parked in LDS.  fp32 keys and queries run on the 32x32x2 fp32 MFMA (fp32
+// products and sums throughout, no conversion).  The plain FMA kernels they replace were bound by their loads (every lane
+// walked a row of its own, one uncoalesced dword at a time): one layer of 8 heads x 1024 keys x 16 rows took 117 + 124 us in
+// two sweeps, 17 us here (+ 2 us for the exchange words), most of it the latencies of one pass and the instruction stream.
+template <int D, int NRB, int NS, int KIND = K_BF16>
+__global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(KIND == K_F32 && D == 128 ? 1 : MADAKV_FUSED_WPE, KIND == K_F32 && D == 128 ? 1 : MADAKV_FUSED_WPE))) void score_fused_kernel(ScoreArgs a) {
+  constexpr bool F8 = KIND == K_E4M3, F32 = KIND == K_F32;
+  constexpr int PF = F32 && D == 128 ? 1 : (MADAKV_FUSED_PF < NS ? MADAKV_FUSED_PF : NS);   // (an fp32 subtile of 128 dims takes 64 registers)
+  constexpr int KS = D / 16;                  // MFMA k-steps (bf16)
+  constexpr int RU = F32 ? 2 * D : D;         // 2-byte units per row
+  constexpr int RS = RU + 8;                  // 2-byte units per LDS row (16 B pad)
+  constexpr int PPR = RU / 8;                 // 16-byte pieces per row
   constexpr int LPS = 32 * PPR / 64;          // 16-byte loads per lane per subtile
   constexpr int CK = 4 * NS * 32;             // keys per workgroup
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -832,7 +851,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(M
   const int Mh = min(a.M - rowbase, a.mpad);  // its rows
   const int kvh = head % a.H;
   const long long lb = head / a.H;            // (layer, batch) index
-  const uint16_t* qg = reinterpret_cast<const uint16_t*>(a.q_win) + ((lb * a.H + kvh) * (long long)a.G * a.W + rowbase) * D;
+  const uint16_t* qg = reinterpret_cast<const uint16_t*>(a.q_win) + ((lb * a.H + kvh) * (long long)a.G * a.W + rowbase) * RU;
   // keys of this head: L rows at head * L, or (ragged: the rows of a reduced cache) seg_len rows at seg_off
   const int Lh = a.seg_len ? a.seg_len[head] : a.L;
   const long long base = a.seg_off ? a.seg_off[head] : (long long)head * a.L;
@@ -842,7 +861,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(M
   const bool parked = split >= fs;            // one of the head's last chunks, run ahead of the others
   // (F8: rows of D bytes; kg then counts in 2-byte units from a byte address that is base * D)
   const uint16_t* kg = F8 ? reinterpret_cast<const uint16_t*>(reinterpret_cast<const unsigned char*>(a.k) + base * D)
-                          : reinterpret_cast<const uint16_t*>(a.k) + base * D;
+                          : reinterpret_cast<const uint16_t*>(a.k) + base * RU;
   const int chunk0 = split * CK;
   const int chunk1 = min(Lh, chunk0 + CK);
   uint16_t* kt = kt_all + (size_t)wave * 32 * RS;
@@ -868,7 +887,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(M
   for (int e = tid; e < a.mpad * PPR; e += SCORE_THREADS) {               // Q tile, padding rows zero
     const int r = e / PPR, c = e % PPR;
     uint4 val = make_uint4(0, 0, 0, 0);
-    if (r < Mh) val = *reinterpret_cast<const uint4*>(qg + (long long)r * D + c * 8);
+    if (r < Mh) val = *reinterpret_cast<const uint4*>(qg + (long long)r * RU + c * 8);
     *reinterpret_cast<uint4*>(qs + r * RS + c * 8) = val;
   }
   __syncthreads();
@@ -877,7 +896,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(M
   const int first_masked = Lh - a.W + 1;      // keys below this are visible to every proxy row
   bf16x8_t areg[KS];                           // one row block: its Q fragments stay in registers
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
+  for (int ks = 0; ks < (F32 ? 0 : KS); ++ks)
     areg[ks] = *reinterpret_cast<const bf16x8_t*>(qs + col * RS + half * (D / 2) + ks * 8);
 
   float lg[NS][NRB][16];                       // scaled logits (log2 domain); masked entries hold NEG_BIG
@@ -902,18 +921,28 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(M
     const int t0 = chunk0 + (it * 4 + wave) * 32;
     const int key = t0 + col;
     const bool tail = (t0 + 32 > first_masked) || (t0 + 32 > chunk1);     // (padding rows need no mask: their offset is +inf)
-    const uint16_t* krow = kt + col * RS + half * (D / 2);
+    const uint16_t* krow = kt + col * RS + half * (RU / 2);
     bf16x8_t bfrag[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) bfrag[ks] = *reinterpret_cast<const bf16x8_t*>(krow + ks * 8);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    for (int ks = 0; ks < (F32 ? 0 : KS); ++ks) bfrag[ks] = *reinterpret_cast<const bf16x8_t*>(krow + ks * 8);
+    if (!F32) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
 #pragma unroll
     for (int b = 0; b < NRB; ++b) {
       f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      const uint16_t* qrow = qs + (b * 32 + col) * RS + half * (D / 2);
+      const uint16_t* qrow = qs + (b * 32 + col) * RS + half * (RU / 2);
+      if (F32) {                                // step s contracts dims s and D/2 + s: a lane's operands are consecutive floats
+#pragma unroll 4
+        for (int c = 0; c < D / 8; ++c) {
+          const f32x4_t qv = *reinterpret_cast<const f32x4_t*>(qrow + c * 8), kv = *reinterpret_cast<const f32x4_t*>(krow + c * 8);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
+          for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qv[e], kv[e], acc, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int ks = 0; ks < (F32 ? 0 : KS); ++ks) {
         const bf16x8_t afrag = (NRB == 1) ? areg[ks] : *reinterpret_cast<const bf16x8_t*>(qrow + ks * 8);
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag, bfrag[ks], acc, 0, 0, 0);
       }
@@ -929,6 +958,10 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(M
           lg[it][b][j] = valid ? acc[j] * a.scale_log2 : NEG_BIG;
         }
       }
+    }
+    if (F32) {                                  // (the operands were read row block by row block: only now is the tile free)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
   }
 #undef MADAKV_FUSED_LOAD
@@ -966,7 +999,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(M
         for (int j = 0; j < 16; ++j) __builtin_nontemporal_store(lg[it][b][j], pk + ((it * NRB + b) * 16 + j) * SCORE_THREADS + tid);
     return;
   }
-  exchange_row_stats<D, F8>(a, hv, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, pm, &s_fail);
+  exchange_row_stats<D, KIND>(a, hv, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, pm, &s_fail);
   __syncthreads();
   if (a.offs_out && split == 0 && tid < a.mpad) a.offs_out[(long long)hv * a.mpad + tid] = offs[tid];
 
@@ -1407,8 +1440,11 @@ ScorePlan score_plan(const Dims& dm, int dtype) {
 // head has few enough chunks that all its workgroups are certain to be on the chip together.
 constexpr int FUSED_NS1 = MADAKV_FUSED_NS1, FUSED_NS2 = MADAKV_FUSED_NS2;
 constexpr int FUSED_MAX_SPLIT = MADAKV_FUSED_MAX_SPLIT;
-static int fused_chunk(const Dims& dm) { return 4 * 32 * ((dm.M + 31) / 32 == 1 ? FUSED_NS1 : FUSED_NS2); }
-static int fused_split(const Dims& dm) { return (dm.L + fused_chunk(dm) - 1) / fused_chunk(dm); }
+// (fp32: half the keys per workgroup, since a wave takes 4-8 times as long over a subtile; few heads spread over more of the chip)
+constexpr int FUSED_NS_F32 = 4;
+static int fused_subtiles(const Dims& dm, int dtype) { return dtype == MADAKV_FP32 ? FUSED_NS_F32 : (dm.M <= 32 ? FUSED_NS1 : FUSED_NS2); }
+static int fused_chunk(const Dims& dm, int dtype) { return 4 * 32 * fused_subtiles(dm, dtype); }
+static int fused_split(const Dims& dm, int dtype) { return (dm.L + fused_chunk(dm, dtype) - 1) / fused_chunk(dm, dtype); }
 static int fused_mpad(const Dims& dm) { return dm.M <= 32 ? 32 : 64; }
 static int fused_blocks(const Dims& dm) { return dm.M <= 64 ? 1 : (dm.M + 63) / 64; }   // blocks of 64 proxy rows handled like heads
 // exchange levels: one up to FUSED_MAX_SPLIT chunks per head, two (groups of XCHG_GROUP chunks) up to
@@ -1433,7 +1469,10 @@ static int fused_parked_chunks(int split) {
 }
 static size_t fused_park_bytes(const Dims& dm, int dtype);
 static bool fused_fits(const Dims& dm, int dtype) {
-  return use_mfma(dm, dtype) && dm.M <= 64 && fused_split(dm) <= FUSED_MAX_SPLIT_2L && dm.heads <= 65535;
+  // fp32: more than 64 proxy rows in blocks of 64 (the alternative is the plain FMA kernels); its LDS holds one or two workgroups
+  // per compute unit, so only heads of up to FUSED_MAX_SPLIT chunks (32768 keys) are certain to be on the chip as a whole
+  if (dtype == MADAKV_FP32) return fused_split(dm, dtype) <= FUSED_MAX_SPLIT && (long long)dm.heads * fused_blocks(dm) <= 65535;
+  return use_mfma(dm, dtype) && dm.M <= 64 && fused_split(dm, dtype) <= FUSED_MAX_SPLIT_2L && dm.heads <= 65535;
 }
 static bool use_fused(const Dims& dm, int dtype) {
   const char* e = getenv("MADAKV_SCORE_TWO_SWEEPS");      // diagnostic switch: the two-sweep kernels everywhere
@@ -1446,13 +1485,13 @@ static size_t rowstat_bytes(const Dims& dm, int dtype) {
   return ((size_t)dm.heads * p.nsplit * p.mpad * 2 * sizeof(float) + 255) / 256 * 256;
 }
 static size_t xchg_bytes(const Dims& dm, int dtype) {
-  const size_t per_head = (size_t)(fused_split(dm) + xchg_groups(fused_split(dm))) * fused_mpad(dm);
+  const size_t per_head = (size_t)(fused_split(dm, dtype) + xchg_groups(fused_split(dm, dtype))) * fused_mpad(dm);
   return fused_fits(dm, dtype) ? ((size_t)dm.heads * fused_blocks(dm) * per_head * 8 + 255) / 256 * 256 : 0;
 }
 static size_t fused_park_bytes(const Dims& dm, int dtype) {
   if (!fused_fits(dm, dtype)) return 0;
-  const int n = fused_parked_chunks(fused_split(dm));
-  const int ns = fused_mpad(dm) == 32 ? FUSED_NS1 : FUSED_NS2, nrb = fused_mpad(dm) / 32;
+  const int n = fused_parked_chunks(fused_split(dm, dtype));
+  const int ns = fused_subtiles(dm, dtype), nrb = fused_mpad(dm) / 32;
   // the parked logits (one float per thread and logit register) and the heads' row offsets
   return n ? ((size_t)dm.heads * n * ns * nrb * 16 * SCORE_THREADS * sizeof(float) + (size_t)dm.heads * fused_mpad(dm) * sizeof(float) + 255) / 256 * 256 : 0;
 }
@@ -1472,6 +1511,22 @@ __global__ __launch_bounds__(256) void score_blocks_sum_kernel(const float* part
   psi[i] = acc;
 }
 
+template <int D, int NRB, int NS, int KIND>
+static void launch_fused_kernel(const ScoreArgs& a, dim3 grid, hipStream_t st) {
+  constexpr int RS = (KIND == K_F32 ? 2 * D : D) + 8;
+  const size_t lds = ((size_t)a.mpad + 4 * 32) * RS * 2 + ((size_t)4 * a.mpad * 2 + a.mpad + 512) * sizeof(float);
+  if (lds > 48 * 1024)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_fused_kernel<D, NRB, NS, KIND>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((score_fused_kernel<D, NRB, NS, KIND>), grid, dim3(SCORE_THREADS), lds, st, a);
+}
+template <int D>
+static void launch_fused_by_kind(const ScoreArgs& a, dim3 grid, hipStream_t st) {
+  const bool one = a.mpad == 32;
+  if (a.k_kind == K_F32) { if (one) launch_fused_kernel<D, 1, FUSED_NS_F32, K_F32>(a, grid, st); else launch_fused_kernel<D, 2, FUSED_NS_F32, K_F32>(a, grid, st); }
+  else if (a.k_kind == K_E4M3) { if (one) launch_fused_kernel<D, 1, FUSED_NS1, K_E4M3>(a, grid, st); else launch_fused_kernel<D, 2, FUSED_NS2, K_E4M3>(a, grid, st); }
+  else { if (one) launch_fused_kernel<D, 1, FUSED_NS1, K_BF16>(a, grid, st); else launch_fused_kernel<D, 2, FUSED_NS2, K_BF16>(a, grid, st); }
+}
+
 // the one-sweep kernel over `heads` heads (each cut into a.rb_count blocks of proxy rows)
 template <int D>
 static void launch_fused(const ScoreArgs& a, int heads, hipStream_t st) {
@@ -1480,23 +1535,10 @@ static void launch_fused(const ScoreArgs& a, int heads, hipStream_t st) {
   if (a.fsplit > 1)
     hipLaunchKernelGGL(score_xchg_init_kernel, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st,
                        a.xchg + (long long)a.head0 * a.rb_count * a.xstride, nx);
-  const size_t ldsf = ((size_t)a.mpad + 4 * 32) * (D + 8) * 2 + ((size_t)4 * a.mpad * 2 + a.mpad + 512) * sizeof(float);
   ScoreArgs b = a;
   b.head0 = a.head0 * a.rb_count;
   // (a.nstrag > 0: a.fsplit counts the chunks that wait for each other; the parked ones are the first in the grid)
-  const dim3 grid(a.nstrag + a.fsplit, vheads);
-  if (a.mpad == 32) {
-    if (a.k_fp8) hipLaunchKernelGGL((score_fused_kernel<D, 1, FUSED_NS1, true>), grid, dim3(SCORE_THREADS), ldsf, st, b);
-    else hipLaunchKernelGGL((score_fused_kernel<D, 1, FUSED_NS1>), grid, dim3(SCORE_THREADS), ldsf, st, b);
-  } else if (a.k_fp8) {
-    if (ldsf > 48 * 1024)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_fused_kernel<D, 2, FUSED_NS2, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsf);
-    hipLaunchKernelGGL((score_fused_kernel<D, 2, FUSED_NS2, true>), grid, dim3(SCORE_THREADS), ldsf, st, b);
-  } else {
-    if (ldsf > 48 * 1024)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_fused_kernel<D, 2, FUSED_NS2>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsf);
-    hipLaunchKernelGGL((score_fused_kernel<D, 2, FUSED_NS2>), grid, dim3(SCORE_THREADS), ldsf, st, b);
-  }
+  launch_fused_by_kind<D>(b, dim3(a.nstrag + a.fsplit, vheads), st);
   if (a.nstrag) {
     if (a.mpad == 32) hipLaunchKernelGGL((score_fused_finish_kernel<1, FUSED_NS1>), dim3(a.nstrag, vheads), dim3(SCORE_THREADS), 0, st, b);
     else hipLaunchKernelGGL((score_fused_finish_kernel<2, FUSED_NS2>), dim3(a.nstrag, vheads), dim3(SCORE_THREADS), 0, st, b);
@@ -1562,7 +1604,7 @@ static void launch_wide_pair(const ScoreArgs& a0, int heads, hipStream_t st) {
 }
 
 // ---- the one-sweep kernel on ragged heads: the rows of a reduced cache, scored against the most recent queries
-static int ragged_split(const Dims& dm, int longest_rows) { return (std::max(longest_rows, 1) + fused_chunk(dm) - 1) / fused_chunk(dm); }
+static int ragged_split(const Dims& dm, int longest_rows) { const int ck = fused_chunk(dm, MADAKV_BF16); return (std::max(longest_rows, 1) + ck - 1) / ck; }
 bool score_ragged_supported(const Dims& dm, const madakv_config& c, int longest_rows) {
   return use_mfma(dm, c.dtype) && dm.M <= 256 && ragged_split(dm, longest_rows) <= FUSED_MAX_SPLIT &&
          (long long)dm.heads * fused_blocks(dm) <= 65535;
@@ -1588,7 +1630,7 @@ hipError_t launch_score_ragged(const Dims& dm, const madakv_config& c, const voi
   a.mpad = fused_mpad(dm); a.nsplit = 0; a.nmerge = 0; a.chunk = 0; a.head0 = 0;
   a.fsplit = ragged_split(dm, longest_rows);
   a.xgroups = 0; a.xstride = (long long)a.fsplit * fused_mpad(dm);
-  a.k_fp8 = c.cache_fp8 ? 1 : 0;                  // the reduced cache is what is scored here
+  a.k_kind = c.cache_fp8 ? K_E4M3 : K_BF16;       // the reduced cache is what is scored here
   const char* spin = getenv("MADAKV_SCORE_SPIN_LIMIT");
   a.spin_limit = spin && atoi(spin) > 0 ? atoi(spin) : FUSED_SPIN_LIMIT;
   const float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)dm.d);
@@ -1605,19 +1647,8 @@ hipError_t launch_score_ragged(const Dims& dm, const madakv_config& c, const voi
     const int vheads = dm.heads * a.rb_count;
     const long long nx = (long long)vheads * a.fsplit * a.mpad;
     if (a.fsplit > 1) hipLaunchKernelGGL(score_xchg_init_kernel, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st, a.xchg, nx);
-    const size_t ldsf = ((size_t)a.mpad + 4 * 32) * (dm.d + 8) * 2 + ((size_t)4 * a.mpad * 2 + a.mpad + 512) * sizeof(float);
     const dim3 grid(a.fsplit, vheads);
-    if (dm.d == 128 && a.k_fp8) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_fused_kernel<128, 2, FUSED_NS2, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsf);
-      hipLaunchKernelGGL((score_fused_kernel<128, 2, FUSED_NS2, true>), grid, dim3(SCORE_THREADS), ldsf, st, b);
-    } else if (dm.d == 128) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_fused_kernel<128, 2, FUSED_NS2>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsf);
-      hipLaunchKernelGGL((score_fused_kernel<128, 2, FUSED_NS2>), grid, dim3(SCORE_THREADS), ldsf, st, b);
-    } else if (a.k_fp8) {
-      hipLaunchKernelGGL((score_fused_kernel<64, 2, FUSED_NS2, true>), grid, dim3(SCORE_THREADS), ldsf, st, b);
-    } else {
-      hipLaunchKernelGGL((score_fused_kernel<64, 2, FUSED_NS2>), grid, dim3(SCORE_THREADS), ldsf, st, b);
-    }
+    if (dm.d == 128) launch_fused_by_kind<128>(b, grid, st); else launch_fused_by_kind<64>(b, grid, st);
     hipLaunchKernelGGL(score_blocks_sum_kernel, dim3((unsigned)((cache_rows + 255) / 256)), dim3(256), 0, st,
                        a.psi_part, a.psi_part_stride, a.rb_count, psi_c, cache_rows);
   }
@@ -1655,7 +1686,7 @@ hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void
   a.psi_part = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + win_xchg_bytes(dm) + win_opart_bytes(dm));
   a.psi_part_stride = (long long)dm.heads * dm.L;
   a.fsplit = win_split(dm);
-  a.xgroups = xchg_groups(a.fsplit); a.xstride = (long long)(a.fsplit + a.xgroups) * 32; a.k_fp8 = 0;   // (two exchange levels above 64 chunks)
+  a.xgroups = xchg_groups(a.fsplit); a.xstride = (long long)(a.fsplit + a.xgroups) * 32; a.k_kind = K_BF16;   // (two exchange levels above 64 chunks)
   const char* spin = getenv("MADAKV_SCORE_SPIN_LIMIT");
   a.spin_limit = spin && atoi(spin) > 0 ? atoi(spin) : FUSED_SPIN_LIMIT;
   const float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)dm.d);
@@ -1693,11 +1724,12 @@ hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_wi
   a.rb_count = fused_blocks(dm);
   a.psi_part = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype) + 256 + xchg_bytes(dm, c.dtype));
   a.psi_part_stride = (long long)dm.heads * dm.L;
-  a.fsplit = (!row_lse && use_fused(dm, c.dtype)) ? fused_split(dm) : 0;
+  a.fsplit = (!row_lse && use_fused(dm, c.dtype)) ? fused_split(dm, c.dtype) : 0;
   a.nstrag = a.fsplit ? fused_parked_chunks(a.fsplit) : 0;
   if (getenv("MADAKV_SCORE_NO_PARKED_CHUNKS")) a.nstrag = 0;                      // (measurement switch)
   a.fsplit -= a.nstrag;                                                            // the chunks of the main launch
-  a.xgroups = xchg_groups(a.fsplit) + a.nstrag; a.xstride = (long long)(a.fsplit + a.xgroups) * fused_mpad(dm); a.k_fp8 = 0;
+  a.xgroups = xchg_groups(a.fsplit) + a.nstrag; a.xstride = (long long)(a.fsplit + a.xgroups) * fused_mpad(dm);
+  a.k_kind = c.dtype == MADAKV_FP32 ? K_F32 : K_BF16;
   {
     char* pk = static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype) + 256 + xchg_bytes(dm, c.dtype) +
                (fused_fits(dm, c.dtype) && fused_blocks(dm) > 1 ? (size_t)fused_blocks(dm) * dm.heads * dm.L * sizeof(float) : 0);
