@@ -37,10 +37,10 @@ long long init_limit_of(const madakv_config& c);
 int page_table_entries(const madakv_config& c);
 
 struct ScorePlan { int nsplit; int chunk; int mpad; int group_heads; };
-struct DecodePlan { int chunk_rows; int max_chunks; };
+struct DecodePlan { int chunk_rows; int max_chunks; int grid_chunks; };   // rows per piece of a head, most pieces of a head, pieces in the grid
 
 ScorePlan score_plan(const Dims& dm, int dtype);
-DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows);
+DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows, size_t ws_bytes);
 size_t score_ws_bytes(const Dims& dm, int dtype);
 size_t select_ws_bytes(const Dims& dm, const madakv_config& c);
 size_t decode_ws_bytes(const Dims& dm, const madakv_config& c);                             // worst case over head lengths
@@ -93,7 +93,7 @@ hipError_t launch_gather(const Dims& dm, const madakv_config& c, int li0, int nl
                          int blocks_per_batch, int grid_blocks, hipStream_t st, bool leave_room = false);
 hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, const void* k_new,
                          const void* v_new, void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
-                         void* out, void* ws, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st);
+                         void* out, void* ws, size_t ws_bytes, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st);
 
 constexpr int GATHER_ROWS = 64;   // rows of the reduced cache one gather workgroup fills
 

@@ -7,10 +7,10 @@
 // instruction and keeps UNROLL K rows and UNROLL V rows in flight.  The dot product is
 // reduced over the LPR lanes of a row with DPP row operations, the softmax is the usual
 // running max / running sum in the log2 domain with fp32 accumulation.  Each head's rows
-// are cut into chunks of `chunk_rows` (one workgroup each): a single layer's 128 ragged heads
-// become ~2000 equal pieces of work that the hardware scheduler spreads over 256 CUs.  The
-// grid is (heads, longest possible head / chunk_rows): workgroups past a head's real length
-// exit at once, and since the chunk index is the slow grid dimension they are dispatched
+// are cut into pieces of `chunk_rows` (one workgroup each): a single layer's 128 ragged heads
+// become ~1100 pieces of work that the hardware scheduler spreads over 256 CUs.  The
+// grid is (heads, pieces of the longest head, at most twice an average head's): workgroups past a head's real
+// length exit at once, and since the piece index is the slow grid dimension they are dispatched
 // after all the real work.  A second, small kernel merges the partial (max, sum, acc) triples
 // of each head in chunk order.  (Merging inside the first kernel by the last workgroup to
 // arrive was measured three times and lost every time: with device-scope fences, which write back and
@@ -27,11 +27,17 @@
 // against 26.9 us for the attention part on 128 heads of ~2K rows, the table of head starts
 // every workgroup has to build first costs what the balance gains.)
 // The appended row is taken from k_new / v_new by the
-// workgroup whose chunk holds it, which also stores it in the cache; kv_len is bumped by
+// workgroup whose piece holds it, which also stores it in the cache; kv_len is bumped by
 // whoever finalises the head.
+//
+// Measured per layer call, attention + merge (attention alone), before -> after the load path was made small and
+// branch-free (instructions are cold at every launch) and four rows instead of eight kept in flight per lane: 128 heads of
+// ~2K bf16 rows, 135 MB, 28.0 -> 26.9 us (23.6: 5.7 TB/s), 8-bit rows 19.0 -> 17.6 (14.5), 32 heads of 4K paged rows,
+// 67 MB, 21.0 -> 15.0 (11.8: 5.7 TB/s), 4 heads of 2K rows with 7 queries each 16.8 -> 10.4 (6.3, latency).
 #include "common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace madakv {
 
@@ -41,7 +47,9 @@ constexpr int DEC_THREADS = 256;
 struct DecodeArgs {
   const void* q; const void* k_new; const void* v_new; void* k_c; void* v_c;
   const int64_t* kv_off; int32_t* kv_len; void* out; float* part;
-  int B, H, G, d, chunk_rows, max_chunks, out_fp32, has_new;
+  int B, H, G, d, chunk_rows, out_fp32, has_new;
+  int max_chunks;       // most pieces a head is cut into (head_chunk_rows): partial results per head in `part`
+  float* part_ml;       // [heads][max_chunks][G][2] (max, sum) of the partial results, behind part = [heads][max_chunks][G][d]
   long long capacity;   // rows in k_c / v_c
   // paged cache (page_rows > 0): see struct Paging
   int page_rows, page_shift, tbl_entries;
@@ -112,20 +120,6 @@ __device__ __forceinline__ void load_floats(const T* p, float* f) {
 #pragma unroll
   for (int j = 0; j < EPL / PER; ++j) Elems<T>::unpack(*reinterpret_cast<const uint4*>(p + j * PER), f + j * PER);
 }
-// 16 bytes of a reduced-cache row made from the caller's new row: a plain copy when the cache
-// has the caller's type, an E4M3 encoding of 16 bf16 values otherwise
-template <typename T, typename CT>
-__device__ __forceinline__ uint4 cache_piece(const T* p) {
-  if (sizeof(T) == sizeof(CT)) return *reinterpret_cast<const uint4*>(p);
-  float f[16];
-  load_floats<T, 16>(p, f);
-  uint32_t w[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    w[i] = f32_to_e4m3(f[i * 4]) | (f32_to_e4m3(f[i * 4 + 1]) << 8) | (f32_to_e4m3(f[i * 4 + 2]) << 16) | (f32_to_e4m3(f[i * 4 + 3]) << 24);
-  return make_uint4(w[0], w[1], w[2], w[3]);
-}
-
 template <typename T>
 __device__ __forceinline__ void store_out(void* out, int out_fp32, long long o, float val) {
   if (out_fp32 || sizeof(T) == 4) reinterpret_cast<float*>(out)[o] = val;
@@ -158,11 +152,12 @@ __device__ __forceinline__ bool can_append_to(const DecodeArgs& a, long long off
 
 // All threads of the workgroup.  rows [r_begin, r_end) are the workgroup's; when the appended row is
 // among them and starts a new page, thread 0 takes the next page from the top of the batch item's region.
+template <bool PAGED>
 __device__ __forceinline__ RowMap make_row_map(const DecodeArgs& a, long long hidx, long long off, int len_old, bool can_append,
                                                int r_begin, int r_end) {
   RowMap m;
   m.off = off; m.init_rows = 0x7fffffff; m.tbl = nullptr; m.shift = 0; m.fresh_slot = -1; m.fresh_page = 0;
-  if (!a.page_rows) return m;
+  if (!PAGED) return m;
   __shared__ long long s_fresh;
   int32_t* tbl = a.page_tbl + (a.head0 + hidx) * a.tbl_entries;
   m.tbl = tbl; m.shift = a.page_shift;
@@ -184,118 +179,190 @@ __device__ __forceinline__ RowMap make_row_map(const DecodeArgs& a, long long hi
   return m;
 }
 
-template <typename T, typename CT, int LPR, int GT, int UNROLL, int NW>   // T: Q / new rows / out; CT: cache elements
+// Rows per piece of a head of `len` rows: a.chunk_rows, or for a head that would need more than max_chunks pieces a
+// larger multiple of 32.  The grid then depends on the budget alone and not on the longest head a layer may have.  The
+// host learns that length only once the eviction has run; sizing the grid for the whole context until then put 65
+// instead of 17 workgroups per head in the grid (16K context, budget 2048), 5 of 36 us per layer call for
+// workgroups that found nothing to do.
+__device__ __forceinline__ int head_chunk_rows(const DecodeArgs& a, int len) {
+  if (len <= a.chunk_rows * a.max_chunks) return a.chunk_rows;
+  return ((len + a.max_chunks - 1) / a.max_chunks + 31) / 32 * 32;
+}
+
+// The head a workgroup works on.  Workgroups go to the 8 XCDs in turn; with the head as the fast grid dimension all
+// pieces of a head would meet on one XCD (128 heads), and XCDs with long heads would finish last: the pieces of a head
+// are rotated over the XCDs instead.
+__device__ __forceinline__ int piece_head() {
+  const int x = (int)blockIdx.x + (int)blockIdx.y;
+  return x < (int)gridDim.x ? x : x % (int)gridDim.x;
+}
+
+// The appended row in the cache's element type: written to the cache (Eq. 4) and left in LDS, K then V, for the tile it
+// belongs to.  All threads; `row` is its place in the cache.  (Kept out of the load path of the tiles: the encoding of
+// an 8-bit row, unrolled there, had made 48 KB of the grouped-query kernel.  Fetching a thread's element before the
+// head's length is known gains nothing: 27.7 against 27.4 us per call, in every workgroup for the sake of one per head.)
+template <typename T, typename CT, int D>
+__device__ __forceinline__ void stage_new_row(const DecodeArgs& a, long long hidx, long long row, CT* s_new) {
+  for (int e = threadIdx.x; e < 2 * D; e += (int)blockDim.x) {
+    const bool is_k = e < D;
+    const int c = is_k ? e : e - D;
+    const T x = (reinterpret_cast<const T*>(is_k ? a.k_new : a.v_new))[hidx * D + c];
+    CT y;
+    if constexpr (sizeof(T) == sizeof(CT)) y = __builtin_bit_cast(CT, x);
+    else y = (CT)f32_to_e4m3(bf16_bits_to_f32(x));
+    (reinterpret_cast<CT*>(is_k ? a.k_c : a.v_c))[row * D + c] = y;
+    s_new[e] = y;
+  }
+  __syncthreads();
+}
+
+// The NW waves' (max, sum, acc) of a piece merged in wave order: the output if the head is this one piece, a partial
+// result otherwise.  The threads share the group's query heads and elements.
+template <typename T, int D, int NW, int GT>
+__device__ __forceinline__ void finish_piece(const DecodeArgs& a, long long hidx, int chunk, bool whole, const float (*s_ml)[GT][2],
+                                             const float (*s_acc)[GT][D]) {
+  const int t = threadIdx.x % D;
+#pragma unroll 1
+  for (int g = threadIdx.x / D; g < a.G; g += NW * 64 / D) {
+    float mx = DNEG_BIG;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mx = fmaxf(mx, s_ml[w][g][0]);
+    float ls = 0.f, av = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float c = exp2f(s_ml[w][g][0] - mx);
+      ls += s_ml[w][g][1] * c;
+      av += s_acc[w][g][t] * c;
+    }
+    if (whole) {
+      store_out<T>(a.out, a.out_fp32, (hidx * a.G + g) * D + t, av / ls);
+    } else {
+      const long long p = (hidx * a.max_chunks + chunk) * a.G + g;
+      a.part[p * D + t] = av;
+      if (t == 0) *reinterpret_cast<float2*>(a.part_ml + p * 2) = make_float2(mx, ls);
+    }
+  }
+}
+
+template <typename T, typename CT, int LPR, int GT, int UNROLL, int NW, bool PAGED>   // T: Q / new rows / out; CT: cache elements
 __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
   constexpr int EPL = Elems<CT>::EPL;
   constexpr int RPI = 64 / LPR;
   constexpr int D = LPR * EPL;
   __shared__ float s_ml[NW][GT][2];
   __shared__ float s_acc[NW][GT][D];
+  __shared__ __attribute__((aligned(16))) CT s_new[2 * D];
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane / LPR, piece = lane % LPR;
-  const long long hidx = blockIdx.x;                 // (layer, batch, kv head) of the call
-  const int chunk = blockIdx.y;                      // which `chunk_rows` rows of the head
+  const long long hidx = piece_head();               // (layer, batch, kv head) of the call
+  const int chunk = blockIdx.y;                      // which piece of the head
   const int len_old = a.kv_len[hidx];
   const long long off = a.kv_off[hidx];
-  // an empty segment (its budgets did not fit the cache) stays empty: no append, output 0/0 = NaN
-  const bool can_append = can_append_to(a, off, len_old);
-  const int len = len_old + (can_append ? 1 : 0);
-  const int nch = max(1, (len + a.chunk_rows - 1) / a.chunk_rows);
-  if (chunk >= nch) return;                          // the grid is sized for the longest possible head
-  const long long lb = hidx / a.H;
-  const int h = (int)(hidx % a.H);
-  const int r_begin = chunk * a.chunk_rows;
-  const int r_end = min(len, r_begin + a.chunk_rows);
-  const RowMap at = make_row_map(a, hidx, off, len_old, can_append, r_begin, r_end);
-  // the NW waves take turns on consecutive RPI * UNROLL-row slices, so that at any moment the
-  // workgroup reads one contiguous stretch of K and one of V
-  constexpr int WSTEP = RPI * UNROLL;
-
-  // queries of the group, pre-multiplied by scale * log2(e)
+  // queries of the group (on their way while the length is), pre-multiplied by scale * log2(e) below
   float qf[GT][EPL];
-  const T* qg = reinterpret_cast<const T*>(a.q) + (lb * a.H + h) * (long long)a.G * D;
+  const T* qg = reinterpret_cast<const T*>(a.q) + hidx * a.G * D;
 #pragma unroll
   for (int g = 0; g < GT; ++g) {
 #pragma unroll
     for (int e = 0; e < EPL; ++e) qf[g][e] = 0.f;
     if (g < a.G) load_floats<T, EPL>(qg + (long long)g * D + piece * EPL, qf[g]);
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) qf[g][e] *= a.scale_log2;
   }
+  // an empty segment (its budgets did not fit the cache) stays empty: no append, output 0/0 = NaN
+  const bool can_append = can_append_to(a, off, len_old);
+  const int len = len_old + (can_append ? 1 : 0);
+  const int rows = head_chunk_rows(a, len);
+  const int r_begin = chunk * rows;
+  if (chunk > 0 && r_begin >= len) return;           // the grid is sized for the longest head
+  const int r_end = min(len, r_begin + rows);
+  const RowMap at = make_row_map<PAGED>(a, hidx, off, len_old, can_append, r_begin, r_end);
+  const bool has_fresh = can_append && len_old >= r_begin && len_old < r_end;   // uniform: the appended row is in this piece
+  if (has_fresh) stage_new_row<T, CT, D>(a, hidx, at(len_old), s_new);
+  // the NW waves take turns on consecutive RPI * UNROLL-row slices, so that at any moment the
+  // workgroup reads one contiguous stretch of K and one of V
+  constexpr int WSTEP = RPI * UNROLL;
 
   float m[GT], l[GT], acc[GT][EPL];
 #pragma unroll
   for (int g = 0; g < GT; ++g) {
     m[g] = DNEG_BIG; l[g] = 0.f;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
+    for (int e = 0; e < EPL; ++e) { acc[g][e] = 0.f; qf[g][e] *= a.scale_log2; }
   }
 
-  const uint4* kc = reinterpret_cast<const uint4*>(a.k_c);
-  const uint4* vc = reinterpret_cast<const uint4*>(a.v_c);
-  const T* kn = reinterpret_cast<const T*>(a.k_new);
-  const T* vn = reinterpret_cast<const T*>(a.v_new);
+  const unsigned char* kc = reinterpret_cast<const unsigned char*>(a.k_c) + (PAGED ? 0 : off * (LPR * 16));
+  const unsigned char* vc = reinterpret_cast<const unsigned char*>(a.v_c) + (PAGED ? 0 : off * (LPR * 16));
 
   for (int row0 = r_begin + wave * WSTEP; row0 < r_end; row0 += NW * WSTEP) {
     uint4 kraw[UNROLL], vraw[UNROLL];
-    bool valid[UNROLL];
+    // rows past the end: the last row once more, masked below (no branch in the loads; a row is at most 2^20 * 512 bytes away)
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      const int r = row0 + u * RPI + sub;
-      valid[u] = r < r_end;
-      kraw[u] = make_uint4(0, 0, 0, 0); vraw[u] = make_uint4(0, 0, 0, 0);
-      if (valid[u]) {
-        if (can_append && r == len_old) {
-          kraw[u] = cache_piece<T, CT>(kn + hidx * D + piece * EPL);
-          vraw[u] = cache_piece<T, CT>(vn + hidx * D + piece * EPL);
-          reinterpret_cast<uint4*>(a.k_c)[at(r) * LPR + piece] = kraw[u];     // Eq. 4: the row joins the cache
-          reinterpret_cast<uint4*>(a.v_c)[at(r) * LPR + piece] = vraw[u];
-        } else {
-          kraw[u] = stream_load16(kc + at(r) * LPR + piece);
-          vraw[u] = stream_load16(vc + at(r) * LPR + piece);
-        }
+      const int r = min(row0 + u * RPI + sub, r_end - 1);
+      if (PAGED) {
+        const long long o = (at(r) * LPR + piece) * 16;
+        kraw[u] = stream_load16(kc + o); vraw[u] = stream_load16(vc + o);
+      } else {
+        const uint32_t o = (uint32_t)(r * LPR + piece) * 16u;
+        kraw[u] = stream_load16(kc + o); vraw[u] = stream_load16(vc + o);
       }
+    }
+    if (has_fresh && row0 <= len_old && len_old < row0 + WSTEP) {        // the appended row comes from LDS
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u)
+        if (row0 + u * RPI + sub >= len_old) {                              // (rows past it are masked)
+          kraw[u] = *reinterpret_cast<const uint4*>(s_new + piece * EPL);
+          vraw[u] = *reinterpret_cast<const uint4*>(s_new + D + piece * EPL);
+        }
+    }
+    if (row0 + WSTEP > r_end) {                                             // what is masked contributes 0 * 0
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u)
+        if (row0 + u * RPI + sub >= r_end) vraw[u] = make_uint4(0, 0, 0, 0);
     }
     float s[UNROLL][GT];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       float kf[EPL];
       Elems<CT>::unpack(kraw[u], kf);
+      const bool valid = row0 + u * RPI + sub < r_end;
 #pragma unroll
       for (int g = 0; g < GT; ++g) {
         float dot = 0.f;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) dot = fmaf(qf[g][e], kf[e], dot);
-        s[u][g] = row_sum<LPR>(dot);
+        dot = row_sum<LPR>(dot);
+        s[u][g] = valid ? dot : 2.f * DNEG_BIG;                            // below every running maximum: exp2 gives 0
       }
     }
-    float vf[UNROLL][EPL];
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) Elems<CT>::unpack(vraw[u], vf[u]);
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
       float mx = m[g];
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) mx = valid[u] ? fmaxf(mx, s[u][g]) : mx;
+      for (int u = 0; u < UNROLL; ++u) mx = fmaxf(mx, s[u][g]);
       const float sc = exp2f(m[g] - mx);
       l[g] *= sc;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) acc[g][e] *= sc;
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        const float p = valid[u] ? exp2f(s[u][g] - mx) : 0.f;
-        l[g] += p;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(p, vf[u][e], acc[g][e]);
-      }
+      for (int u = 0; u < UNROLL; ++u) { s[u][g] = exp2f(s[u][g] - mx); l[g] += s[u][g]; }
       m[g] = mx;
+    }
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      float vf[EPL];
+      Elems<CT>::unpack(vraw[u], vf);
+#pragma unroll
+      for (int g = 0; g < GT; ++g)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(s[u][g], vf[e], acc[g][e]);
     }
   }
 
   // merge the RPI row groups of the wave (fixed butterfly), then the NW waves through LDS
 #pragma unroll
   for (int g = 0; g < GT; ++g) {
+#pragma unroll
     for (int o = LPR; o < 64; o <<= 1) {
       const float m2 = __shfl_xor(m[g], o, 64), l2 = __shfl_xor(l[g], o, 64);
       const float mx = fmaxf(m[g], m2);
@@ -315,29 +382,8 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
     }
   }
   __syncthreads();
-  // thread t < D finishes element t of every query head of the group
-  const int t = threadIdx.x;
-  const long long obase = (lb * a.H + h) * (long long)a.G * D;
-  if (t < D) {
-    for (int g = 0; g < a.G; ++g) {
-      float mx = DNEG_BIG;
-      for (int w = 0; w < NW; ++w) mx = fmaxf(mx, s_ml[w][g][0]);
-      float ls = 0.f, av = 0.f;
-      for (int w = 0; w < NW; ++w) {
-        const float c = exp2f(s_ml[w][g][0] - mx);
-        ls += s_ml[w][g][1] * c;
-        av += s_acc[w][g][t] * c;
-      }
-      if (nch == 1) {
-        store_out<T>(a.out, a.out_fp32, obase + (long long)g * D + t, av / ls);
-      } else {
-        float* p = a.part + ((hidx * a.max_chunks + chunk) * a.G + g) * (long long)(D + 2);
-        p[t] = av;
-        if (t == 0) { p[D] = mx; p[D + 1] = ls; }
-      }
-    }
-  }
-  // kv_len is read by every chunk of the head: with several chunks per head only the merge
+  finish_piece<T, D, NW, GT>(a, hidx, chunk, len <= rows, s_ml, s_acc);
+  // kv_len is read by every workgroup of the head: with several per head only the merge
   // kernel, which runs after all of them, may store the new length
   if (a.max_chunks == 1 && can_append && threadIdx.x == 0) a.kv_len[hidx] = len;
 }
@@ -351,18 +397,25 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
 //                                  16-key block for its query; the contraction index is numbered
 //                                  so that exactly those 8 keys are the lane's A fragment of P
 //                                  (no cross-lane movement); V needs the matching rows per output
-//                                  column, read as 2-byte elements from a wave-private LDS tile
-//                                  that the V rows were written to with coalesced 16-byte loads.
+//                                  column: transposing LDS reads (four rows of 16 columns per 16
+//                                  lanes) of a wave-private LDS tile that the V rows were written to
+//                                  with coalesced 16-byte loads.
 // P goes through the MFMA as bf16 hi + lo parts (two MFMAs), which keeps fp32-level accuracy.
 // The running max / sum live per query in the lanes of S^T; the rescale factors are fetched
 // into the O layout with four lane reads per tile.
+// A layer of a grouped-query model has few KV heads and a few MB of cache: the kernel is bound by the latencies of
+// one workgroup (start, length, rows, two contractions, merge), among them the fetching of its instructions, which are
+// cold at every launch.  So a wave has one tile in the usual piece of 128 rows, the load path appears once and the
+// appended row comes in through LDS.
 // ------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 dbf16x8_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 dbf16x2_t;
 typedef __attribute__((ext_vector_type(4))) float df32x4_t;
 typedef __attribute__((ext_vector_type(4))) unsigned int du32x4_t;
-
 typedef __attribute__((ext_vector_type(2))) unsigned int du32x2_t;
 typedef __attribute__((ext_vector_type(2))) float df32x2_t;
+typedef __attribute__((ext_vector_type(4))) short ds16x4_t;
+typedef __attribute__((address_space(3))) ds16x4_t* lds_s16x4_ptr_t;
 
 // 4 E4M3 bytes -> 4 bf16 (exact: 3 mantissa bits fit bf16's 7), as two packed dwords
 __device__ __forceinline__ du32x2_t e4m3x4_to_bf16x4(uint32_t w) {
@@ -372,23 +425,15 @@ __device__ __forceinline__ du32x2_t e4m3x4_to_bf16x4(uint32_t w) {
   o[1] = (__float_as_uint(b[0]) >> 16) | (__float_as_uint(b[1]) & 0xffff0000u);
   return o;
 }
-// 8 bf16 (16 bytes) -> 8 E4M3 bytes
-__device__ __forceinline__ du32x2_t bf16x8_to_e4m3x8(const du32x4_t& r) {
-  du32x2_t o;
-#pragma unroll
-  for (int w = 0; w < 2; ++w)
-    o[w] = f32_to_e4m3(bf16_lo(r[w * 2])) | (f32_to_e4m3(bf16_hi(r[w * 2])) << 8) |
-           (f32_to_e4m3(bf16_lo(r[w * 2 + 1])) << 16) | (f32_to_e4m3(bf16_hi(r[w * 2 + 1])) << 24);
-  return o;
-}
 
-template <int D, bool FP8>   // FP8: the cache rows are E4M3 bytes, turned into bf16 operands on the fly
+template <int D, bool FP8, bool PAGED>   // FP8: the cache rows are E4M3 bytes, turned into bf16 operands on the fly
 __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
+  using CT = typename std::conditional<FP8, uint8_t, uint16_t>::type;
   constexpr int GT = 8;                // query heads per KV head supported (rows 8..15 of the MFMA tile are padding)
   constexpr int NW = 4;
   constexpr int KS = D / 32;           // MFMA steps over the head dimension
   constexpr int DB = D / 16;           // 16-column blocks of the output
-  constexpr int RS = D + 8;            // bf16 elements per LDS row of the V tile (16 B pad)
+  constexpr int RS = D + 16;           // bf16 elements per LDS row of the V tile (rows 8 banks apart: the transposing reads of a wave do not collide)
   constexpr int CB = FP8 ? 1 : 2;      // bytes per cache element
   constexpr int LPR = D * CB / 16;     // lanes per row in a coalesced 16-byte load
   constexpr int VE = 16 / CB;          // V elements per lane and load
@@ -396,42 +441,38 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
   constexpr int VL = 32 / RPI;         // load instructions per 32-row V tile
   __shared__ float s_ml[NW][GT][2];
   __shared__ __attribute__((aligned(16))) uint16_t s_v[NW][32][RS];
+  __shared__ __attribute__((aligned(16))) CT s_new[2 * D];
   // the per-wave results reuse the V tiles once every wave is through with them
   static_assert(sizeof(float) * NW * GT * D <= sizeof(uint16_t) * NW * 32 * RS, "results must fit the V tiles");
   float (*s_acc)[GT][D] = reinterpret_cast<float (*)[GT][D]>(&s_v[0][0][0]);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j16 = lane & 15, c = lane >> 4;
-  const long long hidx = blockIdx.x;
+  const long long hidx = piece_head();
   const int chunk = blockIdx.y;
   const int len_old = a.kv_len[hidx];
   const long long off = a.kv_off[hidx];
-  const bool can_append = can_append_to(a, off, len_old);
-  const int len = len_old + (can_append ? 1 : 0);
-  const int nch = max(1, (len + a.chunk_rows - 1) / a.chunk_rows);
-  if (chunk >= nch) return;
-  const long long lb = hidx / a.H;
-  const int h = (int)(hidx % a.H);
-  const int r_begin = chunk * a.chunk_rows;
-  const int r_end = min(len, r_begin + a.chunk_rows);
-  const RowMap at = make_row_map(a, hidx, off, len_old, can_append, r_begin, r_end);
-
-  const unsigned char* kc = reinterpret_cast<const unsigned char*>(a.k_c);   // cache rows of D * CB bytes
-  const unsigned char* vc = reinterpret_cast<const unsigned char*>(a.v_c);
-  const uint16_t* kn = reinterpret_cast<const uint16_t*>(a.k_new);
-  const uint16_t* vn = reinterpret_cast<const uint16_t*>(a.v_new);
-  unsigned char* kcw = reinterpret_cast<unsigned char*>(a.k_c);
-  unsigned char* vcw = reinterpret_cast<unsigned char*>(a.v_c);
-
   // Q as the B operand: lane (q = j16, c) holds dims [32 ks + 8 c, +8) of query q
   dbf16x8_t qb[KS];
-  const uint16_t* qg = reinterpret_cast<const uint16_t*>(a.q) + (lb * a.H + h) * (long long)a.G * D;
+  const uint16_t* qg = reinterpret_cast<const uint16_t*>(a.q) + hidx * a.G * D;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     du32x4_t raw = {0u, 0u, 0u, 0u};
     if (j16 < a.G) raw = *reinterpret_cast<const du32x4_t*>(qg + (long long)j16 * D + ks * 32 + c * 8);
     qb[ks] = __builtin_bit_cast(dbf16x8_t, raw);
   }
+  const bool can_append = can_append_to(a, off, len_old);
+  const int len = len_old + (can_append ? 1 : 0);
+  const int rows = head_chunk_rows(a, len);
+  const int r_begin = chunk * rows;
+  if (chunk > 0 && r_begin >= len) return;
+  const int r_end = min(len, r_begin + rows);
+  const RowMap at = make_row_map<PAGED>(a, hidx, off, len_old, can_append, r_begin, r_end);
+  const bool has_fresh = can_append && len_old >= r_begin && len_old < r_end;   // uniform: the appended row is in this piece
+  if (has_fresh) stage_new_row<uint16_t, CT, D>(a, hidx, at(len_old), s_new);
+
+  const unsigned char* kc = reinterpret_cast<const unsigned char*>(a.k_c) + (PAGED ? 0 : off * (D * CB));   // cache rows of D * CB bytes
+  const unsigned char* vc = reinterpret_cast<const unsigned char*>(a.v_c) + (PAGED ? 0 : off * (D * CB));
 
   float m_run = DNEG_BIG, l_run = 0.f;       // for query j16 (every lane group c holds a copy of m, a share of l)
   df32x4_t oacc[DB];                         // O[q = 4c + r][d = 16 db + j16]
@@ -440,61 +481,63 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
   uint16_t* vt = &s_v[wave][0][0];
   const int vsub = lane / LPR, vpiece = lane % LPR;
 
-  // Registers hold the K fragments and V rows of the tile being worked on; each set is refilled
-  // with the next tile's data as soon as it has been consumed (V: once parked in LDS, K: after
-  // the S^T MFMAs), so the loads fly under the softmax and the P.V MFMAs.  Rows past the end of
-  // the chunk are clamped to its last row (valid memory) and masked where they are used.
-  du32x4_t kraw[2][KS], vraw[VL];            // raw cache bytes (E4M3: 8 bytes of a K piece sit in kraw[..][..].xy)
-#define MADAKV_LOAD_V(T0)                                                                          \
-  _Pragma("unroll") for (int i = 0; i < VL; ++i) {                                                 \
-    const int r = (T0) + i * RPI + vsub;                                                           \
-    const int rc = min(r, r_end - 1);                                                              \
-    const bool fresh = can_append && rc == len_old;                                                \
-    if (!fresh) {                                                                                  \
-      vraw[i] = __builtin_nontemporal_load(reinterpret_cast<const du32x4_t*>(vc + (at(rc) * D + vpiece * VE) * CB)); \
-    } else {                                                                                       \
-      const uint16_t* np_ = vn + hidx * D + vpiece * VE;                                           \
-      if (FP8) {                                                                                   \
-        const du32x2_t e0 = bf16x8_to_e4m3x8(*reinterpret_cast<const du32x4_t*>(np_));             \
-        const du32x2_t e1 = bf16x8_to_e4m3x8(*reinterpret_cast<const du32x4_t*>(np_ + 8));         \
-        vraw[i] = du32x4_t{e0[0], e0[1], e1[0], e1[1]};                                            \
-      } else {                                                                                     \
-        vraw[i] = *reinterpret_cast<const du32x4_t*>(np_);                                         \
-      }                                                                                            \
-      if (r == rc) *reinterpret_cast<du32x4_t*>(vcw + (at(rc) * D + vpiece * VE) * CB) = vraw[i]; /* Eq. 4 */ \
-    }                                                                                              \
-  }
-#define MADAKV_LOAD_K(T0)                                                                          \
-  _Pragma("unroll") for (int blk = 0; blk < 2; ++blk) {                                            \
-    const int r = (T0) + blk * 16 + j16;                                                           \
-    const int rc = min(r, r_end - 1);                                                              \
-    const bool fresh = can_append && rc == len_old;                                                \
-    _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) {                                            \
-      const long long eo = at(rc) * D + ks * 32 + c * 8;        /* element offset of the piece */ \
-      if (!fresh) {                                                                                \
-        if (FP8) { const du32x2_t t2 = __builtin_nontemporal_load(reinterpret_cast<const du32x2_t*>(kc + eo)); kraw[blk][ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; } \
-        else kraw[blk][ks] = __builtin_nontemporal_load(reinterpret_cast<const du32x4_t*>(kc + eo * 2)); \
-      } else {                                                                                     \
-        const du32x4_t nb = *reinterpret_cast<const du32x4_t*>(kn + hidx * D + ks * 32 + c * 8);   \
-        if (FP8) {                                                                                 \
-          const du32x2_t t2 = bf16x8_to_e4m3x8(nb);                                                \
-          kraw[blk][ks] = du32x4_t{t2[0], t2[1], 0u, 0u};                                          \
-          if (r == rc) *reinterpret_cast<du32x2_t*>(kcw + eo) = t2;                                \
-        } else {                                                                                   \
-          kraw[blk][ks] = nb;                                                                      \
-          if (r == rc) *reinterpret_cast<du32x4_t*>(kcw + eo * 2) = nb;                            \
-        }                                                                                          \
-      }                                                                                            \
-    }                                                                                              \
-  }
-  const int t_first = r_begin + wave * 32;
-  if (t_first < r_end) {
-    MADAKV_LOAD_V(t_first)
-    MADAKV_LOAD_K(t_first)
-  }
-  for (int t0 = t_first; t0 < r_end; t0 += NW * 32) {
-    const int t_next = t0 + NW * 32;
-    // ---- V rows of the tile: parked in the wave's LDS tile, then the registers are refilled
+  // K fragments and V rows of the wave's tile; rows past the end of the piece: its last row once more, masked where
+  // they are used.  (The waves of other workgroups keep the memory busy while this one computes.)
+  for (int t0 = r_begin + wave * 32; t0 < r_end; t0 += NW * 32) {
+    du32x4_t kraw[2][KS], vraw[VL];            // raw cache bytes (E4M3: 8 bytes of a K piece sit in kraw[..][..].xy)
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+      const int r = min(t0 + blk * 16 + j16, r_end - 1);
+      const unsigned char* kp = PAGED ? kc + at(r) * (D * CB) : kc + (uint32_t)r * (uint32_t)(D * CB);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (FP8) { const du32x2_t t2 = __builtin_nontemporal_load(reinterpret_cast<const du32x2_t*>(kp + ks * 32 + c * 8)); kraw[blk][ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
+        else kraw[blk][ks] = __builtin_nontemporal_load(reinterpret_cast<const du32x4_t*>(kp + ks * 64 + c * 16));
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < VL; ++i) {
+      const int r = min(t0 + i * RPI + vsub, r_end - 1);
+      const unsigned char* vp = PAGED ? vc + at(r) * (D * CB) : vc + (uint32_t)r * (uint32_t)(D * CB);
+      vraw[i] = __builtin_nontemporal_load(reinterpret_cast<const du32x4_t*>(vp + vpiece * 16));
+    }
+    if (has_fresh && t0 <= len_old && len_old < t0 + 32) {          // the appended row (the last of the piece) comes from LDS
+#pragma unroll
+      for (int blk = 0; blk < 2; ++blk)
+        if (t0 + blk * 16 + j16 >= len_old) {
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            if (FP8) { const du32x2_t t2 = *reinterpret_cast<const du32x2_t*>(s_new + ks * 32 + c * 8); kraw[blk][ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
+            else kraw[blk][ks] = *reinterpret_cast<const du32x4_t*>(s_new + ks * 32 + c * 8);
+          }
+        }
+#pragma unroll
+      for (int i = 0; i < VL; ++i)
+        if (t0 + i * RPI + vsub >= len_old) vraw[i] = *reinterpret_cast<const du32x4_t*>(s_new + D + vpiece * VE);
+    }
+    // ---- S^T for the two 16-key blocks
+    float p[2][4];
+    float tmax = DNEG_BIG;
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+      df32x4_t sacc = df32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        du32x4_t kb = kraw[blk][ks];
+        if (FP8) {
+          const du32x2_t c0 = e4m3x4_to_bf16x4(kraw[blk][ks][0]), c1 = e4m3x4_to_bf16x4(kraw[blk][ks][1]);
+          kb = du32x4_t{c0[0], c0[1], c1[0], c1[1]};
+        }
+        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dbf16x8_t, kb), qb[ks], sacc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        const int key = t0 + blk * 16 + 4 * c + rr;      // in S^T the lane holds keys 4c..4c+3 of the block
+        p[blk][rr] = key < r_end ? sacc[rr] * a.scale_log2 : DNEG_BIG;
+        tmax = fmaxf(tmax, p[blk][rr]);
+      }
+    }
+    // ---- V rows parked in the wave's LDS tile
 #pragma unroll
     for (int i = 0; i < VL; ++i) {
       if (FP8) {                                           // 16 bytes -> 16 bf16
@@ -507,33 +550,6 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
         *reinterpret_cast<du32x4_t*>(vt + (i * RPI + vsub) * RS + vpiece * 8) = vraw[i];
       }
     }
-    MADAKV_LOAD_V(t_next)
-    // ---- S^T for the two 16-key blocks
-    float p[2][4];
-    float tmax = DNEG_BIG;
-    df32x4_t sacc[2];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      sacc[blk] = df32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        du32x4_t kb = kraw[blk][ks];
-        if (FP8) {
-          const du32x2_t c0 = e4m3x4_to_bf16x4(kraw[blk][ks][0]), c1 = e4m3x4_to_bf16x4(kraw[blk][ks][1]);
-          kb = du32x4_t{c0[0], c0[1], c1[0], c1[1]};
-        }
-        sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dbf16x8_t, kb), qb[ks], sacc[blk], 0, 0, 0);
-      }
-    }
-    MADAKV_LOAD_K(t_next)
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int key = t0 + blk * 16 + 4 * c + rr;      // in S^T the lane holds keys 4c..4c+3 of the block
-        p[blk][rr] = key < r_end ? sacc[blk][rr] * a.scale_log2 : DNEG_BIG;
-        tmax = fmaxf(tmax, p[blk][rr]);
-      }
     tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
     const float m_new = fmaxf(m_run, tmax);
@@ -542,13 +558,12 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
     float psum = 0.f;
     uint32_t hi[4], lo[4];                                // P as bf16 hi + lo, 8 keys per lane: the A fragment
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float pv = exp2f(p[e >> 2][e & 3] - m_new);
-      psum += pv;
-      const uint32_t hb = f32_to_bf16_rne(pv);
-      const uint32_t lb2 = f32_to_bf16_rne(pv - bf16_bits_to_f32(hb));
-      if (e & 1) { hi[e >> 1] |= hb << 16; lo[e >> 1] |= lb2 << 16; }
-      else { hi[e >> 1] = hb; lo[e >> 1] = lb2; }
+    for (int e = 0; e < 4; ++e) {
+      const df32x2_t pv = {exp2f(p[e >> 1][(e & 1) * 2] - m_new), exp2f(p[e >> 1][(e & 1) * 2 + 1] - m_new)};
+      psum += pv[0] + pv[1];
+      hi[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pv, dbf16x2_t));          // round to nearest even
+      const df32x2_t rest = {pv[0] - bf16_lo(hi[e]), pv[1] - bf16_hi(hi[e])};
+      lo[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, dbf16x2_t));
     }
     l_run = l_run * alpha + psum;
     const dbf16x8_t pa_hi = __builtin_bit_cast(dbf16x8_t, du32x4_t{hi[0], hi[1], hi[2], hi[3]});
@@ -561,17 +576,15 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // B fragment: for output column 16 db + j16 the 8 keys of this lane group (4c..4c+3 of either block).  A transposing
+    // read takes, per 16 lanes, four rows of 16 columns: lane j points at columns 4 (j & 3).. of row j >> 2 and gets
+    // column j of the four rows.
+    const uint16_t* vf = vt + (4 * c + (j16 >> 2)) * RS + 4 * (j16 & 3);
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
-      // B fragment: for output column 16 db + j16 the 8 keys of this lane group (4c..4c+3 of either block)
-      uint32_t w[4];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int row = (e >> 2) * 16 + 4 * c + (e & 3);
-        const uint32_t x = vt[row * RS + db * 16 + j16];
-        if (e & 1) w[e >> 1] |= x << 16; else w[e >> 1] = x;
-      }
-      const dbf16x8_t vb = __builtin_bit_cast(dbf16x8_t, du32x4_t{w[0], w[1], w[2], w[3]});
+      const ds16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)(vf + db * 16));
+      const ds16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)(vf + 16 * RS + db * 16));
+      const dbf16x8_t vb = __builtin_bit_cast(dbf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
       df32x4_t o = oacc[db];
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) o[rr] *= al[rr];
@@ -582,158 +595,170 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
-#undef MADAKV_LOAD_V
-#undef MADAKV_LOAD_K
 
   // ---- per wave: total of the sums over the lane groups, then everything to LDS in [q][d] form
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
   __syncthreads();                                   // all V tiles are dead: their space takes the results
   if (c == 0 && j16 < GT) { s_ml[wave][j16][0] = m_run; s_ml[wave][j16][1] = l_run; }
+  if (c < GT / 4)                                    // (lanes of the padding rows 8..15 have nothing to leave)
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int q = 4 * c + rr;
-      if (q < GT) s_acc[wave][q][db * 16 + j16] = oacc[db][rr];
-    }
+      for (int rr = 0; rr < 4; ++rr) s_acc[wave][4 * c + rr][db * 16 + j16] = oacc[db][rr];
   __syncthreads();
-  const int t = threadIdx.x;
-  const long long obase = (lb * a.H + h) * (long long)a.G * D;
-  if (t < D) {
-    for (int g = 0; g < a.G; ++g) {
-      float mx = DNEG_BIG;
-      for (int w = 0; w < NW; ++w) mx = fmaxf(mx, s_ml[w][g][0]);
-      float ls = 0.f, av = 0.f;
-      for (int w = 0; w < NW; ++w) {
-        const float cf = exp2f(s_ml[w][g][0] - mx);
-        ls += s_ml[w][g][1] * cf;
-        av += s_acc[w][g][t] * cf;
-      }
-      if (nch == 1) {
-        store_out<uint16_t>(a.out, a.out_fp32, obase + (long long)g * D + t, av / ls);
-      } else {
-        float* pp = a.part + ((hidx * a.max_chunks + chunk) * a.G + g) * (long long)(D + 2);
-        pp[t] = av;
-        if (t == 0) { pp[D] = mx; pp[D + 1] = ls; }
-      }
-    }
-  }
+  finish_piece<uint16_t, D, NW, GT>(a, hidx, chunk, len <= rows, s_ml, s_acc);
   if (a.max_chunks == 1 && can_append && threadIdx.x == 0) a.kv_len[hidx] = len;
 }
 
-// Merges the partial (max, sum, acc) triples of every head that was cut into several chunks,
-// in chunk order, and stores the new length.  One workgroup per head, thread t owns element t.
-template <typename T>
+// Merges the partial (max, sum, acc) triples of every head that was cut into several pieces and stores the new
+// length.  One workgroup per head; a thread has four elements of one query head and every KP-th piece, MB of them in
+// flight at a time, the KP shares meet in LDS in a fixed order.  Bound by one trip to memory: the first pieces'
+// partials are fetched before the head's length is known (slots past the head's last piece hold old values and
+// are masked).
+template <typename T, int D, int KP>
 __global__ __launch_bounds__(1024) void decode_merge_kernel(DecodeArgs a) {
+  constexpr int TL = D / 4, MB = 4;                   // threads per row of D elements; pieces in flight per thread
+  __shared__ float4 s_part[KP][8][TL];
+  __shared__ float2 s_mlp[KP][8];
   const long long hidx = blockIdx.x;
-  const int D = a.d;
-  const int g = min((int)threadIdx.x / D, a.G - 1), t = threadIdx.x % D;   // one thread per (query head of the group, element)
-  const long long cstride = (long long)a.G * (D + 2);
-  const float* pg = a.part + (hidx * a.max_chunks * a.G + g) * (long long)(D + 2);
-  // The first eight chunks' partials are fetched before the head's length is known (slots past the
-  // head's last chunk hold old values and are masked below): one round trip to memory instead of two.
+  const int tl = threadIdx.x % TL, kp = (threadIdx.x / TL) % KP, g = threadIdx.x / (TL * KP);   // blockDim = G * KP * TL
+  const float4* pa = reinterpret_cast<const float4*>(a.part) + (hidx * a.max_chunks * a.G + g) * TL + tl;
+  const float2* pm = reinterpret_cast<const float2*>(a.part_ml) + hidx * a.max_chunks * a.G + g;
   const int lim = a.max_chunks - 1;
-  float mc[8], lc[8], ac[8];
+  float4 ac[MB]; float2 ml[MB];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float* p = pg + (long long)min(j, lim) * cstride;
-    mc[j] = p[D]; lc[j] = p[D + 1]; ac[j] = p[t];
+  for (int j = 0; j < MB; ++j) {
+    const int ch = min(kp + j * KP, lim);
+    ac[j] = pa[(long long)ch * a.G * TL]; ml[j] = pm[(long long)ch * a.G];
   }
   const int len_old = a.kv_len[hidx];
-  __syncthreads();                                   // every wave has read the length before anyone stores the new one
   const bool can_append = can_append_to(a, a.kv_off[hidx], len_old);
   const int len = len_old + (can_append ? 1 : 0);
-  const int nch = max(1, (len + a.chunk_rows - 1) / a.chunk_rows);
-  if (can_append && threadIdx.x == 0) a.kv_len[hidx] = len;
-  if (nch == 1) return;                              // output already written by the attention kernel
-  if ((int)threadIdx.x / D >= a.G) return;
-  const long long lb = hidx / a.H;
-  const int h = (int)(hidx % a.H);
-  const long long obase = (lb * a.H + h) * (long long)a.G * D;
-  float m = DNEG_BIG, ls = 0.f, av = 0.f;
-  for (int c0 = 0; c0 < nch; c0 += 8) {              // 24 independent loads in flight per batch
-    if (c0 > 0) {
+  const int rows = head_chunk_rows(a, len);
+  float m = DNEG_BIG, ls = 0.f;
+  float4 av = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int c0 = kp; c0 * rows < len; c0 += KP * MB) {
+    if (c0 != kp) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float* p = pg + (long long)min(c0 + j, lim) * cstride;
-        mc[j] = p[D]; lc[j] = p[D + 1]; ac[j] = p[t];
+      for (int j = 0; j < MB; ++j) {
+        const int ch = min(c0 + j * KP, lim);
+        ac[j] = pa[(long long)ch * a.G * TL]; ml[j] = pm[(long long)ch * a.G];
       }
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const bool ok = c0 + j < nch;
-      mc[j] = ok ? mc[j] : DNEG_BIG; lc[j] = ok ? lc[j] : 0.f; ac[j] = ok ? ac[j] : 0.f;
     }
     float bm = m;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) bm = fmaxf(bm, mc[j]);
+    for (int j = 0; j < MB; ++j) {
+      if ((c0 + j * KP) * rows >= len) { ml[j] = make_float2(DNEG_BIG, 0.f); ac[j] = make_float4(0.f, 0.f, 0.f, 0.f); }
+      bm = fmaxf(bm, ml[j].x);
+    }
     const float sc = exp2f(m - bm);
-    ls *= sc; av *= sc;
+    ls *= sc; av.x *= sc; av.y *= sc; av.z *= sc; av.w *= sc;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float w = exp2f(mc[j] - bm);
-      ls = fmaf(lc[j], w, ls);
-      av = fmaf(ac[j], w, av);
+    for (int j = 0; j < MB; ++j) {
+      const float w = exp2f(ml[j].x - bm);
+      ls = fmaf(ml[j].y, w, ls);
+      av.x = fmaf(ac[j].x, w, av.x); av.y = fmaf(ac[j].y, w, av.y); av.z = fmaf(ac[j].z, w, av.z); av.w = fmaf(ac[j].w, w, av.w);
     }
     m = bm;
   }
-  store_out<T>(a.out, a.out_fp32, obase + (long long)g * D + t, av / ls);
+  s_part[kp][g][tl] = av;
+  if (tl == 0) s_mlp[kp][g] = make_float2(m, ls);
+  __syncthreads();                                   // (also: every wave has read the length before the new one is stored)
+  if (can_append && threadIdx.x == 0) a.kv_len[hidx] = len;
+  if (kp != 0 || len <= rows) return;                // (one piece: the output was written by the attention kernel)
+#pragma unroll
+  for (int k = 1; k < KP; ++k) m = fmaxf(m, s_mlp[k][g].x);
+  ls = 0.f; av = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    const float2 x = s_mlp[k][g];
+    const float4 y = s_part[k][g][tl];
+    const float w = exp2f(x.x - m);
+    ls = fmaf(x.y, w, ls);
+    av.x = fmaf(y.x, w, av.x); av.y = fmaf(y.y, w, av.y); av.z = fmaf(y.z, w, av.z); av.w = fmaf(y.w, w, av.w);
+  }
+  const long long o = (hidx * a.G + g) * D + tl * 4;
+  if (a.out_fp32 || sizeof(T) == 4) {
+    *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + o) = make_float4(av.x / ls, av.y / ls, av.z / ls, av.w / ls);
+  } else {
+    const uint32_t lo = (uint32_t)f32_to_bf16_rne(av.x / ls) | ((uint32_t)f32_to_bf16_rne(av.y / ls) << 16);
+    const uint32_t hi = (uint32_t)f32_to_bf16_rne(av.z / ls) | ((uint32_t)f32_to_bf16_rne(av.w / ls) << 16);
+    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + o) = make_uint2(lo, hi);
+  }
 }
 
 // Rows per workgroup: small for a single layer (many short workgroups balance ragged heads and
 // keep every CU streaming), larger when thousands of heads already fill the chip.
-DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows) {
-  DecodePlan p;
-  // longest_rows: upper bound on any head's length in this call (the worst case if unknown)
-  const int longest = std::max(1, std::min(longest_rows, c.ctx_len + c.max_new_tokens));
+static int plan_chunk_rows(const Dims& dm, const madakv_config& c) {
   // Measured on MI355X: 256-row chunks for a single layer's ragged heads at a 16K context
   // (smaller chunks lose to per-workgroup start-up cost, one workgroup per head to the imbalance
   // of ragged lengths), growing to 1024 rows when the heads are long (un-evicted cache), so that
   // the chip sees about eight workgroups per CU; 512 rows once a call covers >= 1024 heads.
-  int rows = 512;
-  if (dm.heads < 1024) {
-    const long long typical = std::min(c.budget, c.ctx_len) + c.max_new_tokens;    // rows of an average head
-    const long long per = ((long long)dm.heads * typical + 2047) / 2048;
-    const long long by_len = typical / 64;                     // a long head is not cut into more than ~64 chunks
-    rows = (int)std::min<long long>(1024, std::max<long long>(256, std::max(per, by_len) / 256 * 256));
-  }
-  p.chunk_rows = rows;
-  p.max_chunks = (longest + rows - 1) / rows;
+  if (dm.heads >= 1024) return 512;
+  const long long typical = std::min(c.budget, c.ctx_len) + c.max_new_tokens;    // rows of an average head
+  const long long per = ((long long)dm.heads * typical + 2047) / 2048;
+  const long long by_len = typical / 64;                     // a long head is not cut into more than ~64 chunks
+  return (int)std::min<long long>(1024, std::max<long long>(256, std::max(per, by_len) / 256 * 256));
+}
+static int plan_longest(const madakv_config& c, int longest_rows) { return std::max(1, std::min(longest_rows, c.ctx_len + c.max_new_tokens)); }
+
+// The pieces of a launch.  A head is cut into pieces of chunk_rows and at most max_chunks of them, twice what an average
+// head takes (longer heads: longer pieces, see head_chunk_rows).  Neither depends on what the host knows of the
+// longest head, so that a call's result does not either; only the grid, at most max_chunks pieces, shrinks when it is known.
+DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows, size_t ws_bytes) {
+  DecodePlan p;
+  const int worst = plan_longest(c, c.ctx_len + c.max_new_tokens);
+  const int base = plan_chunk_rows(dm, c);
+  p.chunk_rows = base;
+  // grouped queries, few heads: a tile of 32 rows per wave while the launch does not fill the chip with that
+  const long long typical = std::min(c.budget, c.ctx_len) + c.max_new_tokens;
+  if (c.dtype == MADAKV_BF16 && dm.G >= 2 && dm.heads * typical <= 256LL * 128 * 2) p.chunk_rows = 128;
+  const long long want = std::max<long long>((2 * typical + p.chunk_rows - 1) / p.chunk_rows, 512 / dm.heads);
+  // never more partial results than a worst-case head cut into `base` rows has (what decode_ws_bytes is made for), nor
+  // than the workspace at hand holds (madakv_decode_attn_static)
+  const long long room = (long long)(ws_bytes / ((size_t)dm.heads * dm.G * (dm.d + 2) * sizeof(float)));
+  p.max_chunks = (int)std::max<long long>(1, std::min({(long long)(worst + base - 1) / base, std::max<long long>(2, want), room}));
+  p.grid_chunks = std::min(p.max_chunks, (plan_longest(c, longest_rows) + p.chunk_rows - 1) / p.chunk_rows);
   return p;
 }
 
 size_t decode_ws_bytes_for(const Dims& dm, const madakv_config& c, int longest_rows) {
-  DecodePlan p = decode_plan(dm, c, longest_rows);
-  return (size_t)dm.heads * p.max_chunks * dm.G * (dm.d + 2) * sizeof(float) + 64;
+  const int base = plan_chunk_rows(dm, c);
+  const int chunks = (plan_longest(c, longest_rows) + base - 1) / base;
+  return (size_t)dm.heads * chunks * dm.G * (dm.d + 2) * sizeof(float) + 64;
 }
 size_t decode_ws_bytes(const Dims& dm, const madakv_config& c) { return decode_ws_bytes_for(dm, c, c.ctx_len + c.max_new_tokens); }
 
-template <typename T, typename CT, int LPR>
-static hipError_t launch_decode_t(const Dims& dm, DecodeArgs& a, hipStream_t st) {
-  dim3 grid(dm.heads, a.max_chunks), block(DEC_THREADS);
-  if (sizeof(T) == 2 && dm.G >= 2) {
-    // grouped queries in bf16: the MFMA kernel
-    constexpr bool F8 = sizeof(CT) == 1;
-    if (dm.d == 128) hipLaunchKernelGGL((decode_gqa_kernel<128, F8>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((decode_gqa_kernel<64, F8>), grid, block, 0, st, a);
-    if (a.max_chunks > 1) hipLaunchKernelGGL((decode_merge_kernel<T>), dim3(dm.heads), dim3(dm.G * dm.d), 0, st, a);
-    return hipGetLastError();
+template <typename T, int D>
+static void launch_merge(const Dims& dm, const DecodeArgs& a, hipStream_t st) {
+  // as many threads as a workgroup holds: KP of them share a head's pieces
+  if (dm.G * 8 * (D / 4) <= 1024) hipLaunchKernelGGL((decode_merge_kernel<T, D, 8>), dim3(dm.heads), dim3(dm.G * 8 * (D / 4)), 0, st, a);
+  else hipLaunchKernelGGL((decode_merge_kernel<T, D, 4>), dim3(dm.heads), dim3(dm.G * 4 * (D / 4)), 0, st, a);
+}
+
+template <typename T, typename CT, int LPR, bool PAGED>
+static hipError_t launch_decode_t(const Dims& dm, DecodeArgs& a, int grid_chunks, hipStream_t st) {
+  constexpr int D = LPR * 16 / (int)sizeof(CT);
+  dim3 grid(dm.heads, grid_chunks), block(DEC_THREADS);
+  if (sizeof(T) == 2 && dm.G >= 2) hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED>), grid, block, 0, st, a);   // grouped queries in bf16: the MFMA kernel
+  else if (dm.G == 1) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, 4, 4, PAGED>), grid, block, 0, st, a);
+  else if constexpr (sizeof(T) == 4) {
+    if (dm.G == 2) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 2, 4, 4, PAGED>), grid, block, 0, st, a);
+    else if (dm.G <= 4) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 4, 4, 4, PAGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 8, 2, 4, PAGED>), grid, block, 0, st, a);
   }
-  // (8-bit cache: a lane holds 16 elements per 16-byte load; four rows in flight per lane keep the kernel at 3 waves
-  // per SIMD, eight would need 230 registers: 21.2 against 23.3 us per layer call)
-  if (dm.G == 1 && sizeof(CT) == 1) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, 4, 4>), grid, block, 0, st, a);
-  else if (dm.G == 1) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, 8, 4>), grid, block, 0, st, a);
-  else if (dm.G == 2) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 2, 4, 4>), grid, block, 0, st, a);
-  else if (dm.G <= 4) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 4, 4, 4>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 8, 2, 4>), grid, block, 0, st, a);
-  if (a.max_chunks > 1) hipLaunchKernelGGL((decode_merge_kernel<T>), dim3(dm.heads), dim3(dm.G * dm.d), 0, st, a);
+  if (a.max_chunks > 1) launch_merge<T, D>(dm, a, st);
   return hipGetLastError();
+}
+template <typename T, typename CT, int LPR>
+static hipError_t launch_decode_p(const Dims& dm, DecodeArgs& a, int grid_chunks, hipStream_t st) {
+  return a.page_rows ? launch_decode_t<T, CT, LPR, true>(dm, a, grid_chunks, st) : launch_decode_t<T, CT, LPR, false>(dm, a, grid_chunks, st);
 }
 
 hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, const void* k_new,
                          const void* v_new, void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
-                         void* out, void* ws, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st) {
+                         void* out, void* ws, size_t ws_bytes, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st) {
   DecodeArgs a;
   a.capacity = capacity_tokens;
   a.page_rows = pg.page_rows; a.tbl_entries = pg.entries; a.page_tbl = pg.table; a.pool_top = pg.pool_top;
@@ -743,22 +768,23 @@ hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, 
   a.head0 = (long long)layer0 * dm.B * dm.H;
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.k_c = k_c; a.v_c = v_c; a.kv_off = kv_off; a.kv_len = kv_len;
   a.out = out; a.part = reinterpret_cast<float*>(ws);
-  DecodePlan p = decode_plan(dm, c, longest_rows);
+  DecodePlan p = decode_plan(dm, c, longest_rows, ws_bytes);
   a.B = dm.B; a.H = dm.H; a.G = dm.G; a.d = dm.d; a.chunk_rows = p.chunk_rows; a.max_chunks = p.max_chunks;
+  a.part_ml = a.part + (long long)dm.heads * p.max_chunks * dm.G * dm.d;
   a.out_fp32 = c.out_fp32; a.has_new = (k_new != nullptr) ? 1 : 0;
   const float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)dm.d);
   a.scale_log2 = scale * 1.4426950408889634f;
   const int lpr = dm.d * (c.dtype == MADAKV_BF16 ? 2 : 4) / 16;
   if (c.dtype == MADAKV_BF16) {
     if (c.cache_fp8) {                                   // rows of d bytes: d / 16 lanes per row
-      if (dm.d == 128) return launch_decode_t<uint16_t, uint8_t, 8>(dm, a, st);
-      if (dm.d == 64) return launch_decode_t<uint16_t, uint8_t, 4>(dm, a, st);
+      if (dm.d == 128) return launch_decode_p<uint16_t, uint8_t, 8>(dm, a, p.grid_chunks, st);
+      if (dm.d == 64) return launch_decode_p<uint16_t, uint8_t, 4>(dm, a, p.grid_chunks, st);
     }
-    if (lpr == 8) return launch_decode_t<uint16_t, uint16_t, 8>(dm, a, st);
-    if (lpr == 16) return launch_decode_t<uint16_t, uint16_t, 16>(dm, a, st);
+    if (lpr == 8) return launch_decode_p<uint16_t, uint16_t, 8>(dm, a, p.grid_chunks, st);
+    if (lpr == 16) return launch_decode_p<uint16_t, uint16_t, 16>(dm, a, p.grid_chunks, st);
   } else {
-    if (lpr == 16) return launch_decode_t<float, float, 16>(dm, a, st);
-    if (lpr == 32) return launch_decode_t<float, float, 32>(dm, a, st);
+    if (lpr == 16) return launch_decode_p<float, float, 16>(dm, a, p.grid_chunks, st);
+    if (lpr == 32) return launch_decode_p<float, float, 32>(dm, a, p.grid_chunks, st);
   }
   return hipErrorInvalidValue;
 }

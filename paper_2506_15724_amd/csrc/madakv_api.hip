@@ -270,7 +270,7 @@ int32_t decode_impl(madakv_handle* h, int32_t layer0, int32_t n,
     for (int l = layer0; l < layer0 + n; ++l)
       if (h->appended[l] >= h->cfg.max_new_tokens) return MADAKV_ERR_INVALID_ARG;
   }
-  hipError_t e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, ws,
+  hipError_t e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, ws, ws_bytes,
                                region_tokens(h->cfg) * h->cfg.batch, longest, make_paging(h), layer0,
                                reinterpret_cast<hipStream_t>(stream));
   if (e == hipSuccess && k_new) for (int l = layer0; l < layer0 + n; ++l) h->appended[l] += 1;

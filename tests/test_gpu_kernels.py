@@ -69,3 +69,64 @@ def test_fp32_scores(kw, monkeypatch):
     torch.cuda.synchronize()
     assert torch.allclose(eng.psi, one, rtol=2e-5, atol=1e-12)
     eng.close()
+
+
+@pytest.mark.parametrize("kw,lens", [
+    # many heads on a small budget: at most two pieces per head, so a long head takes long pieces
+    (dict(batch=8, n_q_heads=64, n_kv_heads=64, head_dim=64, ctx_len=6000, budget=128), [5001, 512, 513, 511, 1, 31, 0, 545]),
+    (dict(batch=8, n_q_heads=64, n_kv_heads=64, head_dim=128, ctx_len=6000, budget=128, cache_fp8=1), [5001, 512, 513, 511, 1, 32, 0, 545]),
+    (dict(batch=8, n_q_heads=128, n_kv_heads=64, head_dim=64, ctx_len=6000, budget=128), [5001, 512, 513, 511, 1, 33, 0, 545]),
+    # few heads, grouped queries: pieces of 128 rows; more pieces than the merge has in flight at once
+    (dict(n_q_heads=28, n_kv_heads=4, head_dim=128, ctx_len=9000, budget=2000), [6001, 128, 127, 129]),
+    (dict(n_q_heads=8, n_kv_heads=1, head_dim=64, ctx_len=9000, budget=4500), [4499]),
+    (dict(n_q_heads=12, n_kv_heads=2, head_dim=128, ctx_len=5000, budget=1000, cache_fp8=1), [1700, 159]),
+    (dict(n_q_heads=3, n_kv_heads=1, head_dim=128, ctx_len=12000, budget=11000, dtype="fp32"), [10999]),
+    (dict(n_q_heads=2, n_kv_heads=2, head_dim=64, ctx_len=400, budget=300, dtype="fp32"), [299, 255]),
+], ids=lambda x: f"q{x['n_q_heads']}_kv{x['n_kv_heads']}_d{x['head_dim']}_L{x['ctx_len']}_{x.get('dtype', 'bf16')}" if isinstance(x, dict) else "")
+@pytest.mark.parametrize("out_fp32", [1, 0])
+def test_decode_pieces(kw, lens, out_fp32):
+    """Heads cut into pieces in every way the plan has, an appended row at the edges of pieces and tiles, against a 64-bit
+    attention over the rows the cache then holds.  Bound: outputs are means of N(0, 1) rows; a logit of <= 128 fp32
+    products (|logit| < 8) is within 1e-5, P as two bf16 parts within 2^-17: 1e-4 covers both; a bf16 output adds half
+    a unit of its last place (2^-9 of the value)."""
+    args = dict(n_layers=1, batch=1, window=8, dtype="bf16", pool_k=1, max_new_tokens=2, out_fp32=out_fp32)
+    args.update(kw)
+    eng = MB.MadaKV(device=DEV, **args)
+    B, H, Hq, d = args["batch"], args["n_kv_heads"], args["n_q_heads"], args["head_dim"]
+    g = torch.Generator().manual_seed(7)
+    ln = torch.zeros(B * H, dtype=torch.int32)
+    ln[torch.randperm(B * H, generator=g)[:len(lens)]] = torch.tensor(lens, dtype=torch.int32)
+    off = torch.cumsum(ln.long() + args["max_new_tokens"], 0) - ln.long() - args["max_new_tokens"]
+    used = int(off[-1] + ln[-1]) + args["max_new_tokens"]
+    assert used <= eng.capacity
+    eng.kv_off.view(-1).copy_(off); eng.kv_len.view(-1).copy_(ln)
+    rows = torch.randn(2, used, d, generator=g).to(DEV)
+    if args.get("cache_fp8"):
+        eng.k_c[:used] = rows[0].to(torch.float8_e4m3fn).view(torch.uint8); eng.v_c[:used] = rows[1].to(torch.float8_e4m3fn).view(torch.uint8)
+    else:
+        eng.k_c[:used] = rows[0]; eng.v_c[:used] = rows[1]
+    f64 = lambda t: (t.view(torch.float8_e4m3fn) if args.get("cache_fp8") else t).cpu().double()
+    q, kn, vn = (torch.randn(1, B, h, d, generator=g).to(DEV, eng.tdtype) for h in (Hq, H, H))
+    out = torch.empty(1, B, Hq, d, dtype=torch.float32 if out_fp32 else eng.tdtype, device=DEV)
+    worst = 0.0
+    for step in range(2):
+        say(f"{kw} out_fp32={out_fp32} step {step}")
+        eng.decode_attn(0, 1, q, kn, vn, out)
+        torch.cuda.synchronize()
+        assert torch.equal(eng.kv_len.view(-1).cpu(), torch.where(ln > 0, ln + step + 1, ln))
+        res = out.view(B * H, Hq // H, d).cpu().double()
+        for h in range(B * H):
+            n = int(ln[h])
+            if n == 0:
+                assert torch.isnan(res[h]).all()
+                continue
+            lo, hi = int(off[h]), int(off[h]) + n + step + 1
+            k, v = f64(eng.k_c[lo:hi]), f64(eng.v_c[lo:hi])
+            if not args.get("cache_fp8"):
+                assert torch.equal(k[-1], kn.view(-1, d)[h].cpu().double()) and torch.equal(v[-1], vn.view(-1, d)[h].cpu().double())
+            ref = torch.softmax(q.view(B * H, Hq // H, d)[h].cpu().double() @ k.T / d ** 0.5, -1) @ v
+            err = ((res[h] - ref).abs() - (0 if out_fp32 or eng.tdtype == torch.float32 else ref.abs() * 2.0 ** -8)).max()
+            worst = max(worst, float(err))
+    say(f"worst {worst:.2e}")
+    assert worst < 1e-4
+    eng.close()
