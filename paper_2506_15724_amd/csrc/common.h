@@ -193,6 +193,20 @@ __device__ __forceinline__ unsigned long long wave_incl_scan_u63(unsigned long l
   return (unsigned long long)l0 + ((unsigned long long)l1 << 21) + ((unsigned long long)l2 << 42);
 }
 
+__device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long x) {
+#define MADAKV_DPP_ADD64(ctrl, rmask, bctl) \
+  x += ((unsigned long long)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(x >> 32), ctrl, rmask, 0xF, bctl) << 32) | \
+       (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, ctrl, rmask, 0xF, bctl)
+  MADAKV_DPP_ADD64(0x111, 0xF, true);
+  MADAKV_DPP_ADD64(0x112, 0xF, true);
+  MADAKV_DPP_ADD64(0x114, 0xF, true);
+  MADAKV_DPP_ADD64(0x118, 0xF, true);
+  MADAKV_DPP_ADD64(0x142, 0xA, false);
+  MADAKV_DPP_ADD64(0x143, 0xC, false);
+#undef MADAKV_DPP_ADD64
+  return x;
+}
+
 // Order-preserving map float -> uint32 (larger float, larger key); -0 is folded onto +0.
 __device__ __forceinline__ uint32_t float_key(float f) {
   f += 0.0f;

@@ -130,3 +130,44 @@ def test_decode_pieces(kw, lens, out_fp32):
     say(f"worst {worst:.2e}")
     assert worst < 1e-4
     eng.close()
+
+
+@pytest.mark.parametrize("L,W,M,pool_k,avg", [
+    (9, 8, 2, 7, 0), (13, 8, 2, 3, 1), (200, 5, 2, 7, 1), (4096 + 8, 8, 2, 7, 0), (4097 + 8, 8, 3, 5, 0), (16383 + 8, 8, 2, 7, 0),
+    (16384 + 8, 8, 4, 1, 0), (16385 + 8, 8, 2, 9, 0), (20483 + 1, 1, 2, 7, 0), (70001, 8, 2, 7, 0), (70001, 8, 3, 5, 1)])
+def test_statistics_at_edges(L, W, M, pool_k, avg):
+    """Candidate counts at and around the groups, workgroups and chunks of the statistics kernel; one modality's keys point
+    away from the queries, so that its masses are tiny (the descent's open lowest bin).  The rules of the stage-wise tests:
+    masses on the same psi bits, counts that cross theta within 1e-4, pooled maxima bit for bit (averages of up to nine
+    fp32 values: 1e-6 relative)."""
+    H, d, nc = 3, 64, L - W
+    g = torch.Generator().manual_seed(L + M)
+    mask_h = torch.randint(0, M, (1, L), generator=g).to(torch.uint8)
+    q = (torch.randn(1, 1, H, W, d, generator=g) + 1.0)
+    k = torch.randn(1, 1, H, L, d, generator=g)
+    k[0, 0, 1:][:, mask_h[0] == M - 1] -= torch.tensor([1.0, 3.0])[:, None, None]
+    q, k, mask = q.to(DEV, torch.bfloat16), k.to(DEV, torch.bfloat16), mask_h.to(DEV)
+    eng = MB.MadaKV(n_layers=1, batch=1, n_q_heads=H, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=W + max(1, nc // 3) if nc > 1 else L,
+                    dtype="bf16", pool_k=pool_k, pool_mode=avg, n_modalities=M, device=DEV)
+    say(f"statistics L={L} W={W} M={M}")
+    eng.score(0, 1, q, k, mask)
+    torch.cuda.synchronize()
+    psi = eng.psi[0, 0].cpu().numpy().astype(np.float64)
+    w_g, k_g = eng.stats_host()
+    mh = mask_h[0].numpy()
+    w_o, k_o, n_o = O.modality_stats(psi, mh, W, 0.9, 0, M)
+    assert tuple(eng.n_mod.cpu().numpy()[0]) == tuple(n_o)
+    PU.assert_masses_close(w_g[0, 0], w_o, nc)
+    pool_o = O.pool_scores(psi, W, pool_k, avg).astype(np.float32)
+    pool_g = eng.psi_pool[0, 0].cpu().numpy()
+    if avg:
+        np.testing.assert_allclose(pool_g, pool_o, rtol=1e-6)
+    else:
+        np.testing.assert_array_equal(pool_g, pool_o)
+    for h in range(H):
+        for m in range(M):
+            vals = psi[h, :nc][mh[:nc] == m]
+            # (a mass of a few units of the 2^-44 fixed point says nothing about theta)
+            if k_g[0, 0, h, m] != k_o[h, m] and vals.sum() > 1e4 * max(1, vals.size) * 2.0 ** -44:
+                assert PU.k_count_ok(int(k_g[0, 0, h, m]), vals, 0.9), (h, m, k_g[0, 0, h, m], k_o[h, m])
+    eng.close()
