@@ -7,25 +7,26 @@
 //                  cache, inside it layers and heads follow each other; a segment has
 //                  kv_len = b_t + b_v + W rows plus max_new_tokens free rows.  It also fills
 //                  a table "first head that overlaps each 64-row block" for the gather.
-// select_kernel    one workgroup per head; a thread owns 32 consecutive candidates, whose keys
-//                  and modality bits stay in registers (one trip to memory for contexts up to
-//                  16K candidates, chunks of that size beyond).  A 3-level radix select
-//                  (11 + 11 + 10 bits of the order-preserving key) on LDS count histograms
-//                  finds, per modality, the threshold key tau_m and how many elements equal
+// select_kernel    one workgroup per head.  A radix descent (descent.h) over count histograms of the
+//                  order-preserving keys finds, per modality, the threshold key tau_m and how many elements equal
 //                  to tau_m are still needed; then key > tau_m is kept, and key == tau_m while
-//                  its rank by position is below that number.  Workgroup prefix sums give
+//                  its rank by position is below that number.  The last pass goes over the candidates in order, 4096 at
+//                  a time; prefix sums over the workgroup give
 //                  the ranks and the output slots, so the result is ascending by construction.
-#include "common.h"
+//                  Bound like the statistics (stats.hip) by latency and instruction issue; nothing unrolled over a
+//                  thread's candidates, which are read again per level: 9 KB of code instead of 42, one scan instead of
+//                  two in the last pass.  In the path, before -> after: 27.6 -> 11.3 us (8 heads of 1K candidates),
+//                  29.5 -> 18.7 (32 of 8K), 35 -> 29 (128 of 16K), re-eviction's 1024 heads of 2K rows 87 -> 27.
+#include "descent.h"
 
 namespace madakv {
 
-constexpr int SEL_THREADS = 512;
-constexpr int SEL_BINS = 2048;
-
-constexpr int SEL_EPT = 32;                      // consecutive candidates a thread owns per chunk
+constexpr int SEL_THREADS = 1024;
+constexpr int SEL_CHUNK = 16384;                 // candidates per workgroup where a head's chunks have workgroups of their own
+constexpr uint32_t SEL_SH1 = 21;                 // plain first digit of a 32-bit key
 
 // what the walk of one level hands on, per head and modality, and what a chunk reports (phases 1-4 of select_kernel)
-struct SelCarry { uint32_t prefix, need, done, pad; };
+struct SelCarry { DescentRange range; uint32_t need, alive, tau, pad; };
 struct SelChunk { uint32_t gt, pad; unsigned long long eq; };   // kept for sure; threshold-valued ones, 16 bits per modality
 
 struct OffsetsArgs {
@@ -134,113 +135,36 @@ struct SelectArgs {
   // numbers of kept and of threshold-valued candidates; 4 = a chunk's kept positions written behind those
   // of the chunks before it.
   int phase, level, heads, nchunks;
-  uint32_t* gcnt;                 // [3 levels][heads][M][SEL_BINS]
+  uint32_t* gcnt;                 // [3 levels][heads][M][BINS]
   SelCarry* carry;                // [heads][4]
   SelChunk* chunkinfo;            // [heads][nchunks]
 };
 
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
-
-// exclusive prefix over the workgroup of a packed pair of counts (lo16 | hi16; a chunk holds
-// 16384 candidates, so each half stays below 2^16 unless every one of them counts: the
-// caller keeps the totals in 32 bits and the halves are only used below that bound)
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wave_tot, uint32_t& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t incl = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t t = (uint32_t)__shfl((int)incl, max(lane - o, 0), 64);
-    if (lane >= o) incl += t;
-  }
-  if (lane == 63) wave_tot[wave] = incl;
-  __syncthreads();
-  uint32_t before = 0, tot = 0;
-  for (int w = 0; w < SEL_THREADS / 64; ++w) {
-    uint32_t t = wave_tot[w];
-    if (w < wave) before += t;
-    tot += t;
-  }
-  __syncthreads();
-  total = tot;
-  return before + incl - v;
-}
-
-// the same for four 16-bit counts packed in 64 bits (one count per modality)
-__device__ __forceinline__ unsigned long long block_excl_scan64(unsigned long long v, unsigned long long* wave_tot,
-                                                                unsigned long long& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned long long incl = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    unsigned long long t = (unsigned long long)shfl_i64((long long)incl, max(lane - o, 0));
-    if (lane >= o) incl += t;
-  }
-  if (lane == 63) wave_tot[wave] = incl;
-  __syncthreads();
-  unsigned long long before = 0, tot = 0;
-  for (int w = 0; w < SEL_THREADS / 64; ++w) {
-    unsigned long long t = wave_tot[w];
-    if (w < wave) before += t;
-    tot += t;
-  }
-  __syncthreads();
-  total = tot;
-  return before + incl - v;
-}
-
-template <typename T, int N>
-__device__ __forceinline__ T pick(const T (&x)[N], int m) {              // x[m] without indexing registers by m
-  T r = x[0];
-#pragma unroll
-  for (int j = 1; j < N; ++j) r = (m == j) ? x[j] : r;
-  return r;
-}
-
-// Thread t of the workgroup owns SEL_EPT consecutive candidates of a chunk: their keys and
-// modality bits live in registers through the three radix levels and the compaction.
-__device__ __forceinline__ void load_owned(const float* sc, const uint8_t* mask, int i0, int nc, int use_mask, int M,
-                                           uint32_t (&key)[SEL_EPT], unsigned long long& mbits) {
-  const bool full = i0 + SEL_EPT <= nc;
-  if (full && ((reinterpret_cast<uintptr_t>(sc + i0) & 15u) == 0)) {
-#pragma unroll
-    for (int j = 0; j < SEL_EPT / 4; ++j) {
-      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(sc + i0 + j * 4);
-      key[j * 4 + 0] = float_key(v[0]); key[j * 4 + 1] = float_key(v[1]);
-      key[j * 4 + 2] = float_key(v[2]); key[j * 4 + 3] = float_key(v[3]);
-    }
+// the next group of four candidates of a thread: keys, and the bytes of their modality ids (0 where the mask is not used)
+struct KeyGroup { f32x4_any_t x; uint32_t mw; };
+__device__ __forceinline__ KeyGroup load_keys(const float* sc, const uint8_t* mask, int i, int nc, int use_mask) {
+  KeyGroup g;
+  g.x = f32x4_any_t{0.f, 0.f, 0.f, 0.f};
+  g.mw = 0u;
+  if (i + 4 <= nc) {
+    g.x = *reinterpret_cast<const f32x4_any_t*>(sc + i);
+    if (use_mask) g.mw = load_mask4(mask + i);
   } else {
 #pragma unroll
-    for (int e = 0; e < SEL_EPT; ++e) key[e] = (i0 + e < nc) ? float_key(sc[i0 + e]) : 0u;
+    for (int q = 0; q < 3; ++q) if (i + q < nc) { g.x[q] = sc[i + q]; if (use_mask) g.mw |= (uint32_t)mask[i + q] << (8 * q); }
   }
-  mbits = 0ULL;                                   // modality ids, two bits per element
-  const uint32_t top = (uint32_t)(M - 1);
-  if (use_mask) {
-    if (full && ((reinterpret_cast<uintptr_t>(mask + i0) & 15u) == 0)) {
-#pragma unroll
-      for (int j = 0; j < SEL_EPT / 16; ++j) {
-        const u32x4_t w = *reinterpret_cast<const u32x4_t*>(mask + i0 + j * 16);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int bb = 0; bb < 4; ++bb)
-            mbits |= (unsigned long long)min((w[q] >> (8 * bb)) & 0xffu, top) << (2 * (j * 16 + q * 4 + bb));
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < SEL_EPT; ++e)
-        if (i0 + e < nc) mbits |= (unsigned long long)min((uint32_t)mask[i0 + e], top) << (2 * e);
-    }
-  }
+  return g;
 }
 
 template <int MM>   // modalities the kernel is built for (2: the paper's text / image; 4: up to four)
-__global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM == 2 ? 4 : 2, 4))) void select_kernel(SelectArgs a) {
-  __shared__ uint32_t cnt[MM][SEL_BINS];
-  __shared__ uint32_t s_prefix[MM], s_need[MM], s_done[MM];
-  __shared__ uint32_t wave_tot[SEL_THREADS / 64];
-  __shared__ unsigned long long wave_tot64[SEL_THREADS / 64];
+__global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM == 2 ? 8 : 4))) void select_kernel(SelectArgs a) {
+  constexpr int NWAVES = SEL_THREADS / 64;
+  __shared__ __attribute__((aligned(16))) uint32_t cnt[MM][BINS];
+  __shared__ DescentRange s_range[MM];
+  __shared__ uint32_t s_need[MM], s_alive[MM], s_tau[MM], s_before[MM], s_bin[MM], s_part[MM][NWAVES];
+  __shared__ uint32_t s_tot[2][3][NWAVES];
   const int M = a.M;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid0 = threadIdx.x;
   const int phase = a.phase;
   const bool per_chunk = phase == 1 || phase >= 3;             // grid (chunks, heads)
   const int head = per_chunk ? blockIdx.y : blockIdx.x;
@@ -256,201 +180,231 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
 
   if (a.kv_len[head] == 0) return;               // the segment did not fit the region: nothing to write
   if (a.keep_all) {
-    for (int i = tid; i < a.L; i += SEL_THREADS) out[i] = i;
+    for (int i = tid0; i < a.L; i += SEL_THREADS) out[i] = i;
     return;
   }
-  uint32_t bud[MM];
-#pragma unroll
-  for (int m = 0; m < MM; ++m) bud[m] = m < M ? (uint32_t)a.budgets[(long long)head * M + m] : 0u;
   if (a.select_mode == 1) {
     // score-free baseline: the first `sink` candidates and the most recent ones, then the window
     uint32_t btot = 0;
-#pragma unroll
-    for (int m = 0; m < MM; ++m) btot += bud[m];
+    for (int m = 0; m < M; ++m) btot += (uint32_t)a.budgets[(long long)head * M + m];
     const int total = min((int)btot, nc);
     const int sink = min(a.sink_tokens, total);
-    for (int j = tid; j < total + a.W; j += SEL_THREADS)
+    for (int j = tid0; j < total + a.W; j += SEL_THREADS)
       out[j] = j < sink ? j : (j < total ? nc - (total - j) : nc + (j - total));
     return;
   }
-  const int shifts[3] = {21, 10, 0};
-  const int widths[3] = {11, 11, 10};
-  constexpr int CH = SEL_THREADS * SEL_EPT;      // candidates per chunk
-  const int nchunks = (nc + CH - 1) / CH;
-  const int c_first = per_chunk ? blockIdx.x : 0, c_end = per_chunk ? blockIdx.x + 1 : nchunks;
-  const bool single = c_end - c_first == 1;      // the usual case: everything stays in registers
-  const int lv_first = phase == 0 ? 0 : (phase <= 2 ? a.level : 3), lv_end = phase == 0 ? 3 : (phase <= 2 ? a.level + 1 : 3);
-  uint32_t* gcnt = phase ? a.gcnt + ((size_t)(phase <= 2 ? a.level : 0) * a.heads + head) * (size_t)M * SEL_BINS : nullptr;
+  const int i_begin = per_chunk ? (int)blockIdx.x * SEL_CHUNK : 0;
+  const int i_end = per_chunk ? min(nc, i_begin + SEL_CHUNK) : nc;
+  const uint32_t top = (uint32_t)(M - 1);
+  uint32_t* gcnt = phase ? a.gcnt + ((size_t)(phase <= 2 ? a.level : 0) * a.heads + head) * (size_t)M * BINS : nullptr;
   SelCarry* carry = phase ? a.carry + (size_t)head * 4 : nullptr;
-  if (phase != 0 && (phase >= 3 || a.level > 0) && tid < M) {   // what the walks before left
-    const SelCarry cy = carry[tid];
-    s_prefix[tid] = cy.prefix; s_need[tid] = cy.need; s_done[tid] = cy.done;
+  if (tid0 < M) {
+    if (phase != 0 && (phase >= 3 || a.level > 0)) {            // what the walks before left
+      const SelCarry cy = carry[tid0];
+      s_range[tid0] = cy.range; s_need[tid0] = cy.need; s_alive[tid0] = cy.alive; s_tau[tid0] = cy.tau;
+    } else {
+      s_range[tid0] = phase ? descent_plain<SEL_SH1>() : descent_first(1u);
+      s_need[tid0] = (uint32_t)a.budgets[(long long)head * M + tid0]; s_alive[tid0] = 1u; s_tau[tid0] = 0xffffffffu;
+    }
   }
-  if (phase >= 3) __syncthreads();
 
-  uint32_t key[SEL_EPT];
-  unsigned long long mbits = 0ULL;
-  if (single && phase != 2) load_owned(sc, mask, c_first * CH + tid * SEL_EPT, nc, a.mpa_mode, M, key, mbits);
-
-  for (int level = lv_first; level < lv_end; ++level) {
-    for (int e = tid; e < M * SEL_BINS; e += SEL_THREADS) (&cnt[0][0])[e] = 0;
+  for (int level = phase ? a.level : 0; phase < 3; ++level) {
+    // (addresses that depend on the thread are computed level by level: kept over the loop they would spill)
+    int tid = tid0;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int e = tid; e < M * BINS / 4; e += SEL_THREADS) reinterpret_cast<uint4*>(&cnt[0][0])[e] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    const int sh = shifts[level], wd = widths[level];
-    const uint32_t binmask = (1u << wd) - 1u;
-    uint32_t pfx[MM]; bool dn[MM];
+    DescentRange rg[MM];
 #pragma unroll
-    for (int m = 0; m < MM; ++m) {
-      pfx[m] = (level > 0 && m < M) ? s_prefix[m] : 0u;
-      dn[m] = (level > 0 && m < M) ? s_done[m] != 0 : false;
-    }
+    for (int m = 0; m < MM; ++m) rg[m] = descent_uniform(s_range[min(m, M - 1)]);
     if (phase == 2) {                              // the head's histogram of this level, gathered by the chunks' workgroups
-      for (int e = tid; e < M * SEL_BINS; e += SEL_THREADS) (&cnt[0][0])[e] = gcnt[e];
-    }
-    for (int c = (phase == 2 ? c_end : c_first); c < c_end; ++c) {
-      const int i0 = c * CH + tid * SEL_EPT;
-      if (!single) load_owned(sc, mask, i0, nc, a.mpa_mode, M, key, mbits);
-      const int nvalid = min(max(nc - i0, 0), SEL_EPT);
+      for (int e = tid; e < M * BINS; e += SEL_THREADS) (&cnt[0][0])[e] = gcnt[e];
+    } else {
+      const bool all = level == 0;                 // every key is in range
+      const uint32_t span0 = rg[0].hi - rg[0].lo, span1 = rg[1].hi - rg[1].lo;
+      KeyGroup next = load_keys(sc, mask, i_begin + 4 * tid, i_end, a.mpa_mode);
+#pragma unroll 1
+      for (int i = i_begin + 4 * tid; i < i_end; i += 4 * SEL_THREADS) {
+        const KeyGroup g = next;
+        next = load_keys(sc, mask, i + 4 * SEL_THREADS, i_end, a.mpa_mode);
+        const uint32_t ids = mask4_ids<MM>(g.mw, top);
+        if (all) {
 #pragma unroll
-      for (int e = 0; e < SEL_EPT; ++e) {
-        const int m = (int)((mbits >> (2 * e)) & 3ULL);
-        bool match = e < nvalid;
-        if (level > 0) match = match && !pick(dn, m) && ((key[e] >> (sh + wd)) == pick(pfx, m));
-        if (match) atomicAdd(&cnt[m][(key[e] >> sh) & binmask], 1u);
+          for (int q = 0; q < 4; ++q)
+            if (i + q < i_end) atomicAdd(&cnt[id_of<MM>(ids, q)][descent_bin(rg[0], float_key(g.x[q]))], 1u);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const uint32_t m = id_of<MM>(ids, q), key = float_key(g.x[q]);
+            const uint32_t lo = MM == 2 ? (m ? rg[1].lo : rg[0].lo) : s_range[m].lo, sp = MM == 2 ? (m ? span1 : span0) : s_range[m].hi - lo;
+            if (i + q < i_end && key - lo <= sp) {
+              const uint32_t s1 = MM == 2 ? (m ? rg[1].sh : rg[0].sh) : s_range[m].sh;
+              atomicAdd(&cnt[m][(key >> s1) - (MM == 2 ? (m ? rg[1].sub : rg[0].sub) : s_range[m].sub)], 1u);
+            }
+          }
+        }
       }
     }
     __syncthreads();
     if (phase == 1) {                              // add the chunk's bins to the head's and leave
-      for (int e = tid; e < M * SEL_BINS; e += SEL_THREADS) {
+      for (int e = tid; e < M * BINS; e += SEL_THREADS) {
         const uint32_t x = (&cnt[0][0])[e];
         if (x) atomicAdd(&gcnt[e], x);
       }
       return;
     }
-    if (wave < M) {
-      const int m = wave;
-      const int nb = 1 << wd;
-      const int per = (nb + 63) / 64;
-      // lane l owns the `per` bins below nb - l * per; it sums them starting at a lane-dependent
-      // offset so that the 64 lanes read different LDS banks
-      uint32_t lc = 0;
+    // the walk from the top bin down, WPM waves per modality: lane 0 of the first of them has the top bins
+    constexpr int WPM = NWAVES / MM, PER = BINS / (WPM * 64);
+    const int m = wave / WPM, part = wave % WPM;
+    const bool walks = m < M && s_alive[min(m, M - 1)] == 1u;
+    const int tb = BINS - 1 - (part * 64 + lane) * PER;       // bins tb, tb - 1, ..., tb - PER + 1
+    uint32_t share = 0u, incl = 0u;
+    if (walks) {
 #pragma unroll
-      for (int j = 0; j < 32; ++j)
-        if (j < per) lc += cnt[m][nb - 1 - (lane * per + ((j + lane) & (per - 1)))];
-      const uint32_t incl = wave_incl_scan_u32(lc);
-      uint32_t need, prefix_prev; bool done;
-      if (level == 0) {
-        const uint32_t ntot = (uint32_t)__shfl((int)incl, 63, 64);
-        const uint32_t bm = pick(bud, m);
-        need = bm < ntot ? bm : ntot;              // a budget above the candidate count keeps them all
-        done = (need == 0);
-        prefix_prev = 0;
-        if (lane == 0) { s_need[m] = need; s_done[m] = done ? 1u : 0u; s_prefix[m] = 0; }
-      } else {
-        need = s_need[m]; prefix_prev = s_prefix[m]; done = s_done[m] != 0;
-      }
-      const uint32_t before = incl - lc;          // elements in higher bins than this lane's
-      const unsigned long long owner = __ballot(!done && before < need && before + lc >= need);
-      if (owner) {
-        // the owner's bins, one per lane, scanned the same way: the bin where the count reaches `need`
-        const int src = __ffsll((long long)owner) - 1;
-        const uint32_t bsrc = (uint32_t)__shfl((int)before, src, 64);
-        const uint32_t v = lane < per ? cnt[m][nb - 1 - (src * per + lane)] : 0u;
-        const uint32_t inc2 = wave_incl_scan_u32(v);
-        const uint32_t bef2 = bsrc + inc2 - v;
-        const unsigned long long hit = __ballot(lane < per && bef2 < need && bef2 + v >= need);
-        const int hl = __ffsll((long long)hit) - 1;
-        const uint32_t acc = (uint32_t)__shfl((int)bef2, hl, 64);
-        if (lane == 0) {
-          s_prefix[m] = (prefix_prev << wd) | (uint32_t)(nb - 1 - (src * per + hl));
-          s_need[m] = need - acc;                   // still needed from inside this bin
+      for (int j = 0; j < PER; ++j) share += cnt[m][tb - j];
+      incl = wave_incl_scan_u32(share);
+      if (lane == 63) s_part[m][part] = incl;
+    }
+    __syncthreads();
+    uint32_t need = 0u;
+    if (walks) {
+      uint32_t total = 0u, before = incl - share;
+#pragma unroll
+      for (int w = 0; w < WPM; ++w) { const uint32_t x = s_part[m][w]; total += x; before += w < part ? x : 0u; }
+      need = min(s_need[m], total);                // (first level: a budget above the candidate count keeps them all)
+      if (before < need && before + share >= need) {          // one lane of one wave: the bin is among its own
+        uint32_t bin = (uint32_t)tb;
+#pragma unroll 1
+        for (;;) {
+          const uint32_t x = cnt[m][bin];
+          if (before + x >= need) break;
+          before += x; --bin;
         }
+        s_before[m] = before; s_bin[m] = bin;
       }
     }
     __syncthreads();
+    if (walks && part == 0 && lane == 0) {         // the next level's state (everybody has read this one's)
+      if (need == 0u) { s_alive[m] = 0u; s_need[m] = 0u; s_range[m] = descent_none(); }     // nothing to keep: tau stays above every key
+      else {
+        const DescentRange r = s_range[m];
+        s_need[m] = need - s_before[m];            // still needed from inside this bin
+        if (r.sh == 0) { s_tau[m] = r.sub + s_bin[m]; s_alive[m] = 2u; s_range[m] = descent_none(); }
+        else s_range[m] = descent_next<SEL_SH1>(r, s_bin[m]);
+      }
+    }
+    __syncthreads();
+    if (phase == 2) break;
+    bool open = false;
+    for (int mm = 0; mm < M; ++mm) open = open || s_alive[mm] == 1u;
+    if (!open) break;
   }
   if (phase == 2) {                                // hand over to the next level, or to the chunks' compaction
-    if (tid < M) { SelCarry cy; cy.prefix = s_prefix[tid]; cy.need = s_need[tid]; cy.done = s_done[tid]; cy.pad = 0; carry[tid] = cy; }
+    if (tid0 < M) {
+      SelCarry cy;
+      cy.range = s_range[tid0]; cy.need = s_need[tid0]; cy.alive = s_alive[tid0]; cy.tau = s_tau[tid0]; cy.pad = 0u;
+      carry[tid0] = cy;
+    }
     return;
   }
-  // tau_m = s_prefix (full key); take every key > tau_m and the first s_need[m] keys == tau_m.
-  uint32_t tau[MM], ties[MM];
+  if (phase >= 3) __syncthreads();
+
+  // take every key > tau_m and the first ties_m keys == tau_m
+  const int lane = tid0 & 63, wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
+  uint32_t tau[MM], ties[MM], run_eq[MM];
 #pragma unroll
   for (int m = 0; m < MM; ++m) {
-    if (m >= M || s_done[m]) { tau[m] = 0xffffffffu; ties[m] = 0; }   // nothing to keep: no key exceeds or (needed) equals it
-    else { tau[m] = s_prefix[m]; ties[m] = s_need[m]; }
+    tau[m] = m < M ? (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tau[m]) : 0xffffffffu;
+    ties[m] = m < M ? (uint32_t)__builtin_amdgcn_readfirstlane((int)s_need[m]) : 0u;
+    run_eq[m] = 0u;
   }
-  __syncthreads();
-
-  uint32_t run_eq[MM];
-#pragma unroll
-  for (int m = 0; m < MM; ++m) run_eq[m] = 0;
-  uint32_t run_out = 0;
+  uint32_t run_gt = 0u;
   if (phase == 4) {
-    // what the chunks in front of this one keep: their sure ones, and of the threshold-valued ones as many as are needed
+    // what the chunks in front of this one have: sure ones and threshold-valued ones
     const SelChunk* ci = a.chunkinfo + (size_t)head * a.nchunks;
-    for (int c = 0; c < c_first; ++c) {
+    for (int c = 0; c < (int)blockIdx.x; ++c) {
       const SelChunk x = ci[c];
-      run_out += x.gt;
+      run_gt += x.gt;
 #pragma unroll
       for (int m = 0; m < MM; ++m) run_eq[m] += (uint32_t)((x.eq >> (16 * m)) & 0xffffULL);
     }
-#pragma unroll
-    for (int m = 0; m < MM; ++m) run_out += min(run_eq[m], ties[m]);
   }
-  for (int c = c_first; c < c_end; ++c) {
-    const int i0 = c * CH + tid * SEL_EPT;
-    if (!single) load_owned(sc, mask, i0, nc, a.mpa_mode, M, key, mbits);
-    const int nvalid = min(max(nc - i0, 0), SEL_EPT);
-    // ties of this thread's stretch, per modality (four 16-bit counts), then their rank by
-    // position over the workgroup
-    unsigned long long eqbits = 0ULL, gtbits = 0ULL, eqcnt = 0ULL;
+  constexpr int NF = MM == 2 ? 2 : 3;              // words of packed counts: {gt, eq0}, {eq1, eq2}, {eq3, -}
+  KeyGroup next = load_keys(sc, mask, i_begin + 4 * tid0, i_end, a.mpa_mode);
+  int buf = 0;
+#pragma unroll 1
+  for (int base = i_begin; base < i_end; base += 4 * SEL_THREADS, buf ^= 1) {
+    const int i = base + 4 * tid0;
+    const KeyGroup g = next;
+    next = load_keys(sc, mask, i + 4 * SEL_THREADS, i_end, a.mpa_mode);
+    const uint32_t ids = mask4_ids<MM>(g.mw, top);
+    uint32_t gtbits = 0u, eqbits = 0u, pk[3] = {0u, 0u, 0u};
 #pragma unroll
-    for (int e = 0; e < SEL_EPT; ++e) {
-      const int m = (int)((mbits >> (2 * e)) & 3ULL);
-      const bool ok = e < nvalid;
-      const uint32_t tm = pick(tau, m);
-      const bool gt = ok && key[e] > tm;
-      const bool eq = ok && key[e] == tm && pick(ties, m) > 0;
-      gtbits |= (unsigned long long)gt << e;
-      eqbits |= (unsigned long long)eq << e;
-      eqcnt += (unsigned long long)eq << (16 * m);
+    for (int q = 0; q < 4; ++q) {
+      const int m = (int)id_of<MM>(ids, q);
+      const uint32_t key = float_key(g.x[q]), t = MM == 2 ? (m ? tau[1] : tau[0]) : s_tau[m];
+      const bool ok = i + q < i_end, gt = ok && key > t, eq = ok && key == t && (MM == 2 ? (m ? ties[1] : ties[0]) : s_need[m]) > 0u;
+      gtbits |= gt ? 1u << q : 0u;
+      eqbits |= eq ? 1u << q : 0u;
+      if (eq) {
+        if (MM == 2) pk[m ? 1 : 0] += m ? 1u : 65536u;
+        else { pk[0] += m == 0 ? 65536u : 0u; pk[1] += m == 1 ? 1u : (m == 2 ? 65536u : 0u); pk[2] += m == 3 ? 1u : 0u; }
+      }
     }
-    unsigned long long eqtot;
-    const unsigned long long eqbefore = block_excl_scan64(eqcnt, wave_tot64, eqtot);
-    if (phase == 3) {                              // report and leave
-      uint32_t gttot;
-      (void)block_excl_scan((uint32_t)__popcll(gtbits), wave_tot, gttot);
-      if (tid == 0) { SelChunk x; x.gt = gttot; x.pad = 0; x.eq = eqtot; a.chunkinfo[(size_t)head * a.nchunks + c] = x; }
-      return;
+    pk[0] += (uint32_t)__popc(gtbits);
+    // exclusive prefix over the workgroup (4096 candidates: 16 bits hold every count)
+    uint32_t ex[3] = {0u, 0u, 0u}, tot[3] = {0u, 0u, 0u};
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      ex[f] = wave_incl_scan_u32(pk[f]);
+      if (lane == 63) s_tot[buf][f][wave] = ex[f];
+      ex[f] -= pk[f];
     }
-    uint32_t rank[MM];
+    __syncthreads();                               // (two buffers: a wave that is a trip ahead writes the other one)
 #pragma unroll
-    for (int m = 0; m < MM; ++m) rank[m] = run_eq[m] + (uint32_t)((eqbefore >> (16 * m)) & 0xffffULL);
-    unsigned long long keepbits = gtbits;
-    if (eqbits) {
+    for (int f = 0; f < NF; ++f) {
+      const uint32_t w = wave_incl_scan_u32(lane < NWAVES ? s_tot[buf][f][lane] : 0u);
+      tot[f] = (uint32_t)__builtin_amdgcn_readlane((int)w, NWAVES - 1);
+      ex[f] += wave ? (uint32_t)__builtin_amdgcn_readlane((int)w, wave - 1) : 0u;
+    }
+    if (phase != 3) {
+      uint32_t rank[MM], pos = run_gt + (ex[0] & 0xffffu);
 #pragma unroll
-      for (int e = 0; e < SEL_EPT; ++e) {
-        if ((eqbits >> e) & 1ULL) {
-          const int m = (int)((mbits >> (2 * e)) & 3ULL);
-          if (pick(rank, m) < pick(ties, m)) keepbits |= 1ULL << e;
+      for (int m = 0; m < MM; ++m) {
+        rank[m] = run_eq[m] + (m == 0 ? ex[0] >> 16 : m == 1 ? ex[1] & 0xffffu : m == 2 ? ex[1] >> 16 : ex[2]);
+        pos += min(rank[m], ties[m]);
+      }
+      if (gtbits | eqbits) {
 #pragma unroll
-          for (int mm = 0; mm < MM; ++mm) rank[mm] += (mm == m) ? 1u : 0u;
+        for (int q = 0; q < 4; ++q) {
+          const int m = (int)id_of<MM>(ids, q);
+          const bool eq = (eqbits >> q) & 1u;
+          if (((gtbits >> q) & 1u) || (eq && pick(rank, m) < (MM == 2 ? (m ? ties[1] : ties[0]) : s_need[m]))) out[pos++] = i + q;
+#pragma unroll
+          for (int mm = 0; mm < MM; ++mm) rank[mm] += eq && mm == m ? 1u : 0u;
         }
       }
     }
-    uint32_t ktot;
-    uint32_t pos = run_out + block_excl_scan((uint32_t)__popcll(keepbits), wave_tot, ktot);
-    while (keepbits) {                            // ascending by construction: lowest set bit first
-      const int e = __ffsll((long long)keepbits) - 1;
-      out[pos++] = i0 + e;
-      keepbits &= keepbits - 1ULL;
-    }
+    run_gt += tot[0] & 0xffffu;
 #pragma unroll
-    for (int m = 0; m < MM; ++m) run_eq[m] += (uint32_t)((eqtot >> (16 * m)) & 0xffffULL);
-    run_out += ktot;
+    for (int m = 0; m < MM; ++m) run_eq[m] += m == 0 ? tot[0] >> 16 : m == 1 ? tot[1] & 0xffffu : m == 2 ? tot[1] >> 16 : tot[2];
   }
-  if (phase == 4 && c_end != nchunks) return;      // the window positions follow the last chunk's
-  for (int r = tid; r < a.W; r += SEL_THREADS) out[run_out + r] = nc + r;
+  if (phase == 3) {                                // report and leave
+    if (tid0 == 0) {
+      SelChunk x;
+      x.gt = run_gt; x.pad = 0u; x.eq = 0ULL;
+#pragma unroll
+      for (int m = 0; m < MM; ++m) x.eq |= (unsigned long long)run_eq[m] << (16 * m);
+      a.chunkinfo[(size_t)head * a.nchunks + blockIdx.x] = x;
+    }
+    return;
+  }
+  if (per_chunk && i_end != nc) return;            // the window positions follow the last chunk's
+  uint32_t kept = run_gt;
+#pragma unroll
+  for (int m = 0; m < MM; ++m) kept += min(run_eq[m], ties[m]);
+  for (int r = tid0; r < a.W; r += SEL_THREADS) out[kept + r] = nc + r;
 }
 
 size_t select_ws_bytes(const Dims& dm, const madakv_config& c) {
@@ -492,7 +446,7 @@ hipError_t launch_select(const Dims& dm, const madakv_config& c, const float* ps
       split_bytes >= split_buffer_bytes(dm.heads, a.M, nchunks)) {
     // per level: the chunks' workgroups add their count histograms into the head's (in memory), one workgroup per head
     // walks it; then every chunk reports what it keeps and writes it behind the chunks in front of it
-    const size_t hist = (size_t)3 * dm.heads * a.M * SEL_BINS;
+    const size_t hist = (size_t)3 * dm.heads * a.M * BINS;
     a.gcnt = reinterpret_cast<uint32_t*>(split_buf);
     a.carry = reinterpret_cast<SelCarry*>(a.gcnt + hist);
     a.chunkinfo = reinterpret_cast<SelChunk*>(a.carry + (size_t)dm.heads * 4);

@@ -171,3 +171,34 @@ def test_statistics_at_edges(L, W, M, pool_k, avg):
             if k_g[0, 0, h, m] != k_o[h, m] and vals.sum() > 1e4 * max(1, vals.size) * 2.0 ** -44:
                 assert PU.k_count_ok(int(k_g[0, 0, h, m]), vals, 0.9), (h, m, k_g[0, 0, h, m], k_o[h, m])
     eng.close()
+
+
+@pytest.mark.parametrize("L,W,M", [(12, 8, 2), (15, 8, 2), (200, 5, 2), (4096 + 8, 8, 2), (4097 + 8, 8, 3), (16383 + 8, 8, 2), (16384 + 8, 8, 4),
+                                   (16385 + 8, 8, 2), (20483 + 1, 1, 4), (70001, 8, 2), (70001, 8, 3)])
+def test_selection_at_edges(L, W, M):
+    """Kept positions, bit for bit, at and around the groups, workgroups and chunks of the selection kernel, with scores
+    inside and outside the range the descent's first level is made for, plateaus of ties across its passes, and
+    negative scores."""
+    H, d, nc = 6, 64, L - W
+    r = np.random.default_rng(L * 7 + M)
+    mh = r.integers(0, M, size=L).astype(np.uint8)
+    pool = np.exp(r.normal(size=(H, nc)) * 2 - 8).astype(np.float32)
+    pool[1] *= 1e-12                                             # all below the first level's range
+    pool[2] *= 1e9                                               # all above it
+    pool[3] = np.repeat(pool[3][::53], 53)[:nc]                  # plateaus
+    pool[4] = -pool[4]
+    pool[5] = np.where(r.random(nc) < 0.5, 0.0, pool[5])         # many zeros
+    n_m = np.array([(mh[:nc] == m).sum() for m in range(M)])
+    bud = np.stack([(n_m * f).astype(np.int32) for f in (0.3, 0.9, 0.01, 0.5, 0.2, 0.8)])
+    eng = MB.MadaKV(n_layers=1, batch=1, n_q_heads=H, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=L - 1, dtype="bf16",
+                    pool_k=1, n_modalities=M, device=DEV)
+    k = torch.zeros(1, 1, H, L, d, dtype=torch.bfloat16, device=DEV)
+    say(f"selection L={L} W={W} M={M}")
+    eng.select_gather(0, 1, k, k, torch.from_numpy(mh)[None].to(DEV), psi_pool=torch.from_numpy(pool)[None, None].to(DEV),
+                      budgets=torch.from_numpy(bud)[None, None].to(DEV))
+    torch.cuda.synchronize()
+    kept, off, ln = eng.kept_idx.cpu().numpy(), eng.kv_off.cpu().numpy()[0, 0], eng.kv_len.cpu().numpy()[0, 0]
+    for h in range(H):
+        ref = O.select_n(pool[h].astype(np.float64), mh, [int(x) for x in bud[h]], L, W)
+        np.testing.assert_array_equal(kept[off[h]:off[h] + ln[h]], ref)
+    eng.close()
