@@ -81,11 +81,12 @@ def _ptr(t):
     if t is None:
         return None
     assert t.is_contiguous(), "tensors passed to the library must be contiguous"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle of torch.cuda.current_stream(), without the Stream object around it
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check(call, rc):
@@ -204,6 +205,8 @@ class MadaKV:
         self.tdtype = torch.bfloat16 if dtype == "bf16" else torch.float32
         with torch.cuda.device(self.device):
             self.h = madakv_create(self.cfg)
+        self._out_dtype = torch.float32 if out_fp32 else self.tdtype
+        self._out_row, self._heads = batch * n_q_heads * head_dim, batch * n_kv_heads
         self.n_call = layers_per_call or n_layers
         s_ws, sel_ws, d_ws = madakv_workspace_bytes(self.h, self.n_call)
         d1 = madakv_workspace_bytes(self.h, 1)[2]
@@ -268,14 +271,21 @@ class MadaKV:
 
     def _check_out(self, out, numel):
         """`out` is written in the handle's output type: a buffer of another type or size would be overrun."""
-        want = torch.float32 if self.cfg.out_fp32 else self.tdtype
+        want = self._out_dtype
         if out.dtype != want or out.numel() < numel:
             raise ValueError(f"out must hold {numel} elements of {want} (out_fp32={self.cfg.out_fp32}); got {out.numel()} of {out.dtype}")
 
     def decode_attn(self, l0, n, q, k_new, v_new, out):
-        self._check_out(out, n * self.cfg.batch * self.cfg.n_q_heads * self.cfg.head_dim)
-        madakv_decode_attn(self.h, l0, n, q, k_new, v_new, self.k_c, self.v_c, self._sl(self.kv_off, l0, n),
-                           self._sl(self.kv_len, l0, n), out, self.decode_ws)
+        # One call per layer and token: with 4 KV heads the kernels take 10 us and this is what a token waits for.  So no
+        # views of the own buffers and no intermediate call: 13.0 -> 8.8 us on the host, 5.5 of them the two launches.
+        self._check_out(out, n * self._out_row)
+        heads0 = l0 * self._heads
+        ws = self.decode_ws
+        rc = lib().madakv_decode_attn(self.h, l0, n, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(self.k_c), _ptr(self.v_c),
+                                      _ptr(self.kv_off) + 8 * heads0, _ptr(self.kv_len) + 4 * heads0, _ptr(out), _ptr(ws),
+                                      ws.numel() * ws.element_size(), _stream())
+        if rc != OK:
+            raise MadaKVError("madakv_decode_attn", rc)
 
     def decode_attn_static(self, l0, n, q, k_new, v_new, out):
         self._check_out(out, n * self.cfg.batch * self.cfg.n_q_heads * self.cfg.head_dim)
