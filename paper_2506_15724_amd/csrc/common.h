@@ -46,6 +46,7 @@ size_t select_ws_bytes(const Dims& dm, const madakv_config& c);
 size_t decode_ws_bytes(const Dims& dm, const madakv_config& c);                             // worst case over head lengths
 size_t decode_ws_bytes_for(const Dims& dm, const madakv_config& c, int longest_rows);     // for a known longest head
 
+struct AllocArgs;
 // Each launcher validates nothing: shapes were checked by the ABI layer.
 hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_win, const void* k, const float* row_lse,
                         float* psi, void* ws, hipStream_t st);
@@ -62,7 +63,7 @@ hipError_t launch_allocate(const Dims& dm, const madakv_config& c, int layer0, c
                            const int32_t* n_mod, int32_t* budgets, long long* pool_state, hipStream_t st);
 hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, const int32_t* budgets,
                           int64_t* kv_off, int32_t* kv_len, long long* cursor_state, int32_t* layer_maxlen, void* ws,
-                          const Paging& pg, int blocks_per_batch, hipStream_t st);
+                          const Paging& pg, int blocks_per_batch, hipStream_t st, const AllocArgs* alloc = nullptr);   // alloc: the allocation in the same launch
 hipError_t launch_select(const Dims& dm, const madakv_config& c, const float* psi_pool, const uint8_t* mask,
                          const int32_t* budgets, const int64_t* kv_off, const int32_t* kv_len, int32_t* kept_idx,
                          hipStream_t st, const int32_t* seg_len = nullptr, const uint8_t* rowmod = nullptr,

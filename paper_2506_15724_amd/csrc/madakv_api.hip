@@ -1,5 +1,6 @@
 // C ABI of the MadaKV hot path: argument validation, the handle, and the order in which
 // the kernels of each call are enqueued.  No arithmetic of the method lives here.
+#include "allocate.h"
 #include "common.h"
 
 #include <algorithm>
@@ -32,13 +33,13 @@ struct madakv_handle {
   void* d_split; size_t split_bytes;   // long contexts: buffer of the chunk-parallel statistics / selection (null otherwise)
   std::vector<int32_t> appended;   // decode rows appended since the last (re-)eviction, per layer
   std::vector<int32_t> gen_base;   // tokens generated before that, per layer (their original positions are ctx_len + 0, 1, ...)
-  // Longest head of each layer after eviction: written by the device, copied to pinned host
-  // memory asynchronously; decode sizes its grid from it once the copy is known to have landed
-  // (event query, never a wait) and from the worst case before that.
+  // Longest head of each layer after eviction: stored by the layout kernel in pinned host memory (d_maxlen is its
+  // device address); decode sizes its grid from it once it is known to have landed
+  // (event query, never a wait) and from the budget before that.
   int32_t* d_maxlen;
   int32_t* h_maxlen;
   hipEvent_t maxlen_event;
-  // per layer: 0 = nothing known (decode sizes its grid for the worst case), 1 = copy enqueued on
+  // per layer: 0 = nothing known (decode sizes its grid for the worst case), 1 = store enqueued on
   // maxlen_stream and covered by maxlen_event, 2 = the value in h_maxlen has landed
   std::vector<uint8_t> maxlen_state;
   hipStream_t maxlen_stream;
@@ -183,18 +184,15 @@ size_t score_ws_for_call(const madakv_config& c, int n) {
   return need;
 }
 
-// Hands the longest segment of layers [layer0, layer0 + n) to the host without waiting: an
-// asynchronous copy into pinned memory plus an event.  A new pass (layer0 == 0) forgets what was
+// Hands the longest segment of layers [layer0, layer0 + n) to the host without waiting: the layout kernel has
+// stored it in pinned memory, an event says when (a copy behind the gather took 4 us of every eviction call).  A new pass (layer0 == 0) forgets what was
 // known about every layer; a failed enqueue leaves the layers of the call unknown.
 hipError_t publish_maxlen(madakv_handle* h, int layer0, int n, hipStream_t st, hipError_t e) {
-  const madakv_config& c = h->cfg;
   if (layer0 == 0) std::fill(h->maxlen_state.begin(), h->maxlen_state.end(), (uint8_t)0);
-  // copies still in flight on another stream are not covered by the event recorded below
+  // stores still in flight on another stream are not covered by the event recorded below
   if (h->maxlen_stream != st)
     for (auto& sflag : h->maxlen_state) if (sflag == 1) sflag = 0;
   for (int l = layer0; l < layer0 + n; ++l) h->maxlen_state[l] = 0;
-  if (e == hipSuccess) e = hipMemcpyAsync(h->h_maxlen + (size_t)layer0 * c.batch, h->d_maxlen + (size_t)layer0 * c.batch,
-                                             sizeof(int32_t) * n * c.batch, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipEventRecord(h->maxlen_event, st);
   if (e == hipSuccess) {
     for (int l = layer0; l < layer0 + n; ++l) h->maxlen_state[l] = 1;
@@ -317,8 +315,8 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
       if (e == hipSuccess) e = hipMalloc(&h->d_split, h->split_bytes);
     }
   }
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&h->d_maxlen), sizeof(int32_t) * cfg->n_layers * cfg->batch);
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&h->h_maxlen), sizeof(int32_t) * cfg->n_layers * cfg->batch, hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&h->d_maxlen), h->h_maxlen, 0);
   if (e == hipSuccess) memset(h->h_maxlen, 0, sizeof(int32_t) * cfg->n_layers * cfg->batch);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->maxlen_event, hipEventDisableTiming);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
@@ -327,7 +325,6 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   for (int g = 0; g < MAX_GROUPS && e == hipSuccess; ++g) e = hipEventCreateWithFlags(&h->ev_grp[g], hipEventDisableTiming);
   for (int g = 0; g < MAX_GROUPS && e == hipSuccess; ++g) e = hipEventCreateWithFlags(&h->ev_sel[g], hipEventDisableTiming);
   if (e != hipSuccess) {
-    if (h->d_maxlen) (void)hipFree(h->d_maxlen);
     if (h->d_page_tbl) (void)hipFree(h->d_page_tbl);
     if (h->d_split) (void)hipFree(h->d_split);
     if (h->h_maxlen) (void)hipHostFree(h->h_maxlen);
@@ -344,7 +341,6 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
 int32_t madakv_destroy(madakv_handle* h) {
   if (!h) return MADAKV_ERR_INVALID_ARG;
   hipError_t e = hipFree(h->d_state);
-  (void)hipFree(h->d_maxlen);
   if (h->d_page_tbl) (void)hipFree(h->d_page_tbl);
   if (h->d_split) (void)hipFree(h->d_split);
   (void)hipHostFree(h->h_maxlen);
@@ -588,9 +584,9 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
       ss = h->side;
     }
     if (e == hipSuccess) e = launch_stats(dg, c, psi_g, mask, pool_g, stats_g, g0 == 0 ? n_mod : nullptr, layer0 + g0, ss, h->d_split, h->split_bytes);
-    if (e == hipSuccess) e = launch_allocate(dg, c, layer0 + g0, stats_g, n_mod, bud_g, h->d_state, ss);
+    const AllocArgs alloc = alloc_args(dg, c, layer0 + g0, stats_g, n_mod, bud_g, h->d_state);
     if (e == hipSuccess) e = launch_offsets(dg, c, layer0 + g0, bud_g, kv_off + heads0, kv_len + heads0, h->d_state + c.batch,
-                                            h->d_maxlen + (size_t)(layer0 + g0) * c.batch, ws_g, make_paging(h), blocks_per_batch(c, ng), ss);
+                                            h->d_maxlen + (size_t)(layer0 + g0) * c.batch, ws_g, make_paging(h), blocks_per_batch(c, ng), ss, &alloc);
     if (e == hipSuccess) e = launch_select(dg, c, pool_g, mask, bud_g, kv_off + heads0, kv_len + heads0, kept_idx, ss, nullptr, nullptr, h->d_split, h->split_bytes);
     if (overlap && e == hipSuccess) e = hipEventRecord(h->ev_sel[gi], h->side);
     // the gather of the group before goes behind this group's sweeps: this group's statistics and

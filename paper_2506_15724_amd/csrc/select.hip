@@ -17,6 +17,7 @@
 //                  thread's candidates, which are read again per level: 9 KB of code instead of 42, one scan instead of
 //                  two in the last pass.  In the path, before -> after: 27.6 -> 11.3 us (8 heads of 1K candidates),
 //                  29.5 -> 18.7 (32 of 8K), 35 -> 29 (128 of 16K), re-eviction's 1024 heads of 2K rows 87 -> 27.
+#include "allocate.h"
 #include "descent.h"
 
 namespace madakv {
@@ -46,7 +47,9 @@ struct OffsetsArgs {
 constexpr int OFF_THREADS = 256;
 constexpr int OFF_MAX_LAYERS = 1024;
 
-__global__ __launch_bounds__(OFF_THREADS) void offsets_kernel(OffsetsArgs a) {
+// ALLOC: the first wave does the batch item's budget allocation first (madakv_evict: one launch less).
+template <bool ALLOC>
+__global__ __launch_bounds__(OFF_THREADS) void offsets_kernel(OffsetsArgs a, AllocArgs al) {
   __shared__ long long s_wtot[OFF_THREADS / 64];
   __shared__ long long s_used;
   __shared__ int s_first_bad;
@@ -58,6 +61,11 @@ __global__ __launch_bounds__(OFF_THREADS) void offsets_kernel(OffsetsArgs a) {
   const long long region = (long long)b * a.region_tokens;
   const long long blk_base = start / GATHER_ROWS;            // the block table is relative to the call's first block
   for (int li = tid; li < a.n; li += OFF_THREADS) s_lmax[li] = 0;
+  if (ALLOC) {                                                // (totals and budgets go through memory to the threads that read them)
+    if (wave == 0) allocate_wave(al, b, lane);
+    __syncthreads();
+    split_totals(al, b, tid, OFF_THREADS);
+  }
   if (tid == 0) { s_first_bad = 0x7fffffff; s_used = 0; }
   if (tid == 0 && a.page_rows && a.layer0 == 0) a.pool_top[b] = 0ULL;   // a new pass: every page taken for appended rows is free again
   __syncthreads();
@@ -417,7 +425,7 @@ size_t select_ws_bytes(const Dims& dm, const madakv_config& c) {
 
 hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, const int32_t* budgets,
                           int64_t* kv_off, int32_t* kv_len, long long* cursor_state, int32_t* layer_maxlen, void* ws,
-                          const Paging& pg, int blocks_per_batch, hipStream_t st) {
+                          const Paging& pg, int blocks_per_batch, hipStream_t st, const AllocArgs* alloc) {
   OffsetsArgs a;
   a.layer_maxlen = layer_maxlen;
   a.budgets = budgets; a.kv_off = kv_off; a.kv_len = kv_len; a.cursor = cursor_state;
@@ -427,7 +435,8 @@ hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, co
   a.max_new = c.max_new_tokens; a.keep_all = c.budget >= c.ctx_len ? 1 : 0;
   a.blocks_per_batch = blocks_per_batch; a.region_tokens = pg.region_tokens; a.init_limit = pg.init_limit;
   a.page_rows = pg.page_rows; a.tbl_entries = pg.entries; a.page_tbl = pg.table; a.pool_top = pg.pool_top;
-  hipLaunchKernelGGL(offsets_kernel, dim3(dm.B), dim3(OFF_THREADS), 0, st, a);
+  if (alloc) hipLaunchKernelGGL((offsets_kernel<true>), dim3(dm.B), dim3(OFF_THREADS), 0, st, a, *alloc);
+  else hipLaunchKernelGGL((offsets_kernel<false>), dim3(dm.B), dim3(OFF_THREADS), 0, st, a, AllocArgs{});
   return hipGetLastError();
 }
 
