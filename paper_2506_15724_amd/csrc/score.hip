@@ -333,7 +333,11 @@ constexpr int DMA_NBUF = 3;
 typedef __attribute__((address_space(3))) void* lds_void_ptr_t;
 typedef const __attribute__((address_space(1))) void* global_void_ptr_t;
 
-template <int D, int NW, int NRB, int DMA_TK, int BS, int PASS>   // NW waves of NRB row blocks each; tiles of DMA_TK keys; the vector arithmetic runs on BS subtiles at a time
+// NW waves of NRB row blocks each; tiles of DMA_TK keys; the vector arithmetic runs on BS subtiles at a time.
+// CLOSE (sweep 1 for the last-window attention, whose entries get their final value from these statistics): a row's sum is
+// rescaled by the difference of the maxima as rounded, and the terms of a subtile are added among themselves first;
+// log-sum-exp within 5e-6 instead of 1e-5, at the same speed.
+template <int D, int NW, int NRB, int DMA_TK, int BS, int PASS, bool CLOSE = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS == 1 ? MADAKV_P1_WPE : 2, PASS == 1 ? MADAKV_P1_WPE : 2))) void score_wide_dma_kernel(ScoreArgs a) {
   constexpr int NT = NW * 64;
   constexpr int KS = D / 16;                  // MFMA k-steps
@@ -368,7 +372,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
   // other way round (S^T = K Q^T: a lane holds ONE row and 16 keys of a subtile), so its running (max in
   // accumulator units, sum) is one pair per lane and block: row_m, row_l.
   float st_m[PASS == 2 ? NRB : 1][16];
-  float row_m[NRB], row_l[NRB];
+  float row_m[NRB], row_ms[NRB], row_l[NRB];    // (row_ms: the maximum in logit units, as rounded)
   if (PASS == 2) {
     const float* rs = a.rowstat + (long long)head * a.nsplit * a.mpad * 2;
     for (int r = tid; r < a.mpad; r += NT) {
@@ -390,7 +394,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
       if (PASS == 2) st_m[b][j] = row < a.mpad ? offs[row] : __builtin_inff();
     }
 #pragma unroll
-  for (int b = 0; b < NRB; ++b) { row_m[b] = NEG_BIG; row_l[b] = 0.f; }
+  for (int b = 0; b < NRB; ++b) { row_m[b] = NEG_BIG; row_ms[b] = 0.f; row_l[b] = 0.f; }
   __syncthreads();                             // (the last ordinary LDS access of the kernel)
 
   // tile T of the chunk -> ring slot T mod 3.  Load j of wave w fills bytes [(w LPT + j) 1024, + 1024) of the slot:
@@ -494,11 +498,20 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
       }                                                                                              \
       float mn = row_m[b];                                                                           \
       _Pragma("unroll") for (int j = 0; j < 16; ++j) mn = fmaxf(mn, xt[j]);                          \
-      float l = row_l[b] * fast_exp2((row_m[b] - mn) * a.scale_log2);                                \
       /* (no key of the row seen yet: every x is NEG_BIG too, and x * scale - round(NEG_BIG * scale) would be the   \
          product's rounding error, some 1e21 of either sign; against 0 the terms are exp2(-huge) = 0) */            \
       const float ms = mn > 0.5f * NEG_BIG ? mn * a.scale_log2 : 0.f;                                \
-      _Pragma("unroll") for (int j = 0; j < 16; ++j) l += fast_exp2(fmaf(xt[j], a.scale_log2, -ms)); \
+      float l;                                                                                       \
+      if (CLOSE) {                                                                                   \
+        l = row_m[b] > 0.5f * NEG_BIG ? row_l[b] * fast_exp2(row_ms[b] - ms) : 0.f;                  \
+        _Pragma("unroll") for (int j = 0; j < 16; ++j) xt[j] = fast_exp2(fmaf(xt[j], a.scale_log2, -ms)); \
+        _Pragma("unroll") for (int o = 8; o >= 1; o >>= 1) { _Pragma("unroll") for (int j = 0; j < o; ++j) xt[j] += xt[j + o]; } \
+        l += xt[0];                                                                                  \
+      } else {                                                                                       \
+        l = row_l[b] * fast_exp2((row_m[b] - mn) * a.scale_log2);                                    \
+        _Pragma("unroll") for (int j = 0; j < 16; ++j) l += fast_exp2(fmaf(xt[j], a.scale_log2, -ms)); \
+      }                                                                                              \
+      row_ms[b] = ms;                                                                                \
       row_m[b] = mn; row_l[b] = l;                                                                   \
     }
 #pragma unroll 1
@@ -601,12 +614,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
     float* rs = a.rowstat + ((long long)head * a.nsplit + split) * a.mpad * 2;
 #pragma unroll
     for (int b = 0; b < NRB; ++b) {
-      const float m2 = __shfl_xor(row_m[b], 32, 64), l2 = __shfl_xor(row_l[b], 32, 64);
-      const float m = fmaxf(row_m[b], m2);
-      const float l = row_l[b] * fast_exp2((row_m[b] - m) * a.scale_log2) + l2 * fast_exp2((m2 - m) * a.scale_log2);
+      float m, l;                               // (m in logit units)
+      if (CLOSE) {
+        const float ms = row_m[b] > 0.5f * NEG_BIG ? row_ms[b] : NEG_BIG;
+        const float m2 = __shfl_xor(ms, 32, 64), l2 = __shfl_xor(row_l[b], 32, 64);
+        m = fmaxf(ms, m2);
+        l = row_l[b] * fast_exp2(ms - m) + l2 * fast_exp2(m2 - m);
+      } else {
+        const float m2 = __shfl_xor(row_m[b], 32, 64), l2 = __shfl_xor(row_l[b], 32, 64);
+        const float mx = fmaxf(row_m[b], m2);
+        l = row_l[b] * fast_exp2((row_m[b] - mx) * a.scale_log2) + l2 * fast_exp2((m2 - mx) * a.scale_log2);
+        m = mx * a.scale_log2;
+      }
       if (rb0 + b < MB && half == 0) {
         const int row = (rb0 + b) * 32 + col;
-        rs[row * 2] = m * a.scale_log2; rs[row * 2 + 1] = l;
+        rs[row * 2] = m; rs[row * 2 + 1] = l;
       }
     }
   }
@@ -1055,8 +1077,8 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_fused_finish_kernel(Score
 // ------------------------------------------------------------------------------------
 // The prefill attention of the last W prompt positions (paper Sec. 3.1 Eq. 5 for the proxy rows of
 // Sec. 3.3) with the proxy-token scores of Eq. 7 as a by-product: out = softmax(scale Q K^T) V for
-// a block of up to 32 of the G*W proxy rows of a KV head (more rows: more blocks, each with a pass of its own over
-// K and V, their column sums added in block order afterwards), their log-sum-exp, and psi = the column sums of the same
+// a block of up to 32 of the G*W proxy rows of a KV head (up to 64 rows: two blocks, each with a pass of its own over
+// K and V, their column sums added in block order afterwards; more rows: window_wide_kernel below), their log-sum-exp, and psi = the column sums of the same
 // softmax rows.  A model's prefill runs this attention anyway; taking psi from it removes the
 // eviction's own sweep over K.
 // Same structure as score_fused_kernel (a workgroup's logits stay in registers while the row
@@ -1287,6 +1309,269 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2
     for (int e = tid; e < 32 * CR; e += SCORE_THREADS) {
       const int m = e / CR, c = e % CR;
       op[m * D + rd * CR + c] = ((fl[(0 * 32 + m) * CR + c] + fl[(1 * 32 + m) * CR + c]) + fl[(2 * 32 + m) * CR + c]) + fl[(3 * 32 + m) * CR + c];
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// The same for more than 64 proxy rows (grouped queries): one pass over K and V for all of them instead of one per
+// block of 32.  The row statistics come from sweep 1 of the wide scoring kernels (a pass over K of its own), so the softmax
+// entries are final when they are formed: nothing is exchanged, O is never rescaled, and a workgroup may take as many keys
+// as suits the chip.  Wave w owns the rows of block w (Q fragments and 32 x d of O in registers), the waves share the keys:
+// tiles of K and V come straight into a ring of three (global_load_lds, as in score_wide_dma_kernel, all LDS traffic of the
+// loop written out for the same reason).  Per 32 keys: S^T = K Q^T (a lane holds one row against 16 keys), exp2, the
+// row-wise sums for psi over the lanes, P as bf16 hi + lo parts straight from those registers into O += P V, the V
+// fragments through transposing LDS reads (four keys of 16 columns per 16 lanes).  The 16-byte pieces of a row are permuted
+// in the tile so that both kinds of reads are spread over all banks (tile_swizzle).
+// Bound by the vector unit and the matrix unit together (per logit one exp2, two conversions and 3 instructions of
+// the sum over rows; 24 matrix instructions per 32 keys and block), two waves per SIMD to overlap them.
+// 28 layers x 4 heads of 32K keys with 224 rows: 2.73 ms in seven passes -> 1.22 ms for the whole call (sweep 1 0.34, this
+// kernel 0.80: K and V once is 1.9 GB, 0.3 ms; the matrix instructions alone 0.35 ms).
+// ------------------------------------------------------------------------------------
+template <int D> __device__ __forceinline__ int tile_swizzle(int row) {       // piece c of a row sits in slot c ^ tile_swizzle(row)
+  return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : ((row & 2) << 1) | ((row >> 2) & 3);
+}
+
+// sums over the 32 lanes of a half wave of 16 values each, except for the last step: lanes 16 apart keep their halves.
+// Lane c (its low four bits) ends with value c.  Fixed order.
+__device__ __forceinline__ float lanes_sum16(const float (&v)[16], int lane) {
+#define MADAKV_XCHG(ctrl, x) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), ctrl, 0xF, 0xF, true))
+  float a[8], b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) { const bool u = lane & 8; const float send = u ? v[i] : v[i + 8]; a[i] = (u ? v[i + 8] : v[i]) + MADAKV_XCHG(0x140, send); }   // row_mirror
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { const bool u = lane & 4; const float send = u ? a[i] : a[i + 4]; b[i] = (u ? a[i + 4] : a[i]) + MADAKV_XCHG(0x141, send); }   // row_half_mirror
+#pragma unroll
+  for (int i = 0; i < 2; ++i) { const bool u = lane & 2; const float send = u ? b[i] : b[i + 2]; c[i] = (u ? b[i + 2] : b[i]) + MADAKV_XCHG(0x1B, send); }    // quad_perm [3,2,1,0]
+  const bool u = lane & 1;
+  const float send = u ? c[0] : c[1];
+  return (u ? c[1] : c[0]) + MADAKV_XCHG(0xB1, send);                                                                                                          // quad_perm [1,0,3,2]
+#undef MADAKV_XCHG
+}
+
+constexpr float WINDOW_THIRD_PART_FROM = 0.0625f;
+template <int D, int NW>   // NW waves of one row block each
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void window_wide_kernel(WinArgs wa) {
+  const ScoreArgs& a = wa.s;
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+  typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+  constexpr int NT = NW * 64, TK = NW * 8;    // keys per tile
+  constexpr int KS = D / 16, DB = D / 32, PPR = D / 8, ROWB = D * 2;
+  constexpr int TILEB = TK * ROWB;            // one of K, one of V per ring slot
+  constexpr int LPT = 2 * TK * PPR / NT;      // load instructions per thread and tile
+  constexpr int NPART = 2 * NW;               // shares of a key's psi: per wave one of rows 0-15 and one of rows 16-31 of its block
+  static_assert(LPT == 4 || LPT == 2, "the wait below is written for these");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const uint32_t ring_lds = (uint32_t)(uintptr_t)smem, red_lds = ring_lds + DMA_NBUF * 2 * TILEB;    // red: [2][NPART][TK] floats
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int split = blockIdx.x, head = a.head0 + blockIdx.y, kvh = head % a.H;
+  const long long lb = head / a.H;
+  const uint16_t* qg = reinterpret_cast<const uint16_t*>(a.q_win) + (lb * a.H + kvh) * (long long)a.G * a.W * D;
+  const unsigned char* kg = reinterpret_cast<const unsigned char*>(a.k) + (long long)head * a.L * ROWB;
+  const unsigned char* vg = reinterpret_cast<const unsigned char*>(wa.v) + (long long)head * a.L * ROWB;
+  const int chunk0 = split * a.chunk, chunk1 = min(a.L, chunk0 + a.chunk);
+  const int ntiles = (chunk1 - chunk0 + TK - 1) / TK;
+  const int half = lane >> 5, col = lane & 31;
+  const int row = wave * 32 + col;            // this lane's proxy row
+  const bool active = wave < a.rb_count;      // (uniform) the wave has a block
+  const int first_masked = a.L - a.W + 1;     // keys below this are visible to every proxy row
+  const int pos = a.L - a.W + (row % a.W);    // last key the row sees
+
+#define MADAKV_WW_ISSUE(T)                                                                           \
+  {                                                                                                  \
+    const int tt = (T);                                                                              \
+    const int lt0 = chunk0 + tt * TK;                                                                \
+    const uint32_t slot_lds = ring_lds + (uint32_t)(tt % DMA_NBUF) * (2 * TILEB);                    \
+    _Pragma("unroll") for (int j = 0; j < LPT; ++j) {                                                \
+      const int first = __builtin_amdgcn_readfirstlane((wave * LPT + j) * 64);                       \
+      const bool is_v = first >= TK * PPR;                                                           \
+      const int piece = first - (is_v ? TK * PPR : 0) + lane;                                        \
+      const int r = piece / PPR;                                                                     \
+      const int lkey = min(lt0 + r, a.L - 1);                                                        \
+      const unsigned char* src = (is_v ? vg : kg) + (long long)lkey * ROWB + (((piece % PPR) ^ tile_swizzle<D>(r)) * 16); \
+      const uint32_t dst = __builtin_amdgcn_readfirstlane(slot_lds + (uint32_t)first * 16u);         \
+      __builtin_amdgcn_global_load_lds((global_void_ptr_t)(uintptr_t)src, (lds_void_ptr_t)(uintptr_t)dst, 16, 0, 0); \
+    }                                                                                                \
+  }
+  // the row's offset (max + log2 sum over all its keys) and its Q fragments: before the first key is on its way
+  // (maximum and 1 / sum kept apart: max + log2(sum) rounds to 1e-6 of every entry)
+  float rmax = __builtin_inff(), rinv = 0.f;  // padding rows: exp2(-inf) = 0
+  bf16x8_t qfrag[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    uint4 val = make_uint4(0, 0, 0, 0);
+    if (row < a.M) val = *reinterpret_cast<const uint4*>(qg + (long long)row * D + half * (D / 2) + ks * 8);
+    qfrag[ks] = __builtin_bit_cast(bf16x8_t, val);
+  }
+  if (row < a.M) {
+    const float* rs = a.rowstat + (long long)head * a.nsplit * a.mpad * 2 + row * 2;
+    rmax = rs[0]; rinv = 1.0f / rs[1];
+    if (split == 0 && half == 0 && wa.lse) wa.lse[(lb * a.H + kvh) * (long long)a.G * a.W + row] = (rs[0] + log2f(rs[1])) * 0.6931471805599453f;
+  }
+  MADAKV_WW_ISSUE(0)
+  MADAKV_WW_ISSUE(min(1, ntiles - 1))
+
+  // where this lane's operand pieces sit, relative to a 32-key subtile's first byte
+  uint32_t koff[KS], voff[2][DB];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) koff[ks] = (uint32_t)(col * ROWB + (((half * KS + ks) ^ tile_swizzle<D>(col)) * 16));
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      const int r = 8 * e + 4 * half + ((lane >> 2) & 3), c = 4 * db + 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
+      voff[e][db] = (uint32_t)(r * ROWB + ((c ^ tile_swizzle<D>(r)) * 16) + (lane & 1) * 8);
+    }
+  f32x16_t oacc[DB];                          // O[row 8 (j >> 2) + 4 half + (j & 3) of the block][column 32 db + col]
+#pragma unroll
+  for (int db = 0; db < DB; ++db) oacc[db] = f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+  // psi of the keys of tile T: their shares added in wave order
+#define MADAKV_WW_PSI(T)                                                                             \
+  if (tid < TK) {                                                                                    \
+    const int key = chunk0 + (T) * TK + tid;                                                         \
+    const uint32_t r4 = red_lds + (uint32_t)((((T) & 1) * NPART * TK + tid) * 4);                    \
+    float sum = 0.f;                                                                                 \
+    _Pragma("unroll") for (int w = 0; w < NPART; w += 4) {                                           \
+      float c0, c1, c2, c3;                                                                          \
+      asm volatile("ds_read_b32 %0, %4\n\tds_read_b32 %1, %5\n\tds_read_b32 %2, %6\n\tds_read_b32 %3, %7\n\ts_waitcnt lgkmcnt(0)" \
+                   : "=&v"(c0), "=&v"(c1), "=&v"(c2), "=&v"(c3)                                      \
+                   : "v"(r4 + w * TK * 4), "v"(r4 + (w + 1) * TK * 4), "v"(r4 + (w + 2) * TK * 4), "v"(r4 + (w + 3) * TK * 4) : "memory"); \
+      sum = (((sum + c0) + c1) + c2) + c3;                                                           \
+    }                                                                                                \
+    if (key < chunk1) __builtin_nontemporal_store(sum, a.psi + ((long long)head * a.L + key));       \
+  }
+
+  for (int t = 0; t < ntiles; ++t) {
+    // tile t has landed (the loads of tile t + 1 may still be out), this wave's LDS accesses of the last trip are
+    // done; after the barrier that holds for every wave, and nobody reads tile t - 1 any more
+    if (LPT == 4) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    MADAKV_WW_ISSUE(min(t + 2, ntiles - 1))    // into the slot of tile t - 1 (past the end: the last tile once more, which keeps the count of loads in flight)
+    if (t > 0) { MADAKV_WW_PSI(t - 1) }
+    const uint32_t tile_lds = ring_lds + (uint32_t)(t % DMA_NBUF) * (2 * TILEB);
+    const int tile_end = chunk0 + (t + 1) * TK;
+    const bool tail = tile_end > first_masked || tile_end > chunk1;
+    if (active) {
+#pragma unroll 1
+      for (int s0 = 0; s0 < TK / 32; ++s0) {
+        const uint32_t kb = tile_lds + (uint32_t)s0 * 32 * ROWB, vb0 = kb + TILEB;
+        bf16x8_t kfrag[KS];
+        if constexpr (KS == 8) {
+          asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+                       "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\t"
+                       "s_waitcnt lgkmcnt(0)"
+                       : "=&v"(kfrag[0]), "=&v"(kfrag[1]), "=&v"(kfrag[2]), "=&v"(kfrag[3]), "=&v"(kfrag[4 % KS]), "=&v"(kfrag[5 % KS]), "=&v"(kfrag[6 % KS]), "=&v"(kfrag[7 % KS])
+                       : "v"(kb + koff[0]), "v"(kb + koff[1]), "v"(kb + koff[2]), "v"(kb + koff[3]),
+                         "v"(kb + koff[4 % KS]), "v"(kb + koff[5 % KS]), "v"(kb + koff[6 % KS]), "v"(kb + koff[7 % KS]) : "memory");
+        } else {
+          asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+                       : "=&v"(kfrag[0]), "=&v"(kfrag[1]), "=&v"(kfrag[2]), "=&v"(kfrag[3])
+                       : "v"(kb + koff[0]), "v"(kb + koff[1]), "v"(kb + koff[2]), "v"(kb + koff[3]) : "memory");
+        }
+        f32x16_t x = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag[ks], qfrag[ks], x, 0, 0, 0);
+        // V fragments of both 16-key steps, under the contraction: vr[st][e][db] = keys 16 st + 8 e + 4 half .. + 3 of column 32 db + col
+        u32x2_t vr[2][2][DB];
+        if constexpr (DB == 4) {
+          asm volatile("ds_read_b64_tr_b16 %0, %16\n\tds_read_b64_tr_b16 %1, %17\n\tds_read_b64_tr_b16 %2, %18\n\tds_read_b64_tr_b16 %3, %19\n\t"
+                       "ds_read_b64_tr_b16 %4, %20\n\tds_read_b64_tr_b16 %5, %21\n\tds_read_b64_tr_b16 %6, %22\n\tds_read_b64_tr_b16 %7, %23\n\t"
+                       "ds_read_b64_tr_b16 %8, %16 offset:4096\n\tds_read_b64_tr_b16 %9, %17 offset:4096\n\tds_read_b64_tr_b16 %10, %18 offset:4096\n\tds_read_b64_tr_b16 %11, %19 offset:4096\n\t"
+                       "ds_read_b64_tr_b16 %12, %20 offset:4096\n\tds_read_b64_tr_b16 %13, %21 offset:4096\n\tds_read_b64_tr_b16 %14, %22 offset:4096\n\tds_read_b64_tr_b16 %15, %23 offset:4096\n\t"
+                       "s_waitcnt lgkmcnt(0)"
+                       : "=&v"(vr[0][0][0]), "=&v"(vr[0][0][1]), "=&v"(vr[0][0][2 % DB]), "=&v"(vr[0][0][3 % DB]),
+                         "=&v"(vr[0][1][0]), "=&v"(vr[0][1][1]), "=&v"(vr[0][1][2 % DB]), "=&v"(vr[0][1][3 % DB]),
+                         "=&v"(vr[1][0][0]), "=&v"(vr[1][0][1]), "=&v"(vr[1][0][2 % DB]), "=&v"(vr[1][0][3 % DB]),
+                         "=&v"(vr[1][1][0]), "=&v"(vr[1][1][1]), "=&v"(vr[1][1][2 % DB]), "=&v"(vr[1][1][3 % DB])
+                       : "v"(vb0 + voff[0][0]), "v"(vb0 + voff[0][1]), "v"(vb0 + voff[0][2 % DB]), "v"(vb0 + voff[0][3 % DB]),
+                         "v"(vb0 + voff[1][0]), "v"(vb0 + voff[1][1]), "v"(vb0 + voff[1][2 % DB]), "v"(vb0 + voff[1][3 % DB]) : "memory");
+        } else {
+          asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %9\n\tds_read_b64_tr_b16 %2, %10\n\tds_read_b64_tr_b16 %3, %11\n\t"
+                       "ds_read_b64_tr_b16 %4, %8 offset:2048\n\tds_read_b64_tr_b16 %5, %9 offset:2048\n\tds_read_b64_tr_b16 %6, %10 offset:2048\n\tds_read_b64_tr_b16 %7, %11 offset:2048\n\t"
+                       "s_waitcnt lgkmcnt(0)"
+                       : "=&v"(vr[0][0][0]), "=&v"(vr[0][0][1]), "=&v"(vr[0][1][0]), "=&v"(vr[0][1][1]),
+                         "=&v"(vr[1][0][0]), "=&v"(vr[1][0][1]), "=&v"(vr[1][1][0]), "=&v"(vr[1][1][1])
+                       : "v"(vb0 + voff[0][0]), "v"(vb0 + voff[0][1]), "v"(vb0 + voff[1][0]), "v"(vb0 + voff[1][1]) : "memory");
+        }
+        if (tail) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const int key = chunk0 + t * TK + s0 * 32 + 8 * (j >> 2) + 4 * half + (j & 3);
+            x[j] = key < chunk1 && key <= pos ? x[j] : NEG_BIG;
+          }
+        }
+        float pv[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) pv[j] = fast_exp2(fmaf(x[j], a.scale_log2, -rmax));
+        // Two bf16 parts leave 2^-18 of an entry, which shows where the entry is large (the row's largest is 1): there a third
+        // part goes in as well, so that the error against 64 bits stays below what exponentiating against every wave's own
+        // maximum gave (32K keys: 0.75e-6 of the result, two parts 1.13e-6, the kernel above 1.04e-6; from 1/4 on 0.78e-6, from 1/64
+        // on 0.74e-6, a few per cent of the time apart).
+        float big = pv[0];
+#pragma unroll
+        for (int j = 1; j < 16; ++j) big = fmaxf(big, pv[j]);
+        const bool three = __any(big > WINDOW_THIRD_PART_FROM);
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+          uint32_t hi[4], lo[4];
+          f32x2_t left[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const f32x2_t p2 = {pv[8 * st + 2 * i], pv[8 * st + 2 * i + 1]};
+            hi[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(p2, bf16x2_t));          // round to nearest even
+            const f32x2_t rest = {p2[0] - bf16_lo(hi[i]), p2[1] - bf16_hi(hi[i])};
+            lo[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2_t));
+            left[i] = f32x2_t{rest[0] - bf16_lo(lo[i]), rest[1] - bf16_hi(lo[i])};
+          }
+          const bf16x8_t ph = __builtin_bit_cast(bf16x8_t, u32x4_t{hi[0], hi[1], hi[2], hi[3]}), pl = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[0], lo[1], lo[2], lo[3]});
+#pragma unroll
+          for (int db = 0; db < DB; ++db) {
+            const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, u32x4_t{vr[st][0][db][0], vr[st][0][db][1], vr[st][1][db][0], vr[st][1][db][1]});
+            oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ph, vf, oacc[db], 0, 0, 0);
+            oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pl, vf, oacc[db], 0, 0, 0);
+          }
+          if (three) {
+            uint32_t ll[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ll[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(left[i], bf16x2_t));
+            const bf16x8_t p3 = __builtin_bit_cast(bf16x8_t, u32x4_t{ll[0], ll[1], ll[2], ll[3]});
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+              const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, u32x4_t{vr[st][0][db][0], vr[st][0][db][1], vr[st][1][db][0], vr[st][1][db][1]});
+              oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p3, vf, oacc[db], 0, 0, 0);
+            }
+          }
+        }
+        // Eq. 7: this wave's shares of the 32 keys' psi (lane c of a 16-lane row: the key of accumulator register c)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) pv[j] *= rinv;
+        const float cs = lanes_sum16(pv, lane);
+        const int c16 = lane & 15;
+        const uint32_t dst = red_lds + (uint32_t)((((t & 1) * NPART + wave * 2 + ((lane >> 4) & 1)) * TK + s0 * 32 + 8 * (c16 >> 2) + 4 * half + (c16 & 3)) * 4);
+        asm volatile("ds_write_b32 %0, %1" :: "v"(dst), "v"(cs) : "memory");
+      }
+    } else {                                    // a wave without rows: nothing to add
+      for (int x = lane; x < 2 * TK; x += 64) {
+        const uint32_t dst = red_lds + (uint32_t)((((t & 1) * NPART + wave * 2) * TK + x) * 4);
+        asm volatile("ds_write_b32 %0, %1" :: "v"(dst), "v"(0.f) : "memory");
+      }
+    }
+  }
+#undef MADAKV_WW_ISSUE
+  // nothing may still be on its way into this workgroup's LDS when it ends
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  MADAKV_WW_PSI(ntiles - 1)
+#undef MADAKV_WW_PSI
+  if (active) {                                 // this chunk's share of O
+    float* op = wa.opart + (((long long)head * a.rb_count + wave) * a.fsplit + split) * 32 * D;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int m = 8 * (j >> 2) + 4 * half + (j & 3);
+      const float f = __shfl(rinv, m, 64);      // the factor of row m sits in lane m
+#pragma unroll
+      for (int db = 0; db < DB; ++db) op[m * D + db * 32 + col] = oacc[db][j] * f;
     }
   }
 }
@@ -1567,32 +1852,33 @@ static void launch_mfma_pair(const ScoreArgs& a0, int heads, size_t lds1, size_t
   hipLaunchKernelGGL((score_mfma_kernel<D, NRB, 2>), grid, dim3(SCORE_THREADS), lds2, st, a);
 }
 
-// more than 64 proxy rows (up to 128 with WIDE8 = false, else up to 256)
+// More than 64 proxy rows (up to 128 with WIDE8 = false, else up to 256).  Both sweeps: four waves of one or two row blocks,
+// tiles of 64 keys.  Sweep 1 leaves every row's (max, sum) over the head's keys in the first chunk's slot.
+template <int D, bool WIDE8, bool CLOSE>
+static void launch_wide_sweep1(const ScoreArgs& a, int heads, hipStream_t st) {
+  constexpr int NRB1 = WIDE8 ? 2 : 1;
+  const size_t lds1 = (size_t)DMA_NBUF * 64 * D * 2;
+  if (lds1 > 48 * 1024)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_wide_dma_kernel<D, 4, NRB1, 64, 1, 1, CLOSE>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
+  hipLaunchKernelGGL((score_wide_dma_kernel<D, 4, NRB1, 64, 1, 1, CLOSE>), dim3(a.nsplit, heads), dim3(256), lds1, st, a);
+  hipLaunchKernelGGL(score_combine_kernel, dim3(heads), dim3(256), 0, st, a);
+}
 template <int D, bool WIDE8>
 static void launch_wide_pair(const ScoreArgs& a0, int heads, hipStream_t st) {
   ScoreArgs a = a0;
-  dim3 grid(a.nsplit, heads);
-  // both sweeps: four waves of one (up to 128 rows) or two row blocks, tiles of 64 keys, two workgroups per CU
-  constexpr int NW1 = 4, NRB1 = WIDE8 ? 2 : 1, NRB2 = NRB1;
-  constexpr int TK1 = 64, BS1 = 1, BS2 = WIDE8 ? 1 : 2;     // (sweep 2: what the registers hold)
-  const size_t lds1 = (size_t)DMA_NBUF * TK1 * D * 2;
+  constexpr int NRB2 = WIDE8 ? 2 : 1;
+  constexpr int BS2 = WIDE8 ? 1 : 2;            // (sweep 2: what the registers hold)
   const size_t lds2 = (size_t)DMA_NBUF * 64 * D * 2 + ((size_t)a.mpad + 2 * 4 * 64) * sizeof(float);
-  static size_t allowed[2][64] = {};            // (per instantiation and device; set again only when a call needs more)
+  static size_t allowed[64] = {};               // (per instantiation and device; set again only when a call needs more)
   int dev = 0;
   (void)hipGetDevice(&dev);
-  size_t& allowed1 = allowed[0][dev & 63];
-  size_t& allowed2 = allowed[1][dev & 63];
-  if (lds1 > allowed1) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_wide_dma_kernel<D, NW1, NRB1, TK1, BS1, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
-    allowed1 = lds1;
-  }
+  size_t& allowed2 = allowed[dev & 63];
   if (lds2 > allowed2) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_wide_dma_kernel<D, 4, NRB2, 64, BS2, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
     allowed2 = lds2;
   }
   if (!a.lse) {
-    hipLaunchKernelGGL((score_wide_dma_kernel<D, NW1, NRB1, TK1, BS1, 1>), grid, dim3(NW1 * 64), lds1, st, a);
-    hipLaunchKernelGGL(score_combine_kernel, dim3(heads), dim3(256), 0, st, a);
+    launch_wide_sweep1<D, WIDE8, false>(a, heads, st);
     a.nmerge = 1;
   }
   // sweep 2 in chunks of its own (about two workgroups per CU); a.nsplit stays what the row statistics are laid out by
@@ -1671,6 +1957,47 @@ size_t window_attn_ws_bytes(const Dims& dm, const madakv_config& c) {
   // the counter of lone workgroups, the exchange words, the workgroups' shares of O, the row blocks' shares of psi
   return 256 + win_xchg_bytes(dm) + win_opart_bytes(dm) + (win_blocks(dm) > 1 ? (size_t)win_blocks(dm) * dm.heads * dm.L * sizeof(float) : 0);
 }
+// Chunks per head of window_wide_kernel: its workgroups fill a compute unit each (two with four waves); few chunks keep
+// the shares of O small, but the last round of workgroups should be nearly full.
+static int win_wide_split(const Dims& dm, int slots) {
+  const int most = std::min(win_split(dm), 16);           // (what the workspace holds of shares of O)
+  int best = 1; double best_eff = 0.;
+  for (int ns = 1; ns <= most; ++ns) {
+    const long long wgs = (long long)dm.heads * ns, rounds = (wgs + slots - 1) / slots;
+    const double eff = (double)wgs / (double)(rounds * slots);
+    if (eff > best_eff + 0.02) { best = ns; best_eff = eff; }
+  }
+  return best;
+}
+template <int D, int NW>
+static void launch_win_wide(const WinArgs& wa, int heads, hipStream_t st) {
+  const size_t lds = (size_t)DMA_NBUF * 2 * (NW * 8) * D * 2 + (size_t)2 * 2 * NW * (NW * 8) * sizeof(float);
+  if (lds > 48 * 1024)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&window_wide_kernel<D, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((window_wide_kernel<D, NW>), dim3(wa.s.fsplit, heads), dim3(NW * 64), lds, st, wa);
+}
+template <int D>
+static void launch_win_many_rows(WinArgs& wa, const Dims& dm, const madakv_config& c, hipStream_t st) {
+  ScoreArgs& a = wa.s;
+  const ScorePlan p = score_plan(dm, c.dtype);
+  const bool wide8 = p.mpad > 128;
+  // the row statistics go where the row blocks' copies of psi would be: 2 nsplit mpad <= 2 (L / 1024) 32 rb floats per head
+  a.rowstat = a.psi_part;
+  a.mpad = p.mpad; a.nsplit = p.nsplit; a.nmerge = 1;
+  const int fs = win_wide_split(dm, wide8 ? 256 : 512);
+  const int chunk2 = ((dm.L + fs - 1) / fs + 63) / 64 * 64;
+  a.fsplit = (dm.L + chunk2 - 1) / chunk2;
+  for (int h0 = 0; h0 < dm.heads; h0 += 65535) {
+    const int nh = std::min(65535, dm.heads - h0);
+    a.head0 = h0;
+    a.chunk = p.chunk;
+    if (wide8) launch_wide_sweep1<D, true, true>(a, nh, st); else launch_wide_sweep1<D, false, true>(a, nh, st);
+    a.chunk = chunk2;
+    if (wide8) launch_win_wide<D, 8>(wa, nh, st); else launch_win_wide<D, 4>(wa, nh, st);
+    a.head0 = h0 * a.rb_count;
+    hipLaunchKernelGGL(window_attn_reduce_kernel, dim3(nh * a.rb_count, (32 * D / 4 + 255) / 256), dim3(256), 0, st, wa);
+  }
+}
 hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void* q_win, const void* k, const void* v,
                               void* out, float* row_lse, float* psi, void* ws, hipStream_t st) {
   WinArgs wa;
@@ -1693,6 +2020,11 @@ hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void
   a.scale_log2 = scale * 1.4426950408889634f;
   wa.v = v; wa.lse = row_lse; wa.out = out; wa.out_fp32 = c.out_fp32;
   wa.opart = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + win_xchg_bytes(dm));
+  // (below 64 keys the row statistics of the one-pass kernel do not fit where they go)
+  if (dm.M > 64 && dm.L >= 64) {
+    if (dm.d == 128) launch_win_many_rows<128>(wa, dm, c, st); else launch_win_many_rows<64>(wa, dm, c, st);
+    return hipGetLastError();
+  }
   const long long nx = (long long)dm.heads * rb * a.xstride;
   if (a.fsplit > 1) hipLaunchKernelGGL(score_xchg_init_kernel, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st, a.xchg, nx);
   const size_t lds = ((size_t)32 + 4 * 32) * (dm.d + 8) * 2 + ((size_t)4 * 32 * 2 + 32 + 512) * sizeof(float);

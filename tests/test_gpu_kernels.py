@@ -202,3 +202,40 @@ def test_selection_at_edges(L, W, M):
         ref = O.select_n(pool[h].astype(np.float64), mh, [int(x) for x in bud[h]], L, W)
         np.testing.assert_array_equal(kept[off[h]:off[h] + ln[h]], ref)
     eng.close()
+
+
+@pytest.mark.parametrize("Hq,H,W,d,L", [(8, 1, 9, 64, 65), (8, 1, 9, 128, 63), (12, 2, 16, 128, 700), (12, 2, 16, 64, 1025), (28, 4, 32, 128, 2049),
+                                        (16, 2, 32, 64, 4097), (7, 1, 10, 128, 1088), (8, 1, 32, 128, 9000), (6, 2, 40, 64, 20011)])
+@pytest.mark.parametrize("out_fp32", [1, 0])
+def test_window_attention_many_rows(Hq, H, W, d, L, out_fp32):
+    """The last-window attention with 65 to 256 proxy rows per KV head (four and eight waves, ragged last blocks, tiles and
+    chunks, fewer keys than a tile) against 64-bit arithmetic on the same bf16 inputs.  Logits of <= 128 exact products summed
+    in fp32 are within 1e-5, P as two or three bf16 parts within 2^-17: 2e-5 of the result in the 2-norm, 4e-5 on a log-sum-exp;
+    a bf16 output adds half a unit of its last place."""
+    G, B = Hq // H, 2
+    g = torch.Generator().manual_seed(L)
+    q, k, v = (torch.randn(1, B, h, n, d, generator=g).to(DEV, torch.bfloat16) for h, n in ((Hq, W), (H, L), (H, L)))
+    mask = torch.randint(0, 2, (B, L), generator=g).to(torch.uint8).to(DEV)
+    eng = MB.MadaKV(n_layers=1, batch=B, n_q_heads=Hq, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=W + max(1, (L - W) // 2), dtype="bf16",
+                    pool_k=7, out_fp32=out_fp32, device=DEV)
+    out = torch.full((1, B, Hq, W, d), float("nan"), dtype=torch.float32 if out_fp32 else torch.bfloat16, device=DEV)
+    lse = torch.full((1, B, Hq, W), float("nan"), dtype=torch.float32, device=DEV)
+    say(f"window {Hq}/{H} W={W} d={d} L={L} out_fp32={out_fp32}")
+    for _ in range(2):
+        eng.window_attn_score(0, 1, q, k, v, mask, out, lse)
+    torch.cuda.synchronize()
+    for b in range(B):
+        for h in range(H):
+            qq = q[0, b, h * G:(h + 1) * G].cpu().double().reshape(G * W, d)
+            x = qq @ k[0, b, h].cpu().double().T / d ** 0.5
+            pos = (L - W + torch.arange(W)).repeat(G)
+            x = x.masked_fill(torch.arange(L)[None] > pos[:, None], float("-inf"))
+            p = torch.softmax(x, -1)
+            ref = p @ v[0, b, h].cpu().double()
+            got = out[0, b, h * G:(h + 1) * G].cpu().double().reshape(G * W, d)
+            err = float((got - ref).norm() / ref.norm())
+            assert err < (2e-5 if out_fp32 else 2.0 ** -9), err
+            assert float((lse[0, b, h * G:(h + 1) * G].cpu().double().reshape(-1) - torch.logsumexp(x, -1)).abs().max()) < 4e-5
+            nbad, worst = PU.psi_close(eng.psi[0, b, h].cpu().numpy()[None], p.sum(0).numpy()[None], G, W, L)
+            assert nbad == 0, (nbad, worst)
+    eng.close()
