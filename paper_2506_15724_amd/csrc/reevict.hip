@@ -121,7 +121,18 @@ __global__ __launch_bounds__(RE_THREADS) void compact_kernel(CompactArgs a) {
   const int sub = tid / LPR, piece = tid % LPR;
   ru32x4_t* kc = reinterpret_cast<ru32x4_t*>(a.k_c);
   ru32x4_t* vc = reinterpret_cast<ru32x4_t*>(a.v_c);
-  for (int j0 = 0; j0 < keep; j0 += BATCH) {
+  // Rows in front of the first one that goes stay where they are (sel ascends and sel[j] >= j, so sel[j] == j up to there):
+  // after a few tokens that is 1 / (tokens + 1) of the head on average.  1024 heads of 2K rows after 6 tokens, 2.1 GB if
+  // everything is moved: 453 -> 283 us.
+  __shared__ int s_first;
+  if (tid == 0) s_first = min(keep, len0);
+  __syncthreads();
+  int mine = keep;
+  for (int j = tid; j < keep; j += RE_THREADS) if (mine == keep && a.sel[off + j] != j) mine = j;
+  for (int o = 32; o > 0; o >>= 1) mine = min(mine, __shfl_xor(mine, o, 64));
+  if ((tid & 63) == 0 && mine < keep) atomicMin(&s_first, mine);
+  __syncthreads();
+  for (int j0 = s_first; j0 < keep; j0 += BATCH) {
     ru32x4_t kr[UN], vr[UN];
     int org[UN];
 #pragma unroll
