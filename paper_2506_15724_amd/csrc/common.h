@@ -186,14 +186,7 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x) {
 #undef MADAKV_DPP_ADD
   return x;
 }
-// the same for 64-bit values below 2^63 / 64, as three 21-bit limbs (no carries between lanes' limbs)
-__device__ __forceinline__ unsigned long long wave_incl_scan_u63(unsigned long long v) {
-  const uint32_t l0 = wave_incl_scan_u32((uint32_t)(v & 0x1fffffULL));
-  const uint32_t l1 = wave_incl_scan_u32((uint32_t)((v >> 21) & 0x1fffffULL));
-  const uint32_t l2 = wave_incl_scan_u32((uint32_t)(v >> 42));
-  return (unsigned long long)l0 + ((unsigned long long)l1 << 21) + ((unsigned long long)l2 << 42);
-}
-
+// the same for 64-bit values, two moves and an addition with carry per step
 __device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long x) {
 #define MADAKV_DPP_ADD64(ctrl, rmask, bctl) \
   x += ((unsigned long long)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(x >> 32), ctrl, rmask, 0xF, bctl) << 32) | \

@@ -32,7 +32,6 @@ __device__ __forceinline__ bool descent_match(const DescentRange& r, uint32_t ke
 __device__ __forceinline__ uint32_t descent_bin(const DescentRange& r, uint32_t key) {
   return (uint32_t)min(max((int)((key >> r.sh) - r.sub), 0), BINS - 1);
 }
-__device__ __forceinline__ int descent_bins(const DescentRange& r) { return r.sh == 0 ? LAST_BINS : BINS; }
 // The range after a crossing in bin b (at sh == 0 the descent is over: the key is sub + b).  SH1: shift of the plain first digit.
 template <uint32_t SH1>
 __device__ __forceinline__ DescentRange descent_next(const DescentRange& r, uint32_t b) {
@@ -48,44 +47,6 @@ __device__ __forceinline__ DescentRange descent_next(const DescentRange& r, uint
   n.sh = r.sh == SH1 ? SH1 - 11u : 0u;
   n.sub = t >> n.sh;
   return n;
-}
-
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v) { return wave_incl_scan_u32(v); }
-__device__ __forceinline__ unsigned long long wave_scan(unsigned long long v) { return wave_incl_scan_u63(v); }
-__device__ __forceinline__ uint32_t wave_get(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
-__device__ __forceinline__ unsigned long long wave_get(unsigned long long v, int lane) {
-  return ((unsigned long long)wave_get((uint32_t)(v >> 32), lane) << 32) | wave_get((uint32_t)v, lane);
-}
-
-// One wave: a lane's share of the nb bins below the top, lane 0 first (64, 128, ..., 2048 bins), and the sums up to and
-// including it.  The lanes start at different bins of their shares so that they read different LDS banks.
-template <typename V>
-__device__ __forceinline__ V walk_share(const V* hist, int nb, V& incl) {
-  const int lane = threadIdx.x & 63, per = nb >> 6;
-  const V* top = hist + nb - 1 - lane * per;
-  V s = 0;
-#pragma unroll 8
-  for (int j = 0; j < per; ++j) s += top[-((j + lane) & (per - 1))];
-  incl = wave_scan(s);
-  return s;
-}
-// The bin where the running total, base + the bins above, reaches the target; -1 if it does not.  before: the total above that bin.
-template <typename V>
-__device__ __forceinline__ int walk_find(const V* hist, int nb, V share, V incl, V base, V target, V& before, V& in_bin) {
-  const int lane = threadIdx.x & 63, per = nb >> 6;
-  const V bef = base + incl - share;
-  const unsigned long long owner = __ballot(bef < target && bef + share >= target);
-  if (!owner) return -1;
-  // the owner's bins, one per lane, scanned the same way
-  const int src = __ffsll((long long)owner) - 1;
-  const V b0 = wave_get(bef, src);
-  const int bin = nb - 1 - (src * per + min(lane, per - 1));
-  const V v = lane < per ? hist[bin] : V(0);
-  const V sc = wave_scan(v);
-  const unsigned long long hit = __ballot(lane < per && b0 + sc - v < target && b0 + sc >= target);
-  const int hl = __ffsll((long long)hit) - 1;
-  before = wave_get((V)(b0 + sc - v), hl); in_bin = wave_get(v, hl);
-  return nb - 1 - (src * per + hl);
 }
 
 template <typename T, int N>
