@@ -742,6 +742,9 @@ static hipError_t launch_decode_t(const Dims& dm, DecodeArgs& a, int grid_chunks
   constexpr int D = LPR * 16 / (int)sizeof(CT);
   dim3 grid(dm.heads, grid_chunks), block(DEC_THREADS);
   if (sizeof(T) == 2 && dm.G >= 2) hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED>), grid, block, 0, st, a);   // grouped queries in bf16: the MFMA kernel
+  // Four rows in flight per lane; eight where the pieces are long (a cache that was hardly reduced: 128 heads of 16K bf16 rows
+  // 5.42 -> 5.17 ms for 32 layer calls, 6.6 TB/s): with many trips per workgroup the loads in flight count, with one or two its start and its instructions.
+  else if (dm.G == 1 && sizeof(CT) != 1 && a.chunk_rows > 512) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, 8, 4, PAGED>), grid, block, 0, st, a);
   else if (dm.G == 1) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, 4, 4, PAGED>), grid, block, 0, st, a);
   else if constexpr (sizeof(T) == 4) {
     if (dm.G == 2) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 2, 4, 4, PAGED>), grid, block, 0, st, a);
