@@ -82,6 +82,8 @@ def test_fp32_scores(kw, monkeypatch):
     (dict(n_q_heads=12, n_kv_heads=2, head_dim=128, ctx_len=5000, budget=1000, cache_fp8=1), [1700, 159]),
     (dict(n_q_heads=3, n_kv_heads=1, head_dim=128, ctx_len=12000, budget=11000, dtype="fp32"), [10999]),
     (dict(n_q_heads=2, n_kv_heads=2, head_dim=64, ctx_len=400, budget=300, dtype="fp32"), [299, 255]),
+    # long pieces (768 rows): eight rows in flight
+    (dict(batch=4, n_q_heads=64, n_kv_heads=64, head_dim=64, ctx_len=7000, budget=6200), [6190, 769, 768, 767, 1]),
 ], ids=lambda x: f"q{x['n_q_heads']}_kv{x['n_kv_heads']}_d{x['head_dim']}_L{x['ctx_len']}_{x.get('dtype', 'bf16')}" if isinstance(x, dict) else "")
 @pytest.mark.parametrize("out_fp32", [1, 0])
 def test_decode_pieces(kw, lens, out_fp32):
