@@ -290,12 +290,13 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
     for (int e = 0; e < EPL; ++e) { acc[g][e] = 0.f; qf[g][e] *= a.scale_log2; }
   }
 
-  const unsigned char* kc = reinterpret_cast<const unsigned char*>(a.k_c) + (PAGED ? 0 : off * (LPR * 16));
-  const unsigned char* vc = reinterpret_cast<const unsigned char*>(a.v_c) + (PAGED ? 0 : off * (LPR * 16));
+  // the piece's first row (64 bits: a head may take more than 4 GiB); the rows' offsets from it fit 32 bits
+  const unsigned char* kc = reinterpret_cast<const unsigned char*>(a.k_c) + (PAGED ? 0 : (off + r_begin) * (LPR * 16));
+  const unsigned char* vc = reinterpret_cast<const unsigned char*>(a.v_c) + (PAGED ? 0 : (off + r_begin) * (LPR * 16));
 
   for (int row0 = r_begin + wave * WSTEP; row0 < r_end; row0 += NW * WSTEP) {
     uint4 kraw[UNROLL], vraw[UNROLL];
-    // rows past the end: the last row once more, masked below (no branch in the loads; a row is at most 2^20 * 512 bytes away)
+    // rows past the end: the last row once more, masked below (no branch in the loads)
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       const int r = min(row0 + u * RPI + sub, r_end - 1);
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
         const long long o = (at(r) * LPR + piece) * 16;
         kraw[u] = stream_load16(kc + o); vraw[u] = stream_load16(vc + o);
       } else {
-        const uint32_t o = (uint32_t)(r * LPR + piece) * 16u;
+        const uint32_t o = (uint32_t)((r - r_begin) * LPR + piece) * 16u;
         kraw[u] = stream_load16(kc + o); vraw[u] = stream_load16(vc + o);
       }
     }
@@ -471,8 +472,9 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
   const bool has_fresh = can_append && len_old >= r_begin && len_old < r_end;   // uniform: the appended row is in this piece
   if (has_fresh) stage_new_row<uint16_t, CT, D>(a, hidx, at(len_old), s_new);
 
-  const unsigned char* kc = reinterpret_cast<const unsigned char*>(a.k_c) + (PAGED ? 0 : off * (D * CB));   // cache rows of D * CB bytes
-  const unsigned char* vc = reinterpret_cast<const unsigned char*>(a.v_c) + (PAGED ? 0 : off * (D * CB));
+  // the piece's first row (cache rows of D * CB bytes); the rows' offsets from it fit 32 bits
+  const unsigned char* kc = reinterpret_cast<const unsigned char*>(a.k_c) + (PAGED ? 0 : (off + r_begin) * (D * CB));
+  const unsigned char* vc = reinterpret_cast<const unsigned char*>(a.v_c) + (PAGED ? 0 : (off + r_begin) * (D * CB));
 
   float m_run = DNEG_BIG, l_run = 0.f;       // for query j16 (every lane group c holds a copy of m, a share of l)
   df32x4_t oacc[DB];                         // O[q = 4c + r][d = 16 db + j16]
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
       const int r = min(t0 + blk * 16 + j16, r_end - 1);
-      const unsigned char* kp = PAGED ? kc + at(r) * (D * CB) : kc + (uint32_t)r * (uint32_t)(D * CB);
+      const unsigned char* kp = PAGED ? kc + at(r) * (D * CB) : kc + (uint32_t)(r - r_begin) * (uint32_t)(D * CB);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         if (FP8) { const du32x2_t t2 = __builtin_nontemporal_load(reinterpret_cast<const du32x2_t*>(kp + ks * 32 + c * 8)); kraw[blk][ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
 #pragma unroll
     for (int i = 0; i < VL; ++i) {
       const int r = min(t0 + i * RPI + vsub, r_end - 1);
-      const unsigned char* vp = PAGED ? vc + at(r) * (D * CB) : vc + (uint32_t)r * (uint32_t)(D * CB);
+      const unsigned char* vp = PAGED ? vc + at(r) * (D * CB) : vc + (uint32_t)(r - r_begin) * (uint32_t)(D * CB);
       vraw[i] = __builtin_nontemporal_load(reinterpret_cast<const du32x4_t*>(vp + vpiece * 16));
     }
     if (has_fresh && t0 <= len_old && len_old < t0 + 32) {          // the appended row (the last of the piece) comes from LDS

@@ -241,3 +241,29 @@ def test_window_attention_many_rows(Hq, H, W, d, L, out_fp32):
             nbad, worst = PU.psi_close(eng.psi[0, b, h].cpu().numpy()[None], p.sum(0).numpy()[None], G, W, L)
             assert nbad == 0, (nbad, worst)
     eng.close()
+
+
+@pytest.mark.parametrize("dtype,Hq,d,rows", [("fp32", 1, 128, 2 ** 23 + 4000), ("bf16", 4, 128, 2 ** 24 + 4000)])
+def test_decode_beyond_4_gib_of_rows(dtype, Hq, d, rows):
+    """A head whose K rows take more than 4 GiB: all its weight is on four rows beyond that, the output is their mean
+    (the other rows' logits are 0 against 60: 2^24 e^-60 of the weight)."""
+    slack = 64
+    eng = MB.MadaKV(n_layers=1, batch=1, n_q_heads=Hq, n_kv_heads=1, head_dim=d, ctx_len=64, window=8, budget=16, dtype=dtype, pool_k=1,
+                    max_new_tokens=rows + slack, out_fp32=1, device=DEV)
+    g = torch.Generator().manual_seed(3)
+    eng.k_c.zero_(); eng.v_c.zero_()
+    eng.kv_off.zero_(); eng.kv_len.fill_(rows)
+    q = torch.ones(1, 1, Hq, d, device=DEV, dtype=eng.tdtype)
+    at = torch.tensor([rows - 3900, rows - 2049, rows - 1000])
+    vals = torch.randn(4, d, generator=g).to(eng.tdtype)
+    eng.k_c[at.to(DEV)] = 60 / d ** 0.5
+    eng.v_c[at.to(DEV)] = vals[:3].to(DEV)
+    kn = torch.full((1, 1, 1, d), 60 / d ** 0.5, device=DEV, dtype=eng.tdtype)
+    out = torch.empty(1, 1, Hq, d, device=DEV)
+    say(f"decode over {rows} rows of {d} {dtype}")
+    eng.decode_attn(0, 1, q, kn, vals[3:].view(1, 1, 1, d).to(DEV), out)
+    torch.cuda.synchronize()
+    assert int(eng.kv_len) == rows + 1
+    ref = vals.double().mean(0)
+    assert float((out[0, 0].cpu().double() - ref).abs().max()) < 1e-5
+    eng.close()
