@@ -906,10 +906,12 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
 #pragma unroll
   for (int it = 0; it < PF; ++it) MADAKV_FUSED_LOAD(it, it)
 
-  for (int e = tid; e < a.mpad * PPR; e += SCORE_THREADS) {               // Q tile, padding rows zero
+  // Q tile.  Padding rows count for nothing (their offset is +inf) unless they turn an infinite key element into NaN, as rows
+  // of zeros do: fp32 takes the last row once more.  (bf16 keeps zeros: the other costs 2 of 320 us at 128K keys.)
+  for (int e = tid; e < a.mpad * PPR; e += SCORE_THREADS) {
     const int r = e / PPR, c = e % PPR;
     uint4 val = make_uint4(0, 0, 0, 0);
-    if (r < Mh) val = *reinterpret_cast<const uint4*>(qg + (long long)r * RU + c * 8);
+    if (F32 || r < Mh) val = *reinterpret_cast<const uint4*>(qg + (long long)(F32 ? min(r, Mh - 1) : r) * RU + c * 8);
     *reinterpret_cast<uint4*>(qs + r * RS + c * 8) = val;
   }
   __syncthreads();
@@ -994,6 +996,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       float mx = lg[0][b][j];
+      if (F32) mx = fmaxf(mx, NEG_BIG);         // (a row whose logits here are all -Inf: against NEG_BIG its sum is 0)
 #pragma unroll
       for (int it = 1; it < NS; ++it) mx = fmaxf(mx, lg[it][b][j]);
       const float m = half_reduce<0>(mx);

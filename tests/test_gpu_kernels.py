@@ -243,6 +243,48 @@ def test_window_attention_many_rows(Hq, H, W, d, L, out_fp32):
     eng.close()
 
 
+def minus_inf_case(dtype, Hq, H, W, d, L, where, NL=1):
+    """Queries whose first element is negative, keys of which those at `where` hold +Inf there: every row's logit on such
+    a key is -Inf, its softmax entry and its psi are 0, everything else is as if the key were not there."""
+    g = torch.Generator().manual_seed(L + Hq)
+    q, k, v = (torch.randn(NL, 1, h, n, d, generator=g) for h, n in ((Hq, W), (H, L), (H, L)))
+    q[..., 0] = -q[..., 0].abs() - 0.25
+    k[..., list(where), 0] = float("inf")
+    mask = torch.randint(0, 2, (1, L), generator=g).to(torch.uint8).to(DEV)
+    q, k, v = (t.to(DEV, torch.bfloat16 if dtype == "bf16" else torch.float32) for t in (q, k, v))
+    eng = MB.MadaKV(n_layers=NL, batch=1, n_q_heads=Hq, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=W + (L - W) // 2, dtype=dtype,
+                    pool_k=1, out_fp32=1, device=DEV)
+    return eng, q, k, v, mask
+
+
+def softmax_rows(q, k, W, kv_head):
+    """64-bit softmax entries [G * W, L] of one KV head's proxy rows, and their log-sum-exp"""
+    G, L, d = q.shape[0] // k.shape[0], k.shape[1], k.shape[2]
+    x = q[kv_head * G:(kv_head + 1) * G].cpu().double().reshape(G * W, d) @ k[kv_head].cpu().double().T / d ** 0.5
+    pos = (L - W + torch.arange(W)).repeat(G)
+    x = x.masked_fill(torch.arange(L)[None] > pos[:, None], float("-inf"))
+    return torch.softmax(x, -1), torch.logsumexp(x, -1)
+
+
+@pytest.mark.parametrize("Hq,H,W,d,L,where", [
+    (3, 3, 17, 64, 600, [5]), (3, 3, 32, 64, 1100, range(0, 512)), (5, 1, 9, 128, 1100, [31, 32, 700]), (5, 1, 9, 128, 1100, range(512, 1024)),
+    (7, 1, 10, 64, 900, [0, 600]), (2, 2, 16, 64, 400, range(0, 128))],
+    ids=lambda x: str(len(x)) if isinstance(x, (list, range)) else str(x))
+def test_fp32_scores_of_keys_with_infinite_elements(Hq, H, W, d, L, where):
+    """Padding rows (row counts that are no multiple of 32) and waves or chunks that see nothing but -Inf leave no NaN."""
+    eng, q, k, v, mask = minus_inf_case("fp32", Hq, H, W, d, L, where)
+    say(f"fp32 scores with infinite key elements {Hq}/{H} W={W} d={d} L={L}")
+    eng.score(0, 1, q, k, mask)
+    torch.cuda.synchronize()
+    psi = eng.psi[0, 0].cpu()
+    for h in range(H):
+        p, _ = softmax_rows(q[0, 0], k[0, 0], W, h)
+        assert (psi[h, list(where)] == 0).all()
+        nbad, worst = PU.psi_close(psi[h].numpy()[None], p.sum(0).numpy()[None], Hq // H, W, L)
+        assert nbad == 0, (nbad, worst)
+    eng.close()
+
+
 @pytest.mark.parametrize("dtype,Hq,d,rows", [("fp32", 1, 128, 2 ** 23 + 4000), ("bf16", 4, 128, 2 ** 24 + 4000)])
 def test_decode_beyond_4_gib_of_rows(dtype, Hq, d, rows):
     """A head whose K rows take more than 4 GiB: all its weight is on four rows beyond that, the output is their mean
