@@ -1403,9 +1403,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   bf16x8_t qfrag[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (row < a.M) val = *reinterpret_cast<const uint4*>(qg + (long long)row * D + half * (D / 2) + ks * 8);
-    qfrag[ks] = __builtin_bit_cast(bf16x8_t, val);
+    // (padding rows: the last row once more; zeros would turn an infinite key element into NaN, which the key's psi takes in)
+    qfrag[ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qg + (long long)min(row, a.M - 1) * D + half * (D / 2) + ks * 8));
   }
   if (row < a.M) {
     const float* rs = a.rowstat + (long long)head * a.nsplit * a.mpad * 2 + row * 2;

@@ -285,6 +285,28 @@ def test_fp32_scores_of_keys_with_infinite_elements(Hq, H, W, d, L, where):
     eng.close()
 
 
+@pytest.mark.parametrize("NL,Hq,H,W,d,L,where", [
+    (1, 7, 1, 10, 128, 1088, [40]), (1, 7, 1, 10, 64, 1088, range(0, 128)), (8, 48, 16, 23, 64, 4200, [40, 3000]), (8, 56, 8, 21, 128, 4200, [0, 900])],
+    ids=lambda x: str(len(x)) if isinstance(x, (list, range)) else str(x))
+def test_window_attention_of_keys_with_infinite_elements(NL, Hq, H, W, d, L, where):
+    """As above, more than 64 proxy rows that are no multiple of 32, in calls of few and of many heads."""
+    eng, q, k, v, mask = minus_inf_case("bf16", Hq, H, W, d, L, where, NL)
+    out = torch.empty(NL, 1, Hq, W, d, dtype=torch.float32, device=DEV)
+    say(f"window with infinite key elements {NL} x {Hq}/{H} W={W} d={d} L={L}")
+    eng.window_attn_score(0, NL, q, k, v, mask, out)
+    torch.cuda.synchronize()
+    assert (eng.psi[..., list(where)] == 0).all()
+    G = Hq // H
+    for l in (0, NL - 1):
+        for h in (0, H - 1):
+            p, _ = softmax_rows(q[l, 0], k[l, 0], W, h)
+            nbad, worst = PU.psi_close(eng.psi[l, 0, h].cpu().numpy()[None], p.sum(0).numpy()[None], G, W, L)
+            assert nbad == 0, (nbad, worst)
+            ref = p @ v[l, 0, h].cpu().double()
+            assert float((out[l, 0, h * G:(h + 1) * G].cpu().double().reshape(G * W, d) - ref).norm() / ref.norm()) < 2e-5
+    eng.close()
+
+
 @pytest.mark.parametrize("dtype,Hq,d,rows", [("fp32", 1, 128, 2 ** 23 + 4000), ("bf16", 4, 128, 2 ** 24 + 4000)])
 def test_decode_beyond_4_gib_of_rows(dtype, Hq, d, rows):
     """A head whose K rows take more than 4 GiB: all its weight is on four rows beyond that, the output is their mean
