@@ -1080,8 +1080,8 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_fused_finish_kernel(Score
 // ------------------------------------------------------------------------------------
 // The prefill attention of the last W prompt positions (paper Sec. 3.1 Eq. 5 for the proxy rows of
 // Sec. 3.3) with the proxy-token scores of Eq. 7 as a by-product: out = softmax(scale Q K^T) V for
-// a block of up to 32 of the G*W proxy rows of a KV head (up to 64 rows: two blocks, each with a pass of its own over
-// K and V, their column sums added in block order afterwards; more rows: window_wide_kernel below), their log-sum-exp, and psi = the column sums of the same
+// a block of up to 32 of the G*W proxy rows of a KV head (more rows: more blocks, each with a pass of its own over
+// K and V, their column sums added in block order afterwards, or window_wide_kernel below, see win_one_pass), their log-sum-exp, and psi = the column sums of the same
 // softmax rows.  A model's prefill runs this attention anyway; taking psi from it removes the
 // eviction's own sweep over K.
 // Same structure as score_fused_kernel (a workgroup's logits stay in registers while the row
@@ -1959,10 +1959,26 @@ size_t window_attn_ws_bytes(const Dims& dm, const madakv_config& c) {
   // the counter of lone workgroups, the exchange words, the workgroups' shares of O, the row blocks' shares of psi
   return 256 + win_xchg_bytes(dm) + win_opart_bytes(dm) + (win_blocks(dm) > 1 ? (size_t)win_blocks(dm) * dm.heads * dm.L * sizeof(float) : 0);
 }
-// Chunks per head of window_wide_kernel: its workgroups fill a compute unit each (two with four waves); few chunks keep
-// the shares of O small, but the last round of workgroups should be nearly full.
+// More than 64 proxy rows: window_wide_kernel, in one pass for all rows but behind a sweep over K of its own (four launches,
+// one or two workgroups per compute unit, each walking its tiles one after the other), or the kernel above, block by block
+// of 32 rows (three launches, 512 workgroups at a time, 512 or 768 keys each).  With few of the latter's workgroups the chip
+// is not full either way and its shorter chain wins; with more than two rounds of them its repeated passes over K and V cost
+// more.  Measured per call, blocks / one pass, by the number of the blocks' workgroups: head_dim 128, 5-8 blocks of rows, 512
+// (8K keys) 58 / 90 us, 1024 (8K) 84 / 92, 1344 (2K) 109 / 89, 1536 (32K) 132 / 118, 3072 (128K) 286 / 192; up to 4 blocks,
+// whose waves share a compute unit with another workgroup, 512 (8K) 57 / 74, 768 (2K) 75 / 70, 768 (32K) 94 / 100, 2048 (32K)
+// 156 / 116; head_dim 64 516 (32K) 95 / 106, 616 (8K) 81 / 82, 704 (8K) 81 / 72, 1032 (32K) 124 / 106.
+static bool win_one_pass(const Dims& dm) {
+  if (dm.M <= 64 || dm.L < 64) return false;              // (below 64 keys the row statistics do not fit where they go)
+  const long long block_wgs = (long long)dm.heads * win_blocks(dm) * win_split(dm);
+  return block_wgs > ((dm.L > 16384 || (dm.d == 128 && win_blocks(dm) > 4)) ? 1024 : 640);
+}
+// Chunks per head of window_wide_kernel (`slots` workgroups of it are on the chip at a time): the fewest that leave the last
+// round of workgroups nearly full, since every chunk costs a share of O, 32 d floats per block of rows written and read
+// again.  112 heads of 32K keys and 224 rows: 9 chunks, 16 or 32 are 4-9% slower; one head of 128K keys and 256 rows: 16 chunks
+// 549 us, 64 237, 252 174; 4 heads of 128K and 224 rows: 16 chunks 564, 63 266, 256 316.  (At most win_split: shorter chunks
+// than the other kernel's, for which the workspace is made, gain nothing.)
 static int win_wide_split(const Dims& dm, int slots) {
-  const int most = std::min(win_split(dm), 16);           // (what the workspace holds of shares of O)
+  const int most = win_split(dm);
   int best = 1; double best_eff = 0.;
   for (int ns = 1; ns <= most; ++ns) {
     const long long wgs = (long long)dm.heads * ns, rounds = (wgs + slots - 1) / slots;
@@ -2022,8 +2038,7 @@ hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void
   a.scale_log2 = scale * 1.4426950408889634f;
   wa.v = v; wa.lse = row_lse; wa.out = out; wa.out_fp32 = c.out_fp32;
   wa.opart = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + win_xchg_bytes(dm));
-  // (below 64 keys the row statistics of the one-pass kernel do not fit where they go)
-  if (dm.M > 64 && dm.L >= 64) {
+  if (win_one_pass(dm)) {
     if (dm.d == 128) launch_win_many_rows<128>(wa, dm, c, st); else launch_win_many_rows<64>(wa, dm, c, st);
     return hipGetLastError();
   }

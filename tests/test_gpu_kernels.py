@@ -307,6 +307,63 @@ def test_window_attention_of_keys_with_infinite_elements(NL, Hq, H, W, d, L, whe
     eng.close()
 
 
+@pytest.mark.parametrize("NL,Hq,H,W,d,L", [
+    (18, 36, 12, 22, 64, 64), (18, 36, 12, 22, 128, 65), (18, 36, 12, 22, 128, 63),                    # fewest keys of a tile, and one less: the blocks
+    (6, 128, 32, 24, 64, 1025), (14, 32, 8, 32, 128, 1024), (7, 96, 16, 16, 128, 1600), (5, 84, 28, 32, 128, 1537),   # 3 and 4 blocks of rows
+    (10, 40, 8, 31, 128, 2100), (26, 64, 8, 29, 64, 700), (26, 64, 8, 32, 128, 129),                   # 5 and 8 blocks
+    (1, 8, 1, 32, 128, 65536 + 700), (2, 3, 1, 32, 64, 131072), (1, 7, 1, 30, 128, 100003),            # few long heads: many chunks each
+    (8, 4, 1, 32, 64, 32768 - 31), (20, 32, 8, 32, 64, 768), (20, 32, 8, 32, 64, 769)],                # either side of the dispatch
+    ids=lambda x: str(x))
+@pytest.mark.parametrize("out_fp32", [1, 0])
+def test_window_attention_many_rows_many_workgroups(NL, Hq, H, W, d, L, out_fp32):
+    """As test_window_attention_many_rows, in calls large enough for the kernel that takes all rows in one pass, and at the
+    edges of its dispatch and of its chunks; the first, last and some other heads against 64-bit arithmetic (same bounds)."""
+    G = Hq // H
+    g = torch.Generator(device=DEV).manual_seed(L + Hq)
+    q, k, v = (torch.randn(NL, 1, h, n, d, generator=g, device=DEV).to(torch.bfloat16) for h, n in ((Hq, W), (H, L), (H, L)))
+    mask = torch.randint(0, 2, (1, L), generator=g, device=DEV).to(torch.uint8)
+    eng = MB.MadaKV(n_layers=NL, batch=1, n_q_heads=Hq, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=W + max(1, (L - W) // 4), dtype="bf16",
+                    pool_k=7, out_fp32=out_fp32, device=DEV)
+    out = torch.full((NL, 1, Hq, W, d), float("nan"), dtype=torch.float32 if out_fp32 else torch.bfloat16, device=DEV)
+    lse = torch.full((NL, 1, Hq, W), float("nan"), dtype=torch.float32, device=DEV)
+    eng.psi.fill_(float("nan"))
+    say(f"window {NL} x {Hq}/{H} W={W} d={d} L={L} out_fp32={out_fp32}")
+    for _ in range(2):
+        eng.window_attn_score(0, NL, q, k, v, mask, out, lse)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out).all() and torch.isfinite(lse).all() and torch.isfinite(eng.psi).all()
+    for l, h in {(0, 0), (NL - 1, H - 1), (NL // 2, H // 2), (NL // 3, H // 3)}:
+        p, ls = softmax_rows(q[l, 0], k[l, 0], W, h)
+        ref = p @ v[l, 0, h].cpu().double()
+        err = float((out[l, 0, h * G:(h + 1) * G].cpu().double().reshape(G * W, d) - ref).norm() / ref.norm())
+        assert err < (2e-5 if out_fp32 else 2.0 ** -9), err
+        assert float((lse[l, 0, h * G:(h + 1) * G].cpu().double().reshape(-1) - ls).abs().max()) < 4e-5
+        nbad, worst = PU.psi_close(eng.psi[l, 0, h].cpu().numpy()[None], p.sum(0).numpy()[None], G, W, L)
+        assert nbad == 0, (nbad, worst)
+    eng.close()
+
+
+def test_window_attention_of_one_long_head_fills_the_chip():
+    """One layer of one KV head (256 rows, 128K keys) has a quarter of the work of four heads and must not take longer:
+    a fixed number of chunks per head left it to a sixteenth of the compute units (690 us against 560; 174 and 266 with
+    chunks by the launch)."""
+    us = {}
+    for H in (1, 4):
+        q, k, v = (torch.randn(1, 1, h, n, 128, device=DEV, dtype=torch.bfloat16) for h, n in ((8 * H, 32), (H, 131072), (H, 131072)))
+        mask = torch.zeros(1, 131072, dtype=torch.uint8, device=DEV)
+        eng = MB.MadaKV(n_layers=1, batch=1, n_q_heads=8 * H, n_kv_heads=H, head_dim=128, ctx_len=131072, window=32, budget=2048, out_fp32=0, device=DEV)
+        out = torch.empty(1, 1, 8 * H, 32, 128, dtype=torch.bfloat16, device=DEV)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(12)]
+        for e in ev:
+            eng.window_attn_score(0, 1, q, k, v, mask, out)
+            e.record()
+        torch.cuda.synchronize()
+        us[H] = min(a.elapsed_time(b) for a, b in zip(ev[1:], ev[2:])) * 1e3
+        eng.close()
+    say(f"one long head {us[1]:.0f} us, four {us[4]:.0f} us")
+    assert us[1] < us[4]
+
+
 @pytest.mark.parametrize("dtype,Hq,d,rows", [("fp32", 1, 128, 2 ** 23 + 4000), ("bf16", 4, 128, 2 ** 24 + 4000)])
 def test_decode_beyond_4_gib_of_rows(dtype, Hq, d, rows):
     """A head whose K rows take more than 4 GiB: all its weight is on four rows beyond that, the output is their mean
