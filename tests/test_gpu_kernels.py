@@ -364,6 +364,83 @@ def test_window_attention_of_one_long_head_fills_the_chip():
     assert us[1] < us[4]
 
 
+def evicted_engine(lens, **kw):
+    """An engine whose heads (one layer, one batch item) hold `lens` rows after a selection with hand-made budgets."""
+    args = dict(n_layers=1, batch=1, window=8, dtype="bf16", pool_k=1, max_new_tokens=16, out_fp32=1)
+    args.update(kw)
+    eng = MB.MadaKV(device=DEV, **args)
+    H, L, W, d = args["n_kv_heads"], args["ctx_len"], args["window"], args["head_dim"]
+    g = torch.Generator().manual_seed(11)
+    k, v = (torch.randn(1, 1, H, L, d, generator=g).to(DEV, eng.tdtype) for _ in range(2))
+    mask = torch.zeros(1, L, dtype=torch.uint8, device=DEV)
+    bud = torch.zeros(1, 1, H, 2, dtype=torch.int32)
+    bud[0, 0, :, 0] = torch.tensor(lens) - W
+    eng.select_gather(0, 1, k, v, mask, psi_pool=torch.rand(1, 1, H, L - W, generator=g).to(DEV), budgets=bud.to(DEV))
+    torch.cuda.synchronize()
+    assert eng.kv_len.view(-1).tolist() == list(lens)
+    return eng, args
+
+
+def like_without_known_lengths(eng, args):
+    """The same reduced cache in a handle that has made no eviction and so knows nothing of the heads' lengths."""
+    other = MB.MadaKV(device=DEV, **args)
+    for name in ("k_c", "v_c", "kv_off", "kv_len"):
+        getattr(other, name).copy_(getattr(eng, name))
+    return other
+
+
+@pytest.mark.parametrize("kw,lens", [
+    (dict(n_q_heads=4, n_kv_heads=4, head_dim=128, ctx_len=1500, budget=250), [249, 120, 9, 31]),           # one piece each, grows to two
+    (dict(n_q_heads=4, n_kv_heads=1, head_dim=64, ctx_len=1500, budget=130), [121]),                        # grouped queries: pieces of 128 rows
+    (dict(n_q_heads=14, n_kv_heads=2, head_dim=128, ctx_len=1500, budget=130, cache_fp8=1), [127, 126]),
+    (dict(n_q_heads=2, n_kv_heads=2, head_dim=64, ctx_len=1500, budget=256, dtype="fp32"), [254, 200]),
+    (dict(n_q_heads=6, n_kv_heads=3, head_dim=128, ctx_len=9000, budget=700, hcc_rho=1), [1400, 128, 300]), # more rows than the average head's
+], ids=lambda x: f"q{x['n_q_heads']}_kv{x['n_kv_heads']}_d{x['head_dim']}_{x.get('dtype', 'bf16')}" if isinstance(x, dict) else "")
+def test_decode_known_lengths(kw, lens):
+    """The launch is sized by the heads' lengths once the host knows them (no merge while every head is one piece): the same
+    bits as without, at every step of a growth across a piece's end, and the lengths of the heads grow by one."""
+    eng, args = evicted_engine(lens, **kw)
+    other = like_without_known_lengths(eng, args)
+    H, Hq, d = args["n_kv_heads"], args["n_q_heads"], args["head_dim"]
+    g = torch.Generator().manual_seed(5)
+    for step in range(16):
+        q, kn, vn = (torch.randn(1, 1, h, d, generator=g).to(DEV, eng.tdtype) for h in (Hq, H, H))
+        outs = []
+        for e in (eng, other):
+            out = torch.full((1, 1, Hq, d), float("nan"), device=DEV)
+            say(f"known lengths {kw} step {step}")
+            e.decode_attn(0, 1, q, kn, vn, out)
+            torch.cuda.synchronize()
+            outs.append(out)
+            assert e.kv_len.view(-1).tolist() == [n + step + 1 for n in lens]
+        assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1])
+    eng.close(); other.close()
+
+
+def test_decode_of_short_heads_merges_nothing():
+    """Heads of one piece each take one launch once that is known: 5.1 against 6.2 us per call with a merge behind it."""
+    eng, args = evicted_engine([120] * 32, n_q_heads=32, n_kv_heads=32, head_dim=128, ctx_len=4096, budget=120)
+    us = []
+    for e in (eng, like_without_known_lengths(eng, args)):
+        q, out = torch.randn(1, 1, 32, 128, device=DEV).to(e.tdtype), torch.empty(1, 1, 32, 128, device=DEV)
+        for _ in range(2):
+            e.decode_attn(0, 1, q, None, None, out)
+            torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(50):
+                e.decode_attn(0, 1, q, None, None, out)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(12)]
+        for x in ev:
+            graph.replay()
+            x.record()
+        torch.cuda.synchronize()
+        us.append(min(x.elapsed_time(y) for x, y in zip(ev[1:], ev[2:])) * 20)
+        e.close()
+    say(f"short heads: {us[0]:.2f} us per call, lengths unknown {us[1]:.2f}")
+    assert us[0] < 0.95 * us[1]
+
+
 @pytest.mark.parametrize("dtype,Hq,d,rows", [("fp32", 1, 128, 2 ** 23 + 4000), ("bf16", 4, 128, 2 ** 24 + 4000)])
 def test_decode_beyond_4_gib_of_rows(dtype, Hq, d, rows):
     """A head whose K rows take more than 4 GiB: all its weight is on four rows beyond that, the output is their mean
