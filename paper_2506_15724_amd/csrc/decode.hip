@@ -708,22 +708,27 @@ static int plan_longest(const madakv_config& c, int longest_rows) { return std::
 // The pieces of a launch.  A head is cut into pieces of chunk_rows and at most max_chunks of them, twice what an average
 // head takes (longer heads: longer pieces, see head_chunk_rows).  Neither depends on what the host knows of the
 // longest head, so that a call's result does not either; only the grid, at most max_chunks pieces, shrinks when it is known.
+constexpr int SHORT_PIECES = 2000;             // most 128-row pieces of a launch: what the static scratch holds of 8 queries x 128 dims
+static_assert((size_t)SHORT_PIECES * 8 * (128 + 2) * sizeof(float) <= MADAKV_STATIC_SCRATCH_BYTES, "short pieces must fit the static scratch");
 DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows, size_t ws_bytes) {
   DecodePlan p;
   const int worst = plan_longest(c, c.ctx_len + c.max_new_tokens);
   const int base = plan_chunk_rows(dm, c);
   p.chunk_rows = base;
   // grouped queries, few heads: a tile of 32 rows per wave while the launch does not fill the chip with that
-  const long long typical = std::min(c.budget, c.ctx_len) + c.max_new_tokens;
-  if (c.dtype == MADAKV_BF16 && dm.G >= 2 && dm.heads * typical <= 256LL * 128 * 2) p.chunk_rows = 128;
-  const long long want = std::max<long long>((2 * typical + p.chunk_rows - 1) / p.chunk_rows, 512 / dm.heads);
+  const long long typical = std::min(c.budget, c.ctx_len) + (long long)c.max_new_tokens;
+  const bool short_pieces = c.dtype == MADAKV_BF16 && dm.G >= 2 && dm.heads <= 512 && dm.heads * typical <= 256LL * 128 * 2;
+  if (short_pieces) p.chunk_rows = 128;
+  long long want = std::max<long long>((2 * typical + p.chunk_rows - 1) / p.chunk_rows, 512 / dm.heads);
+  if (short_pieces) want = std::min<long long>(want, SHORT_PIECES / dm.heads);
   // never more partial results than a worst-case head cut into `base` rows has (what decode_ws_bytes is made for), nor
-  // than the workspace at hand holds (madakv_decode_attn_static)
+  // than the workspace at hand holds: madakv_decode_attn_static accepts a call if the longest head cut into `base` rows fits,
+  // so that this limit never changes how a head is cut (short pieces: SHORT_PIECES)
   const long long room = (long long)(ws_bytes / ((size_t)dm.heads * dm.G * (dm.d + 2) * sizeof(float)));
   p.max_chunks = (int)std::max<long long>(1, std::min({(long long)(worst + base - 1) / base, std::max<long long>(2, want), room}));
   p.grid_chunks = std::min(p.max_chunks, (plan_longest(c, longest_rows) + p.chunk_rows - 1) / p.chunk_rows);
   // every head is known to be one piece: nothing to merge, the attention kernel stores the new lengths (128 heads of 120 rows
-  // 6.2 -> 5.1 us per call)
+  // 6.3 -> 4.6 us per call)
   if (p.grid_chunks == 1) p.max_chunks = 1;
   return p;
 }
