@@ -395,6 +395,8 @@ def like_without_known_lengths(eng, args):
     (dict(n_q_heads=14, n_kv_heads=2, head_dim=128, ctx_len=1500, budget=130, cache_fp8=1), [127, 126]),
     (dict(n_q_heads=2, n_kv_heads=2, head_dim=64, ctx_len=1500, budget=256, dtype="fp32"), [254, 200]),
     (dict(n_q_heads=6, n_kv_heads=3, head_dim=128, ctx_len=9000, budget=700, hcc_rho=1), [1400, 128, 300]), # more rows than the average head's
+    (dict(n_q_heads=32, n_kv_heads=32, head_dim=64, ctx_len=9000, budget=400, hcc_rho=64), [5100, 2550, 2560, 100] + [40] * 28),   # many times the average
+    (dict(n_q_heads=64, n_kv_heads=16, head_dim=128, ctx_len=9000, budget=600, hcc_rho=1024), [7000, 1270, 511] + [30] * 13),
 ], ids=lambda x: f"q{x['n_q_heads']}_kv{x['n_kv_heads']}_d{x['head_dim']}_{x.get('dtype', 'bf16')}" if isinstance(x, dict) else "")
 def test_decode_known_lengths(kw, lens):
     """The launch is sized by the heads' lengths once the host knows them (no merge while every head is one piece): the same
