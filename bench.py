@@ -203,7 +203,8 @@ def time_config(name, budget=None, steps=None):
            "decode_GBps": dec_bytes / (de * 1e-3) / 1e9, "decode_frac_of_hbm_peak": dec_bytes / (de * 1e-3) / 1e9 / HBM_PEAK_GBS,
            "decode_bytes_per_layer_call": dec_bytes / (S * NL)}
     # the prefill's last-window attention with the scores as a by-product, where the library takes the shape
-    # (more than 32 proxy rows: one pass over K and V per block of 32 rows)
+    # (up to 64 proxy rows: one pass over K and V per block of 32 rows; more, in calls over a whole model: one pass over K and V
+    # for all rows behind one over K)
     try:
         wout = torch.empty(NL, B, Hq, W, d, dtype=wl.torch_dtype, device=dev)
         ts = []
@@ -212,7 +213,9 @@ def time_config(name, budget=None, steps=None):
             torch.cuda.synchronize()
             ts.append(e[0].elapsed_time(e[1]))
         res["window_attn_score_ms"] = float(np.median(ts[1:]))
-        res["window_attn_passes_over_k_and_v"] = ((Hq // H) * W + 31) // 32
+        M = (Hq // H) * W
+        res["window_attn_passes_over_k_and_v"] = (M + 31) // 32 if M <= 64 else 1
+        res["window_attn_passes_over_k_alone"] = 0 if M <= 64 else 1
         del wout
     except MB.MadaKVError as ex:
         res["window_attn_score_ms"] = None
