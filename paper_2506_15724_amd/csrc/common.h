@@ -128,17 +128,6 @@ __device__ __forceinline__ uint32_t f32_to_e4m3(float f) {
   }
   return sign | min(code, 0x7eu);
 }
-// exact: every E4M3 value is a float.  Normal codes: the 7 magnitude bits become a float's low
-// exponent / top mantissa bits with the exponent re-biased (7 -> 127); subnormal codes are m * 2^-9.
-__device__ __forceinline__ float e4m3_to_f32(uint32_t c) {
-  const float normal = __uint_as_float(((c & 0x7fu) << 20) + (120u << 23));
-  const float subnormal = (float)(c & 7u) * 0.001953125f;
-  const float mag = (c & 0x78u) ? normal : subnormal;
-  return (c & 0x80u) ? -mag : mag;
-}
-
-__device__ __forceinline__ float load_elem(const float* p, long long i) { return p[i]; }
-__device__ __forceinline__ float load_elem(const uint16_t* p, long long i) { return bf16_bits_to_f32(p[i]); }
 
 // Sum over the 16 lanes of a DPP row; every lane of the row ends with the total.
 __device__ __forceinline__ float row16_sum(float x) {
@@ -149,14 +138,6 @@ __device__ __forceinline__ float row16_sum(float x) {
   return x;
 }
 
-__device__ __forceinline__ float wave_sum(float x) {
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-__device__ __forceinline__ float wave_max(float x) {
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
-}
 __device__ __forceinline__ long long shfl_i64(long long v, int src) {
   int lo = __shfl((int)(v & 0xffffffffLL), src, 64);
   int hi = __shfl((int)(v >> 32), src, 64);

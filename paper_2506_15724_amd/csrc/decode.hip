@@ -9,10 +9,10 @@
 // running max / running sum in the log2 domain with fp32 accumulation.  Each head's rows
 // are cut into pieces of `chunk_rows` (one workgroup each): a single layer's 128 ragged heads
 // become ~1100 pieces of work that the hardware scheduler spreads over 256 CUs.  The
-// grid is (heads, pieces of the longest head, at most twice an average head's): workgroups past a head's real
-// length exit at once, and since the piece index is the slow grid dimension they are dispatched
+// grid is (heads, most pieces a head is cut into by decode_plan, or the longest head's once the host knows it): workgroups past
+// a head's real length exit at once, and since the piece index is the slow grid dimension they are dispatched
 // after all the real work.  A second, small kernel merges the partial (max, sum, acc) triples
-// of each head in chunk order.  (Merging inside the first kernel by the last workgroup to
+// of each head in chunk order, unless every head is known to be one piece.  (Merging inside the first kernel by the last workgroup to
 // arrive was measured three times and lost every time: with device-scope fences, which write back and
 // invalidate the whole L2 of an XCD per workgroup, 15x slower; with fence-free agent-scope
 // atomic stores / loads of the partials and one arrival counter per head, 10% slower per call
@@ -47,7 +47,7 @@ constexpr int DEC_THREADS = 256;
 struct DecodeArgs {
   const void* q; const void* k_new; const void* v_new; void* k_c; void* v_c;
   const int64_t* kv_off; int32_t* kv_len; void* out; float* part;
-  int B, H, G, d, chunk_rows, out_fp32, has_new;
+  int B, H, G, chunk_rows, out_fp32, has_new;
   int max_chunks;       // most pieces a head is cut into (head_chunk_rows): partial results per head in `part`
   float* part_ml;       // [heads][max_chunks][G][2] (max, sum) of the partial results, behind part = [heads][max_chunks][G][d]
   long long capacity;   // rows in k_c / v_c
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
   const int len = len_old + (can_append ? 1 : 0);
   const int rows = head_chunk_rows(a, len);
   const int r_begin = chunk * rows;
-  if (chunk > 0 && r_begin >= len) return;           // the grid is sized for the longest head
+  if (chunk > 0 && r_begin >= len) return;           // the grid is the same for all heads (decode_plan)
   const int r_end = min(len, r_begin + rows);
   const RowMap at = make_row_map<PAGED>(a, hidx, off, len_old, can_append, r_begin, r_end);
   const bool has_fresh = can_append && len_old >= r_begin && len_old < r_end;   // uniform: the appended row is in this piece
@@ -753,10 +753,14 @@ template <typename T, typename CT, int LPR, bool PAGED>
 static hipError_t launch_decode_t(const Dims& dm, DecodeArgs& a, int grid_chunks, hipStream_t st) {
   constexpr int D = LPR * 16 / (int)sizeof(CT);
   dim3 grid(dm.heads, grid_chunks), block(DEC_THREADS);
-  if (sizeof(T) == 2 && dm.G >= 2) hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED>), grid, block, 0, st, a);   // grouped queries in bf16: the MFMA kernel
   // Four rows in flight per lane; eight where the pieces are long (a cache that was hardly reduced: 128 heads of 16K bf16 rows
-  // 5.42 -> 5.17 ms for 32 layer calls, 6.6 TB/s): with many trips per workgroup the loads in flight count, with one or two its start and its instructions.
-  else if (dm.G == 1 && sizeof(CT) != 1 && a.chunk_rows > 512) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, 8, 4, PAGED>), grid, block, 0, st, a);
+  // 5.42 -> 5.17 ms for 32 layer calls, 6.6 TB/s): with many trips per workgroup the loads in flight count, with one or two its
+  // start and its instructions.  512-row pieces are in between: 128 heads of 8K rows 92 us with four, 90 with eight, 4096 heads
+  // of 256 75 and 70, but 1024 heads of 512 45.6 and 47.6.  8-bit rows, of which a lane has twice the elements, take four always:
+  // 128 heads of 16K rows 89.3 us with either at 128 dims, 50.6 and 52.9 at 64 (64 heads of 32K: 92.8 and 90.4, 50.4 and 48.0).
+  constexpr int LONG_ROWS = sizeof(CT) == 1 ? 4 : 8;
+  if (sizeof(T) == 2 && dm.G >= 2) hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED>), grid, block, 0, st, a);   // grouped queries in bf16: the MFMA kernel
+  else if (dm.G == 1 && a.chunk_rows > 512) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, LONG_ROWS, 4, PAGED>), grid, block, 0, st, a);
   else if (dm.G == 1) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, 4, 4, PAGED>), grid, block, 0, st, a);
   else if constexpr (sizeof(T) == 4) {
     if (dm.G == 2) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 2, 4, 4, PAGED>), grid, block, 0, st, a);
@@ -784,7 +788,7 @@ hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, 
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.k_c = k_c; a.v_c = v_c; a.kv_off = kv_off; a.kv_len = kv_len;
   a.out = out; a.part = reinterpret_cast<float*>(ws);
   DecodePlan p = decode_plan(dm, c, longest_rows, ws_bytes);
-  a.B = dm.B; a.H = dm.H; a.G = dm.G; a.d = dm.d; a.chunk_rows = p.chunk_rows; a.max_chunks = p.max_chunks;
+  a.B = dm.B; a.H = dm.H; a.G = dm.G; a.chunk_rows = p.chunk_rows; a.max_chunks = p.max_chunks;
   a.part_ml = a.part + (long long)dm.heads * p.max_chunks * dm.G * dm.d;
   a.out_fp32 = c.out_fp32; a.has_new = (k_new != nullptr) ? 1 : 0;
   const float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)dm.d);

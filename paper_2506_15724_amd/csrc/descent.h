@@ -28,7 +28,6 @@ __device__ __forceinline__ DescentRange descent_uniform(const DescentRange& r) {
   return {(uint32_t)__builtin_amdgcn_readfirstlane((int)r.lo), (uint32_t)__builtin_amdgcn_readfirstlane((int)r.hi),
           (uint32_t)__builtin_amdgcn_readfirstlane((int)r.sh), (uint32_t)__builtin_amdgcn_readfirstlane((int)r.sub)};
 }
-__device__ __forceinline__ bool descent_match(const DescentRange& r, uint32_t key) { return key - r.lo <= r.hi - r.lo; }
 __device__ __forceinline__ uint32_t descent_bin(const DescentRange& r, uint32_t key) {
   return (uint32_t)min(max((int)((key >> r.sh) - r.sub), 0), BINS - 1);
 }

@@ -39,7 +39,7 @@ struct madakv_handle {
   int32_t* d_maxlen;
   int32_t* h_maxlen;
   hipEvent_t maxlen_event;
-  // per layer: 0 = nothing known (decode sizes its grid for the worst case), 1 = store enqueued on
+  // per layer: 0 = nothing known (decode sizes its grid by the budget, decode_plan), 1 = store enqueued on
   // maxlen_stream and covered by maxlen_event, 2 = the value in h_maxlen has landed
   std::vector<uint8_t> maxlen_state;
   hipStream_t maxlen_stream;

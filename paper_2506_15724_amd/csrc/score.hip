@@ -6,8 +6,10 @@
 //   sweep 1  per row: running max and sum of exp2 (log2 domain), per L-chunk
 //   sweep 2  recompute the logits, p = exp2(s - (m + log2 l)), sum p over the rows
 // Both sweeps are the same small-M contraction S^T = Q K^T (M = G*W rows, N = keys).
-// bf16 inputs run on the 32x32x16 bf16 MFMA with fp32 accumulation; fp32 inputs (and
-// head dims other than 64/128) take a plain FMA kernel.  All reductions have a fixed
+// Where a workgroup's logits fit in its registers one sweep does both (score_fused_kernel: bf16 up to 64 proxy rows, fp32 up
+// to 32768 keys); more bf16 rows, longer heads and given normalisers take the two.
+// bf16 inputs run on the 32x32x16 bf16 MFMA with fp32 accumulation, fp32 inputs on the 32x32x2 fp32 MFMA (a plain FMA kernel
+// above 32768 keys and for given normalisers).  All reductions have a fixed
 // order: psi feeds integer decisions downstream and must not change from run to run.
 #include "common.h"
 
@@ -635,7 +637,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
 }
 
 // ------------------------------------------------------------------------------------
-// One sweep over K (bf16, at most two row blocks: G*W <= 64).  The logits of a workgroup's
+// One sweep over K (bf16 and 8-bit keys in at most two row blocks, G*W <= 64; fp32 in blocks of 64 rows).  The logits of a workgroup's
 // keys fit in its registers: a wave keeps the D tiles of its NS subtiles (NS * NRB * 16 floats
 // per lane) instead of reducing them on the fly.  After its last subtile a workgroup knows the
 // (max, sum) of every proxy row over its own keys; the workgroups of a head exchange these
@@ -1611,11 +1613,11 @@ __global__ __launch_bounds__(256) void window_attn_reduce_kernel(WinArgs wa) {
 }
 
 // ------------------------------------------------------------------------------------
-// Plain FMA path (fp32 inputs, or bf16 with an odd head_dim).  Same two sweeps.
+// Plain FMA path: fp32 heads of more than FUSED_MAX_SPLIT chunks, and fp32 with given normalisers.  Same two sweeps.
 // Sweep 1: wave w takes rows w, w+4, ...; lanes stride over the keys of the chunk.
 // Sweep 2: one thread per key, loop over the rows.
 // ------------------------------------------------------------------------------------
-template <typename T, int PASS>
+template <int PASS>
 __global__ __launch_bounds__(SCORE_THREADS) void score_simple_kernel(ScoreArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   float* qs = reinterpret_cast<float*>(smem);          // [M][d]
@@ -1625,9 +1627,9 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_simple_kernel(ScoreArgs a
   const int head = a.head0 + blockIdx.y;
   const int kvh = head % a.H;
   const long long lb = head / a.H;
-  const T* qg = reinterpret_cast<const T*>(a.q_win) + (lb * a.H + kvh) * (long long)a.G * a.W * a.d;
-  const T* kg = reinterpret_cast<const T*>(a.k) + (long long)head * a.L * a.d;
-  for (int e = tid; e < a.M * a.d; e += SCORE_THREADS) qs[e] = load_elem(qg, e);
+  const float* qg = reinterpret_cast<const float*>(a.q_win) + (lb * a.H + kvh) * (long long)a.G * a.W * a.d;
+  const float* kg = reinterpret_cast<const float*>(a.k) + (long long)head * a.L * a.d;
+  for (int e = tid; e < a.M * a.d; e += SCORE_THREADS) qs[e] = qg[e];
   if (PASS == 2) {
     const float* rs = a.rowstat + (long long)head * a.nsplit * a.mpad * 2;
     for (int r = tid; r < a.M; r += SCORE_THREADS) {
@@ -1647,7 +1649,7 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_simple_kernel(ScoreArgs a
         const int pos = a.L - a.W + (r % a.W);
         for (int key = chunk0 + lane; key < chunk1 && key <= pos; key += 64) {
           float s = 0.f;
-          for (int e = 0; e < a.d; ++e) s = fmaf(qs[r * a.d + e], load_elem(kg, (long long)key * a.d + e), s);
+          for (int e = 0; e < a.d; ++e) s = fmaf(qs[r * a.d + e], kg[(long long)key * a.d + e], s);
           float s2 = s * a.scale_log2;
           float mn = fmaxf(m, s2);
           l = l * exp2f(m - mn) + exp2f(s2 - mn);
@@ -1667,7 +1669,7 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_simple_kernel(ScoreArgs a
         const int pos = a.L - a.W + (r % a.W);
         if (key > pos) continue;
         float s = 0.f;
-        for (int e = 0; e < a.d; ++e) s = fmaf(qs[r * a.d + e], load_elem(kg, (long long)key * a.d + e), s);
+        for (int e = 0; e < a.d; ++e) s = fmaf(qs[r * a.d + e], kg[(long long)key * a.d + e], s);
         sum += exp2f(s * a.scale_log2 - offs[r]);
       }
       a.psi[(long long)head * a.L + key] = sum;
@@ -1999,7 +2001,8 @@ static void launch_win_many_rows(WinArgs& wa, const Dims& dm, const madakv_confi
   ScoreArgs& a = wa.s;
   const ScorePlan p = score_plan(dm, c.dtype);
   const bool wide8 = p.mpad > 128;
-  // the row statistics go where the row blocks' copies of psi would be: 2 nsplit mpad <= 2 (L / 1024) 32 rb floats per head
+  // the row statistics go where the row blocks' copies of psi would be (32 rb = mpad rows): 2 nsplit mpad <= 2 max(1, L / 1024) 32 rb
+  // floats per head against L rb
   a.rowstat = a.psi_part;
   a.mpad = p.mpad; a.nsplit = p.nsplit; a.nmerge = 1;
   const int fs = win_wide_split(dm, wide8 ? 256 : 512);
@@ -2118,13 +2121,8 @@ hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_wi
     } else {
       size_t lds = ((size_t)dm.M * dm.d + dm.M) * sizeof(float);
       dim3 grid(a.nsplit, nh);
-      if (c.dtype == MADAKV_BF16) {
-        if (!a.lse) hipLaunchKernelGGL((score_simple_kernel<uint16_t, 1>), grid, dim3(SCORE_THREADS), lds, st, a);
-        hipLaunchKernelGGL((score_simple_kernel<uint16_t, 2>), grid, dim3(SCORE_THREADS), lds, st, a);
-      } else {
-        if (!a.lse) hipLaunchKernelGGL((score_simple_kernel<float, 1>), grid, dim3(SCORE_THREADS), lds, st, a);
-        hipLaunchKernelGGL((score_simple_kernel<float, 2>), grid, dim3(SCORE_THREADS), lds, st, a);
-      }
+      if (!a.lse) hipLaunchKernelGGL((score_simple_kernel<1>), grid, dim3(SCORE_THREADS), lds, st, a);
+      hipLaunchKernelGGL((score_simple_kernel<2>), grid, dim3(SCORE_THREADS), lds, st, a);
     }
   }
   return hipGetLastError();
