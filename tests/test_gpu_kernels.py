@@ -474,6 +474,89 @@ def test_decode_static_cuts_heads_like_the_workspace_call(kw, lens):
     eng.close()
 
 
+@pytest.mark.parametrize("kw,lens", [
+    (dict(n_q_heads=64, n_kv_heads=64, head_dim=64, ctx_len=30000, budget=25000, page_rows=64), [24990, 769, 768, 767, 64, 63] + [40] * 58),   # pieces of 768 rows
+    (dict(n_q_heads=14, n_kv_heads=2, head_dim=128, ctx_len=2000, budget=400, page_rows=64), [128, 640]),       # grouped queries: pieces of 128 rows
+    (dict(n_q_heads=8, n_kv_heads=1, head_dim=64, ctx_len=2000, budget=400, page_rows=16, cache_fp8=1), [255]),
+    (dict(n_q_heads=8, n_kv_heads=4, head_dim=128, ctx_len=9000, budget=6000, page_rows=256, hcc_rho=16), [8000, 512, 1, 256 + 128]),
+    (dict(n_q_heads=4, n_kv_heads=4, head_dim=128, ctx_len=2000, budget=400, page_rows=32, cache_fp8=1), [256, 255, 512, 33]),
+    (dict(n_q_heads=6, n_kv_heads=2, head_dim=128, ctx_len=1500, budget=600, page_rows=16, dtype="fp32"), [512, 271]),
+], ids=lambda x: f"q{x['n_q_heads']}_kv{x['n_kv_heads']}_d{x['head_dim']}_P{x['page_rows']}_{x.get('dtype', 'bf16')}" if isinstance(x, dict) else "")
+def test_decode_pieces_paged(kw, lens):
+    """The kernels' paged forms at the edges of pieces, tiles and pages, the appended row being the first of a piece and of a
+    page among them: bit for bit what contiguous segments give, which 64-bit attention confirms at the last step."""
+    flat, args = evicted_engine([max(n, 9) for n in lens], max_new_tokens=40, **{k: v for k, v in kw.items() if k != "page_rows"})
+    paged, _ = evicted_engine([max(n, 9) for n in lens], max_new_tokens=40, **kw)
+    H, Hq, d, n0 = args["n_kv_heads"], args["n_q_heads"], args["head_dim"], flat.kv_len.view(-1).tolist()
+    g = torch.Generator().manual_seed(2)
+    for step in range(34):
+        q, kn, vn = (torch.randn(1, 1, h, d, generator=g).to(DEV, flat.tdtype) for h in (Hq, H, H))
+        outs = [torch.full((1, 1, Hq, d), float("nan"), device=DEV) for _ in range(2)]
+        say(f"paged pieces {kw} step {step}")
+        for e, out in zip((flat, paged), outs):
+            e.decode_attn(0, 1, q, kn, vn, out)
+        torch.cuda.synchronize()
+        assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1])
+        assert flat.kv_len.view(-1).tolist() == paged.kv_len.view(-1).tolist() == [n + step + 1 for n in n0]
+    f64 = lambda t: (t.view(torch.float8_e4m3fn) if args.get("cache_fp8") else t).cpu().double()
+    off = flat.kv_off.view(-1).tolist()
+    for h in range(H):
+        k, v = (f64(x[off[h]:off[h] + n0[h] + 34]) for x in (flat.k_c, flat.v_c))
+        ref = torch.softmax(q.view(H, Hq // H, d)[h].cpu().double() @ k.T / d ** 0.5, -1) @ v
+        assert float((outs[0].view(H, Hq // H, d)[h].cpu().double() - ref).abs().max()) < 1e-4          # (the bound of test_decode_pieces)
+    flat.close(); paged.close()
+
+
+@pytest.mark.parametrize("kw", [dict(head_dim=128), dict(head_dim=64, n_q_heads=8), dict(head_dim=128, cache_fp8=1), dict(head_dim=64, page_rows=16)],
+                         ids=lambda kw: "_".join(f"{k}{v}" for k, v in kw.items()))
+@pytest.mark.parametrize("steps,goes", [(0, "none"), (1, "first"), (1, "last"), (5, "first"), (5, "spread"), (12, "late"), (12, "first")])
+def test_compaction_at_edges(kw, steps, goes):
+    """Re-eviction where the first row that goes is the first of the head, the last candidate, as late as it can be (all the
+    last proxy rows and appended candidates) or none: known rows go by construction, the others stay bit for bit and in
+    order, with their positions.  Heads around the number of rows the kernel moves at a time."""
+    W, lens = 8, [40, 255, 256, 257]
+    eng, args = evicted_engine(lens, n_kv_heads=4, ctx_len=1200, budget=300, **dict(dict(n_q_heads=4), **kw))
+    d, Hq = args["head_dim"], args["n_q_heads"]
+    g = torch.Generator().manual_seed(steps + 1)
+    drop = []
+    for n in lens:
+        cand = n + steps - W
+        drop.append({"none": [], "first": [0] + list(range(cand - steps + 1, cand)), "last": [cand - 1], "late": list(range(n - W, n - W + steps)),
+                     "spread": [0, 7, 20, cand - 2, cand - 1]}[goes])
+        assert len(set(drop[-1])) == steps and all(0 <= r < cand for r in drop[-1])
+    def row(head, i):                    # a row's K: against the queries (q = 4) if it goes, with them if it stays
+        return (-0.5 if i in drop[head] else 0.5) + 0.05 * torch.randn(d, generator=g)
+    off = eng.kv_off.view(-1).tolist()
+    store = lambda t: t.to(torch.float8_e4m3fn).view(torch.uint8) if args.get("cache_fp8") else t.to(eng.tdtype)
+    for h, n in enumerate(lens):
+        eng.k_c[off[h]:off[h] + n] = store(torch.stack([row(h, i) for i in range(n)])).to(DEV)
+    q = torch.full((1, 1, Hq, d), 4.0, device=DEV, dtype=eng.tdtype)
+    out = torch.empty(1, 1, Hq, d, device=DEV)
+    for t in range(steps):
+        kn = torch.stack([row(h, n + t) for h, n in enumerate(lens)]).view(1, 1, 4, d).to(DEV, eng.tdtype)
+        eng.decode_attn(0, 1, q, kn, torch.randn(1, 1, 4, d, generator=g).to(DEV, eng.tdtype), out)
+    torch.cuda.synchronize()
+
+    def rows_of(h, n):                   # where the rows of a head are
+        if not args.get("page_rows"):
+            return list(range(off[h], off[h] + n))
+        P, tbl = args["page_rows"], eng.page_table_host()[0, 0, h]
+        return [off[h] + r if r < tbl[0] * P else int(tbl[1 + (r - tbl[0] * P) // P]) * P + (r - tbl[0] * P) % P for r in range(n)]
+    at = [rows_of(h, n + steps) for h, n in enumerate(lens)]
+    k0, v0, idx0 = [[x[a].clone() for a in at] for x in (eng.k_c, eng.v_c, eng.kept_idx)]
+    say(f"compaction {kw} steps={steps} {goes}")
+    eng.reevict(0, 1, q[:, :, :, None].expand(1, 1, Hq, W, d).contiguous(), torch.zeros(1, args["ctx_len"], dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    assert eng.kv_len.view(-1).tolist() == lens
+    for h, n in enumerate(lens):
+        stay = [r for r in range(n + steps) if r not in drop[h]]
+        now = rows_of(h, n)
+        assert torch.equal(eng.k_c[now], k0[h][stay]) and torch.equal(eng.v_c[now], v0[h][stay])
+        want = [int(idx0[h][r]) if r < n else args["ctx_len"] + r - n for r in stay]
+        assert eng.kept_idx[now].tolist() == want
+    eng.close()
+
+
 @pytest.mark.parametrize("dtype,Hq,d,rows", [("fp32", 1, 128, 2 ** 23 + 4000), ("bf16", 4, 128, 2 ** 24 + 4000)])
 def test_decode_beyond_4_gib_of_rows(dtype, Hq, d, rows):
     """A head whose K rows take more than 4 GiB: all its weight is on four rows beyond that, the output is their mean
