@@ -84,9 +84,13 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# the raw handle of a device's current stream, without the Stream object around it (torch keeps it private: the public way is
+# taken where it is missing)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream():
-    # the raw handle of torch.cuda.current_stream(), without the Stream object around it
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(call, rc):

@@ -581,3 +581,14 @@ def test_decode_beyond_4_gib_of_rows(dtype, Hq, d, rows):
     ref = vals.double().mean(0)
     assert float((out[0, 0].cpu().double() - ref).abs().max()) < 1e-5
     eng.close()
+
+
+def test_calls_use_the_current_stream(monkeypatch):
+    """The handle the binding hands to the library is that of torch's current stream, with and without torch's shortcut."""
+    side = torch.cuda.Stream()
+    shortcut = MB._raw_stream
+    for raw in (shortcut, lambda device: torch.cuda.current_stream(device).cuda_stream):
+        monkeypatch.setattr(MB, "_raw_stream", raw)
+        assert MB._stream() == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert MB._stream() == side.cuda_stream
