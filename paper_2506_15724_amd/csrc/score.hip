@@ -1319,8 +1319,8 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2
 }
 
 // ------------------------------------------------------------------------------------
-// The same for more than 64 proxy rows (grouped queries): one pass over K and V for all of them instead of one per
-// block of 32.  The row statistics come from sweep 1 of the wide scoring kernels (a pass over K of its own), so the softmax
+// The same for more than 64 proxy rows (grouped queries) in calls that fill the chip (win_one_pass): one pass over K and V for
+// all of them instead of one per block of 32.  The row statistics come from sweep 1 of the wide scoring kernels (a pass over K of its own), so the softmax
 // entries are final when they are formed: nothing is exchanged, O is never rescaled, and a workgroup may take as many keys
 // as suits the chip.  Wave w owns the rows of block w (Q fragments and 32 x d of O in registers), the waves share the keys:
 // tiles of K and V come straight into a ring of three (global_load_lds, as in score_wide_dma_kernel, all LDS traffic of the
@@ -1328,8 +1328,10 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2
 // row-wise sums for psi over the lanes, P as bf16 hi + lo parts straight from those registers into O += P V, the V
 // fragments through transposing LDS reads (four keys of 16 columns per 16 lanes).  The 16-byte pieces of a row are permuted
 // in the tile so that both kinds of reads are spread over all banks (tile_swizzle).
-// Bound by the vector unit and the matrix unit together (per logit one exp2, two conversions and 3 instructions of
-// the sum over rows; 24 matrix instructions per 32 keys and block), two waves per SIMD to overlap them.
+// Per logit one exp2, two conversions and 3 instructions of the sum over rows; 24 matrix instructions per 32 keys and block (more
+// with third parts), one after the other in a wave; two waves per SIMD overlap them in part: by the counters the matrix unit
+// is busy 36% of the time, a wave issues vector or matrix instructions in 28% of its cycles and waits in 25%; K and V
+// are fetched once.
 // 28 layers x 4 heads of 32K keys with 224 rows: 2.73 ms in seven passes -> 1.22 ms for the whole call (sweep 1 0.34, this
 // kernel 0.80: K and V once is 1.9 GB, 0.3 ms; the matrix instructions alone 0.35 ms).
 // ------------------------------------------------------------------------------------
