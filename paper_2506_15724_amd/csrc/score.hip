@@ -1976,18 +1976,24 @@ static bool win_one_pass(const Dims& dm) {
   const long long block_wgs = (long long)dm.heads * win_blocks(dm) * win_split(dm);
   return block_wgs > ((dm.L > 16384 || (dm.d == 128 && win_blocks(dm) > 4)) ? 1024 : 640);
 }
-// Chunks per head of window_wide_kernel (`slots` workgroups of it are on the chip at a time): the fewest that leave the last
-// round of workgroups nearly full, since every chunk costs a share of O, 32 d floats per block of rows written and read
-// again.  112 heads of 32K keys and 224 rows: 9 chunks, 16 or 32 are 4-9% slower; one head of 128K keys and 256 rows: 16 chunks
-// 549 us, 64 237, 252 174; 4 heads of 128K and 224 rows: 16 chunks 564, 63 266, 256 316.  (At most win_split: shorter chunks
-// than the other kernel's, for which the workspace is made, gain nothing.)
-static int win_wide_split(const Dims& dm, int slots) {
-  const int most = win_split(dm);
-  int best = 1; double best_eff = 0.;
-  for (int ns = 1; ns <= most; ++ns) {
-    const long long wgs = (long long)dm.heads * ns, rounds = (wgs + slots - 1) / slots;
-    const double eff = (double)wgs / (double)(rounds * slots);
-    if (eff > best_eff + 0.02) { best = ns; best_eff = eff; }
+// Keys per chunk of window_wide_kernel: what costs least, counted in tiles of a workgroup.  A call takes as many rounds of
+// workgroups as the chip holds of them (one of eight waves per compute unit, two of four), a round its tiles and about one of 64
+// keys for its start; every chunk leaves a share of O, 32 d floats per block of rows written and read again, 6.5 ns at 128 dims
+// against 2.8 us for a tile of eight waves and 1.7 for one of four (1.2 where a workgroup has its compute unit to itself).  Over 92
+// measured shapes (1-224 heads, 96-256 rows, 2K-128K keys) the choice is within 3% of the best number of chunks.  112 heads
+// of 32K keys and 224 rows: 9 chunks, 16 or 32 are 4-9% slower; one head of 128K keys and 256 rows: 16 chunks 549 us, 64
+// 237, 256 174; 4 heads of 128K and 224 rows: 16 chunks 564, 64 266, 256 316; 112 heads of 8K: 2 chunks 348, 9 376, 16 405.
+// (At most win_split chunks, for which the workspace is made.)
+static int win_wide_chunk(const Dims& dm, bool wide8) {
+  const int slots = wide8 ? 256 : 512, tile = wide8 ? 64 : 32;
+  const double start = wide8 ? 1.0 : 2.0, share = (wide8 ? 0.002 : 0.004) * dm.d / 128 * win_blocks(dm);
+  int best = 0; double least = 0.;
+  for (int ns = 1; ns <= win_split(dm); ++ns) {
+    const int chunk = ((dm.L + ns - 1) / ns + 63) / 64 * 64;
+    const long long wgs = (long long)dm.heads * ((dm.L + chunk - 1) / chunk), rounds = (wgs + slots - 1) / slots;
+    const double tiles = (double)((chunk + tile - 1) / tile) * (!wide8 && wgs <= 256 ? 0.7 : 1.0);
+    const double cost = (double)rounds * (tiles + start) + share * (double)wgs;
+    if (!best || cost < least) { best = chunk; least = cost; }
   }
   return best;
 }
@@ -2007,8 +2013,7 @@ static void launch_win_many_rows(WinArgs& wa, const Dims& dm, const madakv_confi
   // floats per head against L rb
   a.rowstat = a.psi_part;
   a.mpad = p.mpad; a.nsplit = p.nsplit; a.nmerge = 1;
-  const int fs = win_wide_split(dm, wide8 ? 256 : 512);
-  const int chunk2 = ((dm.L + fs - 1) / fs + 63) / 64 * 64;
+  const int chunk2 = win_wide_chunk(dm, wide8);
   a.fsplit = (dm.L + chunk2 - 1) / chunk2;
   for (int h0 = 0; h0 < dm.heads; h0 += 65535) {
     const int nh = std::min(65535, dm.heads - h0);
