@@ -39,10 +39,11 @@
  *   - Arguments are validated on the host before anything is enqueued.  Errors
  *     found there leave all outputs untouched.
  *   - The handle belongs to the HIP device that was current in madakv_create; that device must
- *     be current in every later call on it.  It owns a few KB of device memory (carry state of
- *     the layer recurrence and cache cursors; with a paged cache its page table; for contexts of
+ *     be current in every later call on it.  It owns device memory: a few KB of carry state (layer
+ *     recurrence, cache cursors), the partial results of decode's pieces (1-14% of the reduced cache with
+ *     hcc_rho = 2; every layer has its own), with a paged cache its page table and for contexts of
  *     four or more 16384-token chunks on at most 128 heads per layer a few MB of histograms that
- *     the per-head statistics and selection kernels share between launches), a little pinned
+ *     the per-head statistics and selection kernels share between launches; and a little pinned
  *     host memory, one extra stream of default priority and a few events.  Calls on one handle
  *     must not overlap.
  *   - Layers are addressed as a range [layer0, layer0 + n).  Tensor arguments hold
@@ -261,6 +262,8 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
  *   kv_len   [n, B, H]        in/out: the array madakv_select_gather filled (the library sizes
  *                              its launch from the lengths it produced); incremented by the append
  *   out      [n, B, Hq, d]    float if out_fp32 else dtype
+ *   ws, ws_bytes               at least what madakv_workspace_bytes reports (checked; the partial results now go
+ *                              through the handle's own memory)
  * INVALID_ARG if a layer in the range has already appended max_new_tokens rows. */
 int32_t madakv_decode_attn(madakv_handle* h, int32_t layer0, int32_t n,
                            const void* q, const void* k_new, const void* v_new,
@@ -314,19 +317,14 @@ int32_t madakv_page_table(const madakv_handle* h, const int32_t** table, int32_t
 
 /* madakv_decode_attn for callers that cannot allocate device memory and so have no workspace to
  * pass: code running under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  Same arguments, kernels and results as madakv_decode_attn, without ws: the partial
- * results of heads that are cut into several chunks go to an array of
- * MADAKV_STATIC_SCRATCH_BYTES bytes that is part of the library's device code (one copy per GPU,
- * held until the process ends).  The call allocates and frees nothing.
- *   - MADAKV_ERR_WORKSPACE_TOO_SMALL if this launch needs more than the array holds: the need is
- *     (heads in the call) * (chunks of the longest head) * G * (head_dim + 2) * 4 bytes, with
+ * hipMalloc.  Same arguments, kernels and results as madakv_decode_attn, without ws.  The call allocates and frees
+ * nothing.
+ *   - MADAKV_ERR_WORKSPACE_TOO_SMALL if the pieces of this launch, cut as below, would take more than
+ *     MADAKV_STATIC_SCRATCH_BYTES: (heads in the call) * (chunks of the longest head) * G * (head_dim + 2) * 4 bytes, with
  *     chunks of 256 .. 1024 rows (512 once the call covers >= 1024 heads); the longest head is
  *     taken from what the eviction produced once that has reached the host, from ctx_len +
  *     max_new_tokens before.  One layer of 128 heads of up to 16K rows fits.  Nothing is
  *     enqueued in that case.
- *   - Every call on one GPU, from any handle, uses the same array: calls that may run
- *     concurrently on one GPU (different streams) race on it and must not be issued.  Nothing in
- *     the array has to survive between calls.
  *   - On a stream under graph capture (this call or madakv_decode_attn) the launch is sized for every
  *     row the segments have room for, so that the captured step can be replayed while the heads
  *     grow; each replay appends a row like a call would, but the library's count of appended rows

@@ -36,11 +36,23 @@ long long region_tokens_of(const madakv_config& c);     // rows of the reduced c
 long long init_limit_of(const madakv_config& c);
 int page_table_entries(const madakv_config& c);
 
+// Where the pieces a decode call cuts a head into meet (decode.hip); owned by the handle.
+constexpr int MEET_WAVES = 4;            // counters of a head of grouped queries (a single query head: one)
+constexpr int MEET_COUNT_STRIDE = 32;    // a counter has 128 bytes to itself
+constexpr int MEET_ROOM = 32;            // records behind the last head's that may be read, for nothing
+struct Meet {
+  float* acc;               // [n_layers * B * H][slots][G][d] partial results of the pieces
+  float* ml;                // [n_layers * B * H][slots][G][2] their (max, sum)
+  uint32_t* count;          // [n_layers * B * H][MEET_WAVES if G > 1][MEET_COUNT_STRIDE] arrivals, zero between calls
+  int32_t* len1;            // [n_layers * B * H] 1 + the rows the eviction left each head, 0 before the first one
+  int slots;                // most pieces of a head in any call
+};
+
 struct ScorePlan { int nsplit; int chunk; int mpad; int group_heads; };
 struct DecodePlan { int chunk_rows; int max_chunks; int grid_chunks; };   // rows per piece of a head, most pieces of a head, pieces in the grid
 
 ScorePlan score_plan(const Dims& dm, int dtype);
-DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows, size_t ws_bytes);
+DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows, int slots);
 size_t score_ws_bytes(const Dims& dm, int dtype);
 size_t select_ws_bytes(const Dims& dm, const madakv_config& c);
 size_t decode_ws_bytes(const Dims& dm, const madakv_config& c);                             // worst case over head lengths
@@ -62,7 +74,7 @@ hipError_t launch_stats(const Dims& dm, const madakv_config& c, const float* psi
 hipError_t launch_allocate(const Dims& dm, const madakv_config& c, int layer0, const void* stats,
                            const int32_t* n_mod, int32_t* budgets, long long* pool_state, hipStream_t st);
 hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, const int32_t* budgets,
-                          int64_t* kv_off, int32_t* kv_len, long long* cursor_state, int32_t* layer_maxlen, void* ws,
+                          int64_t* kv_off, int32_t* kv_len, int32_t* len1, long long* cursor_state, int32_t* layer_maxlen, void* ws,
                           const Paging& pg, int blocks_per_batch, hipStream_t st, const AllocArgs* alloc = nullptr);   // alloc: the allocation in the same launch
 hipError_t launch_select(const Dims& dm, const madakv_config& c, const float* psi_pool, const uint8_t* mask,
                          const int32_t* budgets, const int64_t* kv_off, const int32_t* kv_len, int32_t* kept_idx,
@@ -94,7 +106,7 @@ hipError_t launch_gather(const Dims& dm, const madakv_config& c, int li0, int nl
                          int blocks_per_batch, int grid_blocks, hipStream_t st, bool leave_room = false);
 hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, const void* k_new,
                          const void* v_new, void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
-                         void* out, void* ws, size_t ws_bytes, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st);
+                         void* out, const Meet& meet, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st);
 
 constexpr int GATHER_ROWS = 64;   // rows of the reduced cache one gather workgroup fills
 

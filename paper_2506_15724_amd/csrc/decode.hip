@@ -11,29 +11,22 @@
 // become ~1100 pieces of work that the hardware scheduler spreads over 256 CUs.  The
 // grid is (heads, most pieces a head is cut into by decode_plan, or the longest head's once the host knows it): workgroups past
 // a head's real length exit at once, and since the piece index is the slow grid dimension they are dispatched
-// after all the real work.  A second, small kernel merges the partial (max, sum, acc) triples
-// of each head in chunk order, unless every head is known to be one piece.  (Merging inside the first kernel by the last workgroup to
-// arrive was measured three times and lost every time: with device-scope fences, which write back and
-// invalidate the whole L2 of an XCD per workgroup, 15x slower; with fence-free agent-scope
-// atomic stores / loads of the partials and one arrival counter per head, 10% slower per call
-// on 128 heads of ~2K rows and 4x slower on 32 heads of ~4K rows: every workgroup then ends in
-// a store acknowledgement plus an atomic round trip, and the last one adds a dependent read.
-// Without any counter: the workgroup of a head's last chunk, which is
-// dispatched after the others, polls their partials, written as self-validating 64-bit words
-// {value, call number}; 30.2 against 29.5 us per call for the same kernel followed by the merge
-// kernel, and the extra state costs the attention loop registers: 142 instead of 122, or spills.
-// Cutting the rows of all heads, laid end to end, into equal stretches per workgroup, so that
-// the launch has a single, perfectly balanced round of workgroups, was measured too: 27.3 us
-// against 26.9 us for the attention part on 128 heads of ~2K rows, the table of head starts
-// every workgroup has to build first costs what the balance gains.)
-// The appended row is taken from k_new / v_new by the
-// workgroup whose piece holds it, which also stores it in the cache; kv_len is bumped by
-// whoever finalises the head.
+// after all the real work.  The pieces of a head meet inside the same launch (finish_piece): every one leaves its partial
+// (max, sum, acc) in memory, has the stores acknowledged and counts itself at the head's counter, and whoever comes last
+// merges them in piece order.  Nobody waits for another workgroup.  The appended row is taken from k_new / v_new by the
+// workgroup whose piece holds it, which also stores it in the cache; kv_len is bumped by whoever finishes the head.
 //
-// Measured per layer call, attention + merge (attention alone), before -> after the load path was made small and
-// branch-free (instructions are cold at every launch) and four rows instead of eight kept in flight per lane: 128 heads of
-// ~2K bf16 rows, 135 MB, 28.0 -> 26.9 us (23.6: 5.7 TB/s), 8-bit rows 19.0 -> 17.6 (14.5), 32 heads of 4K paged rows,
-// 67 MB, 21.0 -> 15.0 (11.8: 5.7 TB/s), 4 heads of 2K rows with 7 queries each 16.8 -> 10.4 (6.3, latency).
+// Measured per layer call, with a merge kernel behind the attention kernel -> in one launch: 128 heads of ~2K bf16 rows,
+// 135 MB, 28.6 -> 26.8 us (the rows alone take 21.7 at the rate of a large read), 8-bit rows 18.7 -> 16.6, 4 heads of 2K rows
+// with 7 queries each 10.5 -> 8.4.  What the end of a piece costs, from the last row to the output: 0.35 us among the lanes
+// of a wave (row swaps and rotations; shuffles through LDS took 0.75), 0.4 among the waves, 0.6 for acknowledgement and
+// arrival, 0.7-1.3 for reading the pieces, 0.3 for the output.  It is instructions as much as trips to memory: a merge by
+// the whole workgroup with 8-byte accesses, polling for words not yet there instead of counting, took 3.5 us longer than
+// this one on grouped queries and gained nothing over the merge kernel on single ones.  Counters that share a line cost
+// as much as the merge kernel does: hence 128 bytes each.
+// Cutting the rows of all heads, laid end to end, into equal stretches per workgroup, so that the launch has a single,
+// perfectly balanced round of workgroups: 27.3 against 26.9 us for 128 heads of ~2K rows, the table of head starts every
+// workgroup has to build first costs what the balance gains.
 #include "common.h"
 
 #include <algorithm>
@@ -43,13 +36,16 @@ namespace madakv {
 
 constexpr float DNEG_BIG = -1.0e30f;
 constexpr int DEC_THREADS = 256;
+typedef __attribute__((ext_vector_type(4))) unsigned int du32x4_t;
+typedef __attribute__((ext_vector_type(2))) unsigned int du32x2_t;
 
 struct DecodeArgs {
   const void* q; const void* k_new; const void* v_new; void* k_c; void* v_c;
-  const int64_t* kv_off; int32_t* kv_len; void* out; float* part;
+  const int64_t* kv_off; int32_t* kv_len; void* out;
   int B, H, G, chunk_rows, out_fp32, has_new;
-  int max_chunks;       // most pieces a head is cut into (head_chunk_rows): partial results per head in `part`
-  float* part_ml;       // [heads][max_chunks][G][2] (max, sum) of the partial results, behind part = [heads][max_chunks][G][d]
+  int max_chunks;       // most pieces a head is cut into (head_chunk_rows)
+  int max_new;          // rows a segment has room for behind those of the eviction
+  Meet meet;            // where the pieces of a head meet
   long long capacity;   // rows in k_c / v_c
   // paged cache (page_rows > 0): see struct Paging
   int page_rows, page_shift, tbl_entries;
@@ -119,11 +115,6 @@ __device__ __forceinline__ void load_floats(const T* p, float* f) {
   constexpr int PER = 16 / sizeof(T);                 // elements per 16-byte load
 #pragma unroll
   for (int j = 0; j < EPL / PER; ++j) Elems<T>::unpack(*reinterpret_cast<const uint4*>(p + j * PER), f + j * PER);
-}
-template <typename T>
-__device__ __forceinline__ void store_out(void* out, int out_fp32, long long o, float val) {
-  if (out_fp32 || sizeof(T) == 4) reinterpret_cast<float*>(out)[o] = val;
-  else reinterpret_cast<uint16_t*>(out)[o] = f32_to_bf16_rne(val);
 }
 
 // ---- where row r of a head lives ---------------------------------------------------------
@@ -216,32 +207,148 @@ __device__ __forceinline__ void stage_new_row(const DecodeArgs& a, long long hid
   __syncthreads();
 }
 
-// The NW waves' (max, sum, acc) of a piece merged in wave order: the output if the head is this one piece, a partial
-// result otherwise.  The threads share the group's query heads and elements.
+// ---- the end of a piece ------------------------------------------------------------------------
+// exp2 of something <= 0, a weight beside one of 1: the instruction itself (the library call spends seven more on keeping
+// denormal results)
+__device__ __forceinline__ float weight_of(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// The two values of lanes that are O apart (O = 4 ... 32: within a row by rotation, across rows by a swap of rows), the
+// same pair in both lanes up to its order.
+template <int O>
+__device__ __forceinline__ void lane_pair(float x, float& p, float& q) {
+  const uint32_t u = __float_as_uint(x);
+  if constexpr (O == 32) { const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false); p = __uint_as_float(r[0]); q = __uint_as_float(r[1]); }
+  else if constexpr (O == 16) { const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false); p = __uint_as_float(r[0]); q = __uint_as_float(r[1]); }
+  else { p = x; q = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u, 0x120 + O, 0xF, 0xF, true)); }       // row_ror
+}
+// (max, sum, acc) of the lanes LPR, 2 LPR, ... apart merged, the result in all of them
+template <int O, int N>
+__device__ __forceinline__ void merge_lanes(float& m, float& l, float (&acc)[N]) {
+  if constexpr (O < 64) {
+    float m1, m2, l1, l2;
+    lane_pair<O>(m, m1, m2);
+    lane_pair<O>(l, l1, l2);
+    m = fmaxf(m1, m2);
+    const float c1 = weight_of(m1 - m), c2 = weight_of(m2 - m);
+    l = l1 * c1 + l2 * c2;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      float a1, a2;
+      lane_pair<O>(acc[e], a1, a2);
+      acc[e] = a1 * c1 + a2 * c2;
+    }
+    merge_lanes<O * 2, N>(m, l, acc);
+  }
+}
+
+// Workgroups of the grid that arrive at a head's counters: those whose piece may exist before the next eviction.  It follows
+// from what only an eviction changes (len1: 1 + the rows it left; 0: this handle has not seen one) and not from the head's length,
+// which the last one to arrive has replaced by the time a workgroup further back in the grid starts.
+__device__ __forceinline__ int arrivals(const DecodeArgs& a, int len1) {
+  if (len1 == 0) return (int)gridDim.y;
+  return max(1, min((int)gridDim.y, (len1 - 1 + a.max_new + a.chunk_rows - 1) / a.chunk_rows));
+}
+
+// four neighbouring elements of the output
+template <typename T>
+__device__ __forceinline__ void store_out4(const DecodeArgs& a, long long o, float4 x, float ls) {
+  x = make_float4(x.x / ls, x.y / ls, x.z / ls, x.w / ls);
+  if (a.out_fp32 || sizeof(T) == 4) {
+    *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + o) = x;
+  } else {
+    const uint32_t lo = (uint32_t)f32_to_bf16_rne(x.x) | ((uint32_t)f32_to_bf16_rne(x.y) << 16);
+    const uint32_t hi = (uint32_t)f32_to_bf16_rne(x.z) | ((uint32_t)f32_to_bf16_rne(x.w) << 16);
+    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + o) = make_uint2(lo, hi);
+  }
+}
+// Partial results go past the caches that other XCDs do not see (the sc1 bit, which is what an agent-scope atomic access
+// has; those move 8 bytes at most, and two per lane are twice the requests: 16 partial results of 7 query heads took 1.9 us
+// to read instead of 1.3).
+constexpr int AGENT = 16;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t agent_buffer(void* p) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7fffffff, 0x00020000); }
+
+// The NW waves' (max, sum, acc) of a piece merged in wave order: the output if the head is this one piece.  Otherwise the
+// piece's partial result goes to the head's record, and the last workgroup to arrive at the head's counter merges them all,
+// in piece order, and stores the head's new length (everybody has read the old one).  Behind the barrier every wave works
+// for itself, with counters of its own: 64 / (D / 4) query heads per wave, four elements per lane (a single query head:
+// the first wave alone, whose lanes share the pieces); a wave has its stores acknowledged, arrives, and leaves unless it is
+// the last.
 template <typename T, int D, int NW, int GT>
-__device__ __forceinline__ void finish_piece(const DecodeArgs& a, long long hidx, int chunk, bool whole, const float (*s_ml)[GT][2],
-                                             const float (*s_acc)[GT][D]) {
-  const int t = threadIdx.x % D;
-#pragma unroll 1
-  for (int g = threadIdx.x / D; g < a.G; g += NW * 64 / D) {
-    float mx = DNEG_BIG;
+__device__ __forceinline__ void finish_piece(const DecodeArgs& a, long long hidx, int chunk, int len, int rows, bool can_append, int arrive,
+                                             const float (*s_ml)[GT][2], const float (*s_acc)[GT][D]) {
+  constexpr int TL = D / 4, QW = 64 / TL, KP = GT == 1 ? QW : 1, MB = GT == 1 ? 8 : 16;   // MB: pieces in flight per lane
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (GT == 1 ? wave > 0 : wave * QW >= a.G) return;
+  const int t = lane % TL, kp = GT == 1 ? lane / TL : 0, g = GT == 1 ? 0 : wave * QW + lane / TL;
+  const bool act = GT == 1 ? kp == 0 : g < a.G;
+  const int pieces = len <= rows ? 1 : (len + rows - 1) / rows;
+  const long long o = (hidx * a.G + g) * D + 4 * t;
+  // records of a head: [pieces][G][D] accumulated elements, then [pieces][G] (max, sum)
+  const long long head = a.head0 + hidx;
+  const __amdgpu_buffer_rsrc_t rec = agent_buffer(a.meet.acc + head * a.meet.slots * a.G * D);
+  const __amdgpu_buffer_rsrc_t rec_ml = agent_buffer(a.meet.ml + head * a.meet.slots * a.G * 2);
+  if (chunk < pieces && act) {
+    float mx = DNEG_BIG, ls = 0.f;
+    float4 av = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int w = 0; w < NW; ++w) mx = fmaxf(mx, s_ml[w][g][0]);
-    float ls = 0.f, av = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float c = exp2f(s_ml[w][g][0] - mx);
+      const float c = weight_of(s_ml[w][g][0] - mx);
+      const float4 x = *reinterpret_cast<const float4*>(&s_acc[w][g][4 * t]);
       ls += s_ml[w][g][1] * c;
-      av += s_acc[w][g][t] * c;
+      av.x += x.x * c; av.y += x.y * c; av.z += x.z * c; av.w += x.w * c;
     }
-    if (whole) {
-      store_out<T>(a.out, a.out_fp32, (hidx * a.G + g) * D + t, av / ls);
+    if (pieces == 1) {
+      store_out4<T>(a, o, av, ls);
     } else {
-      const long long p = (hidx * a.max_chunks + chunk) * a.G + g;
-      a.part[p * D + t] = av;
-      if (t == 0) *reinterpret_cast<float2*>(a.part_ml + p * 2) = make_float2(mx, ls);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(du32x4_t, av), rec, (g * D + 4 * t) * 4, chunk * a.G * D * 4, AGENT);
+      if (t == 0) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(du32x2_t, make_float2(mx, ls)), rec_ml, g * 8, chunk * a.G * 8, AGENT);
     }
   }
+  if (arrive > 1) {
+    uint32_t* count = a.meet.count + (GT == 1 ? head : head * MEET_WAVES + wave) * MEET_COUNT_STRIDE;
+    uint32_t arrived = 0u;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the wave's stores are where everybody sees them
+    if (lane == 0) arrived = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    arrived = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
+    if (arrived + 1u != (uint32_t)arrive) return;
+    if (lane == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (pieces > 1) {
+      float m = DNEG_BIG, ls = 0.f, av[4] = {0.f, 0.f, 0.f, 0.f};
+      const int gg = act || GT == 1 ? g : 0;                   // (lanes without a query head read along)
+      for (int c0 = 0; c0 < pieces; c0 += KP * MB) {
+        // (past the last piece: slots of the next head, or the room behind the last one's; masked)
+        float4 x[MB]; float2 ml[MB];
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+          ml[j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rec_ml, (kp + gg) * 8, (c0 + j * KP) * a.G * 8, AGENT));
+          x[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rec, ((kp + gg) * D + 4 * t) * 4, (c0 + j * KP) * a.G * D * 4, AGENT));
+        }
+        float bm = m;
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+          const bool mine = c0 + j * KP + kp < pieces;
+          ml[j].x = mine ? ml[j].x : 2.f * DNEG_BIG;          // weight 0
+          ml[j].y = mine ? ml[j].y : 0.f;
+          if (!mine) x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+          bm = fmaxf(bm, ml[j].x);
+        }
+        const float sc = weight_of(m - bm);
+        ls *= sc; av[0] *= sc; av[1] *= sc; av[2] *= sc; av[3] *= sc;
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+          const float f = weight_of(ml[j].x - bm);
+          ls = fmaf(ml[j].y, f, ls);
+          av[0] = fmaf(x[j].x, f, av[0]); av[1] = fmaf(x[j].y, f, av[1]); av[2] = fmaf(x[j].z, f, av[2]); av[3] = fmaf(x[j].w, f, av[3]);
+        }
+        m = bm;
+      }
+      if (KP > 1) merge_lanes<TL, 4>(m, ls, av);
+      if (act) store_out4<T>(a, o, make_float4(av[0], av[1], av[2], av[3]), ls);
+    }
+  }
+  if (can_append && threadIdx.x == 0) a.kv_len[hidx] = len;
 }
 
 template <typename T, typename CT, int LPR, int GT, int UNROLL, int NW, bool PAGED>   // T: Q / new rows / out; CT: cache elements
@@ -250,14 +357,14 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
   constexpr int RPI = 64 / LPR;
   constexpr int D = LPR * EPL;
   __shared__ float s_ml[NW][GT][2];
-  __shared__ float s_acc[NW][GT][D];
+  __shared__ __attribute__((aligned(16))) float s_acc[NW][GT][D];
   __shared__ __attribute__((aligned(16))) CT s_new[2 * D];
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane / LPR, piece = lane % LPR;
   const long long hidx = piece_head();               // (layer, batch, kv head) of the call
   const int chunk = blockIdx.y;                      // which piece of the head
-  const int len_old = a.kv_len[hidx];
+  const int len1 = a.meet.len1[a.head0 + hidx], len_old = a.kv_len[hidx];
   const long long off = a.kv_off[hidx];
   // queries of the group (on their way while the length is), pre-multiplied by scale * log2(e) below
   float qf[GT][EPL];
@@ -268,12 +375,13 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
     for (int e = 0; e < EPL; ++e) qf[g][e] = 0.f;
     if (g < a.G) load_floats<T, EPL>(qg + (long long)g * D + piece * EPL, qf[g]);
   }
+  const int arrive = arrivals(a, len1);
+  if (chunk >= arrive) return;                       // the grid is the same for all heads (decode_plan)
   // an empty segment (its budgets did not fit the cache) stays empty: no append, output 0/0 = NaN
   const bool can_append = can_append_to(a, off, len_old);
   const int len = len_old + (can_append ? 1 : 0);
   const int rows = head_chunk_rows(a, len);
-  const int r_begin = chunk * rows;
-  if (chunk > 0 && r_begin >= len) return;           // the grid is the same for all heads (decode_plan)
+  const int r_begin = chunk * rows;                  // (past the head's end: no rows, the workgroup only arrives)
   const int r_end = min(len, r_begin + rows);
   const RowMap at = make_row_map<PAGED>(a, hidx, off, len_old, can_append, r_begin, r_end);
   const bool has_fresh = can_append && len_old >= r_begin && len_old < r_end;   // uniform: the appended row is in this piece
@@ -341,12 +449,12 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
       float mx = m[g];
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) mx = fmaxf(mx, s[u][g]);
-      const float sc = exp2f(m[g] - mx);
+      const float sc = weight_of(m[g] - mx);
       l[g] *= sc;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) acc[g][e] *= sc;
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) { s[u][g] = exp2f(s[u][g] - mx); l[g] += s[u][g]; }
+      for (int u = 0; u < UNROLL; ++u) { s[u][g] = weight_of(s[u][g] - mx); l[g] += s[u][g]; }
       m[g] = mx;
     }
 #pragma unroll
@@ -360,22 +468,10 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
     }
   }
 
-  // merge the RPI row groups of the wave (fixed butterfly), then the NW waves through LDS
+  // merge the RPI row groups of the wave, then the NW waves through LDS
 #pragma unroll
   for (int g = 0; g < GT; ++g) {
-#pragma unroll
-    for (int o = LPR; o < 64; o <<= 1) {
-      const float m2 = __shfl_xor(m[g], o, 64), l2 = __shfl_xor(l[g], o, 64);
-      const float mx = fmaxf(m[g], m2);
-      const float c1 = exp2f(m[g] - mx), c2 = exp2f(m2 - mx);
-      l[g] = l[g] * c1 + l2 * c2;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const float a2 = __shfl_xor(acc[g][e], o, 64);
-        acc[g][e] = acc[g][e] * c1 + a2 * c2;
-      }
-      m[g] = mx;
-    }
+    merge_lanes<LPR, EPL>(m[g], l[g], acc[g]);
     if (sub == 0) {
       if (piece == 0) { s_ml[wave][g][0] = m[g]; s_ml[wave][g][1] = l[g]; }
 #pragma unroll
@@ -383,10 +479,7 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
     }
   }
   __syncthreads();
-  finish_piece<T, D, NW, GT>(a, hidx, chunk, len <= rows, s_ml, s_acc);
-  // kv_len is read by every workgroup of the head: with several per head only the merge
-  // kernel, which runs after all of them, may store the new length
-  if (a.max_chunks == 1 && can_append && threadIdx.x == 0) a.kv_len[hidx] = len;
+  finish_piece<T, D, NW, GT>(a, hidx, chunk, len, rows, can_append, arrive, s_ml, s_acc);
 }
 
 // ------------------------------------------------------------------------------------
@@ -412,8 +505,6 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
 typedef __attribute__((ext_vector_type(8))) __bf16 dbf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 dbf16x2_t;
 typedef __attribute__((ext_vector_type(4))) float df32x4_t;
-typedef __attribute__((ext_vector_type(4))) unsigned int du32x4_t;
-typedef __attribute__((ext_vector_type(2))) unsigned int du32x2_t;
 typedef __attribute__((ext_vector_type(2))) float df32x2_t;
 typedef __attribute__((ext_vector_type(4))) short ds16x4_t;
 typedef __attribute__((address_space(3))) ds16x4_t* lds_s16x4_ptr_t;
@@ -451,7 +542,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
   const int j16 = lane & 15, c = lane >> 4;
   const long long hidx = piece_head();
   const int chunk = blockIdx.y;
-  const int len_old = a.kv_len[hidx];
+  const int len1 = a.meet.len1[a.head0 + hidx], len_old = a.kv_len[hidx];
   const long long off = a.kv_off[hidx];
   // Q as the B operand: lane (q = j16, c) holds dims [32 ks + 8 c, +8) of query q
   dbf16x8_t qb[KS];
@@ -462,11 +553,12 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
     if (j16 < a.G) raw = *reinterpret_cast<const du32x4_t*>(qg + (long long)j16 * D + ks * 32 + c * 8);
     qb[ks] = __builtin_bit_cast(dbf16x8_t, raw);
   }
+  const int arrive = arrivals(a, len1);
+  if (chunk >= arrive) return;
   const bool can_append = can_append_to(a, off, len_old);
   const int len = len_old + (can_append ? 1 : 0);
   const int rows = head_chunk_rows(a, len);
   const int r_begin = chunk * rows;
-  if (chunk > 0 && r_begin >= len) return;
   const int r_end = min(len, r_begin + rows);
   const RowMap at = make_row_map<PAGED>(a, hidx, off, len_old, can_append, r_begin, r_end);
   const bool has_fresh = can_append && len_old >= r_begin && len_old < r_end;   // uniform: the appended row is in this piece
@@ -555,13 +647,13 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
     tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
     const float m_new = fmaxf(m_run, tmax);
-    const float alpha = exp2f(m_run - m_new);
+    const float alpha = weight_of(m_run - m_new);
     m_run = m_new;
     float psum = 0.f;
     uint32_t hi[4], lo[4];                                // P as bf16 hi + lo, 8 keys per lane: the A fragment
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const df32x2_t pv = {exp2f(p[e >> 1][(e & 1) * 2] - m_new), exp2f(p[e >> 1][(e & 1) * 2 + 1] - m_new)};
+      const df32x2_t pv = {weight_of(p[e >> 1][(e & 1) * 2] - m_new), weight_of(p[e >> 1][(e & 1) * 2 + 1] - m_new)};
       psum += pv[0] + pv[1];
       hi[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pv, dbf16x2_t));          // round to nearest even
       const df32x2_t rest = {pv[0] - bf16_lo(hi[e]), pv[1] - bf16_hi(hi[e])};
@@ -609,85 +701,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) s_acc[wave][4 * c + rr][db * 16 + j16] = oacc[db][rr];
   __syncthreads();
-  finish_piece<uint16_t, D, NW, GT>(a, hidx, chunk, len <= rows, s_ml, s_acc);
-  if (a.max_chunks == 1 && can_append && threadIdx.x == 0) a.kv_len[hidx] = len;
-}
-
-// Merges the partial (max, sum, acc) triples of every head that was cut into several pieces and stores the new
-// length.  One workgroup per head; a thread has four elements of one query head and every KP-th piece, MB of them in
-// flight at a time, the KP shares meet in LDS in a fixed order.  Bound by one trip to memory: the first pieces'
-// partials are fetched before the head's length is known (slots past the head's last piece hold old values and
-// are masked).
-template <typename T, int D, int KP>
-__global__ __launch_bounds__(1024) void decode_merge_kernel(DecodeArgs a) {
-  constexpr int TL = D / 4, MB = 4;                   // threads per row of D elements; pieces in flight per thread
-  __shared__ float4 s_part[KP][8][TL];
-  __shared__ float2 s_mlp[KP][8];
-  const long long hidx = blockIdx.x;
-  const int tl = threadIdx.x % TL, kp = (threadIdx.x / TL) % KP, g = threadIdx.x / (TL * KP);   // blockDim = G * KP * TL
-  const float4* pa = reinterpret_cast<const float4*>(a.part) + (hidx * a.max_chunks * a.G + g) * TL + tl;
-  const float2* pm = reinterpret_cast<const float2*>(a.part_ml) + hidx * a.max_chunks * a.G + g;
-  const int lim = a.max_chunks - 1;
-  float4 ac[MB]; float2 ml[MB];
-#pragma unroll
-  for (int j = 0; j < MB; ++j) {
-    const int ch = min(kp + j * KP, lim);
-    ac[j] = pa[(long long)ch * a.G * TL]; ml[j] = pm[(long long)ch * a.G];
-  }
-  const int len_old = a.kv_len[hidx];
-  const bool can_append = can_append_to(a, a.kv_off[hidx], len_old);
-  const int len = len_old + (can_append ? 1 : 0);
-  const int rows = head_chunk_rows(a, len);
-  float m = DNEG_BIG, ls = 0.f;
-  float4 av = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int c0 = kp; c0 * rows < len; c0 += KP * MB) {
-    if (c0 != kp) {
-#pragma unroll
-      for (int j = 0; j < MB; ++j) {
-        const int ch = min(c0 + j * KP, lim);
-        ac[j] = pa[(long long)ch * a.G * TL]; ml[j] = pm[(long long)ch * a.G];
-      }
-    }
-    float bm = m;
-#pragma unroll
-    for (int j = 0; j < MB; ++j) {
-      if ((c0 + j * KP) * rows >= len) { ml[j] = make_float2(DNEG_BIG, 0.f); ac[j] = make_float4(0.f, 0.f, 0.f, 0.f); }
-      bm = fmaxf(bm, ml[j].x);
-    }
-    const float sc = exp2f(m - bm);
-    ls *= sc; av.x *= sc; av.y *= sc; av.z *= sc; av.w *= sc;
-#pragma unroll
-    for (int j = 0; j < MB; ++j) {
-      const float w = exp2f(ml[j].x - bm);
-      ls = fmaf(ml[j].y, w, ls);
-      av.x = fmaf(ac[j].x, w, av.x); av.y = fmaf(ac[j].y, w, av.y); av.z = fmaf(ac[j].z, w, av.z); av.w = fmaf(ac[j].w, w, av.w);
-    }
-    m = bm;
-  }
-  s_part[kp][g][tl] = av;
-  if (tl == 0) s_mlp[kp][g] = make_float2(m, ls);
-  __syncthreads();                                   // (also: every wave has read the length before the new one is stored)
-  if (can_append && threadIdx.x == 0) a.kv_len[hidx] = len;
-  if (kp != 0 || len <= rows) return;                // (one piece: the output was written by the attention kernel)
-#pragma unroll
-  for (int k = 1; k < KP; ++k) m = fmaxf(m, s_mlp[k][g].x);
-  ls = 0.f; av = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-  for (int k = 0; k < KP; ++k) {
-    const float2 x = s_mlp[k][g];
-    const float4 y = s_part[k][g][tl];
-    const float w = exp2f(x.x - m);
-    ls = fmaf(x.y, w, ls);
-    av.x = fmaf(y.x, w, av.x); av.y = fmaf(y.y, w, av.y); av.z = fmaf(y.z, w, av.z); av.w = fmaf(y.w, w, av.w);
-  }
-  const long long o = (hidx * a.G + g) * D + tl * 4;
-  if (a.out_fp32 || sizeof(T) == 4) {
-    *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + o) = make_float4(av.x / ls, av.y / ls, av.z / ls, av.w / ls);
-  } else {
-    const uint32_t lo = (uint32_t)f32_to_bf16_rne(av.x / ls) | ((uint32_t)f32_to_bf16_rne(av.y / ls) << 16);
-    const uint32_t hi = (uint32_t)f32_to_bf16_rne(av.z / ls) | ((uint32_t)f32_to_bf16_rne(av.w / ls) << 16);
-    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + o) = make_uint2(lo, hi);
-  }
+  finish_piece<uint16_t, D, NW, GT>(a, hidx, chunk, len, rows, can_append, arrive, s_ml, s_acc);
 }
 
 // Rows per workgroup: small for a single layer (many short workgroups balance ragged heads and
@@ -710,9 +724,8 @@ static int plan_longest(const madakv_config& c, int longest_rows) { return std::
 // whatever hcc_rho is, 128 heads of which 8 hold half of the rows, 512 on average, took 21.3 us instead of 14.7, 512 heads of 256,
 // 16 with half of the rows, 34 instead of 21.  Neither depends on what the host knows of the
 // longest head, so that a call's result does not either; only the grid, at most max_chunks pieces, shrinks when it is known.
-constexpr int SHORT_PIECES = 2000;             // most 128-row pieces of a launch: what the static scratch holds of 8 queries x 128 dims
-static_assert((size_t)SHORT_PIECES * 8 * (128 + 2) * sizeof(float) <= MADAKV_STATIC_SCRATCH_BYTES, "short pieces must fit the static scratch");
-DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows, size_t ws_bytes) {
+constexpr int SHORT_PIECES = 2000;             // most 128-row pieces of a launch, some eight per compute unit
+DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows, int slots) {
   DecodePlan p;
   const int worst = plan_longest(c, c.ctx_len + c.max_new_tokens);
   const int base = plan_chunk_rows(dm, c);
@@ -723,31 +736,20 @@ DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows,
   if (short_pieces) p.chunk_rows = 128;
   long long want = std::max<long long>((std::max(2, c.hcc_rho) * typical + p.chunk_rows - 1) / p.chunk_rows, 512 / dm.heads);
   if (short_pieces) want = std::min<long long>(want, SHORT_PIECES / dm.heads);
-  // never more partial results than a worst-case head cut into `base` rows has (what decode_ws_bytes is made for), nor
-  // than the workspace at hand holds: madakv_decode_attn_static accepts a call if the longest head cut into `base` rows fits,
-  // so that this limit never changes how a head is cut (short pieces: SHORT_PIECES)
-  const long long room = (long long)(ws_bytes / ((size_t)dm.heads * dm.G * (dm.d + 2) * sizeof(float)));
-  p.max_chunks = (int)std::max<long long>(1, std::min({(long long)(worst + base - 1) / base, std::max<long long>(2, want), room}));
+  p.max_chunks = (int)std::max<long long>(1, std::min({(long long)(worst + base - 1) / base, std::max<long long>(2, want), (long long)slots}));
   p.grid_chunks = std::min(p.max_chunks, (plan_longest(c, longest_rows) + p.chunk_rows - 1) / p.chunk_rows);
-  // every head is known to be one piece: nothing to merge, the attention kernel stores the new lengths (128 heads of 120 rows
-  // 6.3 -> 4.6 us per call)
+  // every head is known to be one piece: nobody has to arrive anywhere
   if (p.grid_chunks == 1) p.max_chunks = 1;
   return p;
 }
 
+// what a caller's workspace has been asked to hold since before the pieces met in the handle's memory
 size_t decode_ws_bytes_for(const Dims& dm, const madakv_config& c, int longest_rows) {
   const int base = plan_chunk_rows(dm, c);
   const int chunks = (plan_longest(c, longest_rows) + base - 1) / base;
   return (size_t)dm.heads * chunks * dm.G * (dm.d + 2) * sizeof(float) + 64;
 }
 size_t decode_ws_bytes(const Dims& dm, const madakv_config& c) { return decode_ws_bytes_for(dm, c, c.ctx_len + c.max_new_tokens); }
-
-template <typename T, int D>
-static void launch_merge(const Dims& dm, const DecodeArgs& a, hipStream_t st) {
-  // as many threads as a workgroup holds: KP of them share a head's pieces
-  if (dm.G * 8 * (D / 4) <= 1024) hipLaunchKernelGGL((decode_merge_kernel<T, D, 8>), dim3(dm.heads), dim3(dm.G * 8 * (D / 4)), 0, st, a);
-  else hipLaunchKernelGGL((decode_merge_kernel<T, D, 4>), dim3(dm.heads), dim3(dm.G * 4 * (D / 4)), 0, st, a);
-}
 
 template <typename T, typename CT, int LPR, bool PAGED>
 static hipError_t launch_decode_t(const Dims& dm, DecodeArgs& a, int grid_chunks, hipStream_t st) {
@@ -767,7 +769,6 @@ static hipError_t launch_decode_t(const Dims& dm, DecodeArgs& a, int grid_chunks
     else if (dm.G <= 4) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 4, 4, 4, PAGED>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 8, 2, 4, PAGED>), grid, block, 0, st, a);
   }
-  if (a.max_chunks > 1) launch_merge<T, D>(dm, a, st);
   return hipGetLastError();
 }
 template <typename T, typename CT, int LPR>
@@ -777,7 +778,7 @@ static hipError_t launch_decode_p(const Dims& dm, DecodeArgs& a, int grid_chunks
 
 hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, const void* k_new,
                          const void* v_new, void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
-                         void* out, void* ws, size_t ws_bytes, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st) {
+                         void* out, const Meet& meet, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st) {
   DecodeArgs a;
   a.capacity = capacity_tokens;
   a.page_rows = pg.page_rows; a.tbl_entries = pg.entries; a.page_tbl = pg.table; a.pool_top = pg.pool_top;
@@ -786,10 +787,9 @@ hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, 
   a.region_pages = pg.page_rows ? pg.region_tokens / pg.page_rows : 0;
   a.head0 = (long long)layer0 * dm.B * dm.H;
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.k_c = k_c; a.v_c = v_c; a.kv_off = kv_off; a.kv_len = kv_len;
-  a.out = out; a.part = reinterpret_cast<float*>(ws);
-  DecodePlan p = decode_plan(dm, c, longest_rows, ws_bytes);
+  a.out = out; a.meet = meet; a.max_new = c.max_new_tokens;
+  DecodePlan p = decode_plan(dm, c, longest_rows, meet.slots);
   a.B = dm.B; a.H = dm.H; a.G = dm.G; a.chunk_rows = p.chunk_rows; a.max_chunks = p.max_chunks;
-  a.part_ml = a.part + (long long)dm.heads * p.max_chunks * dm.G * dm.d;
   a.out_fp32 = c.out_fp32; a.has_new = (k_new != nullptr) ? 1 : 0;
   const float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)dm.d);
   a.scale_log2 = scale * 1.4426950408889634f;

@@ -6,7 +6,6 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -14,21 +13,11 @@ using namespace madakv;
 
 constexpr int MAX_GROUPS = 4;      // layer groups a multi-layer call is cut into for the overlap
 
-// Scratch of madakv_decode_attn_static: the partial results of heads that are cut into several
-// chunks.  One copy per GPU, at an address of its own on each, held until the process ends.  In
-// host code the name below is only a handle for hipGetSymbolAddress; the device address is
-// resolved once per device (static_scratch_on_current_device) and passed to the kernels.
-constexpr size_t STATIC_SCRATCH_BYTES = MADAKV_STATIC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
-constexpr int MAX_DEVICES = 64;
-static void* g_scratch_ptr[MAX_DEVICES];
-static std::mutex g_scratch_mutex;
-
 struct madakv_handle {
   madakv_config cfg;
   int device;
   int32_t last_hip_error;
-  long long* d_state;              // [3 * B]: HCC pool, cache cursor, pages taken for appended rows (paged cache), per batch item
+  long long* d_state;              // the handle's allocation (create_memory); [3 * B]: HCC pool, cache cursor, pages taken for appended rows (paged cache), per batch item
   int32_t* d_page_tbl;             // paged cache: [n_layers * B * H][entries] page table (null otherwise)
   void* d_split; size_t split_bytes;   // long contexts: buffer of the chunk-parallel statistics / selection (null otherwise)
   std::vector<int32_t> appended;   // decode rows appended since the last (re-)eviction, per layer
@@ -43,7 +32,7 @@ struct madakv_handle {
   // maxlen_stream and covered by maxlen_event, 2 = the value in h_maxlen has landed
   std::vector<uint8_t> maxlen_state;
   hipStream_t maxlen_stream;
-  void* static_scratch;            // this device's copy of the static scratch array
+  Meet meet;                       // where the pieces of a head meet in decode
   // Side stream and events for the overlap of the bandwidth-bound kernels (score sweeps, gather)
   // with the latency-bound per-head kernels (statistics, selection) inside one call.  The side
   // stream forks from and joins the caller's stream through events; default priority.
@@ -230,27 +219,42 @@ hipError_t join_side(madakv_handle* h, hipStream_t st, hipError_t e) {
   return e != hipSuccess ? e : j;
 }
 
-// Device address of the static scratch array on the current device (resolved once per device).
-hipError_t static_scratch_on_current_device(int device, void** out) {
-  if (device < 0 || device >= MAX_DEVICES) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lock(g_scratch_mutex);
-  if (!g_scratch_ptr[device]) {
-    void* ptr = nullptr;
-    hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return e;
-    g_scratch_ptr[device] = ptr;
-  }
-  *out = g_scratch_ptr[device];
-  return hipSuccess;
+constexpr size_t NO_WORKSPACE = ~(size_t)0;
+// The handle's device memory but for d_split, in one allocation that starts with what has to be zero: the carry state, the
+// page table, the counters and lengths of decode's pieces.  Then the partial results of the pieces, as many as a call over any
+// number of layers cuts a head into: a record is under 1% of the rows of a 256-row piece of single queries, 7% of a 128-row
+// piece of eight; together 1-14% of the reduced cache (hcc_rho = 2).
+hipError_t create_memory(madakv_handle* h) {
+  const madakv_config& c = h->cfg;
+  Meet& m = h->meet;
+  m.slots = 1;
+  for (int n = 1; n <= c.n_layers; ++n) m.slots = std::max(m.slots, decode_plan(make_dims(c, n), c, c.ctx_len + c.max_new_tokens, 0x7fffffff).max_chunks);
+  const size_t heads = (size_t)c.n_layers * c.batch * c.n_kv_heads, G = c.n_q_heads / c.n_kv_heads, rows = (heads * m.slots + MEET_ROOM) * G;
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  const size_t table = up(sizeof(long long) * 3 * c.batch), count = table + up(sizeof(int32_t) * heads * page_table_entries(c));
+  const size_t len = count + heads * (G > 1 ? MEET_WAVES : 1) * MEET_COUNT_STRIDE * sizeof(uint32_t), acc = len + up(heads * sizeof(int32_t));
+  const size_t ml = acc + up(rows * c.head_dim * sizeof(float));
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&h->d_state), ml + rows * 2 * sizeof(float));
+  if (e != hipSuccess) { h->d_state = nullptr; return e; }
+  char* p = reinterpret_cast<char*>(h->d_state);
+  if (c.page_rows) h->d_page_tbl = reinterpret_cast<int32_t*>(p + table);
+  m.count = reinterpret_cast<uint32_t*>(p + count);
+  m.len1 = reinterpret_cast<int32_t*>(p + len);
+  m.acc = reinterpret_cast<float*>(p + acc);
+  m.ml = reinterpret_cast<float*>(p + ml);
+  e = hipMemset(p, 0, acc);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);          // (a caller's stream need not wait for the null stream)
+  return e;
 }
+int32_t* len1_of(madakv_handle* h, int layer) { return h->meet.len1 + (size_t)layer * h->cfg.batch * h->cfg.n_kv_heads; }
 
 int32_t decode_impl(madakv_handle* h, int32_t layer0, int32_t n,
                     const void* q, const void* k_new, const void* v_new,
                     void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
-                    void* out, void* ws, size_t ws_bytes, bool ws_is_static, void* stream) {
+                    void* out, const void* ws, size_t ws_bytes, void* stream) {
   int32_t r = check_range(h, layer0, n);
   if (r != MADAKV_OK) return r;
-  if (bad_ptr(q) || bad_ptr(k_c) || bad_ptr(v_c) || bad_ptr(kv_off, 8) || bad_ptr(kv_len, 4) || bad_ptr(out) || bad_ptr(ws))
+  if (bad_ptr(q) || bad_ptr(k_c) || bad_ptr(v_c) || bad_ptr(kv_off, 8) || bad_ptr(kv_len, 4) || bad_ptr(out) || (ws_bytes != NO_WORKSPACE && bad_ptr(ws)))
     return MADAKV_ERR_INVALID_ARG;
   if ((k_new == nullptr) != (v_new == nullptr)) return MADAKV_ERR_INVALID_ARG;
   if (k_new && (!aligned16(k_new) || !aligned16(v_new))) return MADAKV_ERR_INVALID_ARG;
@@ -261,14 +265,14 @@ int32_t decode_impl(madakv_handle* h, int32_t layer0, int32_t n,
   const bool replayed = hipStreamIsCapturing(reinterpret_cast<hipStream_t>(stream), &capturing) != hipSuccess ||
                         capturing != hipStreamCaptureStatusNone;
   const int longest = longest_rows(h, layer0, n, replayed);
-  // a caller's workspace is sized for the worst case; the static one must hold what this launch uses
-  const size_t need = ws_is_static ? decode_ws_bytes_for(dm, h->cfg, longest) : decode_ws_bytes(dm, h->cfg);
-  if (ws_bytes < need) return MADAKV_ERR_WORKSPACE_TOO_SMALL;
+  // what each entry point has always asked for or refused (the kernels use the handle's own memory)
+  if (ws_bytes == NO_WORKSPACE ? decode_ws_bytes_for(dm, h->cfg, longest) > MADAKV_STATIC_SCRATCH_BYTES : ws_bytes < decode_ws_bytes(dm, h->cfg))
+    return MADAKV_ERR_WORKSPACE_TOO_SMALL;
   if (k_new) {
     for (int l = layer0; l < layer0 + n; ++l)
       if (h->appended[l] >= h->cfg.max_new_tokens) return MADAKV_ERR_INVALID_ARG;
   }
-  hipError_t e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, ws, ws_bytes,
+  hipError_t e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, h->meet,
                                region_tokens(h->cfg) * h->cfg.batch, longest, make_paging(h), layer0,
                                reinterpret_cast<hipStream_t>(stream));
   if (e == hipSuccess && k_new) for (int l = layer0; l < layer0 + n; ++l) h->appended[l] += 1;
@@ -294,17 +298,10 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   for (int g = 0; g < MAX_GROUPS; ++g) { h->ev_grp[g] = nullptr; h->ev_sel[g] = nullptr; }
   h->appended.assign(cfg->n_layers, 0);
   h->gen_base.assign(cfg->n_layers, 0);
-  h->static_scratch = nullptr; h->d_page_tbl = nullptr;
+  h->meet = Meet{}; h->d_page_tbl = nullptr;
   h->d_split = nullptr; h->split_bytes = 0;
   hipError_t e = hipGetDevice(&h->device);
-  if (e == hipSuccess) e = static_scratch_on_current_device(h->device, &h->static_scratch);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&h->d_state), sizeof(long long) * 3 * cfg->batch);
-  if (e == hipSuccess) e = hipMemset(h->d_state, 0, sizeof(long long) * 3 * cfg->batch);
-  if (cfg->page_rows) {
-    const size_t tb = sizeof(int32_t) * (size_t)cfg->n_layers * cfg->batch * cfg->n_kv_heads * page_table_entries(*cfg);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&h->d_page_tbl), tb);
-    if (e == hipSuccess) e = hipMemset(h->d_page_tbl, 0, tb);
-  }
+  if (e == hipSuccess) e = create_memory(h);
   {
     // long contexts on few heads: room for the largest launch that would use the chunk-parallel statistics / selection
     Dims d1 = make_dims(*cfg, 1);
@@ -325,7 +322,6 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   for (int g = 0; g < MAX_GROUPS && e == hipSuccess; ++g) e = hipEventCreateWithFlags(&h->ev_grp[g], hipEventDisableTiming);
   for (int g = 0; g < MAX_GROUPS && e == hipSuccess; ++g) e = hipEventCreateWithFlags(&h->ev_sel[g], hipEventDisableTiming);
   if (e != hipSuccess) {
-    if (h->d_page_tbl) (void)hipFree(h->d_page_tbl);
     if (h->d_split) (void)hipFree(h->d_split);
     if (h->h_maxlen) (void)hipHostFree(h->h_maxlen);
     if (h->maxlen_event) (void)hipEventDestroy(h->maxlen_event);
@@ -341,7 +337,6 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
 int32_t madakv_destroy(madakv_handle* h) {
   if (!h) return MADAKV_ERR_INVALID_ARG;
   hipError_t e = hipFree(h->d_state);
-  if (h->d_page_tbl) (void)hipFree(h->d_page_tbl);
   if (h->d_split) (void)hipFree(h->d_split);
   (void)hipHostFree(h->h_maxlen);
   (void)hipEventDestroy(h->maxlen_event);
@@ -510,7 +505,7 @@ int32_t madakv_select_gather(madakv_handle* h, int32_t layer0, int32_t n,
     const float* pool_g = psi_pool ? psi_pool + heads0 * (size_t)(c.ctx_len - c.window) : nullptr;
     const int32_t* bud_g = budgets ? budgets + heads0 * M : nullptr;
     const int bpb = blocks_per_batch(c, ng);
-    e = launch_offsets(dg, c, layer0 + g0, bud_g, kv_off + heads0, kv_len + heads0, h->d_state + c.batch,
+    e = launch_offsets(dg, c, layer0 + g0, bud_g, kv_off + heads0, kv_len + heads0, len1_of(h, layer0 + g0), h->d_state + c.batch,
                        h->d_maxlen + (size_t)(layer0 + g0) * c.batch, ws_g, make_paging(h), bpb, ss);
     if (e == hipSuccess) e = launch_select(dg, c, pool_g, mask, bud_g, kv_off + heads0, kv_len + heads0, kept_idx, ss, nullptr, nullptr, h->d_split, h->split_bytes);
     if (overlap && e == hipSuccess) e = hipEventRecord(h->ev_sel[gi], h->side);
@@ -585,7 +580,7 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
     }
     if (e == hipSuccess) e = launch_stats(dg, c, psi_g, mask, pool_g, stats_g, g0 == 0 ? n_mod : nullptr, layer0 + g0, ss, h->d_split, h->split_bytes);
     const AllocArgs alloc = alloc_args(dg, c, layer0 + g0, stats_g, n_mod, bud_g, h->d_state);
-    if (e == hipSuccess) e = launch_offsets(dg, c, layer0 + g0, bud_g, kv_off + heads0, kv_len + heads0, h->d_state + c.batch,
+    if (e == hipSuccess) e = launch_offsets(dg, c, layer0 + g0, bud_g, kv_off + heads0, kv_len + heads0, len1_of(h, layer0 + g0), h->d_state + c.batch,
                                             h->d_maxlen + (size_t)(layer0 + g0) * c.batch, ws_g, make_paging(h), blocks_per_batch(c, ng), ss, &alloc);
     if (e == hipSuccess) e = launch_select(dg, c, pool_g, mask, bud_g, kv_off + heads0, kv_len + heads0, kept_idx, ss, nullptr, nullptr, h->d_split, h->split_bytes);
     if (overlap && e == hipSuccess) e = hipEventRecord(h->ev_sel[gi], h->side);
@@ -604,7 +599,7 @@ int32_t madakv_decode_attn(madakv_handle* h, int32_t layer0, int32_t n,
                            const void* q, const void* k_new, const void* v_new,
                            void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
                            void* out, void* ws, size_t ws_bytes, void* stream) {
-  return decode_impl(h, layer0, n, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, ws, ws_bytes, false, stream);
+  return decode_impl(h, layer0, n, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, ws, ws_bytes, stream);
 }
 
 int32_t madakv_decode_attn_static(madakv_handle* h, int32_t layer0, int32_t n,
@@ -612,9 +607,7 @@ int32_t madakv_decode_attn_static(madakv_handle* h, int32_t layer0, int32_t n,
                                   void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
                                   void* out, void* stream) {
   if (!h) return MADAKV_ERR_INVALID_ARG;
-  // no allocation on this path: this device's copy of the static array is all it uses beyond the caller's tensors
-  return decode_impl(h, layer0, n, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, h->static_scratch, STATIC_SCRATCH_BYTES,
-                     true, stream);
+  return decode_impl(h, layer0, n, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, nullptr, NO_WORKSPACE, stream);
 }
 
 namespace {

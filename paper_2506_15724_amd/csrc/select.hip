@@ -31,7 +31,7 @@ struct SelCarry { DescentRange range; uint32_t need, alive, tau, pad; };
 struct SelChunk { uint32_t gt, pad; unsigned long long eq; };   // kept for sure; threshold-valued ones, 16 bits per modality
 
 struct OffsetsArgs {
-  const int32_t* budgets; int64_t* kv_off; int32_t* kv_len; long long* cursor; int32_t* blk2head; long long* call_range; int32_t* layer_maxlen;
+  const int32_t* budgets; int64_t* kv_off; int32_t* kv_len; int32_t* len1; long long* cursor; int32_t* blk2head; long long* call_range; int32_t* layer_maxlen;
   int n, B, H, L, W, layer0, max_new, keep_all, blocks_per_batch, M;
   long long region_tokens;       // rows of one batch item's region
   long long init_limit;          // rows of it the segments laid out here may fill
@@ -111,6 +111,7 @@ __global__ __launch_bounds__(OFF_THREADS) void offsets_kernel(OffsetsArgs a, All
       atomicMax(&s_lmax[li], (int)len);                       // longest segment of the layer, for the decode grid
       a.kv_off[idx] = region + off;
       a.kv_len[idx] = (int32_t)len;
+      a.len1[idx] = (int32_t)len + 1;
       if (a.page_rows) a.page_tbl[(((long long)(a.layer0 + li) * a.B + b) * a.H + h) * a.tbl_entries] = (int32_t)(seg / a.page_rows);
       // blocks whose first row lies inside this segment
       const long long b0 = (off + GATHER_ROWS - 1) / GATHER_ROWS, b1 = seg > 0 ? (off + seg - 1) / GATHER_ROWS : b0 - 1;
@@ -424,11 +425,11 @@ size_t select_ws_bytes(const Dims& dm, const madakv_config& c) {
 }
 
 hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, const int32_t* budgets,
-                          int64_t* kv_off, int32_t* kv_len, long long* cursor_state, int32_t* layer_maxlen, void* ws,
+                          int64_t* kv_off, int32_t* kv_len, int32_t* len1, long long* cursor_state, int32_t* layer_maxlen, void* ws,
                           const Paging& pg, int blocks_per_batch, hipStream_t st, const AllocArgs* alloc) {
   OffsetsArgs a;
   a.layer_maxlen = layer_maxlen;
-  a.budgets = budgets; a.kv_off = kv_off; a.kv_len = kv_len; a.cursor = cursor_state;
+  a.budgets = budgets; a.kv_off = kv_off; a.kv_len = kv_len; a.len1 = len1; a.cursor = cursor_state;
   a.call_range = reinterpret_cast<long long*>(ws);
   a.blk2head = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(ws) + ((size_t)dm.B * 2 * sizeof(long long) + 63) / 64 * 64);
   a.n = dm.n; a.B = dm.B; a.H = dm.H; a.L = dm.L; a.W = dm.W; a.layer0 = layer0; a.M = c.n_modalities;

@@ -592,3 +592,47 @@ def test_calls_use_the_current_stream(monkeypatch):
         assert MB._stream() == torch.cuda.current_stream().cuda_stream
         with torch.cuda.stream(side):
             assert MB._stream() == side.cuda_stream
+
+
+@pytest.mark.parametrize("kw", [dict(n_q_heads=5, n_kv_heads=5, head_dim=128), dict(n_q_heads=5, n_kv_heads=5, head_dim=64, dtype="fp32"),
+                                dict(n_q_heads=35, n_kv_heads=5, head_dim=128), dict(n_q_heads=10, n_kv_heads=5, head_dim=64),
+                                dict(n_q_heads=15, n_kv_heads=5, head_dim=128, dtype="fp32"), dict(n_q_heads=5, n_kv_heads=5, head_dim=64, cache_fp8=1)],
+                         ids=lambda kw: "_".join(f"{k}{v}" for k, v in kw.items()))
+def test_decode_pieces_that_come_into_being(kw):
+    """Heads that grow into pieces which held nothing before, with many workgroups that only arrive (room for 700 appended
+    rows): two layers in turn, two steps on two streams, calls that append nothing in between; lengths after every call and the
+    last output against a 64-bit attention (bound: that of test_decode_pieces)."""
+    lens = [255, 256, 511, 127, 384]
+    args = dict(dict(n_layers=2, batch=1, window=8, dtype="bf16", pool_k=1, ctx_len=1200, budget=400, max_new_tokens=700, out_fp32=1), **kw)
+    eng = MB.MadaKV(device=DEV, **args)
+    H, Hq, d, L = args["n_kv_heads"], args["n_q_heads"], args["head_dim"], args["ctx_len"]
+    g = torch.Generator().manual_seed(4)
+    k, v = (torch.randn(2, 1, H, L, d, generator=g).to(DEV, eng.tdtype) for _ in range(2))
+    bud = torch.stack([torch.tensor(lens + lens) - 8, torch.zeros(2 * H, dtype=torch.int64)], -1).view(2, 1, H, 2).to(DEV, torch.int32)
+    eng.select_gather(0, 2, k, v, torch.zeros(1, L, dtype=torch.uint8, device=DEV), psi_pool=torch.rand(2, 1, H, L - 8, generator=g).to(DEV), budgets=bud)
+    side = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs = [torch.full((1, 1, Hq, d), float("nan"), device=DEV) for _ in range(2)]
+    for step in range(4):
+        rows = [[torch.randn(1, 1, h, d, generator=g).to(DEV, eng.tdtype) for h in (Hq, H, H)] for _ in range(2)]
+        torch.cuda.synchronize()
+        say(f"growing pieces {kw} step {step}")
+        for l in (0, 1):
+            with torch.cuda.stream(side[l] if step >= 2 else torch.cuda.current_stream()):
+                eng.decode_attn(l, 1, *rows[l], outs[l])
+        torch.cuda.synchronize()
+        assert eng.kv_len.view(-1).tolist() == [n + step + 1 for n in lens + lens]
+        again = [torch.empty_like(outs[l]) for l in (0, 1)]
+        for l in (0, 1):
+            eng.decode_attn(l, 1, rows[l][0], None, None, again[l])
+        torch.cuda.synchronize()
+        assert eng.kv_len.view(-1).tolist() == [n + step + 1 for n in lens + lens]
+        assert all(torch.isfinite(outs[l]).all() and torch.equal(outs[l], again[l]) for l in (0, 1))
+    f64 = lambda t: (t.view(torch.float8_e4m3fn) if args.get("cache_fp8") else t).cpu().double()
+    off = eng.kv_off.view(-1).tolist()
+    for l in (0, 1):
+        for h in range(H):
+            lo, hi = off[l * H + h], off[l * H + h] + lens[h] + 4
+            k, v = f64(eng.k_c[lo:hi]), f64(eng.v_c[lo:hi])
+            ref = torch.softmax(rows[l][0].view(H, Hq // H, d)[h].cpu().double() @ k.T / d ** 0.5, -1) @ v
+            assert float((outs[l].view(H, Hq // H, d)[h].cpu().double() - ref).abs().max()) < 1e-4
+    eng.close()
