@@ -242,8 +242,8 @@ hipError_t create_memory(madakv_handle* h) {
   m.len1 = reinterpret_cast<int32_t*>(p + len);
   m.acc = reinterpret_cast<float*>(p + acc);
   m.ml = reinterpret_cast<float*>(p + ml);
-  e = hipMemset(p, 0, acc);
-  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);          // (a caller's stream need not wait for the null stream)
+  e = hipMemsetAsync(p, 0, acc, h->side);
+  if (e == hipSuccess) e = hipStreamSynchronize(h->side);          // (a caller's stream need not wait for the null stream, nor this for its work)
   return e;
 }
 int32_t* len1_of(madakv_handle* h, int layer) { return h->meet.len1 + (size_t)layer * h->cfg.batch * h->cfg.n_kv_heads; }
@@ -301,6 +301,7 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   h->meet = Meet{}; h->d_page_tbl = nullptr;
   h->d_split = nullptr; h->split_bytes = 0;
   hipError_t e = hipGetDevice(&h->device);
+  if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
   if (e == hipSuccess) e = create_memory(h);
   {
     // long contexts on few heads: room for the largest launch that would use the chunk-parallel statistics / selection
@@ -316,7 +317,6 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&h->d_maxlen), h->h_maxlen, 0);
   if (e == hipSuccess) memset(h->h_maxlen, 0, sizeof(int32_t) * cfg->n_layers * cfg->batch);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->maxlen_event, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming);
   for (int g = 0; g < MAX_GROUPS && e == hipSuccess; ++g) e = hipEventCreateWithFlags(&h->ev_grp[g], hipEventDisableTiming);
