@@ -62,12 +62,13 @@ struct AllocArgs;
 // Each launcher validates nothing: shapes were checked by the ABI layer.
 hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_win, const void* k, const float* row_lse,
                         float* psi, void* ws, hipStream_t st);
-// Long heads on few heads: statistics and selection give every 16384-candidate chunk of a head a workgroup of its own
-// and go through a buffer of split_buffer_bytes (owned by the handle) in several launches; split_chunks = chunks per
-// head then, 0 otherwise.
+// Long heads on few heads: statistics and selection give every 16384-candidate chunk of a head a workgroup of its own, and
+// the chunks of a head meet in a record of split_head_bytes (owned by the handle); split_chunks = chunks per head then, 0
+// otherwise.
 int split_chunks(const Dims& dm);
-size_t split_buffer_bytes(int heads, int M, int nchunks);
-void launch_split_zero(uint32_t* p, long long words, hipStream_t st);   // a fill kernel (no memset node in captured streams)
+size_t split_head_bytes(int M, int nchunks);
+size_t stats_split_bytes(int M, int nchunks);
+size_t select_split_bytes(int M, int nchunks);
 hipError_t launch_stats(const Dims& dm, const madakv_config& c, const float* psi, const uint8_t* mask,
                         float* psi_pool, void* stats, int32_t* n_mod, int layer0, hipStream_t st,
                         void* split_buf = nullptr, size_t split_bytes = 0);

@@ -309,8 +309,10 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
     if (split_chunks(d1) > 0) {
       const int nchunks = (d1.nc + 16383) / 16384;
       const int heads = std::min(cfg->n_layers * cfg->batch * cfg->n_kv_heads, 128);
-      h->split_bytes = split_buffer_bytes(heads, cfg->n_modalities, nchunks);
+      h->split_bytes = heads * split_head_bytes(cfg->n_modalities, nchunks);
       if (e == hipSuccess) e = hipMalloc(&h->d_split, h->split_bytes);
+      if (e == hipSuccess) e = hipMemsetAsync(h->d_split, 0, h->split_bytes, h->side);
+      if (e == hipSuccess) e = hipStreamSynchronize(h->side);
     }
   }
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&h->h_maxlen), sizeof(int32_t) * cfg->n_layers * cfg->batch, hipHostMallocDefault);

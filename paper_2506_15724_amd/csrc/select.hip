@@ -7,16 +7,17 @@
 //                  cache, inside it layers and heads follow each other; a segment has
 //                  kv_len = b_t + b_v + W rows plus max_new_tokens free rows.  It also fills
 //                  a table "first head that overlaps each 64-row block" for the gather.
-// select_kernel    one workgroup per head.  A radix descent (descent.h) over count histograms of the
-//                  order-preserving keys finds, per modality, the threshold key tau_m and how many elements equal
-//                  to tau_m are still needed; then key > tau_m is kept, and key == tau_m while
-//                  its rank by position is below that number.  The last pass goes over the candidates in order, 4096 at
-//                  a time; prefix sums over the workgroup give
-//                  the ranks and the output slots, so the result is ascending by construction.
-//                  Bound like the statistics (stats.hip) by latency and instruction issue; nothing unrolled over a
-//                  thread's candidates, which are read again per level: 9 KB of code instead of 42, one scan instead of
-//                  two in the last pass.  In the path, before -> after: 27.6 -> 11.3 us (8 heads of 1K candidates),
-//                  29.5 -> 18.7 (32 of 8K), 35 -> 29 (128 of 16K), re-eviction's 1024 heads of 2K rows 87 -> 27.
+// select_kernel    one workgroup per head.  A radix descent (descent.h) over count histograms of the order-preserving keys, over
+//                  all candidates at the first level, then over a list of those of the crossing bin, until few are left that are
+//                  ranked by key and position: the last one that is kept gives, per modality, the threshold key tau_m and the
+//                  position up to which candidates of that key are kept.  The last pass writes what is above, 16384 candidates
+//                  at a time; prefix sums over the workgroup give the output slots, so the result is ascending by
+//                  construction.  (Where more candidates share a bin than a list holds, and do so to the last bit, the number
+//                  of them that is still needed is handed out by rank, 4096 candidates at a time.)
+//                  Bound like the statistics (stats.hip) by latency and instruction issue.  Per head of 16K candidates, in us:
+//                  clearing 0.7, counts 3.5, walk 1.8, list 3.6, ranking 1, last pass 4.2.  One launch, against three levels
+//                  over all candidates and a last pass 4096 at a time: 128 heads of 16K 21.8 -> 15.0 us, 112 of 32K 37 (the
+//                  slowest 67) -> 25 (30), 32 of 8K 14.1 -> 11.2, 8 of 1K 10.1 -> 8.3.
 #include "allocate.h"
 #include "descent.h"
 
@@ -26,9 +27,19 @@ constexpr int SEL_THREADS = 1024;
 constexpr int SEL_CHUNK = 16384;                 // candidates per workgroup where a head's chunks have workgroups of their own
 constexpr uint32_t SEL_SH1 = 21;                 // plain first digit of a 32-bit key
 
-// what the walk of one level hands on, per head and modality, and what a chunk reports (phases 1-4 of select_kernel)
-struct SelCarry { DescentRange range; uint32_t need, alive, tau, pad; };
-struct SelChunk { uint32_t gt, pad; unsigned long long eq; };   // kept for sure; threshold-valued ones, 16 bits per modality
+// candidates of the crossing bins: how many a workgroup lists per modality, how many of a head's chunk (on average) fit the
+// head's list in memory, and up to how many are ranked one against the other
+template <int MM> constexpr int SEL_LIST = MM == 2 ? 2048 : 1024;
+constexpr int SEL_GLIST_PER_CHUNK = 1024, SEL_RANK_MAX = 256;
+constexpr int SEL_MAX_CHUNKS = 64;               // 2^20 candidates
+
+// Long heads on few heads (see launch_select): what a head's chunks share, and what a launch leaves to the next.  All zero
+// between calls but for the last line.
+struct SelMeet {
+  uint32_t arrived[2], listed[4], pad[2];
+  DescentRange range[4];
+  uint32_t need[4], alive[4], tau[4], pos[4], done, pad2[3];
+};
 
 struct OffsetsArgs {
   const int32_t* budgets; int64_t* kv_off; int32_t* kv_len; int32_t* len1; long long* cursor; int32_t* blk2head; long long* call_range; int32_t* layer_maxlen;
@@ -138,16 +149,23 @@ struct SelectArgs {
   const float* psi_pool; const uint8_t* mask; const int32_t* budgets; const int64_t* kv_off; const int32_t* kv_len; int32_t* kept_idx;
   int B, H, L, W, nc, mpa_mode, keep_all, select_mode, sink_tokens, M;
   const int32_t* seg_len; const uint8_t* rowmod;   // ragged candidates (re-eviction), else null
-  // Long heads on few heads (see launch_select): the chunks of a head go to workgroups of their own.
-  // phase 0 = the whole head in one workgroup; 1 = count histogram of one chunk at `level`, added to the
-  // head's histogram in memory; 2 = the walk over that histogram (one workgroup per head); 3 = a chunk's
-  // numbers of kept and of threshold-valued candidates; 4 = a chunk's kept positions written behind those
-  // of the chunks before it.
-  int phase, level, heads, nchunks;
-  uint32_t* gcnt;                 // [3 levels][heads][M][BINS]
-  SelCarry* carry;                // [heads][4]
-  SelChunk* chunkinfo;            // [heads][nchunks]
+  // Phase 0 = the whole head in one workgroup.  Long heads on few heads: a workgroup per chunk; 1 = its counts, added to the
+  // head's in memory, which the last one to arrive walks; 2 = its candidates of the crossing bins, added to the head's list,
+  // which the last one to arrive ranks; 3 = its kept positions written behind those of the chunks before it.
+  char* split;                    // a record of split_stride bytes per head (SelSplit)
+  long long split_stride;
 };
+
+// a head's record: [M][BINS] counts, SelMeet, [nchunks] kept for sure and then kept by the chunks before, [M][gcap] list
+struct SelSplit { uint32_t* cnt; SelMeet* meet; uint32_t* chunk_kept; unsigned long long* list; };
+__host__ __device__ inline SelSplit select_split(char* p, int M, int nchunks) {
+  SelSplit x;
+  x.cnt = reinterpret_cast<uint32_t*>(p);
+  x.meet = reinterpret_cast<SelMeet*>(x.cnt + M * BINS);
+  x.chunk_kept = reinterpret_cast<uint32_t*>(x.meet + 1);
+  x.list = reinterpret_cast<unsigned long long*>(x.chunk_kept + (nchunks + 1) / 2 * 2);
+  return x;
+}
 
 // the next group of four candidates of a thread: keys, and the bytes of their modality ids (0 where the mask is not used)
 struct KeyGroup { f32x4_any_t x; uint32_t mw; };
@@ -165,18 +183,97 @@ __device__ __forceinline__ KeyGroup load_keys(const float* sc, const uint8_t* ma
   return g;
 }
 
-template <int MM>   // modalities the kernel is built for (2: the paper's text / image; 4: up to four)
-__global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM == 2 ? 8 : 4))) void select_kernel(SelectArgs a) {
+// Writes the kept positions of [i_begin, i_end): key > tau, or key == tau up to position last (-1: none), in ascending order from
+// out[run] on; returns the end.  16384 candidates and one barrier per trip: a thread has four groups of four, 4096 apart, whose
+// counts it scans together (16 bits hold the count of a group column: 4096).
+template <int MM>
+__device__ __forceinline__ uint32_t write_kept(const float* sc, const uint8_t* mask, int use_mask, int32_t* out, int i_begin, int i_end, uint32_t top,
+                                               const uint32_t* s_tau, const uint32_t* s_pos, uint32_t run, uint32_t (*s_tot)[3][SEL_THREADS / 64]) {
   constexpr int NWAVES = SEL_THREADS / 64;
-  __shared__ __attribute__((aligned(16))) uint32_t cnt[MM][BINS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t tau0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tau[0]), tau1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tau[1]);
+  const int pos0 = __builtin_amdgcn_readfirstlane((int)s_pos[0]), pos1 = __builtin_amdgcn_readfirstlane((int)s_pos[1]);
+  int buf = 0;
+#pragma unroll 1
+  for (int base = i_begin; base < i_end; base += 16 * SEL_THREADS, buf ^= 1) {
+    KeyGroup g[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) g[j] = load_keys(sc, mask, base + 4 * (tid + j * SEL_THREADS), i_end, use_mask);
+    uint32_t bits = 0u, pk[2] = {0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t ids = mask4_ids<MM>(g[j].mw, top);
+      uint32_t kb = 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m = (int)id_of<MM>(ids, q), i = base + 4 * (tid + j * SEL_THREADS) + q;
+        const uint32_t key = float_key(g[j].x[q]), t = MM == 2 ? (m ? tau1 : tau0) : s_tau[m];
+        const int p = MM == 2 ? (m ? pos1 : pos0) : (int)s_pos[m];
+        // (what lies past the end is not kept, whatever tau is)
+        kb |= i < i_end && (key > t || (key == t && i <= p)) ? 1u << q : 0u;
+      }
+      bits |= kb << (4 * j);
+      pk[j >> 1] += (uint32_t)__popc(kb) << (16 * (j & 1));
+    }
+    uint32_t ex[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      ex[f] = wave_incl_scan_u32(pk[f]);
+      if (lane == 63) s_tot[buf][f][wave] = ex[f];
+      ex[f] -= pk[f];
+    }
+    __syncthreads();                               // (two buffers: a wave that is a trip ahead writes the other one)
+    uint32_t tot[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      const uint32_t w = wave_incl_scan_u32(lane < NWAVES ? s_tot[buf][f][lane] : 0u);
+      tot[f] = (uint32_t)__builtin_amdgcn_readlane((int)w, NWAVES - 1);
+      ex[f] += wave ? (uint32_t)__builtin_amdgcn_readlane((int)w, wave - 1) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t pos = run + ((ex[j >> 1] >> (16 * (j & 1))) & 0xffffu);
+      const int i = base + 4 * (tid + j * SEL_THREADS);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if ((bits >> (4 * j + q)) & 1u) out[pos++] = i + q;
+      run += (tot[j >> 1] >> (16 * (j & 1))) & 0xffffu;
+    }
+  }
+  return run;
+}
+
+// LDS in front of the list: the counts, in whose place the waves' buffers and the ranks are when they have been walked
+__host__ __device__ constexpr int select_front(int M) { return 4 * M * (BINS + 64) > SEL_THREADS / 64 * WAVE_BUF * 8 ? 4 * M * (BINS + 64) : SEL_THREADS / 64 * WAVE_BUF * 8; }
+
+// f(candidate's group, its first candidate) for this thread's groups of [i_first, i_end), the next one on its way.  WHOLE: all
+// lanes of a wave make the same trips, some with groups past the end.
+template <bool WHOLE = false, typename F>
+__device__ __forceinline__ void for_key_groups(const float* sc, const uint8_t* mask, int i_first, int i_end, int use_mask, F f) {
+  KeyGroup next = load_keys(sc, mask, i_first, i_end, use_mask);
+#pragma unroll 1
+  for (int i = i_first; (WHOLE ? __builtin_amdgcn_readfirstlane(i) : i) < i_end; i += 4 * SEL_THREADS) {
+    const KeyGroup g = next;
+    next = load_keys(sc, mask, i + 4 * SEL_THREADS, i_end, use_mask);
+    f(g, i);
+  }
+}
+
+template <int MM, int PHASE>   // modalities the kernel is built for (2, or 4 for three and four), phase (SelectArgs)
+__global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM == 2 ? 8 : 4))) void select_kernel(SelectArgs a) {
+  constexpr int NWAVES = SEL_THREADS / 64, WPM = NWAVES / MM;   // waves per modality
+  constexpr int phase = PHASE, CAP = SEL_LIST<MM>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char select_smem[];
+  const int M = MM == 2 ? 2 : a.M;
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(select_smem);                          // [M][BINS] counts, [M][64] of the lowest bin
+  uint32_t* low = cnt + M * BINS;
+  unsigned long long* list = reinterpret_cast<unsigned long long*>(select_smem + select_front(M));   // [M][CAP] key, ~position
+  uint32_t* rank = cnt;                                                              // [M][SEL_RANK_MAX] larger ones (in the place of the counts)
   __shared__ DescentRange s_range[MM];
-  __shared__ uint32_t s_need[MM], s_alive[MM], s_tau[MM], s_before[MM], s_bin[MM], s_part[MM][NWAVES];
-  __shared__ uint32_t s_tot[2][3][NWAVES];
-  const int M = a.M;
+  __shared__ uint32_t s_need[MM], s_alive[MM], s_tau[MM], s_pos[MM], s_before[MM], s_bin[MM], s_part[MM][NWAVES], s_listed[MM], s_glisted[MM], s_sure, s_flag;
+  __shared__ uint32_t s_tot[2][3][NWAVES], s_chunk[SEL_MAX_CHUNKS];
   const int tid0 = threadIdx.x;
-  const int phase = a.phase;
-  const bool per_chunk = phase == 1 || phase >= 3;             // grid (chunks, heads)
-  const int head = per_chunk ? blockIdx.y : blockIdx.x;
+  const int head = phase ? blockIdx.y : blockIdx.x;            // chunks: grid (chunks, heads)
   const int b = (head / a.H) % a.B;
   // candidates of this head: the L - W prompt positions before the window with the batch item's modality
   // mask, or (ragged: the rows of a reduced cache, re-eviction) the rows before the head's last W with a
@@ -188,11 +285,11 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
   int32_t* out = a.kept_idx + a.kv_off[head];
 
   if (a.kv_len[head] == 0) return;               // the segment did not fit the region: nothing to write
-  if (a.keep_all) {
+  if (phase == 0 && a.keep_all) {
     for (int i = tid0; i < a.L; i += SEL_THREADS) out[i] = i;
     return;
   }
-  if (a.select_mode == 1) {
+  if (phase == 0 && a.select_mode == 1) {
     // score-free baseline: the first `sink` candidates and the most recent ones, then the window
     uint32_t btot = 0;
     for (int m = 0; m < M; ++m) btot += (uint32_t)a.budgets[(long long)head * M + m];
@@ -202,124 +299,309 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       out[j] = j < sink ? j : (j < total ? nc - (total - j) : nc + (j - total));
     return;
   }
-  const int i_begin = per_chunk ? (int)blockIdx.x * SEL_CHUNK : 0;
-  const int i_end = per_chunk ? min(nc, i_begin + SEL_CHUNK) : nc;
+  int i_begin = phase ? (int)blockIdx.x * SEL_CHUNK : 0;
+  int i_end = phase ? min(nc, i_begin + SEL_CHUNK) : nc;
   const uint32_t top = (uint32_t)(M - 1);
-  uint32_t* gcnt = phase ? a.gcnt + ((size_t)(phase <= 2 ? a.level : 0) * a.heads + head) * (size_t)M * BINS : nullptr;
-  SelCarry* carry = phase ? a.carry + (size_t)head * 4 : nullptr;
-  if (tid0 < M) {
-    if (phase != 0 && (phase >= 3 || a.level > 0)) {            // what the walks before left
-      const SelCarry cy = carry[tid0];
-      s_range[tid0] = cy.range; s_need[tid0] = cy.need; s_alive[tid0] = cy.alive; s_tau[tid0] = cy.tau;
+  const SelSplit split = phase ? select_split(a.split + head * a.split_stride, M, gridDim.x) : SelSplit{};
+  SelMeet* meet = split.meet;
+  uint32_t* chunk_kept = split.chunk_kept;
+  if (phase == 3 && meet->done) return;           // (written by the second launch)
+  if (tid0 < MM) {
+    if (phase >= 2 && tid0 < M) {                  // what the launches before left
+      s_range[tid0] = meet->range[tid0]; s_need[tid0] = meet->need[tid0]; s_alive[tid0] = meet->alive[tid0]; s_tau[tid0] = meet->tau[tid0];
+      s_pos[tid0] = meet->pos[tid0];
     } else {
-      s_range[tid0] = phase ? descent_plain<SEL_SH1>() : descent_first(1u);
-      s_need[tid0] = (uint32_t)a.budgets[(long long)head * M + tid0]; s_alive[tid0] = 1u; s_tau[tid0] = 0xffffffffu;
+      s_range[tid0] = descent_first(1u);
+      s_need[tid0] = tid0 < M ? (uint32_t)a.budgets[(long long)head * M + tid0] : 0u;
+      s_alive[tid0] = tid0 < M ? 1u : 0u; s_tau[tid0] = 0xffffffffu; s_pos[tid0] = 0xffffffffu;
+    }
+  }
+  if constexpr (PHASE == 3) {
+    __syncthreads();
+    const uint32_t end = write_kept<MM>(sc, mask, a.mpa_mode, out, i_begin, i_end, top, s_tau, s_pos, chunk_kept[blockIdx.x], &s_tot[0]);
+    if (i_end != nc) return;                       // the window positions follow the last chunk's
+    for (int r = tid0; r < a.W; r += SEL_THREADS) out[end + r] = nc + r;
+  } else {
+  const int wave0 = __builtin_amdgcn_readfirstlane(tid0 >> 6), m_of = wave0 / WPM, part = wave0 % WPM;
+  const auto clear = [&](int tid) {
+    for (int e = tid; e < M * (BINS + 64) / 4; e += SEL_THREADS) reinterpret_cast<uint4*>(cnt)[e] = make_uint4(0u, 0u, 0u, 0u);
+  };
+  if (phase != 2) {                                // level 0: the counts of all keys; those of the lowest bin have an address per lane
+    const int tid = tid0, lane = tid & 63;
+    clear(tid);
+    __syncthreads();
+    for_key_groups(sc, mask, i_begin + 4 * tid, i_end, a.mpa_mode, [&](const KeyGroup& g, int i) {
+      const uint32_t ids = mask4_ids<MM>(g.mw, top);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m = (int)id_of<MM>(ids, q), bin = descent_first_bin(float_key(g.x[q]), 1u);
+        if (i + q < i_end) atomicAdd(&cnt[bin > 0 ? m * BINS + bin : M * BINS + m * 64 + lane], 1u);
+      }
+    });
+    __syncthreads();
+    if (m_of < M && part == WPM - 1) {             // (the lane that gets the lowest bin looks at it)
+      const uint32_t x = wave_incl_scan_u32(low[m_of * 64 + lane]);
+      if (lane == 63) cnt[m_of * BINS] = x;
+    }
+    if (phase == 1) {                              // add the chunk's bins to the head's; the last workgroup takes them all
+      __syncthreads();
+      uint32_t* gcnt = split.cnt;
+      for (int e = tid; e < M * BINS; e += SEL_THREADS) {
+        const uint32_t x = cnt[e];
+        if (x) (void)__hip_atomic_fetch_add(&gcnt[e], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (!arrive_last(&meet->arrived[0], gridDim.x, &s_flag)) return;
+      for (int e = tid; e < M * BINS; e += SEL_THREADS) { cnt[e] = agent_load(&gcnt[e]); agent_store(&gcnt[e], 0u); }
+      if (tid == 0) agent_store(&meet->arrived[0], 0u);
+      __syncthreads();
     }
   }
 
-  for (int level = phase ? a.level : 0; phase < 3; ++level) {
+  bool alone = phase == 0;                         // this workgroup writes all of the head's positions
+  bool ranked = false;                             // tau and the last position that is kept with it are known from a list
+  int have = 0;                                    // the keys of the ranges: 0 = among the scores, 1 = in the list, 2 = in the head's list in memory
+  const int gcap = (int)gridDim.x * SEL_GLIST_PER_CHUNK;
+  unsigned long long* glist = split.list;
+  // (what is listed of a modality whose descent is over is nobody's business)
+  const auto listed = [&](int m) { return s_alive[m] == 1u ? (int)s_listed[m] : 0; };
+  const auto glisted = [&](int m) { return s_alive[m] == 1u ? (int)s_glisted[m] : 0; };
+#pragma unroll 1
+  for (int level = 0;; ++level) {
     // (addresses that depend on the thread are computed level by level: kept over the loop they would spill)
     int tid = tid0;
     asm volatile("" : "+v"(tid));
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int e = tid; e < M * BINS / 4; e += SEL_THREADS) reinterpret_cast<uint4*>(&cnt[0][0])[e] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-    DescentRange rg[MM];
+    const int lane = tid & 63;
+    if (phase != 2 || level > 0) {
+      // the walk from the top bin down, WPM waves per modality: lane 0 of the first of them has the top bins
+      constexpr int PER = BINS / (WPM * 64);
+      const int m = m_of;
+      const bool walks = m < M && s_alive[min(m, M - 1)] == 1u;
+      const int tb = BINS - 1 - (part * 64 + lane) * PER;     // bins tb, tb - 1, ..., tb - PER + 1
+      uint32_t share = 0u, incl = 0u;
+      if (walks) {
 #pragma unroll
-    for (int m = 0; m < MM; ++m) rg[m] = descent_uniform(s_range[min(m, M - 1)]);
-    if (phase == 2) {                              // the head's histogram of this level, gathered by the chunks' workgroups
-      for (int e = tid; e < M * BINS; e += SEL_THREADS) (&cnt[0][0])[e] = gcnt[e];
-    } else {
-      const bool all = level == 0;                 // every key is in range
-      const uint32_t span0 = rg[0].hi - rg[0].lo, span1 = rg[1].hi - rg[1].lo;
-      KeyGroup next = load_keys(sc, mask, i_begin + 4 * tid, i_end, a.mpa_mode);
+        for (int j = 0; j < PER; ++j) share += cnt[m * BINS + tb - j];
+        incl = wave_incl_scan_u32(share);
+        if (lane == 63) s_part[m][part] = incl;
+      }
+      __syncthreads();
+      uint32_t need = 0u;
+      if (walks) {
+        uint32_t total = 0u, before = incl - share;
+#pragma unroll
+        for (int w = 0; w < WPM; ++w) { const uint32_t x = s_part[m][w]; total += x; before += w < part ? x : 0u; }
+        need = min(s_need[m], total);              // (first level: a budget above the candidate count keeps them all)
+        if (before < need && before + share >= need) {        // one lane of one wave: the bin is among its own
+          uint32_t bin = (uint32_t)tb;
 #pragma unroll 1
-      for (int i = i_begin + 4 * tid; i < i_end; i += 4 * SEL_THREADS) {
-        const KeyGroup g = next;
-        next = load_keys(sc, mask, i + 4 * SEL_THREADS, i_end, a.mpa_mode);
-        const uint32_t ids = mask4_ids<MM>(g.mw, top);
-        if (all) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (i + q < i_end) atomicAdd(&cnt[id_of<MM>(ids, q)][descent_bin(rg[0], float_key(g.x[q]))], 1u);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const uint32_t m = id_of<MM>(ids, q), key = float_key(g.x[q]);
-            const uint32_t lo = MM == 2 ? (m ? rg[1].lo : rg[0].lo) : s_range[m].lo, sp = MM == 2 ? (m ? span1 : span0) : s_range[m].hi - lo;
-            if (i + q < i_end && key - lo <= sp) {
-              const uint32_t s1 = MM == 2 ? (m ? rg[1].sh : rg[0].sh) : s_range[m].sh;
-              atomicAdd(&cnt[m][(key >> s1) - (MM == 2 ? (m ? rg[1].sub : rg[0].sub) : s_range[m].sub)], 1u);
-            }
+          for (;;) {
+            const uint32_t x = cnt[m * BINS + bin];
+            if (before + x >= need) break;
+            before += x; --bin;
           }
+          s_before[m] = before; s_bin[m] = bin;
         }
       }
-    }
-    __syncthreads();
-    if (phase == 1) {                              // add the chunk's bins to the head's and leave
-      for (int e = tid; e < M * BINS; e += SEL_THREADS) {
-        const uint32_t x = (&cnt[0][0])[e];
-        if (x) atomicAdd(&gcnt[e], x);
-      }
-      return;
-    }
-    // the walk from the top bin down, WPM waves per modality: lane 0 of the first of them has the top bins
-    constexpr int WPM = NWAVES / MM, PER = BINS / (WPM * 64);
-    const int m = wave / WPM, part = wave % WPM;
-    const bool walks = m < M && s_alive[min(m, M - 1)] == 1u;
-    const int tb = BINS - 1 - (part * 64 + lane) * PER;       // bins tb, tb - 1, ..., tb - PER + 1
-    uint32_t share = 0u, incl = 0u;
-    if (walks) {
-#pragma unroll
-      for (int j = 0; j < PER; ++j) share += cnt[m][tb - j];
-      incl = wave_incl_scan_u32(share);
-      if (lane == 63) s_part[m][part] = incl;
-    }
-    __syncthreads();
-    uint32_t need = 0u;
-    if (walks) {
-      uint32_t total = 0u, before = incl - share;
-#pragma unroll
-      for (int w = 0; w < WPM; ++w) { const uint32_t x = s_part[m][w]; total += x; before += w < part ? x : 0u; }
-      need = min(s_need[m], total);                // (first level: a budget above the candidate count keeps them all)
-      if (before < need && before + share >= need) {          // one lane of one wave: the bin is among its own
-        uint32_t bin = (uint32_t)tb;
-#pragma unroll 1
-        for (;;) {
-          const uint32_t x = cnt[m][bin];
-          if (before + x >= need) break;
-          before += x; --bin;
+      __syncthreads();
+      if (walks && part == 0 && lane == 0) {       // the next level's state (everybody has read this one's)
+        if (need == 0u) { s_alive[m] = 0u; s_need[m] = 0u; s_range[m] = descent_none(); }     // nothing to keep: tau stays above every key
+        else {
+          const DescentRange r = s_range[m];
+          s_need[m] = need - s_before[m];          // still needed from inside this bin
+          if (r.sh == 0) { s_tau[m] = r.sub + s_bin[m]; s_alive[m] = 2u; s_range[m] = descent_none(); }
+          else s_range[m] = descent_next<SEL_SH1>(r, s_bin[m]);
         }
-        s_before[m] = before; s_bin[m] = bin;
+      }
+      __syncthreads();
+      if (phase == 1) break;
+      bool open = false, walked = false;
+      for (int mm = 0; mm < M; ++mm) { open = open || s_alive[mm] == 1u; walked = walked || s_alive[mm] == 2u; }
+      if (!open) { ranked = !walked; break; }      // (nothing to keep of any modality: as good as ranked)
+    }
+
+    // ---- the next level: the candidates of the crossing bins, about a hundredth of all, go into a list; the descent goes on over
+    // that, or ends where they are few enough to rank each of them against the others
+    if (have != 1) {
+      if (tid < MM) s_listed[tid] = 0u;
+      if (tid == 0) s_sure = 0u;
+      __syncthreads();
+    }
+    auto push = [&](int m, unsigned long long x) {
+      const uint32_t at = atomicAdd(&s_listed[m], 1u);
+      if (at < (uint32_t)CAP) list[m * CAP + at] = x;
+    };
+    auto within = [&](int m, uint32_t key) { return key - s_range[m].lo <= s_range[m].hi - s_range[m].lo; };
+    if (have == 0) {                               // from the scores
+      // (in the place of the counts, which have been walked)
+      WaveBuf<unsigned long long> wb{reinterpret_cast<unsigned long long*>(select_smem) + wave0 * WAVE_BUF, 0u};
+      const auto take = [&](unsigned long long x) {
+        const uint32_t m = ((uint32_t)x >> 30) ^ 3u;
+        push((int)m, x ^ (m << 30));
+      };
+      DescentRange rg[MM];
+      uint32_t hi[MM], sure = 0u;                  // keys above hi are kept for sure (chunks)
+#pragma unroll
+      for (int m = 0; m < MM; ++m) {
+        rg[m] = descent_uniform(s_range[min(m, M - 1)]);
+        hi[m] = __builtin_amdgcn_readfirstlane((int)s_alive[min(m, M - 1)]) == 1 ? rg[m].hi : 0xffffffffu;
+      }
+      for_key_groups<true>(sc, mask, i_begin + 4 * tid, i_end, a.mpa_mode, [&](const KeyGroup& g, int i) {
+        const uint32_t ids = mask4_ids<MM>(g.mw, top);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int m = (int)id_of<MM>(ids, q);
+          const uint32_t key = float_key(g.x[q]);
+          const uint32_t lo = MM == 2 ? (m ? rg[1].lo : rg[0].lo) : s_range[m].lo, sp = (MM == 2 ? (m ? rg[1].hi : rg[0].hi) : s_range[m].hi) - lo;
+          // (a position takes 20 bits: two of the others say the modality)
+          wb.put(i + q < i_end && key - lo <= sp, ((unsigned long long)key << 32) | (~(uint32_t)(i + q) ^ ((uint32_t)m << 30)));
+          if (phase == 2) sure += i + q < i_end && key > pick(hi, m) ? 1u : 0u;
+        }
+        if (wb.n > 64u) wb.flush(lane, take);
+      });
+      wb.flush(lane, take);
+      if (phase == 2) {
+        const uint32_t x = wave_incl_scan_u32(sure);
+        if (lane == 63 && x) atomicAdd(&s_sure, x);
+      }
+    } else if (have == 2) {                        // from the head's list in memory
+      for (int m = 0; m < M; ++m)
+        for (int e = tid; e < glisted(m); e += SEL_THREADS) {
+          const unsigned long long x = agent_load(glist + m * gcap + e);
+          if (within(m, (uint32_t)(x >> 32))) push(m, x);
+        }
+    } else {                                       // from the list itself
+      constexpr int PT = MM * CAP / SEL_THREADS;
+      unsigned long long x[PT];
+      bool in[PT];
+#pragma unroll
+      for (int j = 0; j < PT; ++j) {
+        const int e = tid + j * SEL_THREADS, m = e / CAP;
+        in[j] = m < M && e % CAP < listed(min(m, M - 1));
+        x[j] = in[j] ? list[e] : 0ULL;
+      }
+      __syncthreads();
+      if (tid < M) s_listed[tid] = 0u;
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < PT; ++j) {
+        const int m = min((tid + j * SEL_THREADS) / CAP, M - 1);
+        if (in[j] && within(m, (uint32_t)(x[j] >> 32))) push(m, x[j]);
       }
     }
     __syncthreads();
-    if (walks && part == 0 && lane == 0) {         // the next level's state (everybody has read this one's)
-      if (need == 0u) { s_alive[m] = 0u; s_need[m] = 0u; s_range[m] = descent_none(); }     // nothing to keep: tau stays above every key
-      else {
-        const DescentRange r = s_range[m];
-        s_need[m] = need - s_before[m];            // still needed from inside this bin
-        if (r.sh == 0) { s_tau[m] = r.sub + s_bin[m]; s_alive[m] = 2u; s_range[m] = descent_none(); }
-        else s_range[m] = descent_next<SEL_SH1>(r, s_bin[m]);
+    if (phase == 2 && level == 0) {                // add the chunk's candidates to the head's; the last workgroup goes on with them all
+      __shared__ uint32_t s_base[MM];
+      if (tid < M) {
+        const uint32_t n = s_listed[tid];
+        // (too many for the list: a number that says so, whatever the others add)
+        s_base[tid] = n ? __hip_atomic_fetch_add(&meet->listed[tid], n <= (uint32_t)CAP ? n : 1u << 24, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
       }
+      if (tid == 0) agent_store(&chunk_kept[blockIdx.x], s_sure);
+      __syncthreads();
+      for (int m = 0; m < M; ++m)
+        for (int e = tid; e < min((int)s_listed[m], CAP); e += SEL_THREADS)
+          if (s_base[m] + e < (uint32_t)gcap) agent_store(glist + m * gcap + s_base[m] + e, list[m * CAP + e]);
+      if (!arrive_last(&meet->arrived[1], gridDim.x, &s_flag)) return;
+      if (tid < M) { s_glisted[tid] = s_listed[tid] = agent_load(&meet->listed[tid]); agent_store(&meet->listed[tid], 0u); }
+      if (tid == 0) agent_store(&meet->arrived[1], 0u);
+      for (int c = tid; c < (int)gridDim.x; c += SEL_THREADS) s_chunk[c] = agent_load(&chunk_kept[c]);
+      __syncthreads();
+      bool here = true, there = true;
+      for (int m = 0; m < M; ++m) {
+        here = here && (s_alive[m] != 1u || s_glisted[m] <= (uint32_t)CAP);
+        there = there && (s_alive[m] != 1u || s_glisted[m] <= (uint32_t)gcap);
+      }
+      alone = !there;
+      if (here)
+        for (int m = 0; m < M; ++m)
+          for (int e = tid; e < min((int)s_glisted[m], CAP); e += SEL_THREADS) list[m * CAP + e] = agent_load(glist + m * gcap + e);
+      have = here ? 1 : there ? 2 : 0;
+      __syncthreads();
+      i_begin = 0; i_end = nc;                     // from here on the whole head is this workgroup's
+    } else if (have != 1) {
+      bool here = true;
+      for (int m = 0; m < M; ++m) here = here && (s_alive[m] != 1u || s_listed[m] <= (uint32_t)CAP);
+      have = here ? 1 : have;
+    }
+    bool few = have == 1;
+    for (int m = 0; m < M; ++m) few = few && s_alive[m] != 2u && (s_alive[m] != 1u || s_listed[m] <= (uint32_t)SEL_RANK_MAX);
+    if (few) {
+      for (int e = tid; e < M * SEL_RANK_MAX; e += SEL_THREADS) rank[e] = 0u;
+      __syncthreads();
+      const bool mine = m_of < M && s_alive[min(m_of, M - 1)] == 1u;
+      const int n = mine ? (int)s_listed[m_of] : 0;
+      for (int i0 = 0; i0 < n; i0 += 64) {
+        const unsigned long long x = list[m_of * CAP + min(i0 + lane, n - 1)];
+        uint32_t above = 0u;
+#pragma unroll 4
+        for (int j = part; j < n; j += WPM) above += list[m_of * CAP + j] > x ? 1u : 0u;
+        if (i0 + lane < n) atomicAdd(&rank[m_of * SEL_RANK_MAX + i0 + lane], above);
+      }
+      __syncthreads();
+      if (mine) {
+        const uint32_t need = s_need[m_of];
+        for (int i = part * 64 + lane; i < n; i += WPM * 64) {
+          const uint32_t above = rank[m_of * SEL_RANK_MAX + i];
+          const unsigned long long x = list[m_of * CAP + i];
+          if (above + 1u == need) { s_tau[m_of] = (uint32_t)(x >> 32); s_pos[m_of] = ~(uint32_t)x; }
+        }
+      }
+      __syncthreads();
+      ranked = true;
+      break;
+    }
+    clear(tid);
+    __syncthreads();
+    auto add = [&](int m, uint32_t key) {
+      const DescentRange r = s_range[m];
+      if (key - r.lo <= r.hi - r.lo) atomicAdd(&cnt[m * BINS + (key >> r.sh) - r.sub], 1u);
+    };
+    if (have == 0) {
+      for_key_groups(sc, mask, i_begin + 4 * tid, i_end, a.mpa_mode, [&](const KeyGroup& g, int i) {
+        const uint32_t ids = mask4_ids<MM>(g.mw, top);
+        for (int q = 0; q < 4; ++q)
+          if (i + q < i_end) add((int)id_of<MM>(ids, q), float_key(q & 2 ? (q & 1 ? g.x[3] : g.x[2]) : (q & 1 ? g.x[1] : g.x[0])));
+      });
+    } else {
+      for (int m = 0; m < M; ++m)
+        for (int e = tid; e < (have == 1 ? listed(m) : glisted(m)); e += SEL_THREADS)
+          add(m, (uint32_t)((have == 1 ? list[m * CAP + e] : agent_load(glist + m * gcap + e)) >> 32));
     }
     __syncthreads();
-    if (phase == 2) break;
-    bool open = false;
-    for (int mm = 0; mm < M; ++mm) open = open || s_alive[mm] == 1u;
-    if (!open) break;
   }
-  if (phase == 2) {                                // hand over to the next level, or to the chunks' compaction
+  if (phase == 1 || (phase == 2 && ranked && !alone)) {        // hand over to the next launch
     if (tid0 < M) {
-      SelCarry cy;
-      cy.range = s_range[tid0]; cy.need = s_need[tid0]; cy.alive = s_alive[tid0]; cy.tau = s_tau[tid0]; cy.pad = 0u;
-      carry[tid0] = cy;
+      meet->range[tid0] = s_range[tid0]; meet->need[tid0] = s_need[tid0]; meet->alive[tid0] = s_alive[tid0]; meet->tau[tid0] = s_tau[tid0];
+      meet->pos[tid0] = s_pos[tid0];
+    }
+    if (tid0 == 0) meet->done = 0u;
+    if (phase == 2) {
+      // where the chunks begin: the sure ones of the chunks before, and what the head's list has of them.  (The list in memory
+      // holds all candidates of the first crossing bins, those of a range that was narrowed since among them.)
+      for (int m = 0; m < M; ++m)
+        if (s_alive[m] == 1u)
+          for (int e = tid0; e < (int)s_glisted[m]; e += SEL_THREADS) {
+            const unsigned long long x = agent_load(glist + m * gcap + e);
+            const uint32_t key = (uint32_t)(x >> 32), pos = ~(uint32_t)x;
+            if (key > s_tau[m] || (key == s_tau[m] && (int)pos <= (int)s_pos[m])) atomicAdd(&s_chunk[pos / SEL_CHUNK], 1u);
+          }
+      __syncthreads();
+      if (tid0 < 64) {                             // exclusive prefix over the chunks
+        const uint32_t x = tid0 < (int)gridDim.x ? s_chunk[tid0] : 0u, incl = wave_incl_scan_u32(x);
+        if (tid0 < (int)gridDim.x) chunk_kept[tid0] = incl - x;
+      }
     }
     return;
   }
-  if (phase >= 3) __syncthreads();
+  if constexpr (PHASE != 1) {
+  if (phase == 2 && tid0 == 0) meet->done = 1u;
+  if (ranked) {
+    const uint32_t end = write_kept<MM>(sc, mask, a.mpa_mode, out, 0, nc, top, s_tau, s_pos, 0u, &s_tot[0]);
+    for (int r = tid0; r < a.W; r += SEL_THREADS) out[end + r] = nc + r;
+    return;
+  }
 
-  // take every key > tau_m and the first ties_m keys == tau_m
+  // Many candidates share a threshold's bin: take every key > tau_m and the first ties_m keys == tau_m, 4096 candidates at a time.
   const int lane = tid0 & 63, wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
   uint32_t tau[MM], ties[MM], run_eq[MM];
 #pragma unroll
@@ -329,16 +611,6 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
     run_eq[m] = 0u;
   }
   uint32_t run_gt = 0u;
-  if (phase == 4) {
-    // what the chunks in front of this one have: sure ones and threshold-valued ones
-    const SelChunk* ci = a.chunkinfo + (size_t)head * a.nchunks;
-    for (int c = 0; c < (int)blockIdx.x; ++c) {
-      const SelChunk x = ci[c];
-      run_gt += x.gt;
-#pragma unroll
-      for (int m = 0; m < MM; ++m) run_eq[m] += (uint32_t)((x.eq >> (16 * m)) & 0xffffULL);
-    }
-  }
   constexpr int NF = MM == 2 ? 2 : 3;              // words of packed counts: {gt, eq0}, {eq1, eq2}, {eq3, -}
   KeyGroup next = load_keys(sc, mask, i_begin + 4 * tid0, i_end, a.mpa_mode);
   int buf = 0;
@@ -377,7 +649,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       tot[f] = (uint32_t)__builtin_amdgcn_readlane((int)w, NWAVES - 1);
       ex[f] += wave ? (uint32_t)__builtin_amdgcn_readlane((int)w, wave - 1) : 0u;
     }
-    if (phase != 3) {
+    {
       uint32_t rank[MM], pos = run_gt + (ex[0] & 0xffffu);
 #pragma unroll
       for (int m = 0; m < MM; ++m) {
@@ -399,21 +671,16 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
 #pragma unroll
     for (int m = 0; m < MM; ++m) run_eq[m] += m == 0 ? tot[0] >> 16 : m == 1 ? tot[1] & 0xffffu : m == 2 ? tot[1] >> 16 : tot[2];
   }
-  if (phase == 3) {                                // report and leave
-    if (tid0 == 0) {
-      SelChunk x;
-      x.gt = run_gt; x.pad = 0u; x.eq = 0ULL;
-#pragma unroll
-      for (int m = 0; m < MM; ++m) x.eq |= (unsigned long long)run_eq[m] << (16 * m);
-      a.chunkinfo[(size_t)head * a.nchunks + blockIdx.x] = x;
-    }
-    return;
-  }
-  if (per_chunk && i_end != nc) return;            // the window positions follow the last chunk's
   uint32_t kept = run_gt;
 #pragma unroll
   for (int m = 0; m < MM; ++m) kept += min(run_eq[m], ties[m]);
   for (int r = tid0; r < a.W; r += SEL_THREADS) out[kept + r] = nc + r;
+  }
+  }
+}
+
+size_t select_split_bytes(int M, int nchunks) {
+  return reinterpret_cast<size_t>(select_split(nullptr, M, nchunks).list + (size_t)M * nchunks * SEL_GLIST_PER_CHUNK);
 }
 
 size_t select_ws_bytes(const Dims& dm, const madakv_config& c) {
@@ -441,6 +708,14 @@ hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, co
   return hipGetLastError();
 }
 
+template <int MM, int PHASE>
+static hipError_t launch_select_t(const SelectArgs& a, dim3 grid, hipStream_t st) {
+  const size_t lds = PHASE == 3 ? 0 : select_front(a.M) + (size_t)a.M * SEL_LIST<MM> * sizeof(unsigned long long);
+  if (lds > 48 * 1024) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<MM, PHASE>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((select_kernel<MM, PHASE>), grid, dim3(SEL_THREADS), lds, st, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_select(const Dims& dm, const madakv_config& c, const float* psi_pool, const uint8_t* mask,
                          const int32_t* budgets, const int64_t* kv_off, const int32_t* kv_len, int32_t* kept_idx,
                          hipStream_t st, const int32_t* seg_len, const uint8_t* rowmod, void* split_buf, size_t split_bytes) {
@@ -450,30 +725,20 @@ hipError_t launch_select(const Dims& dm, const madakv_config& c, const float* ps
   a.B = dm.B; a.H = dm.H; a.L = dm.L; a.W = dm.W; a.nc = dm.nc; a.mpa_mode = c.mpa_mode;
   a.keep_all = (c.budget >= c.ctx_len && !seg_len) ? 1 : 0;
   a.select_mode = c.select_mode; a.sink_tokens = c.sink_tokens; a.M = c.n_modalities;
-  a.phase = 0; a.level = 0; a.heads = dm.heads; a.nchunks = 0; a.gcnt = nullptr; a.carry = nullptr; a.chunkinfo = nullptr;
+  a.split = nullptr; a.split_stride = 0;
   const int nchunks = split_chunks(dm);
+  const dim3 whole(dm.heads), chunks(nchunks, dm.heads);
+  const bool two = a.M == 2;
   if (nchunks && !seg_len && !a.keep_all && a.select_mode != 1 && split_buf &&
-      split_bytes >= split_buffer_bytes(dm.heads, a.M, nchunks)) {
-    // per level: the chunks' workgroups add their count histograms into the head's (in memory), one workgroup per head
-    // walks it; then every chunk reports what it keeps and writes it behind the chunks in front of it
-    const size_t hist = (size_t)3 * dm.heads * a.M * BINS;
-    a.gcnt = reinterpret_cast<uint32_t*>(split_buf);
-    a.carry = reinterpret_cast<SelCarry*>(a.gcnt + hist);
-    a.chunkinfo = reinterpret_cast<SelChunk*>(a.carry + (size_t)dm.heads * 4);
-    a.nchunks = nchunks;
-    launch_split_zero(a.gcnt, (long long)hist, st);
-    for (int step = 0; step < 8; ++step) {
-      a.phase = step < 6 ? 1 + (step & 1) : step - 3;          // 1, 2, 1, 2, 1, 2, 3, 4
-      a.level = step < 6 ? step / 2 : 0;
-      const dim3 grid = a.phase == 2 ? dim3(dm.heads) : dim3(nchunks, dm.heads);
-      if (a.M == 2) hipLaunchKernelGGL((select_kernel<2>), grid, dim3(SEL_THREADS), 0, st, a);
-      else hipLaunchKernelGGL((select_kernel<4>), grid, dim3(SEL_THREADS), 0, st, a);
-    }
-    return hipGetLastError();
+      split_bytes >= dm.heads * split_head_bytes(a.M, nchunks)) {
+    a.split = static_cast<char*>(split_buf) + stats_split_bytes(a.M, nchunks);
+    a.split_stride = (long long)split_head_bytes(a.M, nchunks);
+    hipError_t e = two ? launch_select_t<2, 1>(a, chunks, st) : launch_select_t<4, 1>(a, chunks, st);
+    if (e == hipSuccess) e = two ? launch_select_t<2, 2>(a, chunks, st) : launch_select_t<4, 2>(a, chunks, st);
+    if (e == hipSuccess) e = two ? launch_select_t<2, 3>(a, chunks, st) : launch_select_t<4, 3>(a, chunks, st);
+    return e;
   }
-  if (a.M == 2) hipLaunchKernelGGL((select_kernel<2>), dim3(dm.heads), dim3(SEL_THREADS), 0, st, a);
-  else hipLaunchKernelGGL((select_kernel<4>), dim3(dm.heads), dim3(SEL_THREADS), 0, st, a);
-  return hipGetLastError();
+  return two ? launch_select_t<2, 0>(a, whole, st) : launch_select_t<4, 0>(a, whole, st);
 }
 
 }  // namespace madakv

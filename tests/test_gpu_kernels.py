@@ -636,3 +636,82 @@ def test_decode_pieces_that_come_into_being(kw):
             ref = torch.softmax(rows[l][0].view(H, Hq // H, d)[h].cpu().double() @ k.T / d ** 0.5, -1) @ v
             assert float((outs[l].view(H, Hq // H, d)[h].cpu().double() - ref).abs().max()) < 1e-4
     eng.close()
+
+
+@pytest.mark.parametrize("L,W,M", [(3000, 8, 2), (9001, 8, 3), (20000, 8, 2), (70001, 8, 2), (70001, 8, 3), (200001, 16, 2)])
+def test_statistics_of_crowded_bins(L, W, M):
+    """Scores so close together that the bin where the running mass crosses theta holds a few, hundreds (ranked, or walked once
+    more), thousands (more than a workgroup's list, or than the chunk's share of the head's) or all of the candidates, equal ones
+    among them; two layers in one call and one after the other.  The rules of test_statistics_at_edges."""
+    scale = [0.0, 0.001, 0.01, 0.03, 0.1, 0.4]
+    H, d, nc = len(scale), 64, L - W
+    g = torch.Generator().manual_seed(L + M)
+    mask_h = torch.randint(0, M, (1, L), generator=g).to(torch.uint8)
+    q = torch.randn(2, 1, H, W, d, generator=g).to(DEV, torch.bfloat16)
+    k = (torch.randn(2, 1, H, L, d, generator=g) * torch.tensor(scale)[None, None, :, None, None]).to(DEV, torch.bfloat16)
+    eng = MB.MadaKV(n_layers=2, batch=1, n_q_heads=H, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=W + nc // 3, dtype="bf16", pool_k=7,
+                    n_modalities=M, device=DEV)
+    mask, mh = mask_h.to(DEV), mask_h[0].numpy()
+    say(f"crowded bins L={L} M={M}")
+    eng.score(0, 2, q, k, mask)
+    torch.cuda.synchronize()
+    w_g, k_g = eng.stats_host()
+    pool = eng.psi_pool.clone()
+    for l in range(2):
+        eng.score(l, 1, q[l:l + 1], k[l:l + 1], mask)
+        torch.cuda.synchronize()
+    w_1, k_1 = eng.stats_host()
+    assert np.array_equal(w_g, w_1) and np.array_equal(k_g, k_1) and torch.equal(pool, eng.psi_pool)
+    for l in range(2):
+        psi = eng.psi[l, 0].cpu().numpy().astype(np.float64)
+        w_o, k_o, _ = O.modality_stats(psi, mh, W, 0.9, 0, M)
+        PU.assert_masses_close(w_g[l, 0], w_o, nc)
+        for h in range(H):
+            for m in range(M):
+                if k_g[l, 0, h, m] != k_o[h, m]:
+                    assert PU.k_count_ok(int(k_g[l, 0, h, m]), psi[h, :nc][mh[:nc] == m], 0.9), (l, h, m, k_g[l, 0, h, m], k_o[h, m])
+    eng.close()
+
+
+@pytest.mark.parametrize("L,M", [(9000, 2), (9000, 3), (20001, 2), (70001, 2), (70001, 4), (200001, 2)])
+def test_selection_of_crowded_bins(L, M):
+    """Kept positions, bit for bit, where the threshold is among 2 to 5000 scores of one bin (or all of them), at and around
+    what is ranked at once and what a list holds, in bins of either width and next to their boundary, with ties; two layers in
+    one call and one after the other."""
+    W, d, nc = 8, 64, L - 8
+    sizes = [2, 63, 65, 255, 257, 1023, 1025, 2047, 2049, 5000, nc]
+    H = len(sizes)
+    r = np.random.default_rng(L + M)
+    mh = r.integers(0, M, size=L).astype(np.uint8)
+    pool = np.empty((2, H, nc), dtype=np.float32)
+    bud = np.zeros((2, H, M), dtype=np.int32)
+    for l in range(2):
+        for h, n in enumerate(sizes):
+            at = (2.0 ** -3, 2.0 ** -16, 2.0 ** -20 * 1.01)[(h + l) % 3]           # the crowd: 1 / 128 wide, from `at` on
+            row = np.where(r.random(nc) < 0.3, at * 8 * (1 + r.random(nc)), at / 8 * r.random(nc))
+            for m in range(M):
+                who = r.permutation(np.flatnonzero(mh[:nc] == m))[:n]
+                row[who] = at * (1 + r.integers(0, max(2, n // 2), size=len(who)) / max(2, n // 2) / 128)
+                above = int(((row > at * 2) & (mh[:nc] == m)).sum())
+                bud[l, h, m] = above + max(1, int(len(who) * (0.1, 0.5, 0.97)[m % 3]))
+            pool[l, h] = row
+    eng = MB.MadaKV(n_layers=2, batch=1, n_q_heads=H, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=L - 1, dtype="bf16", pool_k=1,
+                    n_modalities=M, device=DEV)
+    k = torch.zeros(2, 1, H, L, d, dtype=torch.bfloat16, device=DEV)
+    args = dict(psi_pool=torch.from_numpy(pool)[:, None].to(DEV), budgets=torch.from_numpy(bud)[:, None].to(DEV))
+    mask = torch.from_numpy(mh)[None].to(DEV)
+    say(f"crowded selection L={L} M={M}")
+    eng.select_gather(0, 2, k, k, mask, **args)
+    torch.cuda.synchronize()
+    kept, off, ln = eng.kept_idx.clone(), eng.kv_off.cpu().numpy()[:, 0], eng.kv_len.cpu().numpy()[:, 0]
+    for l in range(2):
+        eng.select_gather(l, 1, k[l:l + 1], k[l:l + 1], mask, **{x: t[l:l + 1] for x, t in args.items()})
+    torch.cuda.synchronize()
+    used = int(off[-1, -1] + ln[-1, -1])
+    assert torch.equal(kept[:used], eng.kept_idx[:used])
+    kept = kept.cpu().numpy()
+    for l in range(2):
+        for h in range(H):
+            ref = O.select_n(pool[l, h].astype(np.float64), mh, [int(x) for x in bud[l, h]], L, W)
+            np.testing.assert_array_equal(kept[off[l, h]:off[l, h] + ln[l, h]], ref)
+    eng.close()
