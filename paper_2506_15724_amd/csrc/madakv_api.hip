@@ -32,6 +32,10 @@ struct madakv_handle {
   // maxlen_stream and covered by maxlen_event, 2 = the value in h_maxlen has landed
   std::vector<uint8_t> maxlen_state;
   hipStream_t maxlen_stream;
+  // The handle's memory is cleared on the null stream when it is created, without waiting; calls on other streams wait for it
+  // (cleared_first) until it is known to be done.
+  hipEvent_t cleared_event;
+  bool cleared;
   Meet meet;                       // where the pieces of a head meet in decode
   // Side stream and events for the overlap of the bandwidth-bound kernels (score sweeps, gather)
   // with the latency-bound per-head kernels (statistics, selection) inside one call.  The side
@@ -128,9 +132,21 @@ int32_t validate(const madakv_config& c) {
   return MADAKV_OK;
 }
 
+// Before the first work that uses the handle's memory: see cleared_event.
+hipError_t cleared_first(madakv_handle* h, hipStream_t st) {
+  if (h->cleared || st == nullptr) return hipSuccess;
+  // (a captured call is replayed behind whatever its caller has waited for since the handle was made; no event query on its behalf)
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return hipSuccess;
+  const hipError_t q = hipEventQuery(h->cleared_event);
+  h->cleared = q == hipSuccess;
+  return q == hipErrorNotReady ? hipStreamWaitEvent(st, h->cleared_event, 0) : q;
+}
+
 void destroy_side(madakv_handle* h) {
   if (h->side) { (void)hipStreamSynchronize(h->side); (void)hipStreamDestroy(h->side); }
   if (h->ev_fork) (void)hipEventDestroy(h->ev_fork);
+  if (h->cleared_event) (void)hipEventDestroy(h->cleared_event);
   if (h->ev_join) (void)hipEventDestroy(h->ev_join);
   for (int g = 0; g < MAX_GROUPS; ++g) if (h->ev_grp[g]) (void)hipEventDestroy(h->ev_grp[g]);
   for (int g = 0; g < MAX_GROUPS; ++g) if (h->ev_sel[g]) (void)hipEventDestroy(h->ev_sel[g]);
@@ -242,9 +258,7 @@ hipError_t create_memory(madakv_handle* h) {
   m.len1 = reinterpret_cast<int32_t*>(p + len);
   m.acc = reinterpret_cast<float*>(p + acc);
   m.ml = reinterpret_cast<float*>(p + ml);
-  e = hipMemsetAsync(p, 0, acc, h->side);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->side);          // (a caller's stream need not wait for the null stream, nor this for its work)
-  return e;
+  return hipMemsetAsync(p, 0, acc, nullptr);
 }
 int32_t* len1_of(madakv_handle* h, int layer) { return h->meet.len1 + (size_t)layer * h->cfg.batch * h->cfg.n_kv_heads; }
 
@@ -272,9 +286,10 @@ int32_t decode_impl(madakv_handle* h, int32_t layer0, int32_t n,
     for (int l = layer0; l < layer0 + n; ++l)
       if (h->appended[l] >= h->cfg.max_new_tokens) return MADAKV_ERR_INVALID_ARG;
   }
-  hipError_t e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, h->meet,
-                               region_tokens(h->cfg) * h->cfg.batch, longest, make_paging(h), layer0,
-                               reinterpret_cast<hipStream_t>(stream));
+  hipError_t e = cleared_first(h, reinterpret_cast<hipStream_t>(stream));
+  if (e == hipSuccess) e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, h->meet,
+                                         region_tokens(h->cfg) * h->cfg.batch, longest, make_paging(h), layer0,
+                                         reinterpret_cast<hipStream_t>(stream));
   if (e == hipSuccess && k_new) for (int l = layer0; l < layer0 + n; ++l) h->appended[l] += 1;
   return hip_fail(h, e);
 }
@@ -294,6 +309,7 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   h->d_state = nullptr;
   h->d_maxlen = nullptr; h->h_maxlen = nullptr; h->maxlen_event = nullptr;
   h->maxlen_state.assign(cfg->n_layers, 0); h->maxlen_stream = nullptr;
+  h->cleared_event = nullptr; h->cleared = false;
   h->side = nullptr; h->ev_fork = nullptr; h->ev_join = nullptr;
   for (int g = 0; g < MAX_GROUPS; ++g) { h->ev_grp[g] = nullptr; h->ev_sel[g] = nullptr; }
   h->appended.assign(cfg->n_layers, 0);
@@ -301,7 +317,6 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   h->meet = Meet{}; h->d_page_tbl = nullptr;
   h->d_split = nullptr; h->split_bytes = 0;
   hipError_t e = hipGetDevice(&h->device);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
   if (e == hipSuccess) e = create_memory(h);
   {
     // long contexts on few heads: room for the largest launch that would use the chunk-parallel statistics / selection
@@ -311,14 +326,16 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
       const int heads = std::min(cfg->n_layers * cfg->batch * cfg->n_kv_heads, 128);
       h->split_bytes = heads * split_head_bytes(cfg->n_modalities, nchunks);
       if (e == hipSuccess) e = hipMalloc(&h->d_split, h->split_bytes);
-      if (e == hipSuccess) e = hipMemsetAsync(h->d_split, 0, h->split_bytes, h->side);
-      if (e == hipSuccess) e = hipStreamSynchronize(h->side);
+      if (e == hipSuccess) e = hipMemsetAsync(h->d_split, 0, h->split_bytes, nullptr);
     }
   }
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&h->h_maxlen), sizeof(int32_t) * cfg->n_layers * cfg->batch, hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&h->d_maxlen), h->h_maxlen, 0);
   if (e == hipSuccess) memset(h->h_maxlen, 0, sizeof(int32_t) * cfg->n_layers * cfg->batch);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->maxlen_event, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&h->cleared_event, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventRecord(h->cleared_event, nullptr);
+  if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming);
   for (int g = 0; g < MAX_GROUPS && e == hipSuccess; ++g) e = hipEventCreateWithFlags(&h->ev_grp[g], hipEventDisableTiming);
@@ -393,7 +410,7 @@ static int32_t score_impl(madakv_handle* h, int32_t layer0, int32_t n,
   const int ngroups = layer_groups(c, n, gb);
   const bool overlap = ngroups > 1;
   const size_t es = c.dtype == MADAKV_BF16 ? 2 : 4;
-  hipError_t e = hipSuccess;
+  hipError_t e = cleared_first(h, st);
   for (int gi = 0; gi < ngroups && e == hipSuccess; ++gi) {
     const int g0 = gb[gi];
     Dims dg = make_dims(c, gb[gi + 1] - g0);
@@ -462,8 +479,9 @@ int32_t madakv_allocate(madakv_handle* h, int32_t layer0, int32_t n,
   if (r != MADAKV_OK) return r;
   if (bad_ptr(stats, 4) || bad_ptr(n_mod, 4) || bad_ptr(budgets, 4)) return MADAKV_ERR_INVALID_ARG;
   Dims dm = make_dims(h->cfg, n);
-  return hip_fail(h, launch_allocate(dm, h->cfg, layer0, stats, n_mod, budgets, h->d_state,
-                                     reinterpret_cast<hipStream_t>(stream)));
+  hipError_t e = cleared_first(h, reinterpret_cast<hipStream_t>(stream));
+  if (e == hipSuccess) e = launch_allocate(dm, h->cfg, layer0, stats, n_mod, budgets, h->d_state, reinterpret_cast<hipStream_t>(stream));
+  return hip_fail(h, e);
 }
 
 int32_t madakv_select_gather(madakv_handle* h, int32_t layer0, int32_t n,
@@ -493,8 +511,8 @@ int32_t madakv_select_gather(madakv_handle* h, int32_t layer0, int32_t n,
   const bool overlap = ngroups > 1;
   const size_t es = c.dtype == MADAKV_BF16 ? 2 : 4;
   const size_t M = (size_t)c.n_modalities;
-  hipError_t e = hipSuccess;
-  if (overlap) {
+  hipError_t e = cleared_first(h, st);
+  if (overlap && e == hipSuccess) {
     e = hipEventRecord(h->ev_fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(h->side, h->ev_fork, 0);
   }
@@ -546,7 +564,7 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
   const size_t es = c.dtype == MADAKV_BF16 ? 2 : 4;
   const long long region = region_tokens(c);
   const size_t M = (size_t)c.n_modalities;
-  hipError_t e = hipSuccess;
+  hipError_t e = cleared_first(h, st);
   // Caller's stream: sweeps of group 0, sweeps of group 1, gather of group 0, sweeps of group 2, gather
   // of group 1, ..., gather of the last group.  Side stream: statistics, allocation, segment layout and
   // selection of a group as soon as its sweeps are done.  Only group 0's run beside sweeps (which they
@@ -672,7 +690,7 @@ int32_t madakv_reevict(madakv_handle* h, int32_t layer0, int32_t n,
   int32_t* sel = reinterpret_cast<int32_t*>(wsb + w.sel);
   uint8_t* rowmod = reinterpret_cast<uint8_t*>(wsb + w.rowmod);
   const size_t es = c.dtype == MADAKV_BF16 ? 2 : 4;
-  hipError_t e = hipSuccess;
+  hipError_t e = cleared_first(h, st);
   // paged cache: the kernels below work on a linear copy of the call's heads
   void* k_work = k_c; void* v_work = v_c; int32_t* idx_work = kept_idx; const int64_t* off_work = kv_off;
   const long long cache_rows = region_tokens(c) * c.batch;
