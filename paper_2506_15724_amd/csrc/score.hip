@@ -1697,10 +1697,7 @@ constexpr int COMBINE_FROM = 8;
 #ifndef MADAKV_WIDE_WGS
 #define MADAKV_WIDE_WGS 768
 #endif
-#ifndef MADAKV_WIDE_WGS2
-#define MADAKV_WIDE_WGS2 512
-#endif
-constexpr int WIDE_WGS = MADAKV_WIDE_WGS, WIDE_WGS2 = MADAKV_WIDE_WGS2;   // workgroups per launch the chunking aims at with more than 64 proxy rows: sweep 1, sweep 2
+constexpr int WIDE_WGS = MADAKV_WIDE_WGS;       // workgroups the chunking of sweep 1 aims at with more than 64 proxy rows
 
 static bool use_mfma(const Dims& dm, int dtype) { return dtype == MADAKV_BF16 && (dm.d == 64 || dm.d == 128); }
 
@@ -1869,6 +1866,26 @@ static void launch_wide_sweep1(const ScoreArgs& a, int heads, hipStream_t st) {
   hipLaunchKernelGGL((score_wide_dma_kernel<D, 4, NRB1, 64, 1, 1, CLOSE>), dim3(a.nsplit, heads), dim3(256), lds1, st, a);
   hipLaunchKernelGGL(score_combine_kernel, dim3(heads), dim3(256), 0, st, a);
 }
+// Keys per chunk of sweep 2: what costs least, counted in tiles of a workgroup.  The chip holds two workgroups per compute unit;
+// a last round that leaves compute units with one of them takes some 0.6 of a full one, a workgroup's start about a tile.
+// 112 heads of 32K keys and 224 rows (statistics kernel included): 4 chunks per head (448 workgroups) 325 us, 5 (560, what "about
+// 512" had meant) 389-442, 7 (784) 359, 9 (1008) 318, 14 (1568) 341, 16 (1792) 305, 27 (3024) 322; of 4K keys: 4 chunks 60, 5
+// 70, 11 64; 128 heads of 16K and 128 rows: 4 chunks (512) 137, 5 170, 7 148, 8 138.  Few heads: flat (4 of 32K: 45-51 from
+// 128 to 1800 workgroups).  psi does not depend on it.
+static int wide_chunk2(int L, int heads) {
+  constexpr int SLOTS = 512, TILE = 64;
+  int best = 0; double least = 0.;
+  const int most = std::max(1, std::min(L / 512, (2048 + heads - 1) / heads));
+  for (int ns = 1; ns <= most; ++ns) {
+    const int chunk = ((L + ns - 1) / ns + TILE - 1) / TILE * TILE;
+    const long long wgs = (long long)heads * ((L + chunk - 1) / chunk);
+    const int left = (int)(wgs % SLOTS);
+    const double rounds = (double)(wgs / SLOTS) + (left == 0 ? 0. : left <= SLOTS / 2 ? 0.6 : 1.);
+    const double cost = rounds * (chunk / TILE + 1);
+    if (!best || cost < least) { best = chunk; least = cost; }
+  }
+  return best;
+}
 template <int D, bool WIDE8>
 static void launch_wide_pair(const ScoreArgs& a0, int heads, hipStream_t st) {
   ScoreArgs a = a0;
@@ -1887,10 +1904,8 @@ static void launch_wide_pair(const ScoreArgs& a0, int heads, hipStream_t st) {
     launch_wide_sweep1<D, WIDE8, false>(a, heads, st);
     a.nmerge = 1;
   }
-  // sweep 2 in chunks of its own (about two workgroups per CU); a.nsplit stays what the row statistics are laid out by
-  const int want2 = std::max(1, (WIDE_WGS2 + heads / 2) / heads);
-  const int ns2 = std::min(want2, std::max(1, a.L / 512));
-  a.chunk = ((a.L + ns2 - 1) / ns2 + 63) / 64 * 64;
+  // sweep 2 in chunks of its own; a.nsplit stays what the row statistics are laid out by
+  a.chunk = wide_chunk2(a.L, heads);
   dim3 grid2((a.L + a.chunk - 1) / a.chunk, heads);
   hipLaunchKernelGGL((score_wide_dma_kernel<D, 4, NRB2, 64, BS2, 2>), grid2, dim3(SCORE_THREADS), lds2, st, a);
 }
