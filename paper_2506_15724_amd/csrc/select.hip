@@ -65,6 +65,7 @@ __global__ __launch_bounds__(OFF_THREADS) void offsets_kernel(OffsetsArgs a, All
   __shared__ long long s_used;
   __shared__ int s_first_bad;
   __shared__ int s_lmax[OFF_MAX_LAYERS];
+  __shared__ int2 s_blk[OFF_THREADS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = blockIdx.x;
   const int nh = a.n * a.H;
@@ -124,17 +125,18 @@ __global__ __launch_bounds__(OFF_THREADS) void offsets_kernel(OffsetsArgs a, All
       a.kv_len[idx] = (int32_t)len;
       a.len1[idx] = (int32_t)len + 1;
       if (a.page_rows) a.page_tbl[(((long long)(a.layer0 + li) * a.B + b) * a.H + h) * a.tbl_entries] = (int32_t)(seg / a.page_rows);
-      // blocks whose first row lies inside this segment
+      // blocks whose first row lies inside this segment, relative to the table
       const long long b0 = (off + GATHER_ROWS - 1) / GATHER_ROWS, b1 = seg > 0 ? (off + seg - 1) / GATHER_ROWS : b0 - 1;
-      for (long long blk = b0; blk <= b1; ++blk) {
-        const long long t = blk - blk_base;
-        if (t >= 0 && t < a.blocks_per_batch) a.blk2head[(long long)b * a.blocks_per_batch + t] = f;
-      }
+      s_blk[tid] = make_int2((int)max(0LL, b0 - blk_base), (int)min((long long)a.blocks_per_batch - 1, b1 - blk_base));
       if (f == 0 && (start % GATHER_ROWS) != 0 && 0 < a.blocks_per_batch)
         a.blk2head[(long long)b * a.blocks_per_batch] = 0;    // the call starts inside a block: its first head is head 0
     }
     carry = now_over ? used : carry + tot;
     overflowed = now_over;
+    __syncthreads();
+    // the table, a wave per head (a thread per head took 6 us where 32 heads of 4K rows had 64 to 128 blocks each)
+    for (int g = wave; g < min(OFF_THREADS, nh - f0); g += OFF_THREADS / 64)
+      for (int t = s_blk[g].x + lane; t <= s_blk[g].y; t += 64) a.blk2head[(long long)b * a.blocks_per_batch + t] = f0 + g;
     __syncthreads();
   }
   for (int li = tid; li < a.n; li += OFF_THREADS) a.layer_maxlen[(long long)li * a.B + b] = s_lmax[li];
