@@ -58,10 +58,16 @@ size_t select_ws_bytes(const Dims& dm, const madakv_config& c);
 size_t decode_ws_bytes(const Dims& dm, const madakv_config& c);                             // worst case over head lengths
 size_t decode_ws_bytes_for(const Dims& dm, const madakv_config& c, int longest_rows);     // for a known longest head
 
+// The words in which the workgroups of a head exchange their row statistics (score.hip): where those of the call's first layer are,
+// and how many per head a launch has used (0: none), for the statistics kernel to empty.
+struct Exchange { unsigned long long* words; long long per_head; };
+
 struct AllocArgs;
 // Each launcher validates nothing: shapes were checked by the ABI layer.
 hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_win, const void* k, const float* row_lse,
-                        float* psi, void* ws, hipStream_t st);
+                        float* psi, void* ws, Exchange& x, hipStream_t st);
+size_t xchg_layer_words(const madakv_config& c, const Dims& one);
+void launch_xchg_clear(unsigned long long* words, size_t n, hipStream_t st);
 // Long heads on few heads: statistics and selection give every 16384-candidate chunk of a head a workgroup of its own, and
 // the chunks of a head meet in a record of split_head_bytes (owned by the handle); split_chunks = chunks per head then, 0
 // otherwise.
@@ -70,7 +76,7 @@ size_t split_head_bytes(int M, int nchunks);
 size_t stats_split_bytes(int M, int nchunks);
 size_t select_split_bytes(int M, int nchunks);
 hipError_t launch_stats(const Dims& dm, const madakv_config& c, const float* psi, const uint8_t* mask,
-                        float* psi_pool, void* stats, int32_t* n_mod, int layer0, hipStream_t st,
+                        float* psi_pool, void* stats, int32_t* n_mod, const Exchange& x, hipStream_t st,
                         void* split_buf = nullptr, size_t split_bytes = 0);
 hipError_t launch_allocate(const Dims& dm, const madakv_config& c, int layer0, const void* stats,
                            const int32_t* n_mod, int32_t* budgets, long long* pool_state, hipStream_t st);
@@ -91,7 +97,7 @@ hipError_t launch_score_ragged(const Dims& dm, const madakv_config& c, const voi
 bool window_attn_supported(const Dims& dm, const madakv_config& c);
 size_t window_attn_ws_bytes(const Dims& dm, const madakv_config& c);
 hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void* q_win, const void* k, const void* v,
-                              void* out, float* row_lse, float* psi, void* ws, hipStream_t st);
+                              void* out, float* row_lse, float* psi, void* ws, Exchange& x, hipStream_t st);
 hipError_t launch_restats(const Dims& dm, const madakv_config& c, const float* psi_c, const int32_t* kept_idx, const uint8_t* mask,
                           const int64_t* seg_off, const int32_t* seg_len, int appended, float* pool_c, uint8_t* rowmod,
                           void* stats, int32_t* budgets, hipStream_t st);

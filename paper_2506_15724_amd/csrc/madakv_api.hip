@@ -36,6 +36,9 @@ struct madakv_handle {
   // (cleared_first) until it is known to be done.
   hipEvent_t cleared_event;
   bool cleared;
+  unsigned long long* xchg;        // [n_layers][xchg_words] exchange words of the scoring kernels, XCHG_EMPTY between calls
+  size_t xchg_words;
+  bool xchg_used;                  // words may have been left behind (a launch failed): cleared before they are used again
   Meet meet;                       // where the pieces of a head meet in decode
   // Side stream and events for the overlap of the bandwidth-bound kernels (score sweeps, gather)
   // with the latency-bound per-head kernels (statistics, selection) inside one call.  The side
@@ -141,6 +144,14 @@ hipError_t cleared_first(madakv_handle* h, hipStream_t st) {
   const hipError_t q = hipEventQuery(h->cleared_event);
   h->cleared = q == hipSuccess;
   return q == hipErrorNotReady ? hipStreamWaitEvent(st, h->cleared_event, 0) : q;
+}
+
+// The exchange words of the layers from `layer` on, clean.  A caller sets xchg_used before it launches a scoring kernel and takes
+// it back when the statistics kernel that empties the words is on its way too.
+Exchange exchange_of(madakv_handle* h, int layer, hipStream_t st) {
+  if (h->xchg_used) launch_xchg_clear(h->xchg, h->cfg.n_layers * h->xchg_words, st);
+  h->xchg_used = false;
+  return Exchange{h->xchg + (size_t)layer * h->xchg_words, 0};
 }
 
 void destroy_side(madakv_handle* h) {
@@ -250,7 +261,9 @@ hipError_t create_memory(madakv_handle* h) {
   const size_t table = up(sizeof(long long) * 3 * c.batch), count = table + up(sizeof(int32_t) * heads * page_table_entries(c));
   const size_t len = count + heads * (G > 1 ? MEET_WAVES : 1) * MEET_COUNT_STRIDE * sizeof(uint32_t), acc = len + up(heads * sizeof(int32_t));
   const size_t ml = acc + up(rows * c.head_dim * sizeof(float));
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&h->d_state), ml + rows * 2 * sizeof(float));
+  h->xchg_words = xchg_layer_words(c, make_dims(c, 1));
+  const size_t xchg = up(ml + rows * 2 * sizeof(float)), xbytes = c.n_layers * h->xchg_words * sizeof(unsigned long long);
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&h->d_state), xchg + xbytes);
   if (e != hipSuccess) { h->d_state = nullptr; return e; }
   char* p = reinterpret_cast<char*>(h->d_state);
   if (c.page_rows) h->d_page_tbl = reinterpret_cast<int32_t*>(p + table);
@@ -258,7 +271,10 @@ hipError_t create_memory(madakv_handle* h) {
   m.len1 = reinterpret_cast<int32_t*>(p + len);
   m.acc = reinterpret_cast<float*>(p + acc);
   m.ml = reinterpret_cast<float*>(p + ml);
-  return hipMemsetAsync(p, 0, acc, nullptr);
+  h->xchg = reinterpret_cast<unsigned long long*>(p + xchg);
+  e = hipMemsetAsync(p, 0, acc, nullptr);
+  if (e == hipSuccess && xbytes) e = hipMemsetAsync(h->xchg, 0xff, xbytes, nullptr);
+  return e;
 }
 int32_t* len1_of(madakv_handle* h, int layer) { return h->meet.len1 + (size_t)layer * h->cfg.batch * h->cfg.n_kv_heads; }
 
@@ -314,6 +330,7 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   for (int g = 0; g < MAX_GROUPS; ++g) { h->ev_grp[g] = nullptr; h->ev_sel[g] = nullptr; }
   h->appended.assign(cfg->n_layers, 0);
   h->gen_base.assign(cfg->n_layers, 0);
+  h->xchg = nullptr; h->xchg_words = 0; h->xchg_used = false;
   h->meet = Meet{}; h->d_page_tbl = nullptr;
   h->d_split = nullptr; h->split_bytes = 0;
   hipError_t e = hipGetDevice(&h->device);
@@ -420,13 +437,15 @@ static int32_t score_impl(madakv_handle* h, int32_t layer0, int32_t n,
     float* psi_g = psi + lb * c.n_kv_heads * (size_t)c.ctx_len;
     float* pool_g = psi_pool + lb * c.n_kv_heads * (size_t)(c.ctx_len - c.window);
     const float* lse_g = row_lse ? row_lse + lb * c.n_q_heads * c.window : nullptr;
+    Exchange x = exchange_of(h, layer0 + g0, st);
+    h->xchg_used = true;
     if (window_attn) {
       const size_t oes = c.out_fp32 ? 4 : es;
       e = launch_window_attn(dg, c, qg, kg, static_cast<const char*>(v) + lb * c.n_kv_heads * (size_t)c.ctx_len * c.head_dim * es,
                              static_cast<char*>(out) + lb * c.n_q_heads * c.window * c.head_dim * oes,
-                             lse_out ? lse_out + lb * c.n_q_heads * c.window : nullptr, psi_g, ws, st);
+                             lse_out ? lse_out + lb * c.n_q_heads * c.window : nullptr, psi_g, ws, x, st);
     } else {
-      e = launch_score(dg, c, qg, kg, lse_g, psi_g, ws, st);
+      e = launch_score(dg, c, qg, kg, lse_g, psi_g, ws, x, st);
     }
     hipStream_t ss = st;
     if (overlap && e == hipSuccess) {
@@ -436,7 +455,8 @@ static int32_t score_impl(madakv_handle* h, int32_t layer0, int32_t n,
     }
     if (e == hipSuccess)
       e = launch_stats(dg, c, psi_g, mask, pool_g, static_cast<char*>(stats) + lb * c.n_kv_heads * 8 * (size_t)c.n_modalities,
-                       g0 == 0 ? n_mod : nullptr, layer0 + g0, ss, h->d_split, h->split_bytes);
+                       g0 == 0 ? n_mod : nullptr, x, ss, h->d_split, h->split_bytes);
+    h->xchg_used = e != hipSuccess;
   }
   if (overlap) e = join_side(h, st, e);
   return hip_fail(h, e);
@@ -591,14 +611,17 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
     char* stats_g = static_cast<char*>(stats) + heads0 * 8 * M;
     int32_t* bud_g = budgets + heads0 * M;
     char* ws_g = static_cast<char*>(select_ws) + sel_slice * gi;
-    e = launch_score(dg, c, qg, kg, nullptr, psi_g, score_ws, st);
+    Exchange x = exchange_of(h, layer0 + g0, st);
+    h->xchg_used = true;
+    e = launch_score(dg, c, qg, kg, nullptr, psi_g, score_ws, x, st);
     hipStream_t ss = st;
     if (overlap && e == hipSuccess) {
       e = hipEventRecord(h->ev_grp[gi], st);
       if (e == hipSuccess) e = hipStreamWaitEvent(h->side, h->ev_grp[gi], 0);
       ss = h->side;
     }
-    if (e == hipSuccess) e = launch_stats(dg, c, psi_g, mask, pool_g, stats_g, g0 == 0 ? n_mod : nullptr, layer0 + g0, ss, h->d_split, h->split_bytes);
+    if (e == hipSuccess) e = launch_stats(dg, c, psi_g, mask, pool_g, stats_g, g0 == 0 ? n_mod : nullptr, x, ss, h->d_split, h->split_bytes);
+    h->xchg_used = e != hipSuccess;
     const AllocArgs alloc = alloc_args(dg, c, layer0 + g0, stats_g, n_mod, bud_g, h->d_state);
     if (e == hipSuccess) e = launch_offsets(dg, c, layer0 + g0, bud_g, kv_off + heads0, kv_len + heads0, len1_of(h, layer0 + g0), h->d_state + c.batch,
                                             h->d_maxlen + (size_t)(layer0 + g0) * c.batch, ws_g, make_paging(h), blocks_per_batch(c, ng), ss, &alloc);

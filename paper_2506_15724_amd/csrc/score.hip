@@ -43,6 +43,7 @@ struct ScoreArgs {
   // one-sweep kernel: row statistics of the head's chunks as (max, sum) pairs in one 64-bit word each,
   // [heads, fsplit, mpad], all ones = not yet there; status[0] != 0 = a workgroup gave up waiting
   unsigned long long* xchg;
+  bool xchg_clean = false;      // (host) its words are XCHG_EMPTY already
   int k_kind;             // type of the keys of the one-sweep kernel: K_BF16, K_E4M3 or K_F32
   int xgroups;            // 0: every workgroup reads every chunk's words; else the number of groups of XCHG_GROUP chunks (two levels)
   long long xstride;      // exchange words per head: (fsplit + xgroups) * mpad
@@ -1820,7 +1821,7 @@ template <int D>
 static void launch_fused(const ScoreArgs& a, int heads, hipStream_t st) {
   const int vheads = heads * a.rb_count;
   const long long nx = (long long)vheads * a.xstride;
-  if (a.fsplit > 1)
+  if (a.fsplit > 1 && !a.xchg_clean)
     hipLaunchKernelGGL(score_xchg_init_kernel, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st,
                        a.xchg + (long long)a.head0 * a.rb_count * a.xstride, nx);
   ScoreArgs b = a;
@@ -2042,13 +2043,13 @@ static void launch_win_many_rows(WinArgs& wa, const Dims& dm, const madakv_confi
   }
 }
 hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void* q_win, const void* k, const void* v,
-                              void* out, float* row_lse, float* psi, void* ws, hipStream_t st) {
+                              void* out, float* row_lse, float* psi, void* ws, Exchange& x, hipStream_t st) {
   WinArgs wa;
   ScoreArgs& a = wa.s;
   a.lse = nullptr; a.q_win = q_win; a.k = k; a.psi = psi;
   a.status = reinterpret_cast<int*>(ws);
   a.rowstat = nullptr; a.sink = nullptr; a.seg_off = nullptr; a.seg_len = nullptr;
-  a.xchg = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + 256);
+  a.xchg = x.words; a.xchg_clean = true;
   a.H = dm.H; a.G = dm.G; a.d = dm.d; a.L = dm.L; a.W = dm.W; a.M = dm.M;
   a.mpad = 32; a.nsplit = 0; a.nmerge = 0; a.chunk = 0; a.head0 = 0;
   const int rb = win_blocks(dm);
@@ -2067,8 +2068,7 @@ hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void
     if (dm.d == 128) launch_win_many_rows<128>(wa, dm, c, st); else launch_win_many_rows<64>(wa, dm, c, st);
     return hipGetLastError();
   }
-  const long long nx = (long long)dm.heads * rb * a.xstride;
-  if (a.fsplit > 1) hipLaunchKernelGGL(score_xchg_init_kernel, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st, a.xchg, nx);
+  x.per_head = rb * a.xstride;
   const size_t lds = ((size_t)32 + 4 * 32) * (dm.d + 8) * 2 + ((size_t)4 * 32 * 2 + 32 + 512) * sizeof(float);
   const int vheads = dm.heads * rb, step = 65535 / rb * rb;       // whole heads per launch (the grid's y limit)
   for (int h0 = 0; h0 < vheads; h0 += step) {
@@ -2085,8 +2085,20 @@ hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void
   return hipGetLastError();
 }
 
+// Words the workgroups of a layer's heads may exchange in, whichever of the kernels takes the call.  They are the handle's, a
+// layer's at a place of its own, and XCHG_EMPTY between calls: the statistics kernel, which every scoring call runs behind the
+// scores, empties them again (a launch of its own for that took 2 to 5 us of every call).
+size_t xchg_layer_words(const madakv_config& c, const Dims& one) {
+  size_t n = xchg_bytes(one, c.dtype);
+  if (window_attn_supported(one, c) && !win_one_pass(one)) n = std::max(n, win_xchg_bytes(one));
+  return n / 8;
+}
+void launch_xchg_clear(unsigned long long* words, size_t n, hipStream_t st) {
+  if (n) hipLaunchKernelGGL(score_xchg_init_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, words, (long long)n);
+}
+
 hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_win, const void* k, const float* row_lse,
-                        float* psi, void* ws, hipStream_t st) {
+                        float* psi, void* ws, Exchange& x, hipStream_t st) {
   ScorePlan p = score_plan(dm, c.dtype);
   ScoreArgs a;
   a.lse = row_lse;
@@ -2094,7 +2106,7 @@ hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_wi
   a.status = reinterpret_cast<int*>(ws);
   a.rowstat = reinterpret_cast<float*>(static_cast<char*>(ws) + 256);
   a.sink = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype));
-  a.xchg = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype) + 256);
+  a.xchg = x.words; a.xchg_clean = true;
   a.rb_count = fused_blocks(dm);
   a.psi_part = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype) + 256 + xchg_bytes(dm, c.dtype));
   a.psi_part_stride = (long long)dm.heads * dm.L;
@@ -2120,6 +2132,7 @@ hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_wi
   a.scale_log2 = scale * 1.4426950408889634f;
   if (a.fsplit > 0) {                                      // one sweep (heads * row blocks fit one launch)
     a.mpad = fused_mpad(dm);
+    x.per_head = a.rb_count * a.xstride;
     if (dm.d == 128) launch_fused<128>(a, dm.heads, st); else launch_fused<64>(a, dm.heads, st);
     return hipGetLastError();
   }

@@ -50,6 +50,7 @@ struct StatsArgs {
   // Phase 0 = the whole head in one workgroup.  Long heads on few heads: a workgroup per chunk; 1 = its masses, added to the
   // head's in memory, which the last one to arrive walks; 2 = its keys of the crossing bins, added to the head's list, which
   // the last one to arrive ranks.
+  unsigned long long* xchg; long long xchg_per_head;   // the exchange words of the scoring kernels, to be emptied (Exchange)
   char* split;                                   // a record of split_stride bytes per head (StatsSplit)
   long long split_stride;
 };
@@ -224,6 +225,8 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
   };
 
   if (phase != 2) {                                // level 0: the masses of all keys
+    for (long long i = tid0 + (phase ? (int)blockIdx.x * STATS_THREADS : 0); i < a.xchg_per_head; i += (phase ? (int)gridDim.x : 1) * STATS_THREADS)
+      a.xchg[head * a.xchg_per_head + i] = ~0ULL;
     const int tid = tid0, lane = tid & 63, i_first = i_begin + 4 * tid;
     clear(tid);
     __syncthreads();
@@ -584,12 +587,12 @@ static hipError_t launch_stats_t(const StatsArgs& a, dim3 grid, size_t lds, hipS
 }
 
 hipError_t launch_stats(const Dims& dm, const madakv_config& c, const float* psi, const uint8_t* mask,
-                        float* psi_pool, void* stats, int32_t* n_mod, int layer0, hipStream_t st,
+                        float* psi_pool, void* stats, int32_t* n_mod, const Exchange& x, hipStream_t st,
                         void* split_buf, size_t split_bytes) {
   StatsArgs a;
   a.psi = psi; a.mask = mask; a.psi_pool = psi_pool; a.stats = stats; a.n_mod = n_mod;
   a.B = dm.B; a.H = dm.H; a.L = dm.L; a.W = dm.W; a.nc = dm.nc; a.pool_r = (c.pool_k - 1) / 2;
-  (void)layer0;
+  a.xchg = x.words; a.xchg_per_head = x.per_head;
   a.pool_mode = c.pool_mode; a.share_mode = c.share_mode; a.theta = (double)c.theta;
   a.M = c.n_modalities;
   a.split = nullptr; a.split_stride = 0;
