@@ -18,7 +18,7 @@
 //
 // Measured per layer call, with a merge kernel behind the attention kernel -> in one launch: 128 heads of ~2K bf16 rows,
 // 135 MB, 28.6 -> 26.8 us (the rows alone take 21.7 at the rate of a large read), 8-bit rows 18.7 -> 16.6, 4 heads of 2K rows
-// with 7 queries each 10.5 -> 8.4.  What the end of a piece costs, from the last row to the output: 0.35 us among the lanes
+// with 7 queries each 10.5 -> 8.3.  What the end of a piece costs, from the last row to the output: 0.35 us among the lanes
 // of a wave (row swaps and rotations; shuffles through LDS took 0.75), 0.4 among the waves, 0.6 for acknowledgement and
 // arrival, 0.7-1.3 for reading the pieces, 0.3 for the output.  It is instructions as much as trips to memory: a merge by
 // the whole workgroup with 8-byte accesses, polling for words not yet there instead of counting, took 3.5 us longer than
@@ -644,8 +644,9 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
         *reinterpret_cast<du32x4_t*>(vt + (i * RPI + vsub) * RS + vpiece * 8) = vraw[i];
       }
     }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    float lo_m, hi_m;
+    lane_pair<16>(tmax, lo_m, hi_m); tmax = fmaxf(lo_m, hi_m);
+    lane_pair<32>(tmax, lo_m, hi_m); tmax = fmaxf(lo_m, hi_m);
     const float m_new = fmaxf(m_run, tmax);
     const float alpha = weight_of(m_run - m_new);
     m_run = m_new;
@@ -662,10 +663,17 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
     l_run = l_run * alpha + psum;
     const dbf16x8_t pa_hi = __builtin_bit_cast(dbf16x8_t, du32x4_t{hi[0], hi[1], hi[2], hi[3]});
     const dbf16x8_t pa_lo = __builtin_bit_cast(dbf16x8_t, du32x4_t{lo[0], lo[1], lo[2], lo[3]});
-    // rescale factors of the queries this lane holds in the O layout (q = 4c + r)
-    float al[4];
+    // (the wave's first tile, its only one in a piece of 128 rows, finds nothing to rescale)
+    if (t0 >= r_begin + NW * 32) {
+      // rescale factors of the queries this lane holds in the O layout (q = 4c + r)
+      float al[4];
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) al[rr] = __shfl(alpha, (c << 4) | (4 * c + rr), 64);
+      for (int rr = 0; rr < 4; ++rr) al[rr] = __shfl(alpha, (c << 4) | (4 * c + rr), 64);
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) oacc[db][rr] *= al[rr];
+    }
     // the V tile must be complete before it is read with another lane mapping (same wave: in order)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -680,8 +688,6 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
       const ds16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)(vf + 16 * RS + db * 16));
       const dbf16x8_t vb = __builtin_bit_cast(dbf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
       df32x4_t o = oacc[db];
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) o[rr] *= al[rr];
       o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_hi, vb, o, 0, 0, 0);
       o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_lo, vb, o, 0, 0, 0);
       oacc[db] = o;
@@ -691,8 +697,11 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
   }
 
   // ---- per wave: total of the sums over the lane groups, then everything to LDS in [q][d] form
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  {
+    float x, y;
+    lane_pair<16>(l_run, x, y); l_run = x + y;
+    lane_pair<32>(l_run, x, y); l_run = x + y;
+  }
   __syncthreads();                                   // all V tiles are dead: their space takes the results
   if (c == 0 && j16 < GT) { s_ml[wave][j16][0] = m_run; s_ml[wave][j16][1] = l_run; }
   if (c < GT / 4)                                    // (lanes of the padding rows 8..15 have nothing to leave)
