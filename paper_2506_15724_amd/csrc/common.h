@@ -17,6 +17,7 @@ struct Dims {
   int M;        // G * W proxy rows per KV head
   int nc;       // L - W candidates
   int heads;    // n * B * H
+  int model_heads;   // n_layers * B * H
 };
 
 // Paged reduced cache (config.page_rows > 0): a head's kept rows fill whole pages that follow each other

@@ -77,7 +77,7 @@ Dims make_dims(const madakv_config& c, int n) {
   Dims dm;
   dm.n = n; dm.B = c.batch; dm.Hq = c.n_q_heads; dm.H = c.n_kv_heads; dm.G = c.n_q_heads / c.n_kv_heads;
   dm.d = c.head_dim; dm.L = c.ctx_len; dm.W = c.window; dm.M = dm.G * dm.W; dm.nc = dm.L - dm.W;
-  dm.heads = n * c.batch * c.n_kv_heads;
+  dm.heads = n * c.batch * c.n_kv_heads; dm.model_heads = c.n_layers * c.batch * c.n_kv_heads;
   return dm;
 }
 

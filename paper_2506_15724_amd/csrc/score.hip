@@ -43,6 +43,7 @@ struct ScoreArgs {
   // one-sweep kernel: row statistics of the head's chunks as (max, sum) pairs in one 64-bit word each,
   // [heads, fsplit, mpad], all ones = not yet there; status[0] != 0 = a workgroup gave up waiting
   unsigned long long* xchg;
+  int subtiles = 0;             // (host) of a wave, fp32
   bool xchg_clean = false;      // (host) its words are XCHG_EMPTY already
   int k_kind;             // type of the keys of the one-sweep kernel: K_BF16, K_E4M3 or K_F32
   int xgroups;            // 0: every workgroup reads every chunk's words; else the number of groups of XCHG_GROUP chunks (two levels)
@@ -1729,13 +1730,23 @@ ScorePlan score_plan(const Dims& dm, int dtype) {
 // head has few enough chunks that all its workgroups are certain to be on the chip together.
 constexpr int FUSED_NS1 = MADAKV_FUSED_NS1, FUSED_NS2 = MADAKV_FUSED_NS2;
 constexpr int FUSED_MAX_SPLIT = MADAKV_FUSED_MAX_SPLIT;
-// (fp32: half the keys per workgroup, since a wave takes 4-8 times as long over a subtile; few heads spread over more of the chip)
+static int fused_blocks(const Dims& dm) { return dm.M <= 64 ? 1 : (dm.M + 63) / 64; }   // blocks of 64 proxy rows handled like heads
+// fp32: half the keys per workgroup, since a wave takes 4-8 times as long over a subtile; where even a call over the whole model
+// leaves most of the chip idle, a quarter or an eighth.  (By the model and not by the call: psi depends on it in the last bits, and
+// is the same layer by layer and in one call.)  Scores and statistics, 4 / 2 / 1 subtiles per wave: 8 heads of 1K keys and 64 dims
+// 23.6 / 20.5 / 18.7 us, 64 of them 24.8 / 22.1 / 21.4, 256 33 / 43 / 56; 32 heads of 1K and 128 dims 29 / 24 / 22, of 4K 33 / 42 / 57.
 constexpr int FUSED_NS_F32 = 4;
-static int fused_subtiles(const Dims& dm, int dtype) { return dtype == MADAKV_FP32 ? FUSED_NS_F32 : (dm.M <= 32 ? FUSED_NS1 : FUSED_NS2); }
+static int fused_subtiles(const Dims& dm, int dtype) {
+  if (dtype != MADAKV_FP32) return dm.M <= 32 ? FUSED_NS1 : FUSED_NS2;
+  for (int ns = 1; ns < FUSED_NS_F32; ns *= 2) {
+    const int chunks = (dm.L + 128 * ns - 1) / (128 * ns);
+    if (chunks <= FUSED_MAX_SPLIT && (long long)dm.model_heads * fused_blocks(dm) * chunks <= (dm.d == 64 ? 512 : 256)) return ns;
+  }
+  return FUSED_NS_F32;
+}
 static int fused_chunk(const Dims& dm, int dtype) { return 4 * 32 * fused_subtiles(dm, dtype); }
 static int fused_split(const Dims& dm, int dtype) { return (dm.L + fused_chunk(dm, dtype) - 1) / fused_chunk(dm, dtype); }
 static int fused_mpad(const Dims& dm) { return dm.M <= 32 ? 32 : 64; }
-static int fused_blocks(const Dims& dm) { return dm.M <= 64 ? 1 : (dm.M + 63) / 64; }   // blocks of 64 proxy rows handled like heads
 // exchange levels: one up to FUSED_MAX_SPLIT chunks per head, two (groups of XCHG_GROUP chunks) up to
 // FUSED_MAX_SPLIT_2L.  All workgroups of a head wait for each other, so a head must never need more
 // workgroups than the chip holds at once (512 of this kernel): half of that is the limit.
@@ -1811,7 +1822,11 @@ static void launch_fused_kernel(const ScoreArgs& a, dim3 grid, hipStream_t st) {
 template <int D>
 static void launch_fused_by_kind(const ScoreArgs& a, dim3 grid, hipStream_t st) {
   const bool one = a.mpad == 32;
-  if (a.k_kind == K_F32) { if (one) launch_fused_kernel<D, 1, FUSED_NS_F32, K_F32>(a, grid, st); else launch_fused_kernel<D, 2, FUSED_NS_F32, K_F32>(a, grid, st); }
+  if (a.k_kind == K_F32) {
+    if (a.subtiles == 1) { if (one) launch_fused_kernel<D, 1, 1, K_F32>(a, grid, st); else launch_fused_kernel<D, 2, 1, K_F32>(a, grid, st); }
+    else if (a.subtiles == 2) { if (one) launch_fused_kernel<D, 1, 2, K_F32>(a, grid, st); else launch_fused_kernel<D, 2, 2, K_F32>(a, grid, st); }
+    else { if (one) launch_fused_kernel<D, 1, FUSED_NS_F32, K_F32>(a, grid, st); else launch_fused_kernel<D, 2, FUSED_NS_F32, K_F32>(a, grid, st); }
+  }
   else if (a.k_kind == K_E4M3) { if (one) launch_fused_kernel<D, 1, FUSED_NS1, K_E4M3>(a, grid, st); else launch_fused_kernel<D, 2, FUSED_NS2, K_E4M3>(a, grid, st); }
   else { if (one) launch_fused_kernel<D, 1, FUSED_NS1, K_BF16>(a, grid, st); else launch_fused_kernel<D, 2, FUSED_NS2, K_BF16>(a, grid, st); }
 }
@@ -2131,7 +2146,7 @@ hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_wi
   float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)dm.d);
   a.scale_log2 = scale * 1.4426950408889634f;
   if (a.fsplit > 0) {                                      // one sweep (heads * row blocks fit one launch)
-    a.mpad = fused_mpad(dm);
+    a.mpad = fused_mpad(dm); a.subtiles = fused_subtiles(dm, c.dtype);
     x.per_head = a.rb_count * a.xstride;
     if (dm.d == 128) launch_fused<128>(a, dm.heads, st); else launch_fused<64>(a, dm.heads, st);
     return hipGetLastError();

@@ -715,3 +715,29 @@ def test_selection_of_crowded_bins(L, M):
             ref = O.select_n(pool[l, h].astype(np.float64), mh, [int(x) for x in bud[l, h]], L, W)
             np.testing.assert_array_equal(kept[off[l, h]:off[l, h] + ln[l, h]], ref)
     eng.close()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(head_dim=64, n_q_heads=2, n_kv_heads=2, window=16, ctx_len=129, budget=40),         # one key in the second chunk of 128
+    dict(head_dim=64, n_q_heads=3, n_kv_heads=3, window=16, ctx_len=9000, budget=200),       # chunks of 256 keys
+    dict(head_dim=128, n_q_heads=20, n_kv_heads=20, window=32, ctx_len=1025, budget=100),    # chunks of 256 keys, 128 dims
+    dict(head_dim=128, n_q_heads=32, n_kv_heads=32, window=33, ctx_len=1100, budget=100),    # of 512, two row blocks
+], ids=lambda kw: f"d{kw['head_dim']}_q{kw['n_q_heads']}_w{kw['window']}_L{kw['ctx_len']}")
+def test_fp32_scores_by_size(kw):
+    """The chunks of the fp32 kernel by the size of the model (tolerance: test_fp32_scores); the layers of a model one by one
+    give the bits of one call."""
+    wl = workload("fp32_sizes", dtype="fp32", n_layers=2, **kw)
+    q, k, v, mask, masks = PU.make_inputs(wl, DEV)
+    eng = engine(wl)
+    eng.score(0, 2, q, k, mask)
+    torch.cuda.synchronize()
+    worst = check_psi(eng, wl, q, k)
+    say(f"{kw}: psi worst scaled error {worst:.2e}")
+    assert worst < 1e-4
+    one = eng.psi.clone()
+    eng.psi.zero_()
+    for l in range(2):
+        eng.score(l, 1, q[l:l + 1], k[l:l + 1], mask)
+    torch.cuda.synchronize()
+    assert torch.equal(one, eng.psi)
+    eng.close()
