@@ -110,6 +110,30 @@ __device__ __forceinline__ float half_reduce(float x) {
   return x;
 }
 
+// The same sums, in the same order, of 16 values: at each step a lane goes on with half of its values and takes what its
+// partner had of them; lane i of a half-wave gets the sum of x[i & 15].  (Half the instructions of 16 single
+// reductions, one wide store instead of 16.)
+__device__ __forceinline__ float half_fold(const float (&x)[16], int lane) {
+#define MADAKV_DPP(v, ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xF, 0xF, true))
+  float a[8], b[4], c[2];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) { const bool o = lane & 1; const float keep = o ? x[2 * k + 1] : x[2 * k], give = o ? x[2 * k] : x[2 * k + 1]; a[k] = keep + MADAKV_DPP(give, 0xB1); }   // lane ^ 1
+#pragma unroll
+  for (int k = 0; k < 4; ++k) { const bool o = lane & 2; const float keep = o ? a[2 * k + 1] : a[2 * k], give = o ? a[2 * k] : a[2 * k + 1]; b[k] = keep + MADAKV_DPP(give, 0x4E); }   // lane ^ 2
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {                                                     // lane ^ 4: mirrored in 8, then in 4
+    const bool o = lane & 4;
+    const float keep = o ? b[2 * k + 1] : b[2 * k], give = o ? b[2 * k] : b[2 * k + 1];
+    const float m = MADAKV_DPP(give, 0x141);
+    c[k] = keep + MADAKV_DPP(m, 0x1B);
+  }
+  const bool o = lane & 8;
+  const float keep = o ? c[1] : c[0], give = o ? c[0] : c[1];
+  const float d = keep + MADAKV_DPP(give, 0x128);                                   // lane ^ 8: rotated by 8 in 16
+#undef MADAKV_DPP
+  return d + __shfl_xor(d, 16, 64);                                                 // the two 16-lane rows of the half
+}
+
 template <int D, int NRB, int PASS>
 __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void score_mfma_kernel(ScoreArgs a) {
   constexpr int KS = D / 16;                  // MFMA k-steps
@@ -1094,8 +1118,8 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_fused_finish_kernel(Score
 // column sums of Eq. 7 one half-wave reduction per key, and P is already laid out as the A
 // operand of O += P V: the contraction index of that product is numbered so that a lane's
 // eight keys of a 16-key step are the eight it holds.  V subtiles are streamed through the same
-// wave-private LDS tile as K was; a B fragment (eight keys of one output column) is gathered
-// from it two bytes at a time.  P goes in as bf16 hi + lo parts (two MFMAs), which keeps
+// wave-private LDS tile as K was; a B fragment (eight keys of one output column) is read
+// from it by two transposing reads.  P goes in as bf16 hi + lo parts (two MFMAs), which keeps
 // fp32-level accuracy.  The V sweep does not wait for the exchange: it exponentiates against the
 // wave's own row maxima, and the head-wide statistics, collected after it, enter as one factor per
 // row (for O and for the column sums alike).  Every workgroup leaves its share of O, normalised
@@ -1110,6 +1134,10 @@ struct WinArgs {
   int out_fp32;
 };
 
+typedef __attribute__((ext_vector_type(2))) float win_f32x2_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 win_bf16x2_t;
+typedef __attribute__((ext_vector_type(4))) short win_s16x4_t;
+typedef __attribute__((address_space(3))) win_s16x4_t* win_lds_s16x4_ptr_t;
 template <int D, int NS>
 __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void window_attn_kernel(WinArgs wa) {
   const ScoreArgs& a = wa.s;
@@ -1179,6 +1207,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2
   for (int it = 0; it < NS; ++it) {
     MADAKV_WIN_PARK(it % PF)
     if (it + PF < NS) MADAKV_WIN_LOAD(kg, it % PF, it + PF)
+    else MADAKV_WIN_LOAD(vg, it % PF, it + PF - NS)          // V's first subtiles: the loads don't pause for the statistics
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1218,13 +1247,16 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2
     sm += __shfl_xor(sm, 32, 64);
     if (half == 0) { part[(wave * 32 + col) * 2] = mx; part[(wave * 32 + col) * 2 + 1] = sm; }
   }
-#pragma unroll
-  for (int it = 0; it < PF; ++it) MADAKV_WIN_LOAD(vg, it, it)
   __syncthreads();
   post_row_stats(a, hv, split, fs, part);
 
   // ---- O += P V with p taken against the wave's own row maxima, so that nothing here waits for the
   // other workgroups of the head; the head-wide statistics come in as one factor per row afterwards
+  // where this lane's transposing reads start: per 16 lanes four rows of 16 columns, lane j pointing at columns 4 (j & 3).. of row
+  // j >> 2 and getting column j of the four.  (For 32 heads of 8K keys, 40 us with eight single
+  // 2-byte reads per operand and P rounded in integer instructions, 34 us so; 31 us with V's first loads under the statistics
+  // and the column sums folded.  K and V alone take 24 us at the rate of a copy.)
+  const uint16_t* vtr = kt + (4 * half + ((lane & 15) >> 2)) * RS + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
   f32x16_t oacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) oacc[db] = f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1239,27 +1271,22 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
     for (int st = 0; st < 2; ++st) {                       // two 16-key steps of the subtile
-      uint32_t hi[4], lo[4];
+      uint32_t hi[4], lo[4];                               // round to nearest even, in pairs
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float pv = lg[it][8 * st + i];
-        const uint32_t hb = f32_to_bf16_rne(pv);
-        const uint32_t lb2 = f32_to_bf16_rne(pv - bf16_bits_to_f32(hb));
-        if (i & 1) { hi[i >> 1] |= hb << 16; lo[i >> 1] |= lb2 << 16; }
-        else { hi[i >> 1] = hb; lo[i >> 1] = lb2; }
+      for (int i = 0; i < 4; ++i) {
+        const win_f32x2_t pv = {lg[it][8 * st + 2 * i], lg[it][8 * st + 2 * i + 1]};
+        hi[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pv, win_bf16x2_t));
+        const win_f32x2_t rest = {pv[0] - bf16_lo(hi[i]), pv[1] - bf16_hi(hi[i])};
+        lo[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, win_bf16x2_t));
       }
       const bf16x8_t pa_hi = __builtin_bit_cast(bf16x8_t, u32x4_t{hi[0], hi[1], hi[2], hi[3]});
       const bf16x8_t pa_lo = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[0], lo[1], lo[2], lo[3]});
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {                      // V[key of contraction index 8 half + i][32 db + col]
-          const int row = 16 * st + 8 * (i >> 2) + 4 * half + (i & 3);
-          const uint32_t x = kt[row * RS + db * 32 + col];
-          if (i & 1) w[i >> 1] |= x << 16; else w[i >> 1] = x;
-        }
-        const bf16x8_t vb = __builtin_bit_cast(bf16x8_t, u32x4_t{w[0], w[1], w[2], w[3]});
+        // V[key of contraction index 8 half + i][32 db + col], keys 16 st + 8 (i >> 2) + 4 half + (i & 3): transposing reads
+        const win_s16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((win_lds_s16x4_ptr_t)(vtr + 16 * st * RS + db * 32));
+        const win_s16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((win_lds_s16x4_ptr_t)(vtr + (16 * st + 8) * RS + db * 32));
+        const bf16x8_t vb = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
         oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa_hi, vb, oacc[db], 0, 0, 0);
         oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa_lo, vb, oacc[db], 0, 0, 0);
       }
@@ -1281,14 +1308,14 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
   for (int it = 0; it < NS; ++it) {
     const int t0 = chunk0 + (it * 4 + wave) * 32;
+    float cs[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const float cs = half_reduce<1>(lg[it][j] * rs);     // over the 32 rows: psi of this key
-      const int key = t0 + 8 * (j >> 2) + 4 * half + (j & 3);
-      // (more than 32 proxy rows: the block's share of psi, added to the other blocks' in block order afterwards)
-      float* psi_dst = a.rb_count > 1 ? a.psi_part + (hv % a.rb_count) * a.psi_part_stride : a.psi;
-      if (col == 0 && key < chunk1) psi_dst[(long long)head * a.L + key] = cs;
-    }
+    for (int j = 0; j < 16; ++j) cs[j] = lg[it][j] * rs;
+    const float sum = half_fold(cs, lane);                 // over the 32 rows: psi of the key that this lane (of the first 16) has
+    const int key = t0 + 8 * ((lane & 15) >> 2) + 4 * half + (lane & 3);
+    // (more than 32 proxy rows: the block's share of psi, added to the other blocks' in block order afterwards)
+    float* psi_dst = a.rb_count > 1 ? a.psi_part + (hv % a.rb_count) * a.psi_part_stride : a.psi;
+    if (col < 16 && key < chunk1) psi_dst[(long long)head * a.L + key] = sum;
   }
   // ---- O rows take their factor: row m of the tile sits in lane m's rs
 #pragma unroll
