@@ -338,7 +338,7 @@ def main():
     launches = S * NL
     per_launch_us = decode_med * 1e3 / launches
     achieved = decode_bytes / (decode_med * 1e-3) / 1e9
-    roofline = {"bound": "hbm", "kernel": "decode_attn_kernel (+ its merge kernel), one launch per layer",
+    roofline = {"bound": "hbm", "kernel": "decode_attn_kernel, one launch per layer",
                 "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                 "traffic": read_traffic("decode_attn_kernel_llava_16k") if wl.name == "llava_16k" else None,
                 "bytes_per_launch": decode_bytes / launches, "us_per_launch": per_launch_us}
@@ -410,7 +410,7 @@ def main():
                   "above); in madakv_evict three of the four run beside the next group's statistics and selection kernels and "
                   "hold 4 workgroups per compute unit; one gather over all layers with nothing beside it takes 1.49 ms "
                   "(0.72 of peak); copy ceiling 5.2-5.7 TB/s", None),
-            dict(roofline, kernel="decode_attn_kernel + decode_merge_kernel (one call per layer)",
+            dict(roofline, kernel="decode_attn_kernel (one call per layer)",
                  note="a plain streaming read of the same 135 MB takes 22.6-25.6 us on this machine (0.66-0.75 of peak)",
                  kernel_only_us_from_profile=read_profile(prof, "decode_attn_kernel_avg_us"),
                  kernel_only_frac_from_profile=(decode_bytes / launches) / (read_profile(prof, "decode_attn_kernel_avg_us") * 1e-6) / 1e9 / HBM_PEAK_GBS

@@ -45,7 +45,8 @@
  *     four or more 16384-token chunks on at most 128 heads per layer a few MB of histograms that
  *     the per-head statistics and selection kernels share between launches; and a little pinned
  *     host memory, one extra stream of default priority and a few events.  Calls on one handle
- *     must not overlap.
+ *     must not overlap, a graph that holds captured calls is not replayed after madakv_destroy, and a handle's
+ *     lengths are those of one cache: a second cache that is evicted while the first is still decoded has a handle of its own.
  *   - Layers are addressed as a range [layer0, layer0 + n).  Tensor arguments hold
  *     only the n layers of the call, layer-major.  madakv_allocate and
  *     madakv_select_gather carry state from layer to layer and must be called in
