@@ -127,7 +127,8 @@ typedef struct {
 
 typedef struct madakv_handle madakv_handle;
 
-/* Creates a handle on the current HIP device.  *out is set only on success.
+/* Creates a handle on the current HIP device.  *out is set only on success.  The handle's memory is set
+ * up when the call returns: its first call may be on any stream, under graph capture too.
  * Errors: INVALID_ARG (null), BAD_SHAPE, BAD_BUDGET, UNSUPPORTED_DTYPE, HIP. */
 int32_t madakv_create(const madakv_config* cfg, madakv_handle** out);
 int32_t madakv_destroy(madakv_handle* h);

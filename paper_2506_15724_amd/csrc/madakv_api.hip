@@ -32,10 +32,6 @@ struct madakv_handle {
   // maxlen_stream and covered by maxlen_event, 2 = the value in h_maxlen has landed
   std::vector<uint8_t> maxlen_state;
   hipStream_t maxlen_stream;
-  // The handle's memory is cleared on the null stream when it is created, without waiting; calls on other streams wait for it
-  // (cleared_first) until it is known to be done.
-  hipEvent_t cleared_event;
-  bool cleared;
   unsigned long long* xchg;        // [n_layers][xchg_words] exchange words of the scoring kernels, XCHG_EMPTY between calls
   size_t xchg_words;
   bool xchg_used;                  // words may have been left behind (a launch failed): cleared before they are used again
@@ -135,17 +131,6 @@ int32_t validate(const madakv_config& c) {
   return MADAKV_OK;
 }
 
-// Before the first work that uses the handle's memory: see cleared_event.
-hipError_t cleared_first(madakv_handle* h, hipStream_t st) {
-  if (h->cleared || st == nullptr) return hipSuccess;
-  // (a captured call is replayed behind whatever its caller has waited for since the handle was made; no event query on its behalf)
-  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return hipSuccess;
-  const hipError_t q = hipEventQuery(h->cleared_event);
-  h->cleared = q == hipSuccess;
-  return q == hipErrorNotReady ? hipStreamWaitEvent(st, h->cleared_event, 0) : q;
-}
-
 // The exchange words of the layers from `layer` on, clean.  A caller sets xchg_used before it launches a scoring kernel and takes
 // it back when the statistics kernel that empties the words is on its way too.
 Exchange exchange_of(madakv_handle* h, int layer, hipStream_t st) {
@@ -157,7 +142,6 @@ Exchange exchange_of(madakv_handle* h, int layer, hipStream_t st) {
 void destroy_side(madakv_handle* h) {
   if (h->side) { (void)hipStreamSynchronize(h->side); (void)hipStreamDestroy(h->side); }
   if (h->ev_fork) (void)hipEventDestroy(h->ev_fork);
-  if (h->cleared_event) (void)hipEventDestroy(h->cleared_event);
   if (h->ev_join) (void)hipEventDestroy(h->ev_join);
   for (int g = 0; g < MAX_GROUPS; ++g) if (h->ev_grp[g]) (void)hipEventDestroy(h->ev_grp[g]);
   for (int g = 0; g < MAX_GROUPS; ++g) if (h->ev_sel[g]) (void)hipEventDestroy(h->ev_sel[g]);
@@ -272,8 +256,8 @@ hipError_t create_memory(madakv_handle* h) {
   m.acc = reinterpret_cast<float*>(p + acc);
   m.ml = reinterpret_cast<float*>(p + ml);
   h->xchg = reinterpret_cast<unsigned long long*>(p + xchg);
-  e = hipMemsetAsync(p, 0, acc, nullptr);
-  if (e == hipSuccess && xbytes) e = hipMemsetAsync(h->xchg, 0xff, xbytes, nullptr);
+  e = hipMemsetAsync(p, 0, acc, h->side);
+  if (e == hipSuccess && xbytes) e = hipMemsetAsync(h->xchg, 0xff, xbytes, h->side);
   return e;
 }
 int32_t* len1_of(madakv_handle* h, int layer) { return h->meet.len1 + (size_t)layer * h->cfg.batch * h->cfg.n_kv_heads; }
@@ -302,10 +286,9 @@ int32_t decode_impl(madakv_handle* h, int32_t layer0, int32_t n,
     for (int l = layer0; l < layer0 + n; ++l)
       if (h->appended[l] >= h->cfg.max_new_tokens) return MADAKV_ERR_INVALID_ARG;
   }
-  hipError_t e = cleared_first(h, reinterpret_cast<hipStream_t>(stream));
-  if (e == hipSuccess) e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, h->meet,
-                                         region_tokens(h->cfg) * h->cfg.batch, longest, make_paging(h), layer0,
-                                         reinterpret_cast<hipStream_t>(stream));
+  hipError_t e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, h->meet,
+                               region_tokens(h->cfg) * h->cfg.batch, longest, make_paging(h), layer0,
+                               reinterpret_cast<hipStream_t>(stream));
   if (e == hipSuccess && k_new) for (int l = layer0; l < layer0 + n; ++l) h->appended[l] += 1;
   return hip_fail(h, e);
 }
@@ -325,7 +308,6 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   h->d_state = nullptr;
   h->d_maxlen = nullptr; h->h_maxlen = nullptr; h->maxlen_event = nullptr;
   h->maxlen_state.assign(cfg->n_layers, 0); h->maxlen_stream = nullptr;
-  h->cleared_event = nullptr; h->cleared = false;
   h->side = nullptr; h->ev_fork = nullptr; h->ev_join = nullptr;
   for (int g = 0; g < MAX_GROUPS; ++g) { h->ev_grp[g] = nullptr; h->ev_sel[g] = nullptr; }
   h->appended.assign(cfg->n_layers, 0);
@@ -334,6 +316,7 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   h->meet = Meet{}; h->d_page_tbl = nullptr;
   h->d_split = nullptr; h->split_bytes = 0;
   hipError_t e = hipGetDevice(&h->device);
+  if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
   if (e == hipSuccess) e = create_memory(h);
   {
     // long contexts on few heads: room for the largest launch that would use the chunk-parallel statistics / selection
@@ -343,20 +326,20 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
       const int heads = std::min(cfg->n_layers * cfg->batch * cfg->n_kv_heads, 128);
       h->split_bytes = heads * split_head_bytes(cfg->n_modalities, nchunks);
       if (e == hipSuccess) e = hipMalloc(&h->d_split, h->split_bytes);
-      if (e == hipSuccess) e = hipMemsetAsync(h->d_split, 0, h->split_bytes, nullptr);
+      if (e == hipSuccess) e = hipMemsetAsync(h->d_split, 0, h->split_bytes, h->side);
     }
   }
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&h->h_maxlen), sizeof(int32_t) * cfg->n_layers * cfg->batch, hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&h->d_maxlen), h->h_maxlen, 0);
   if (e == hipSuccess) memset(h->h_maxlen, 0, sizeof(int32_t) * cfg->n_layers * cfg->batch);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->maxlen_event, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&h->cleared_event, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventRecord(h->cleared_event, nullptr);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming);
   for (int g = 0; g < MAX_GROUPS && e == hipSuccess; ++g) e = hipEventCreateWithFlags(&h->ev_grp[g], hipEventDisableTiming);
   for (int g = 0; g < MAX_GROUPS && e == hipSuccess; ++g) e = hipEventCreateWithFlags(&h->ev_sel[g], hipEventDisableTiming);
+  // The clears are done when the handle is handed over: its first call may be on any stream, and one that is captured could not
+  // be made to wait for them.  (On a stream of the handle's own: what the null stream holds is not waited for.)
+  if (e == hipSuccess) e = hipStreamSynchronize(h->side);
   if (e != hipSuccess) {
     if (h->d_split) (void)hipFree(h->d_split);
     if (h->h_maxlen) (void)hipHostFree(h->h_maxlen);
@@ -427,7 +410,7 @@ static int32_t score_impl(madakv_handle* h, int32_t layer0, int32_t n,
   const int ngroups = layer_groups(c, n, gb);
   const bool overlap = ngroups > 1;
   const size_t es = c.dtype == MADAKV_BF16 ? 2 : 4;
-  hipError_t e = cleared_first(h, st);
+  hipError_t e = hipSuccess;
   for (int gi = 0; gi < ngroups && e == hipSuccess; ++gi) {
     const int g0 = gb[gi];
     Dims dg = make_dims(c, gb[gi + 1] - g0);
@@ -499,9 +482,8 @@ int32_t madakv_allocate(madakv_handle* h, int32_t layer0, int32_t n,
   if (r != MADAKV_OK) return r;
   if (bad_ptr(stats, 4) || bad_ptr(n_mod, 4) || bad_ptr(budgets, 4)) return MADAKV_ERR_INVALID_ARG;
   Dims dm = make_dims(h->cfg, n);
-  hipError_t e = cleared_first(h, reinterpret_cast<hipStream_t>(stream));
-  if (e == hipSuccess) e = launch_allocate(dm, h->cfg, layer0, stats, n_mod, budgets, h->d_state, reinterpret_cast<hipStream_t>(stream));
-  return hip_fail(h, e);
+  return hip_fail(h, launch_allocate(dm, h->cfg, layer0, stats, n_mod, budgets, h->d_state,
+                                     reinterpret_cast<hipStream_t>(stream)));
 }
 
 int32_t madakv_select_gather(madakv_handle* h, int32_t layer0, int32_t n,
@@ -531,8 +513,8 @@ int32_t madakv_select_gather(madakv_handle* h, int32_t layer0, int32_t n,
   const bool overlap = ngroups > 1;
   const size_t es = c.dtype == MADAKV_BF16 ? 2 : 4;
   const size_t M = (size_t)c.n_modalities;
-  hipError_t e = cleared_first(h, st);
-  if (overlap && e == hipSuccess) {
+  hipError_t e = hipSuccess;
+  if (overlap) {
     e = hipEventRecord(h->ev_fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(h->side, h->ev_fork, 0);
   }
@@ -584,7 +566,7 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
   const size_t es = c.dtype == MADAKV_BF16 ? 2 : 4;
   const long long region = region_tokens(c);
   const size_t M = (size_t)c.n_modalities;
-  hipError_t e = cleared_first(h, st);
+  hipError_t e = hipSuccess;
   // Caller's stream: sweeps of group 0, sweeps of group 1, gather of group 0, sweeps of group 2, gather
   // of group 1, ..., gather of the last group.  Side stream: statistics, allocation, segment layout and
   // selection of a group as soon as its sweeps are done.  Only group 0's run beside sweeps (which they
@@ -713,7 +695,7 @@ int32_t madakv_reevict(madakv_handle* h, int32_t layer0, int32_t n,
   int32_t* sel = reinterpret_cast<int32_t*>(wsb + w.sel);
   uint8_t* rowmod = reinterpret_cast<uint8_t*>(wsb + w.rowmod);
   const size_t es = c.dtype == MADAKV_BF16 ? 2 : 4;
-  hipError_t e = cleared_first(h, st);
+  hipError_t e = hipSuccess;
   // paged cache: the kernels below work on a linear copy of the call's heads
   void* k_work = k_c; void* v_work = v_c; int32_t* idx_work = kept_idx; const int64_t* off_work = kv_off;
   const long long cache_rows = region_tokens(c) * c.batch;

@@ -741,3 +741,47 @@ def test_fp32_scores_by_size(kw):
     torch.cuda.synchronize()
     assert torch.equal(one, eng.psi)
     eng.close()
+
+
+@pytest.mark.parametrize("kw", [dict(ctx_len=5000, budget=600), dict(ctx_len=66000, budget=1500, n_layers=1), dict(ctx_len=3000, budget=300, page_rows=16)],
+                         ids=lambda kw: f"L{kw['ctx_len']}")
+def test_first_call_is_captured(kw):
+    """A handle's first work is captured on a stream that waits for nobody and replayed while the null stream still has in front
+    of it what it had when the handle was made: eviction (chunks that meet in the handle's words and records) and decode over
+    several pieces (the handle's counters).  Every replay against the same calls made eagerly, bit for bit."""
+    paged = kw.get("page_rows", 0)
+    kw = {x: y for x, y in kw.items() if x != "page_rows"}
+    wl = workload("captured", **dict(dict(n_layers=2, head_dim=128, n_q_heads=4, n_kv_heads=2, window=16), **kw))
+    NL = wl.n_layers
+    q, k, v, mask, masks = PU.make_inputs(wl, DEV)
+    dq, dk, dv = (torch.randn(NL, 1, h, wl.head_dim, device=DEV).to(torch.bfloat16) for h in (wl.n_q_heads, wl.n_kv_heads, wl.n_kv_heads))
+    outs = [torch.full((NL, 1, wl.n_q_heads, wl.head_dim), float("nan"), device=DEV) for _ in range(2)]
+
+    def calls(eng, out):
+        eng.evict(0, NL, q, k, v, mask)
+        for l in range(NL):
+            eng.decode_attn(l, 1, dq[l:l + 1], dk[l:l + 1], dv[l:l + 1], out[l:l + 1])
+
+    eager = engine(wl, page_rows=paged)
+    calls(eager, outs[0])
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    say(f"captured first call {kw}")
+    torch.cuda._sleep(20_000_000)
+    eng = engine(wl, page_rows=paged)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        calls(eng, outs[1])
+        graph.capture_end()
+    for replay in range(3):
+        with torch.cuda.stream(side):
+            graph.replay()
+        side.synchronize()
+        for name in ("psi", "psi_pool", "stats", "budgets", "kv_len", "kv_off"):
+            assert torch.equal(getattr(eng, name), getattr(eager, name)), (replay, name)
+        assert torch.equal(outs[0], outs[1]), replay
+        outs[1].fill_(float("nan"))
+        torch.cuda.synchronize()
+    del graph
+    eng.close(); eager.close()
