@@ -68,7 +68,7 @@ struct AllocArgs;
 hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_win, const void* k, const float* row_lse,
                         float* psi, void* ws, Exchange& x, hipStream_t st);
 size_t xchg_layer_words(const madakv_config& c, const Dims& one);
-void launch_xchg_clear(unsigned long long* words, size_t n, hipStream_t st);
+hipError_t launch_xchg_clear(unsigned long long* words, size_t n, hipStream_t st);
 // Long heads on few heads: statistics and selection give every 16384-candidate chunk of a head a workgroup of its own, and
 // the chunks of a head meet in a record of split_head_bytes (owned by the handle); split_chunks = chunks per head then, 0
 // otherwise.

@@ -34,7 +34,7 @@ struct madakv_handle {
   hipStream_t maxlen_stream;
   unsigned long long* xchg;        // [n_layers][xchg_words] exchange words of the scoring kernels, XCHG_EMPTY between calls
   size_t xchg_words;
-  bool xchg_used;                  // words may have been left behind (a launch failed): cleared before they are used again
+  bool xchg_left;                  // a call has left words behind and they could not be emptied: done in front of the next scores
   Meet meet;                       // where the pieces of a head meet in decode
   // Side stream and events for the overlap of the bandwidth-bound kernels (score sweeps, gather)
   // with the latency-bound per-head kernels (statistics, selection) inside one call.  The side
@@ -131,12 +131,22 @@ int32_t validate(const madakv_config& c) {
   return MADAKV_OK;
 }
 
-// The exchange words of the layers from `layer` on, clean.  A caller sets xchg_used before it launches a scoring kernel and takes
-// it back when the statistics kernel that empties the words is on its way too.
-Exchange exchange_of(madakv_handle* h, int layer, hipStream_t st) {
-  if (h->xchg_used) launch_xchg_clear(h->xchg, h->cfg.n_layers * h->xchg_words, st);
-  h->xchg_used = false;
-  return Exchange{h->xchg + (size_t)layer * h->xchg_words, 0};
+// What is launched on this stream runs later, as often as its graph is replayed.
+bool replayed_later(hipStream_t st) {
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone;
+}
+
+// All exchange words emptied.  (While the stream is captured nothing has happened yet, so the next call empties them again.)
+hipError_t empty_exchange(madakv_handle* h, hipStream_t st) {
+  const hipError_t e = launch_xchg_clear(h->xchg, h->cfg.n_layers * h->xchg_words, st);
+  h->xchg_left = e != hipSuccess || replayed_later(st);
+  return e;
+}
+// The exchange words of the layers from `layer` on, empty; the statistics kernel behind the scores empties them for the next call.
+hipError_t exchange_of(madakv_handle* h, int layer, hipStream_t st, Exchange& x) {
+  x = Exchange{h->xchg + (size_t)layer * h->xchg_words, 0};
+  return h->xchg_left ? empty_exchange(h, st) : hipSuccess;
 }
 
 void destroy_side(madakv_handle* h) {
@@ -275,10 +285,7 @@ int32_t decode_impl(madakv_handle* h, int32_t layer0, int32_t n,
   Dims dm = make_dims(h->cfg, n);
   // Under graph capture the launch is sized once and replayed while the heads grow: the grid (and the share of the
   // workspace) then covers all the rows the segments have room for.
-  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  const bool replayed = hipStreamIsCapturing(reinterpret_cast<hipStream_t>(stream), &capturing) != hipSuccess ||
-                        capturing != hipStreamCaptureStatusNone;
-  const int longest = longest_rows(h, layer0, n, replayed);
+  const int longest = longest_rows(h, layer0, n, replayed_later(reinterpret_cast<hipStream_t>(stream)));
   // what each entry point has always asked for or refused (the kernels use the handle's own memory)
   if (ws_bytes == NO_WORKSPACE ? decode_ws_bytes_for(dm, h->cfg, longest) > MADAKV_STATIC_SCRATCH_BYTES : ws_bytes < decode_ws_bytes(dm, h->cfg))
     return MADAKV_ERR_WORKSPACE_TOO_SMALL;
@@ -312,7 +319,7 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   for (int g = 0; g < MAX_GROUPS; ++g) { h->ev_grp[g] = nullptr; h->ev_sel[g] = nullptr; }
   h->appended.assign(cfg->n_layers, 0);
   h->gen_base.assign(cfg->n_layers, 0);
-  h->xchg = nullptr; h->xchg_words = 0; h->xchg_used = false;
+  h->xchg = nullptr; h->xchg_words = 0; h->xchg_left = false;
   h->meet = Meet{}; h->d_page_tbl = nullptr;
   h->d_split = nullptr; h->split_bytes = 0;
   hipError_t e = hipGetDevice(&h->device);
@@ -420,8 +427,9 @@ static int32_t score_impl(madakv_handle* h, int32_t layer0, int32_t n,
     float* psi_g = psi + lb * c.n_kv_heads * (size_t)c.ctx_len;
     float* pool_g = psi_pool + lb * c.n_kv_heads * (size_t)(c.ctx_len - c.window);
     const float* lse_g = row_lse ? row_lse + lb * c.n_q_heads * c.window : nullptr;
-    Exchange x = exchange_of(h, layer0 + g0, st);
-    h->xchg_used = true;
+    Exchange x;
+    e = exchange_of(h, layer0 + g0, st, x);
+    if (e != hipSuccess) break;
     if (window_attn) {
       const size_t oes = c.out_fp32 ? 4 : es;
       e = launch_window_attn(dg, c, qg, kg, static_cast<const char*>(v) + lb * c.n_kv_heads * (size_t)c.ctx_len * c.head_dim * es,
@@ -439,7 +447,7 @@ static int32_t score_impl(madakv_handle* h, int32_t layer0, int32_t n,
     if (e == hipSuccess)
       e = launch_stats(dg, c, psi_g, mask, pool_g, static_cast<char*>(stats) + lb * c.n_kv_heads * 8 * (size_t)c.n_modalities,
                        g0 == 0 ? n_mod : nullptr, x, ss, h->d_split, h->split_bytes);
-    h->xchg_used = e != hipSuccess;
+    if (e != hipSuccess) (void)empty_exchange(h, st);      // (at once: a graph captured before has no clear in it)
   }
   if (overlap) e = join_side(h, st, e);
   return hip_fail(h, e);
@@ -593,8 +601,9 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
     char* stats_g = static_cast<char*>(stats) + heads0 * 8 * M;
     int32_t* bud_g = budgets + heads0 * M;
     char* ws_g = static_cast<char*>(select_ws) + sel_slice * gi;
-    Exchange x = exchange_of(h, layer0 + g0, st);
-    h->xchg_used = true;
+    Exchange x;
+    e = exchange_of(h, layer0 + g0, st, x);
+    if (e != hipSuccess) break;
     e = launch_score(dg, c, qg, kg, nullptr, psi_g, score_ws, x, st);
     hipStream_t ss = st;
     if (overlap && e == hipSuccess) {
@@ -603,7 +612,7 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
       ss = h->side;
     }
     if (e == hipSuccess) e = launch_stats(dg, c, psi_g, mask, pool_g, stats_g, g0 == 0 ? n_mod : nullptr, x, ss, h->d_split, h->split_bytes);
-    h->xchg_used = e != hipSuccess;
+    if (e != hipSuccess) (void)empty_exchange(h, st);      // (at once: a graph captured before has no clear in it)
     const AllocArgs alloc = alloc_args(dg, c, layer0 + g0, stats_g, n_mod, bud_g, h->d_state);
     if (e == hipSuccess) e = launch_offsets(dg, c, layer0 + g0, bud_g, kv_off + heads0, kv_len + heads0, len1_of(h, layer0 + g0), h->d_state + c.batch,
                                             h->d_maxlen + (size_t)(layer0 + g0) * c.batch, ws_g, make_paging(h), blocks_per_batch(c, ng), ss, &alloc);

@@ -2135,8 +2135,9 @@ size_t xchg_layer_words(const madakv_config& c, const Dims& one) {
   if (window_attn_supported(one, c) && !win_one_pass(one)) n = std::max(n, win_xchg_bytes(one));
   return n / 8;
 }
-void launch_xchg_clear(unsigned long long* words, size_t n, hipStream_t st) {
+hipError_t launch_xchg_clear(unsigned long long* words, size_t n, hipStream_t st) {
   if (n) hipLaunchKernelGGL(score_xchg_init_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, words, (long long)n);
+  return hipGetLastError();
 }
 
 hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_win, const void* k, const float* row_lse,

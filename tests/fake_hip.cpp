@@ -1,6 +1,7 @@
 // Stands in for the HIP runtime under the host side of libmadakv.so, so that what a call allocates, clears, launches and
 // waits for can be looked at without a GPU: every function the library imports, none of which does anything but leave a line
 // in a log.  Device memory is host memory that nobody touches.  Loaded before the library with its symbols global.
+#include <algorithm>
 #include <cstddef>
 #include <cstdio>
 #include <cstdlib>
@@ -14,7 +15,7 @@ struct Launch { Dim3 grid, block; size_t lds; void* stream; };
 std::string text;                    // the log
 std::map<const void*, std::string> names;
 Launch pushed;
-std::string failing;                 // launches of kernels whose name contains this fail
+std::string failing;                 // launches of kernels whose name contains one of these parts, separated by |, fail
 void* capturing = nullptr;           // the stream under capture
 int last_error = 0;
 long made = 0;                       // streams and events
@@ -24,6 +25,14 @@ template <typename... A> void note(const char* f, A... a) {
   snprintf(line, sizeof line, f, a...);
   text += line;
   text += '\n';
+}
+bool fails(const std::string& name) {
+  for (size_t i = 0; i < failing.size();) {
+    const size_t j = std::min(failing.find('|', i), failing.size());
+    if (name.find(failing.substr(i, j - i)) != std::string::npos) return true;
+    i = j + 1;
+  }
+  return false;
 }
 void* next_object() { return reinterpret_cast<void*>(0x1000 + 16 * ++made); }
 }  // namespace
@@ -58,7 +67,7 @@ int hipEventSynchronize(void*) { return 0; }
 int hipFuncSetAttribute(const void*, int, int) { return 0; }
 int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t lds, void* st) {
   const std::string& name = names[f];
-  if (!failing.empty() && name.find(failing) != std::string::npos) { last_error = 1; note("failed %s", name.c_str()); return 1; }
+  if (fails(name)) { last_error = 1; note("failed %s", name.c_str()); return 1; }
   // the first argument's leading 256 bytes: the kernels take one struct, which starts with its pointers
   std::string words;
   for (int i = 0; args && i < 32; ++i) {

@@ -84,3 +84,52 @@ def test_creation_leaves_no_clear_behind(runtime):
         print("ok")
         """, good(), good(ctx_len=131072, window=64, budget=4096), good(page_rows=16), good(n_layers=28, n_q_heads=28, n_kv_heads=4))
     assert out.strip() == "ok"
+
+
+def test_exchange_words_after_a_failed_launch(runtime):
+    """The words in which the workgroups of a head exchange row statistics are empty when a call begins, also after one whose
+    statistics (which empty them) could not be launched: they are emptied at once, so that a graph that was captured before
+    finds them so; if that fails too, in front of the next scores, which are not launched without it.  A clear that is only
+    captured has not happened yet."""
+    body = """
+        h = create(sys.argv[3])
+        NL = 8
+        s, s2 = 0x77000, 0x88000
+        def score(st):
+            return lib.madakv_score(h, I(0), I(NL), P(T().p), P(T().p), P(T().p), P(T().p), P(T().p), P(T().p), P(T().p), P(T().p), Z(1 << 30), P(st))
+        def evict(st):
+            t = [P(T().p) for _ in range(14)]
+            return lib.madakv_evict(h, I(0), I(NL), *t, P(T().p), Z(1 << 30), P(T().p), Z(1 << 30), P(st))
+        def kinds():
+            what = dict(clear="xchg_init", score="score_fused")
+            return [(x.kind, next((w for w in what if what[w] in str(x)), ""), x.rest[0]) for x in log() if x.kind in ("launch", "failed")]
+        launched = lambda k, what: [x for x in k if x[0] == "launch" and x[1] == what]
+        log()
+        for call in (score, evict):
+            assert call(s) == 0
+            assert not launched(kinds(), "clear")                       # nothing was left behind
+            fake.fake_fail(b"stats_kernel")
+            assert call(s) == -6
+            k = kinds()
+            last = max(i for i, x in enumerate(k) if x[:2] == ("launch", "score"))
+            clears = [i for i, x in enumerate(k) if x[:2] == ("launch", "clear")]
+            assert clears and clears[-1] > last and k[clears[-1]][2] == hex(s), k
+            fake.fake_fail(b"")
+            assert call(s2) == 0 and not launched(kinds(), "clear")
+        # neither the statistics nor the clear behind them
+        fake.fake_fail(b"stats_kernel|xchg_init")
+        assert score(s) == -6; kinds()
+        assert score(s) == -6
+        assert not launched(kinds(), "score")
+        fake.fake_fail(b"")
+        fake.fake_capture(P(s))
+        assert score(s) == 0
+        assert kinds()[0][1] == "clear"
+        fake.fake_capture(P(0))
+        assert score(s) == 0
+        assert kinds()[0][1] == "clear"
+        assert score(s) == 0 and not launched(kinds(), "clear")
+        print("ok")
+        """
+    cfg = good(n_layers=8, ctx_len=5000, budget=600)
+    assert scenario(runtime, body, cfg).strip() == "ok"
