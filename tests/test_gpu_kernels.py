@@ -600,7 +600,7 @@ def test_calls_use_the_current_stream(monkeypatch):
                          ids=lambda kw: "_".join(f"{k}{v}" for k, v in kw.items()))
 def test_decode_pieces_that_come_into_being(kw):
     """Heads that grow into pieces which held nothing before, with many workgroups that only arrive (room for 700 appended
-    rows): two layers in turn, two steps on two streams, calls that append nothing in between; lengths after every call and the
+    rows): two layers in turn, two steps on two streams one behind the other, calls that append nothing in between; lengths after every call and the
     last output against a 64-bit attention (bound: that of test_decode_pieces)."""
     lens = [255, 256, 511, 127, 384]
     args = dict(dict(n_layers=2, batch=1, window=8, dtype="bf16", pool_k=1, ctx_len=1200, budget=400, max_new_tokens=700, out_fp32=1), **kw)
@@ -618,6 +618,7 @@ def test_decode_pieces_that_come_into_being(kw):
         say(f"growing pieces {kw} step {step}")
         for l in (0, 1):
             with torch.cuda.stream(side[l] if step >= 2 else torch.cuda.current_stream()):
+                torch.cuda.current_stream().wait_stream(side[1 - l])          # calls on one handle do not overlap
                 eng.decode_attn(l, 1, *rows[l], outs[l])
         torch.cuda.synchronize()
         assert eng.kv_len.view(-1).tolist() == [n + step + 1 for n in lens + lens]
