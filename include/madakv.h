@@ -39,11 +39,13 @@
  *   - Arguments are validated on the host before anything is enqueued.  Errors
  *     found there leave all outputs untouched.
  *   - The handle belongs to the HIP device that was current in madakv_create; that device must
- *     be current in every later call on it.  It owns device memory: a few KB of carry state (layer
- *     recurrence, cache cursors), the partial results of decode's pieces (1-14% of the reduced cache with
- *     hcc_rho = 2; every layer has its own), with a paged cache its page table and for contexts of
- *     four or more 16384-token chunks on at most 128 heads per layer a few MB of histograms that
- *     the per-head statistics and selection kernels share between launches; and a little pinned
+ *     be current in every later call on it.  It owns device memory: carry state (layer recurrence, cache
+ *     cursors), per head of the model up to 516 bytes in which decode's pieces count themselves, the words in which the
+ *     scoring kernels exchange row statistics (per head up to about 1 byte per key of the prompt with G * W <= 64, up to 4.3
+ *     beyond, or less than 1 MB in all), up to MADAKV_STATIC_SCRATCH_BYTES for madakv_decode_attn_static, with a paged cache
+ *     its page table, and for contexts of four or more 16384-token chunks on at most 128 heads per layer 25 to 72 KB per
+ *     chunk of up to 128 heads for the lists and histograms that the per-head statistics and selection kernels share
+ *     between launches; and a little pinned
  *     host memory, one extra stream of default priority and a few events.  Calls on one handle
  *     must not overlap, a graph that holds captured calls is not replayed after madakv_destroy, and a handle's
  *     lengths are those of one cache: a second cache that is evicted while the first is still decoded has a handle of its own.
@@ -264,8 +266,8 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
  *   kv_len   [n, B, H]        in/out: the array madakv_select_gather filled (the library sizes
  *                              its launch from the lengths it produced); incremented by the append
  *   out      [n, B, Hq, d]    float if out_fp32 else dtype
- *   ws, ws_bytes               at least what madakv_workspace_bytes reports (checked; the partial results now go
- *                              through the handle's own memory)
+ *   ws, ws_bytes               at least what madakv_workspace_bytes reports; the partial results of heads that are cut
+ *                              into several pieces go through it
  * INVALID_ARG if a layer in the range has already appended max_new_tokens rows. */
 int32_t madakv_decode_attn(madakv_handle* h, int32_t layer0, int32_t n,
                            const void* q, const void* k_new, const void* v_new,
@@ -319,10 +321,10 @@ int32_t madakv_page_table(const madakv_handle* h, const int32_t** table, int32_t
 
 /* madakv_decode_attn for callers that cannot allocate device memory and so have no workspace to
  * pass: code running under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  Same arguments, kernels and results as madakv_decode_attn, without ws.  The call allocates and frees
- * nothing.
- *   - MADAKV_ERR_WORKSPACE_TOO_SMALL if the pieces of this launch, cut as below, would take more than
- *     MADAKV_STATIC_SCRATCH_BYTES: (heads in the call) * (chunks of the longest head) * G * (head_dim + 2) * 4 bytes, with
+ * hipMalloc.  Same arguments, kernels and results as madakv_decode_attn, without ws: the partial results go to a
+ * scratch array of the handle's, of at most MADAKV_STATIC_SCRATCH_BYTES.  The call allocates and frees nothing.
+ *   - MADAKV_ERR_WORKSPACE_TOO_SMALL if that might not hold what this launch needs, taken as
+ *     (heads in the call) * (chunks of the longest head) * G * (head_dim + 2) * 4 bytes, with
  *     chunks of 256 .. 1024 rows (512 once the call covers >= 1024 heads); the longest head is
  *     taken from what the eviction produced once that has reached the host, from ctx_len +
  *     max_new_tokens before.  One layer of 128 heads of up to 16K rows fits.  Nothing is

@@ -37,27 +37,25 @@ long long region_tokens_of(const madakv_config& c);     // rows of the reduced c
 long long init_limit_of(const madakv_config& c);
 int page_table_entries(const madakv_config& c);
 
-// Where the pieces a decode call cuts a head into meet (decode.hip); owned by the handle.
+// How the pieces a decode call cuts a head into meet (decode.hip); owned by the handle.  Their partial results are in the
+// call's workspace.
 constexpr int MEET_WAVES = 4;            // counters of a head of grouped queries (a single query head: one)
 constexpr int MEET_COUNT_STRIDE = 32;    // a counter has 128 bytes to itself
-constexpr int MEET_ROOM = 32;            // records behind the last head's that may be read, for nothing
 struct Meet {
-  float* acc;               // [n_layers * B * H][slots][G][d] partial results of the pieces
-  float* ml;                // [n_layers * B * H][slots][G][2] their (max, sum)
   uint32_t* count;          // [n_layers * B * H][MEET_WAVES if G > 1][MEET_COUNT_STRIDE] arrivals, zero between calls
   int32_t* len1;            // [n_layers * B * H] 1 + the rows the eviction left each head, 0 before the first one
-  int slots;                // most pieces of a head in any call
 };
 
 struct ScorePlan { int nsplit; int chunk; int mpad; int group_heads; };
 struct DecodePlan { int chunk_rows; int max_chunks; int grid_chunks; };   // rows per piece of a head, most pieces of a head, pieces in the grid
 
 ScorePlan score_plan(const Dims& dm, int dtype);
-DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows, int slots);
+DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows);
 size_t score_ws_bytes(const Dims& dm, int dtype);
 size_t select_ws_bytes(const Dims& dm, const madakv_config& c);
 size_t decode_ws_bytes(const Dims& dm, const madakv_config& c);                             // worst case over head lengths
 size_t decode_ws_bytes_for(const Dims& dm, const madakv_config& c, int longest_rows);     // for a known longest head
+size_t decode_part_bytes(const Dims& dm, const madakv_config& c, int longest_rows);       // what such a launch uses of it
 
 // The words in which the workgroups of a head exchange their row statistics (score.hip): where those of the call's first layer are,
 // and how many per head a launch has used (0: none), for the statistics kernel to empty.
@@ -114,7 +112,7 @@ hipError_t launch_gather(const Dims& dm, const madakv_config& c, int li0, int nl
                          int blocks_per_batch, int grid_blocks, hipStream_t st, bool leave_room = false);
 hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, const void* k_new,
                          const void* v_new, void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
-                         void* out, const Meet& meet, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st);
+                         void* out, const Meet& meet, void* ws, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st);
 
 constexpr int GATHER_ROWS = 64;   // rows of the reduced cache one gather workgroup fills
 

@@ -45,7 +45,10 @@ struct DecodeArgs {
   int B, H, G, chunk_rows, out_fp32, has_new;
   int max_chunks;       // most pieces a head is cut into (head_chunk_rows)
   int max_new;          // rows a segment has room for behind those of the eviction
-  Meet meet;            // where the pieces of a head meet
+  float* part;          // [heads][slots][G][d] partial results of the pieces of the call's heads
+  float* part_ml;       // [heads][slots][G][2] their (max, sum)
+  int slots;            // most pieces of a head
+  Meet meet;            // how they meet
   long long capacity;   // rows in k_c / v_c
   // paged cache (page_rows > 0): see struct Paging
   int page_rows, page_shift, tbl_entries;
@@ -265,10 +268,11 @@ __device__ __forceinline__ void store_out4(const DecodeArgs& a, long long o, flo
 // has; those move 8 bytes at most, and two per lane are twice the requests: 16 partial results of 7 query heads took 1.9 us
 // to read instead of 1.3).
 constexpr int AGENT = 16;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t agent_buffer(void* p) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7fffffff, 0x00020000); }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t agent_buffer(void* p, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00020000); }
+constexpr int NOWHERE = 0x7ffffff0;      // past the end of any of them: a read gives zeros and touches nothing
 
 // The NW waves' (max, sum, acc) of a piece merged in wave order: the output if the head is this one piece.  Otherwise the
-// piece's partial result goes to the head's record, and the last workgroup to arrive at the head's counter merges them all,
+// piece's partial result goes to the head's record in the workspace, and the last workgroup to arrive at the head's counter merges them all,
 // in piece order, and stores the head's new length (everybody has read the old one).  Behind the barrier every wave works
 // for itself, with counters of its own: 64 / (D / 4) query heads per wave, four elements per lane (a single query head:
 // the first wave alone, whose lanes share the pieces); a wave has its stores acknowledged, arrives, and leaves unless it is
@@ -283,10 +287,10 @@ __device__ __forceinline__ void finish_piece(const DecodeArgs& a, long long hidx
   const bool act = GT == 1 ? kp == 0 : g < a.G;
   const int pieces = len <= rows ? 1 : (len + rows - 1) / rows;
   const long long o = (hidx * a.G + g) * D + 4 * t;
-  // records of a head: [pieces][G][D] accumulated elements, then [pieces][G] (max, sum)
-  const long long head = a.head0 + hidx;
-  const __amdgpu_buffer_rsrc_t rec = agent_buffer(a.meet.acc + head * a.meet.slots * a.G * D);
-  const __amdgpu_buffer_rsrc_t rec_ml = agent_buffer(a.meet.ml + head * a.meet.slots * a.G * 2);
+  // records of a head: [slots][G][D] accumulated elements, [slots][G] (max, sum)
+  const int step = a.G * D * 4, step_ml = a.G * 8;
+  const __amdgpu_buffer_rsrc_t rec = agent_buffer(a.part + hidx * a.slots * a.G * D, a.slots * step);
+  const __amdgpu_buffer_rsrc_t rec_ml = agent_buffer(a.part_ml + hidx * a.slots * a.G * 2, a.slots * step_ml);
   if (chunk < pieces && act) {
     float mx = DNEG_BIG, ls = 0.f;
     float4 av = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -302,11 +306,12 @@ __device__ __forceinline__ void finish_piece(const DecodeArgs& a, long long hidx
     if (pieces == 1) {
       store_out4<T>(a, o, av, ls);
     } else {
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(du32x4_t, av), rec, (g * D + 4 * t) * 4, chunk * a.G * D * 4, AGENT);
-      if (t == 0) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(du32x2_t, make_float2(mx, ls)), rec_ml, g * 8, chunk * a.G * 8, AGENT);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(du32x4_t, av), rec, (g * D + 4 * t) * 4, chunk * step, AGENT);
+      if (t == 0) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(du32x2_t, make_float2(mx, ls)), rec_ml, g * 8, chunk * step_ml, AGENT);
     }
   }
   if (arrive > 1) {
+    const long long head = a.head0 + hidx;
     uint32_t* count = a.meet.count + (GT == 1 ? head : head * MEET_WAVES + wave) * MEET_COUNT_STRIDE;
     uint32_t arrived = 0u;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the wave's stores are where everybody sees them
@@ -317,21 +322,20 @@ __device__ __forceinline__ void finish_piece(const DecodeArgs& a, long long hidx
     if (pieces > 1) {
       float m = DNEG_BIG, ls = 0.f, av[4] = {0.f, 0.f, 0.f, 0.f};
       const int gg = act || GT == 1 ? g : 0;                   // (lanes without a query head read along)
+      const int at = ((kp + gg) * D + 4 * t) * 4, at_ml = (kp + gg) * 8;       // (kp > 0: a single query head)
       for (int c0 = 0; c0 < pieces; c0 += KP * MB) {
-        // (past the last piece: slots of the next head, or the room behind the last one's; masked)
         float4 x[MB]; float2 ml[MB];
 #pragma unroll
         for (int j = 0; j < MB; ++j) {
-          ml[j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rec_ml, (kp + gg) * 8, (c0 + j * KP) * a.G * 8, AGENT));
-          x[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rec, ((kp + gg) * D + 4 * t) * 4, (c0 + j * KP) * a.G * D * 4, AGENT));
+          const int c = c0 + j * KP;
+          const bool mine = c + kp < pieces;
+          ml[j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rec_ml, mine ? at_ml + c * step_ml : NOWHERE, 0, AGENT));
+          x[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rec, mine ? at + c * step : NOWHERE, 0, AGENT));
         }
         float bm = m;
 #pragma unroll
         for (int j = 0; j < MB; ++j) {
-          const bool mine = c0 + j * KP + kp < pieces;
-          ml[j].x = mine ? ml[j].x : 2.f * DNEG_BIG;          // weight 0
-          ml[j].y = mine ? ml[j].y : 0.f;
-          if (!mine) x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+          ml[j].x = c0 + j * KP + kp < pieces ? ml[j].x : 2.f * DNEG_BIG;          // weight 0, of zeros
           bm = fmaxf(bm, ml[j].x);
         }
         const float sc = weight_of(m - bm);
@@ -733,8 +737,9 @@ static int plan_longest(const madakv_config& c, int longest_rows) { return std::
 // whatever hcc_rho is, 128 heads of which 8 hold half of the rows, 512 on average, took 21.3 us instead of 14.7, 512 heads of 256,
 // 16 with half of the rows, 34 instead of 21.  Neither depends on what the host knows of the
 // longest head, so that a call's result does not either; only the grid, at most max_chunks pieces, shrinks when it is known.
-constexpr int SHORT_PIECES = 2000;             // most 128-row pieces of a launch, some eight per compute unit
-DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows, int slots) {
+constexpr int SHORT_PIECES = 2000;             // most 128-row pieces of a launch: what the static scratch holds of 8 queries x 128 dims
+static_assert((size_t)SHORT_PIECES * 8 * (128 + 2) * sizeof(float) <= MADAKV_STATIC_SCRATCH_BYTES, "short pieces must fit the static scratch");
+DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows) {
   DecodePlan p;
   const int worst = plan_longest(c, c.ctx_len + c.max_new_tokens);
   const int base = plan_chunk_rows(dm, c);
@@ -745,14 +750,21 @@ DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows,
   if (short_pieces) p.chunk_rows = 128;
   long long want = std::max<long long>((std::max(2, c.hcc_rho) * typical + p.chunk_rows - 1) / p.chunk_rows, 512 / dm.heads);
   if (short_pieces) want = std::min<long long>(want, SHORT_PIECES / dm.heads);
-  p.max_chunks = (int)std::max<long long>(1, std::min({(long long)(worst + base - 1) / base, std::max<long long>(2, want), (long long)slots}));
+  // never more partial results than a worst-case head cut into `base` rows has: what decode_ws_bytes is made for
+  p.max_chunks = (int)std::min<long long>((worst + base - 1) / base, std::max<long long>(2, want));
   p.grid_chunks = std::min(p.max_chunks, (plan_longest(c, longest_rows) + p.chunk_rows - 1) / p.chunk_rows);
   // every head is known to be one piece: nobody has to arrive anywhere
   if (p.grid_chunks == 1) p.max_chunks = 1;
   return p;
 }
 
-// what a caller's workspace has been asked to hold since before the pieces met in the handle's memory
+// The partial results of the heads' pieces, as many per head as the longest one has.  (decode_part_bytes: those of a launch, in
+// pieces of its own size; never more than decode_ws_bytes_for of the same head, since max_chunks is not, but for short pieces of
+// fewer rows than `base`, of which there are SHORT_PIECES.)
+size_t decode_part_bytes(const Dims& dm, const madakv_config& c, int longest_rows) {
+  const DecodePlan p = decode_plan(dm, c, longest_rows);
+  return p.max_chunks == 1 ? 0 : (size_t)dm.heads * p.grid_chunks * dm.G * (dm.d + 2) * sizeof(float);
+}
 size_t decode_ws_bytes_for(const Dims& dm, const madakv_config& c, int longest_rows) {
   const int base = plan_chunk_rows(dm, c);
   const int chunks = (plan_longest(c, longest_rows) + base - 1) / base;
@@ -787,7 +799,7 @@ static hipError_t launch_decode_p(const Dims& dm, DecodeArgs& a, int grid_chunks
 
 hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, const void* k_new,
                          const void* v_new, void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
-                         void* out, const Meet& meet, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st) {
+                         void* out, const Meet& meet, void* ws, long long capacity_tokens, int longest_rows, const Paging& pg, int layer0, hipStream_t st) {
   DecodeArgs a;
   a.capacity = capacity_tokens;
   a.page_rows = pg.page_rows; a.tbl_entries = pg.entries; a.page_tbl = pg.table; a.pool_top = pg.pool_top;
@@ -797,8 +809,10 @@ hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, 
   a.head0 = (long long)layer0 * dm.B * dm.H;
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.k_c = k_c; a.v_c = v_c; a.kv_off = kv_off; a.kv_len = kv_len;
   a.out = out; a.meet = meet; a.max_new = c.max_new_tokens;
-  DecodePlan p = decode_plan(dm, c, longest_rows, meet.slots);
+  DecodePlan p = decode_plan(dm, c, longest_rows);
   a.B = dm.B; a.H = dm.H; a.G = dm.G; a.chunk_rows = p.chunk_rows; a.max_chunks = p.max_chunks;
+  a.slots = p.grid_chunks;
+  a.part = reinterpret_cast<float*>(ws); a.part_ml = a.part + (long long)dm.heads * a.slots * dm.G * dm.d;
   a.out_fp32 = c.out_fp32; a.has_new = (k_new != nullptr) ? 1 : 0;
   const float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)dm.d);
   a.scale_log2 = scale * 1.4426950408889634f;

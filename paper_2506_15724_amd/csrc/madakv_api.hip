@@ -35,7 +35,8 @@ struct madakv_handle {
   unsigned long long* xchg;        // [n_layers][xchg_words] exchange words of the scoring kernels, XCHG_EMPTY between calls
   size_t xchg_words;
   bool xchg_left;                  // a call has left words behind and they could not be emptied: done in front of the next scores
-  Meet meet;                       // where the pieces of a head meet in decode
+  Meet meet;                       // how the pieces of a head meet in decode
+  void* scratch; size_t scratch_bytes;   // their partial results where the caller has no workspace
   // Side stream and events for the overlap of the bandwidth-bound kernels (score sweeps, gather)
   // with the latency-bound per-head kernels (statistics, selection) inside one call.  The side
   // stream forks from and joins the caller's stream through events; default priority.
@@ -242,31 +243,28 @@ hipError_t join_side(madakv_handle* h, hipStream_t st, hipError_t e) {
 
 constexpr size_t NO_WORKSPACE = ~(size_t)0;
 // The handle's device memory but for d_split, in one allocation that starts with what has to be zero: the carry state, the
-// page table, the counters and lengths of decode's pieces.  Then the partial results of the pieces, as many as a call over any
-// number of layers cuts a head into: a record is under 1% of the rows of a 256-row piece of single queries, 7% of a 128-row
-// piece of eight; together 1-14% of the reduced cache (hcc_rho = 2).
+// page table, the counters and lengths of decode's pieces (132 bytes per head, 516 with grouped queries).  Then the exchange words of the scoring
+// kernels, and the partial results of one madakv_decode_attn_static call, whatever layers it is over.
 hipError_t create_memory(madakv_handle* h) {
   const madakv_config& c = h->cfg;
   Meet& m = h->meet;
-  m.slots = 1;
-  for (int n = 1; n <= c.n_layers; ++n) m.slots = std::max(m.slots, decode_plan(make_dims(c, n), c, c.ctx_len + c.max_new_tokens, 0x7fffffff).max_chunks);
-  const size_t heads = (size_t)c.n_layers * c.batch * c.n_kv_heads, G = c.n_q_heads / c.n_kv_heads, rows = (heads * m.slots + MEET_ROOM) * G;
+  for (int n = 1; n <= c.n_layers; ++n) h->scratch_bytes = std::max(h->scratch_bytes, decode_part_bytes(make_dims(c, n), c, c.ctx_len + c.max_new_tokens));
+  h->scratch_bytes = std::min(h->scratch_bytes, MADAKV_STATIC_SCRATCH_BYTES);
+  const size_t heads = (size_t)c.n_layers * c.batch * c.n_kv_heads, G = c.n_q_heads / c.n_kv_heads;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t table = up(sizeof(long long) * 3 * c.batch), count = table + up(sizeof(int32_t) * heads * page_table_entries(c));
-  const size_t len = count + heads * (G > 1 ? MEET_WAVES : 1) * MEET_COUNT_STRIDE * sizeof(uint32_t), acc = len + up(heads * sizeof(int32_t));
-  const size_t ml = acc + up(rows * c.head_dim * sizeof(float));
+  const size_t len = count + heads * (G > 1 ? MEET_WAVES : 1) * MEET_COUNT_STRIDE * sizeof(uint32_t), xchg = len + up(heads * sizeof(int32_t));
   h->xchg_words = xchg_layer_words(c, make_dims(c, 1));
-  const size_t xchg = up(ml + rows * 2 * sizeof(float)), xbytes = c.n_layers * h->xchg_words * sizeof(unsigned long long);
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&h->d_state), xchg + xbytes);
+  const size_t xbytes = c.n_layers * h->xchg_words * sizeof(unsigned long long), scratch = xchg + up(xbytes);
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&h->d_state), scratch + h->scratch_bytes);
   if (e != hipSuccess) { h->d_state = nullptr; return e; }
   char* p = reinterpret_cast<char*>(h->d_state);
   if (c.page_rows) h->d_page_tbl = reinterpret_cast<int32_t*>(p + table);
   m.count = reinterpret_cast<uint32_t*>(p + count);
   m.len1 = reinterpret_cast<int32_t*>(p + len);
-  m.acc = reinterpret_cast<float*>(p + acc);
-  m.ml = reinterpret_cast<float*>(p + ml);
   h->xchg = reinterpret_cast<unsigned long long*>(p + xchg);
-  e = hipMemsetAsync(p, 0, acc, h->side);
+  h->scratch = p + scratch;
+  e = hipMemsetAsync(p, 0, xchg, h->side);
   if (e == hipSuccess && xbytes) e = hipMemsetAsync(h->xchg, 0xff, xbytes, h->side);
   return e;
 }
@@ -275,7 +273,7 @@ int32_t* len1_of(madakv_handle* h, int layer) { return h->meet.len1 + (size_t)la
 int32_t decode_impl(madakv_handle* h, int32_t layer0, int32_t n,
                     const void* q, const void* k_new, const void* v_new,
                     void* k_c, void* v_c, const int64_t* kv_off, int32_t* kv_len,
-                    void* out, const void* ws, size_t ws_bytes, void* stream) {
+                    void* out, void* ws, size_t ws_bytes, void* stream) {
   int32_t r = check_range(h, layer0, n);
   if (r != MADAKV_OK) return r;
   if (bad_ptr(q) || bad_ptr(k_c) || bad_ptr(v_c) || bad_ptr(kv_off, 8) || bad_ptr(kv_len, 4) || bad_ptr(out) || (ws_bytes != NO_WORKSPACE && bad_ptr(ws)))
@@ -286,14 +284,19 @@ int32_t decode_impl(madakv_handle* h, int32_t layer0, int32_t n,
   // Under graph capture the launch is sized once and replayed while the heads grow: the grid (and the share of the
   // workspace) then covers all the rows the segments have room for.
   const int longest = longest_rows(h, layer0, n, replayed_later(reinterpret_cast<hipStream_t>(stream)));
-  // what each entry point has always asked for or refused (the kernels use the handle's own memory)
-  if (ws_bytes == NO_WORKSPACE ? decode_ws_bytes_for(dm, h->cfg, longest) > MADAKV_STATIC_SCRATCH_BYTES : ws_bytes < decode_ws_bytes(dm, h->cfg))
-    return MADAKV_ERR_WORKSPACE_TOO_SMALL;
+  // a caller's workspace is sized for the worst case; the handle's scratch must hold what this launch uses
+  if (ws_bytes != NO_WORKSPACE) {
+    if (ws_bytes < decode_ws_bytes(dm, h->cfg)) return MADAKV_ERR_WORKSPACE_TOO_SMALL;
+  } else {
+    if (decode_ws_bytes_for(dm, h->cfg, longest) > MADAKV_STATIC_SCRATCH_BYTES || decode_part_bytes(dm, h->cfg, longest) > h->scratch_bytes)
+      return MADAKV_ERR_WORKSPACE_TOO_SMALL;
+    ws = h->scratch;
+  }
   if (k_new) {
     for (int l = layer0; l < layer0 + n; ++l)
       if (h->appended[l] >= h->cfg.max_new_tokens) return MADAKV_ERR_INVALID_ARG;
   }
-  hipError_t e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, h->meet,
+  hipError_t e = launch_decode(dm, h->cfg, q, k_new, v_new, k_c, v_c, kv_off, kv_len, out, h->meet, ws,
                                region_tokens(h->cfg) * h->cfg.batch, longest, make_paging(h), layer0,
                                reinterpret_cast<hipStream_t>(stream));
   if (e == hipSuccess && k_new) for (int l = layer0; l < layer0 + n; ++l) h->appended[l] += 1;
@@ -320,7 +323,7 @@ int32_t madakv_create(const madakv_config* cfg, madakv_handle** out) {
   h->appended.assign(cfg->n_layers, 0);
   h->gen_base.assign(cfg->n_layers, 0);
   h->xchg = nullptr; h->xchg_words = 0; h->xchg_left = false;
-  h->meet = Meet{}; h->d_page_tbl = nullptr;
+  h->meet = Meet{}; h->scratch = nullptr; h->scratch_bytes = 0; h->d_page_tbl = nullptr;
   h->d_split = nullptr; h->split_bytes = 0;
   hipError_t e = hipGetDevice(&h->device);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);

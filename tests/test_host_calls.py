@@ -133,3 +133,55 @@ def test_exchange_words_after_a_failed_launch(runtime):
         """
     cfg = good(n_layers=8, ctx_len=5000, budget=600)
     assert scenario(runtime, body, cfg).strip() == "ok"
+
+
+def configs_of_size():
+    from perf import cases
+    names = [f[0] for f in MB.Config._fields_]
+    for c in cases.listed():
+        kw = {k: v for k, v in c.items() if k in names}
+        yield c["name"], good(**dict(kw, dtype=MB.BF16 if c["dtype"] == "bf16" else MB.FP32, max_new_tokens=c["steps"] + 1))
+    yield "few heads, little kept", good(n_layers=8, n_q_heads=8, n_kv_heads=1, ctx_len=65536, window=32, budget=256, hcc_rho=1024)
+    yield "many heads", good(n_layers=64, batch=2, n_q_heads=64, n_kv_heads=32, ctx_len=8192, budget=512, hcc_rho=64)
+    yield "paged", good(n_layers=4, ctx_len=9000, budget=700, page_rows=32, cache_fp8=1)
+
+
+@pytest.mark.parametrize("cfg", [pytest.param(c, id=n.replace(" ", "_")) for n, c in configs_of_size()])
+def test_where_partial_results_of_decode_go(runtime, cfg):
+    """A launch of madakv_decode_attn leaves the pieces' partial results in the caller's workspace, within what
+    madakv_workspace_bytes reports; one of madakv_decode_attn_static in the handle's scratch, or it is refused.  The handle
+    holds what the header says."""
+    heads = cfg.n_layers * cfg.batch * cfg.n_kv_heads
+    G = cfg.n_q_heads // cfg.n_kv_heads
+    per_key = 1.1 if G * cfg.window <= 64 else 4.4
+    most = (8 << 20) + (1 << 20) + int(heads * (516 + per_key * cfg.ctx_len))
+    if cfg.page_rows:
+        most += heads * 4 * (2 + (cfg.ctx_len + cfg.max_new_tokens) // cfg.page_rows)
+    scenario(runtime, f"""
+        h = create(sys.argv[3])
+        mallocs = [(num(x.rest[0]), int(x.rest[1])) for x in log() if x.kind == "malloc"]
+        assert mallocs[0][1] <= {most}, (mallocs, {most})
+        assert len(mallocs) == 1 or mallocs[1][1] <= 128 * {72 * 1024} * {(cfg.ctx_len + 16383) // 16384}
+        heads1, G, d = {cfg.batch * cfg.n_kv_heads}, {G}, {cfg.head_dim}
+        def launch(static, n):
+            b = Z()
+            assert lib.madakv_workspace_bytes(h, I(n), None, None, C.byref(b)) == 0
+            ws = T(b.value)
+            t = [P(T().p), None, None, *(P(T().p) for _ in range(5))]
+            if static: rc = lib.madakv_decode_attn_static(h, I(0), I(n), *t, P(0))
+            else: rc = lib.madakv_decode_attn(h, I(0), I(n), *t, P(ws.p), b, P(0))
+            if rc == -4 and static: return
+            assert rc == 0
+            (x,) = [x for x in log() if x.kind == "launch" and "decode" in str(x)]
+            grid = [int(g) for g in x.rest[1].split(",")]
+            if grid[1] == 1: return                                  # nothing to leave
+            size = heads1 * n * grid[1] * G * (d + 2) * 4            # as many pieces per head as the grid has
+            lo, hi = (mallocs[0][0], mallocs[0][0] + mallocs[0][1]) if static else (ws.p, ws.p + ws.size)
+            words = [int(w, 16) for w in x.rest[4:]]
+            # the array of partial results and, behind it, that of their (max, sum) pairs
+            found = [w for w in words if lo <= w < hi and w + heads1 * n * grid[1] * G * d * 4 in words]
+            assert len(found) == 1 and found[0] + size <= hi, (found, lo, hi, size)
+        for n in sorted({{1, {min(2, cfg.n_layers)}, {cfg.n_layers}}}):
+            launch(False, n)
+            launch(True, n)
+        """, cfg)

@@ -1,5 +1,5 @@
 """madakv_decode_attn_static (the decode step for callers that cannot allocate: its scratch is an
-array inside the library's device code) against madakv_decode_attn on the same cache, through the
+array of the handle's) against madakv_decode_attn on the same cache, through the
 C ABI: two calls in a row, the second on a smaller input, then an appending call against the
 oracle.  Collected last, so that a failure here hides no other test."""
 import sys
