@@ -41,7 +41,8 @@ struct ScoreArgs {
   int H, G, d, L, W, M, mpad, nsplit, chunk;
   int nmerge;          // chunks whose row statistics sweep 2 still has to merge (1 after score_combine_kernel)
   // one-sweep kernel: row statistics of the head's chunks as (max, sum) pairs in one 64-bit word each,
-  // [heads, fsplit, mpad], all ones = not yet there; status[0] != 0 = a workgroup gave up waiting
+  // [heads, fsplit, mpad], all ones = not yet there; status[0] != 0 = a workgroup gave up waiting.  (In the handle; those of
+  // ragged heads in the workspace.)
   unsigned long long* xchg;
   int subtiles = 0;             // (host) of a wave, fp32
   bool xchg_clean = false;      // (host) its words are XCHG_EMPTY already
@@ -1823,10 +1824,10 @@ static size_t fused_park_bytes(const Dims& dm, int dtype) {
   return n ? ((size_t)dm.heads * n * ns * nrb * 16 * SCORE_THREADS * sizeof(float) + (size_t)dm.heads * fused_mpad(dm) * sizeof(float) + 255) / 256 * 256 : 0;
 }
 size_t score_ws_bytes(const Dims& dm, int dtype) {
-  // the counter of lone workgroups, the row statistics of the two sweeps, the store sink, the exchange array of the
-  // one-sweep kernel, its per-row-block copies of psi when there are more than 64 proxy rows
+  // the counter of lone workgroups, the row statistics of the two sweeps, the store sink, the one-sweep kernel's
+  // per-row-block copies of psi when there are more than 64 proxy rows, its parked chunks
   const size_t part = fused_fits(dm, dtype) && fused_blocks(dm) > 1 ? (size_t)fused_blocks(dm) * dm.heads * dm.L * sizeof(float) : 0;
-  return 256 + rowstat_bytes(dm, dtype) + 256 + xchg_bytes(dm, dtype) + part + fused_park_bytes(dm, dtype);
+  return 256 + rowstat_bytes(dm, dtype) + 256 + part + fused_park_bytes(dm, dtype);
 }
 
 // psi = the row blocks' column sums added in block order (more than 64 proxy rows)
@@ -2018,8 +2019,8 @@ static size_t win_xchg_bytes(const Dims& dm) {
 static size_t win_opart_bytes(const Dims& dm) { return ((size_t)dm.heads * win_blocks(dm) * win_split(dm) * 32 * dm.d * sizeof(float) + 255) / 256 * 256; }
 size_t window_attn_ws_bytes(const Dims& dm, const madakv_config& c) {
   if (!window_attn_supported(dm, c)) return 256;
-  // the counter of lone workgroups, the exchange words, the workgroups' shares of O, the row blocks' shares of psi
-  return 256 + win_xchg_bytes(dm) + win_opart_bytes(dm) + (win_blocks(dm) > 1 ? (size_t)win_blocks(dm) * dm.heads * dm.L * sizeof(float) : 0);
+  // the counter of lone workgroups, the workgroups' shares of O, the row blocks' shares of psi
+  return 256 + win_opart_bytes(dm) + (win_blocks(dm) > 1 ? (size_t)win_blocks(dm) * dm.heads * dm.L * sizeof(float) : 0);
 }
 // More than 64 proxy rows: window_wide_kernel, in one pass for all rows but behind a sweep over K of its own (four launches,
 // one or two workgroups per compute unit, each walking its tiles one after the other), or the kernel above, block by block
@@ -2096,7 +2097,7 @@ hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void
   a.mpad = 32; a.nsplit = 0; a.nmerge = 0; a.chunk = 0; a.head0 = 0;
   const int rb = win_blocks(dm);
   a.rb_count = rb;
-  a.psi_part = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + win_xchg_bytes(dm) + win_opart_bytes(dm));
+  a.psi_part = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + win_opart_bytes(dm));
   a.psi_part_stride = (long long)dm.heads * dm.L;
   a.fsplit = win_split(dm);
   a.xgroups = xchg_groups(a.fsplit); a.xstride = (long long)(a.fsplit + a.xgroups) * 32; a.k_kind = K_BF16;   // (two exchange levels above 64 chunks)
@@ -2105,7 +2106,7 @@ hipError_t launch_window_attn(const Dims& dm, const madakv_config& c, const void
   const float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)dm.d);
   a.scale_log2 = scale * 1.4426950408889634f;
   wa.v = v; wa.lse = row_lse; wa.out = out; wa.out_fp32 = c.out_fp32;
-  wa.opart = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + win_xchg_bytes(dm));
+  wa.opart = reinterpret_cast<float*>(static_cast<char*>(ws) + 256);
   if (win_one_pass(dm)) {
     if (dm.d == 128) launch_win_many_rows<128>(wa, dm, c, st); else launch_win_many_rows<64>(wa, dm, c, st);
     return hipGetLastError();
@@ -2151,7 +2152,7 @@ hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_wi
   a.sink = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype));
   a.xchg = x.words; a.xchg_clean = true;
   a.rb_count = fused_blocks(dm);
-  a.psi_part = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype) + 256 + xchg_bytes(dm, c.dtype));
+  a.psi_part = reinterpret_cast<float*>(static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype) + 256);
   a.psi_part_stride = (long long)dm.heads * dm.L;
   a.fsplit = (!row_lse && use_fused(dm, c.dtype)) ? fused_split(dm, c.dtype) : 0;
   a.nstrag = a.fsplit ? fused_parked_chunks(a.fsplit) : 0;
@@ -2160,7 +2161,7 @@ hipError_t launch_score(const Dims& dm, const madakv_config& c, const void* q_wi
   a.xgroups = xchg_groups(a.fsplit) + a.nstrag; a.xstride = (long long)(a.fsplit + a.xgroups) * fused_mpad(dm);
   a.k_kind = c.dtype == MADAKV_FP32 ? K_F32 : K_BF16;
   {
-    char* pk = static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype) + 256 + xchg_bytes(dm, c.dtype) +
+    char* pk = static_cast<char*>(ws) + 256 + rowstat_bytes(dm, c.dtype) + 256 +
                (fused_fits(dm, c.dtype) && fused_blocks(dm) > 1 ? (size_t)fused_blocks(dm) * dm.heads * dm.L * sizeof(float) : 0);
     a.offs_out = a.nstrag ? reinterpret_cast<float*>(pk) : nullptr;
     a.park = a.nstrag ? reinterpret_cast<float*>(pk) + (size_t)dm.heads * fused_mpad(dm) : nullptr;
