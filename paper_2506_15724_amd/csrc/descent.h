@@ -63,10 +63,18 @@ __device__ __forceinline__ T pick(const T (&x)[N], int m) {              // x[m]
   return r;
 }
 
+// Entries that a workgroup's list has per modality, log2.  About a hundredth of a head's candidates falls into the crossing bin;
+// where they do not fit, another pass over all of them is due: 2048 for heads of more than 32K candidates of two modalities (192
+// heads of 128K: statistics 92 us, selection 99, with 1024 entries 127 and 141; of 64K 51 and 54, with 1024 70 and 54), else 1024 (of 32K
+// 30 and 32 either way), which leaves the workgroup smaller: where it runs beside a gather it has to find room on a compute
+// unit (launch_gather).
+constexpr int LIST_SHIFT_MIN = 10, LIST_SHIFT_MAX = 11;
+inline int list_shift_of(int M, int nc) { return M == 2 && nc > 32768 ? LIST_SHIFT_MAX : LIST_SHIFT_MIN; }
+
 // Few lanes of a wave find something for a list now and then: they leave it in a buffer of the wave's own, which needs no
 // atomic and waits for nothing, and the buffer goes to the list once it holds a wave's worth (push per entry).  All lanes of
 // the wave take part in every call.
-constexpr int WAVE_BUF = 64 + 256;               // entries: a rest, and a group of four of every lane
+constexpr int WAVE_BUF = 64 + 64;                // entries: a rest, and one of every lane
 template <typename E>
 struct WaveBuf {
   E* buf;                                        // this wave's

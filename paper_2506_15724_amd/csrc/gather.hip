@@ -11,7 +11,7 @@
 
 namespace madakv {
 
-constexpr size_t GATHER_ROOM_LDS = 36 * 1024;   // four claims fit the 160 KB of a compute unit, five do not
+constexpr size_t GATHER_ROOM_LDS = 41 * 1024;   // three claims fit the 160 KB of a compute unit, four do not
 
 // native vector type: arrays of it stay in registers (the HIP uint4 struct ends up in scratch)
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
@@ -147,8 +147,11 @@ hipError_t launch_gather(const Dims& dm, const madakv_config& c, int li0, int nl
   dim3 grid(std::min(grid_blocks, blocks_per_batch), dm.B);
   // leave_room: statistics / selection kernels of another layer group run on a second stream meanwhile.
   // Eight of these workgroups fit a compute unit and would keep it full until the grid has drained; the
-  // claim of GATHER_ROOM_LDS bytes of (unused) LDS holds them to four, which costs the copy nothing
-  // (measured: 2 to 8 workgroups per compute unit move the same bytes per second) and lets the others in.
+  // claim of GATHER_ROOM_LDS bytes of (unused) LDS holds them to three and leaves 37 KB: enough for a selection
+  // workgroup (34 KB; statistics, 50 KB, once one of the three has left).  Eviction of 32 layers of 128 heads of 16K in one
+  // call, median us: claims of 36 KB (four, 16 KB left) 4808, 41 KB 4795, 54 KB (two, 52 KB left) 4923; of 8 layers 1277,
+  // 1274, 1292.  Beside such gathers a selection took 122 us and the statistics 125 on average (alone 40 and 59), when they
+  // were 73 and 58 KB large and the claim 36 KB 245 and 166; the gather 444 instead of 425.
   const size_t lds = leave_room ? GATHER_ROOM_LDS : 0;
   if (c.cache_fp8) {
     if (lpr == 8) hipLaunchKernelGGL((gather_kernel<8, true>), grid, dim3(256), lds, st, a);

@@ -27,9 +27,8 @@ constexpr int SEL_THREADS = 1024;
 constexpr int SEL_CHUNK = 16384;                 // candidates per workgroup where a head's chunks have workgroups of their own
 constexpr uint32_t SEL_SH1 = 21;                 // plain first digit of a 32-bit key
 
-// candidates of the crossing bins: how many a workgroup lists per modality, how many of a head's chunk (on average) fit the
-// head's list in memory, and up to how many are ranked one against the other
-template <int MM> constexpr int SEL_LIST = MM == 2 ? 2048 : 1024;
+// candidates of the crossing bins: how many of a head's chunk (on average) fit the head's list in memory, and up to how many
+// are ranked one against the other
 constexpr int SEL_GLIST_PER_CHUNK = 1024, SEL_RANK_MAX = 256;
 constexpr int SEL_MAX_CHUNKS = 64;               // 2^20 candidates
 
@@ -154,6 +153,7 @@ struct SelectArgs {
   // Phase 0 = the whole head in one workgroup.  Long heads on few heads: a workgroup per chunk; 1 = its counts, added to the
   // head's in memory, which the last one to arrive walks; 2 = its candidates of the crossing bins, added to the head's list,
   // which the last one to arrive ranks; 3 = its kept positions written behind those of the chunks before it.
+  int list_shift;                 // log2 of what a workgroup lists per modality (list_shift_of)
   char* split;                    // a record of split_stride bytes per head (SelSplit)
   long long split_stride;
 };
@@ -264,7 +264,8 @@ __device__ __forceinline__ void for_key_groups(const float* sc, const uint8_t* m
 template <int MM, int PHASE>   // modalities the kernel is built for (2, or 4 for three and four), phase (SelectArgs)
 __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM == 2 ? 8 : 4))) void select_kernel(SelectArgs a) {
   constexpr int NWAVES = SEL_THREADS / 64, WPM = NWAVES / MM;   // waves per modality
-  constexpr int phase = PHASE, CAP = SEL_LIST<MM>;
+  constexpr int phase = PHASE;
+  const int CS = MM == 2 ? a.list_shift : LIST_SHIFT_MIN, CAP = 1 << CS;
   extern __shared__ __attribute__((aligned(16))) unsigned char select_smem[];
   const int M = MM == 2 ? 2 : a.M;
   uint32_t* cnt = reinterpret_cast<uint32_t*>(select_smem);                          // [M][BINS] counts, [M][64] of the lowest bin
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
     }
     auto push = [&](int m, unsigned long long x) {
       const uint32_t at = atomicAdd(&s_listed[m], 1u);
-      if (at < (uint32_t)CAP) list[m * CAP + at] = x;
+      if (at < (uint32_t)CAP) list[(m << CS) + at] = x;
     };
     auto within = [&](int m, uint32_t key) { return key - s_range[m].lo <= s_range[m].hi - s_range[m].lo; };
     if (have == 0) {                               // from the scores
@@ -457,8 +458,8 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
           // (a position takes 20 bits: two of the others say the modality)
           wb.put(i + q < i_end && key - lo <= sp, ((unsigned long long)key << 32) | (~(uint32_t)(i + q) ^ ((uint32_t)m << 30)));
           if (phase == 2) sure += i + q < i_end && key > pick(hi, m) ? 1u : 0u;
+          if (wb.n > 64u) wb.flush(lane, take);
         }
-        if (wb.n > 64u) wb.flush(lane, take);
       });
       wb.flush(lane, take);
       if (phase == 2) {
@@ -472,13 +473,13 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
           if (within(m, (uint32_t)(x >> 32))) push(m, x);
         }
     } else {                                       // from the list itself
-      constexpr int PT = MM * CAP / SEL_THREADS;
+      constexpr int PT = (MM << (MM == 2 ? LIST_SHIFT_MAX : LIST_SHIFT_MIN)) / SEL_THREADS;
       unsigned long long x[PT];
       bool in[PT];
 #pragma unroll
       for (int j = 0; j < PT; ++j) {
-        const int e = tid + j * SEL_THREADS, m = e / CAP;
-        in[j] = m < M && e % CAP < listed(min(m, M - 1));
+        const int e = tid + j * SEL_THREADS, m = e >> CS;
+        in[j] = m < M && (e & (CAP - 1)) < listed(min(m, M - 1));
         x[j] = in[j] ? list[e] : 0ULL;
       }
       __syncthreads();
@@ -486,7 +487,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < PT; ++j) {
-        const int m = min((tid + j * SEL_THREADS) / CAP, M - 1);
+        const int m = min((tid + j * SEL_THREADS) >> CS, M - 1);
         if (in[j] && within(m, (uint32_t)(x[j] >> 32))) push(m, x[j]);
       }
     }
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       __syncthreads();
       for (int m = 0; m < M; ++m)
         for (int e = tid; e < min((int)s_listed[m], CAP); e += SEL_THREADS)
-          if (s_base[m] + e < (uint32_t)gcap) agent_store(glist + m * gcap + s_base[m] + e, list[m * CAP + e]);
+          if (s_base[m] + e < (uint32_t)gcap) agent_store(glist + m * gcap + s_base[m] + e, list[(m << CS) + e]);
       if (!arrive_last(&meet->arrived[1], gridDim.x, &s_flag)) return;
       if (tid < M) { s_glisted[tid] = s_listed[tid] = agent_load(&meet->listed[tid]); agent_store(&meet->listed[tid], 0u); }
       if (tid == 0) agent_store(&meet->arrived[1], 0u);
@@ -516,7 +517,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       alone = !there;
       if (here)
         for (int m = 0; m < M; ++m)
-          for (int e = tid; e < min((int)s_glisted[m], CAP); e += SEL_THREADS) list[m * CAP + e] = agent_load(glist + m * gcap + e);
+          for (int e = tid; e < min((int)s_glisted[m], CAP); e += SEL_THREADS) list[(m << CS) + e] = agent_load(glist + m * gcap + e);
       have = here ? 1 : there ? 2 : 0;
       __syncthreads();
       i_begin = 0; i_end = nc;                     // from here on the whole head is this workgroup's
@@ -533,10 +534,10 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       const bool mine = m_of < M && s_alive[min(m_of, M - 1)] == 1u;
       const int n = mine ? (int)s_listed[m_of] : 0;
       for (int i0 = 0; i0 < n; i0 += 64) {
-        const unsigned long long x = list[m_of * CAP + min(i0 + lane, n - 1)];
+        const unsigned long long x = list[(m_of << CS) + min(i0 + lane, n - 1)];
         uint32_t above = 0u;
 #pragma unroll 4
-        for (int j = part; j < n; j += WPM) above += list[m_of * CAP + j] > x ? 1u : 0u;
+        for (int j = part; j < n; j += WPM) above += list[(m_of << CS) + j] > x ? 1u : 0u;
         if (i0 + lane < n) atomicAdd(&rank[m_of * SEL_RANK_MAX + i0 + lane], above);
       }
       __syncthreads();
@@ -544,7 +545,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
         const uint32_t need = s_need[m_of];
         for (int i = part * 64 + lane; i < n; i += WPM * 64) {
           const uint32_t above = rank[m_of * SEL_RANK_MAX + i];
-          const unsigned long long x = list[m_of * CAP + i];
+          const unsigned long long x = list[(m_of << CS) + i];
           if (above + 1u == need) { s_tau[m_of] = (uint32_t)(x >> 32); s_pos[m_of] = ~(uint32_t)x; }
         }
       }
@@ -567,7 +568,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
     } else {
       for (int m = 0; m < M; ++m)
         for (int e = tid; e < (have == 1 ? listed(m) : glisted(m)); e += SEL_THREADS)
-          add(m, (uint32_t)((have == 1 ? list[m * CAP + e] : agent_load(glist + m * gcap + e)) >> 32));
+          add(m, (uint32_t)((have == 1 ? list[(m << CS) + e] : agent_load(glist + m * gcap + e)) >> 32));
     }
     __syncthreads();
   }
@@ -712,7 +713,7 @@ hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, co
 
 template <int MM, int PHASE>
 static hipError_t launch_select_t(const SelectArgs& a, dim3 grid, hipStream_t st) {
-  const size_t lds = PHASE == 3 ? 0 : select_front(a.M) + (size_t)a.M * SEL_LIST<MM> * sizeof(unsigned long long);
+  const size_t lds = PHASE == 3 ? 0 : select_front(a.M) + ((size_t)a.M << a.list_shift) * sizeof(unsigned long long);
   if (lds > 48 * 1024) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<MM, PHASE>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL((select_kernel<MM, PHASE>), grid, dim3(SEL_THREADS), lds, st, a);
   return hipGetLastError();
@@ -727,7 +728,7 @@ hipError_t launch_select(const Dims& dm, const madakv_config& c, const float* ps
   a.B = dm.B; a.H = dm.H; a.L = dm.L; a.W = dm.W; a.nc = dm.nc; a.mpa_mode = c.mpa_mode;
   a.keep_all = (c.budget >= c.ctx_len && !seg_len) ? 1 : 0;
   a.select_mode = c.select_mode; a.sink_tokens = c.sink_tokens; a.M = c.n_modalities;
-  a.split = nullptr; a.split_stride = 0;
+  a.split = nullptr; a.split_stride = 0; a.list_shift = list_shift_of(a.M, dm.nc);
   const int nchunks = split_chunks(dm);
   const dim3 whole(dm.heads), chunks(nchunks, dm.heads);
   const bool two = a.M == 2;

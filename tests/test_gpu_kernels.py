@@ -639,7 +639,7 @@ def test_decode_pieces_that_come_into_being(kw):
     eng.close()
 
 
-@pytest.mark.parametrize("L,W,M", [(3000, 8, 2), (9001, 8, 3), (20000, 8, 2), (70001, 8, 2), (70001, 8, 3), (200001, 16, 2)])
+@pytest.mark.parametrize("L,W,M", [(3000, 8, 2), (9001, 8, 3), (20000, 8, 2), (40001, 8, 2), (70001, 8, 2), (70001, 8, 3), (200001, 16, 2)])
 def test_statistics_of_crowded_bins(L, W, M):
     """Scores so close together that the bin where the running mass crosses theta holds a few, hundreds (ranked, or walked once
     more), thousands (more than a workgroup's list, or than the chunk's share of the head's) or all of the candidates, equal ones
@@ -674,7 +674,7 @@ def test_statistics_of_crowded_bins(L, W, M):
     eng.close()
 
 
-@pytest.mark.parametrize("L,M", [(9000, 2), (9000, 3), (20001, 2), (70001, 2), (70001, 4), (200001, 2)])
+@pytest.mark.parametrize("L,M", [(9000, 2), (9000, 3), (20001, 2), (40001, 2), (70001, 2), (70001, 4), (200001, 2)])
 def test_selection_of_crowded_bins(L, M):
     """Kept positions, bit for bit, where the threshold is among 2 to 5000 scores of one bin (or all of them), at and around
     what is ranked at once and what a list holds, in bins of either width and next to their boundary, with ties; two layers in

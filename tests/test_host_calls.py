@@ -204,3 +204,26 @@ def test_scoring_workspaces_hold_no_exchange_words(runtime, cfg):
         assert lib.madakv_workspace_bytes(h, n, C.byref(a), None, None) == 0 and lib.madakv_window_attn_workspace_bytes(h, n, C.byref(b)) == 0
         assert b.value <= {window} and a.value <= {score}, (a.value, {score}, b.value, {window})
         """, cfg)
+
+
+@pytest.mark.parametrize("cfg", [good(n_layers=32, batch=4, n_q_heads=32, n_kv_heads=32, ctx_len=16384, budget=2048), good(n_layers=64, ctx_len=4096, cache_fp8=1),
+                                 good(n_layers=48, batch=4, n_q_heads=28, n_kv_heads=4, ctx_len=32768, budget=2048)], ids=lambda c: f"layers{c.n_layers}")
+def test_per_head_kernels_fit_beside_a_gather(runtime, cfg):
+    """In a call over several layer groups statistics and selection run beside a gather, whose workgroups claim LDS to leave them
+    room: what the claims leave of a compute unit's 160 KB takes a selection workgroup at once, and one of the statistics when a
+    single gather workgroup has left (2 KB for what the kernels declare themselves)."""
+    scenario(runtime, f"""
+        h = create(sys.argv[3])
+        log()
+        t = [P(T().p) for _ in range(14)]
+        assert lib.madakv_evict(h, I(0), I({cfg.n_layers}), *t, P(T().p), Z(1 << 34), P(T().p), Z(1 << 34), P(0)) == 0
+        lds = {{}}
+        for x in log():
+            if x.kind == "launch":
+                for name in ("gather", "select", "stats"):
+                    if name + "_kernel" in str(x): lds.setdefault(name, set()).add(int(x.rest[2]))
+        unit = 160 * 1024
+        (claim,) = lds["gather"]
+        left = unit - unit // claim * claim
+        assert max(lds["select"]) + 2048 <= left and max(lds["stats"]) + 2048 <= left + claim, (lds, left)
+        """, cfg)
