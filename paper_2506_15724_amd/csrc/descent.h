@@ -63,13 +63,13 @@ __device__ __forceinline__ T pick(const T (&x)[N], int m) {              // x[m]
   return r;
 }
 
-// Entries that a workgroup's list has per modality, log2.  About a hundredth of a head's candidates falls into the crossing bin;
-// where they do not fit, another pass over all of them is due: 2048 for heads of more than 32K candidates of two modalities (192
-// heads of 128K: statistics 92 us, selection 99, with 1024 entries 127 and 141; of 64K 51 and 54, with 1024 70 and 54), else 1024 (of 32K
-// 30 and 32 either way), which leaves the workgroup smaller: where it runs beside a gather it has to find room on a compute
-// unit (launch_gather).
+// Entries that a workgroup's list has per modality, log2.  Some hundredths of a head's candidates fall into the crossing bin;
+// where they do not fit, another pass over all of them is due: 2048 for heads of more than 16K candidates of two modalities (192
+// heads of 128K: statistics 92 us, selection 99, with 1024 entries 127 and 141; 112 of 32K and 224 proxy rows 29 and 32, with
+// 1024 39 and 32), else 1024 (of 16K and 224 rows 22 and 23, 23 and 24), which leaves the workgroup smaller: where it runs
+// beside a gather it has to find room on a compute unit (launch_gather).
 constexpr int LIST_SHIFT_MIN = 10, LIST_SHIFT_MAX = 11;
-inline int list_shift_of(int M, int nc) { return M == 2 && nc > 32768 ? LIST_SHIFT_MAX : LIST_SHIFT_MIN; }
+inline int list_shift_of(int M, int nc) { return M == 2 && nc > 16384 ? LIST_SHIFT_MAX : LIST_SHIFT_MIN; }
 
 // Few lanes of a wave find something for a list now and then: they leave it in a buffer of the wave's own, which needs no
 // atomic and waits for nothing, and the buffer goes to the list once it holds a wave's worth (push per entry).  All lanes of

@@ -207,11 +207,11 @@ def test_scoring_workspaces_hold_no_exchange_words(runtime, cfg):
 
 
 @pytest.mark.parametrize("cfg", [good(n_layers=32, batch=4, n_q_heads=32, n_kv_heads=32, ctx_len=16384, budget=2048), good(n_layers=64, ctx_len=4096, cache_fp8=1),
-                                 good(n_layers=48, batch=4, n_q_heads=28, n_kv_heads=4, ctx_len=32768, budget=2048)], ids=lambda c: f"layers{c.n_layers}")
+                                 good(n_layers=48, batch=4, n_q_heads=28, n_kv_heads=4, ctx_len=12000, budget=1000)], ids=lambda c: f"layers{c.n_layers}")
 def test_per_head_kernels_fit_beside_a_gather(runtime, cfg):
     """In a call over several layer groups statistics and selection run beside a gather, whose workgroups claim LDS to leave them
-    room: what the claims leave of a compute unit's 160 KB takes a selection workgroup at once, and one of the statistics when a
-    single gather workgroup has left (2 KB for what the kernels declare themselves)."""
+    room: what the claims leave of a compute unit's 160 KB takes a selection workgroup over up to 16K candidates at once, and one
+    of the statistics when a single gather workgroup has left (2 KB for what the kernels declare themselves)."""
     scenario(runtime, f"""
         h = create(sys.argv[3])
         log()
