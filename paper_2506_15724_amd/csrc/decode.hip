@@ -215,8 +215,9 @@ __device__ __forceinline__ void stage_new_row(const DecodeArgs& a, long long hid
 // denormal results)
 __device__ __forceinline__ float weight_of(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// The two values of lanes that are O apart (O = 4 ... 32: within a row by rotation, across rows by a swap of rows), the
-// same pair in both lanes up to its order.
+// The two values of lanes that are O apart (O = 4 ... 32: within a row by rotation, across rows by a swap of rows): the same
+// pair in both lanes up to its order.  (Rotated by 4, lane i is paired with lane i - 4 and that one with i - 8: only the merge over 8
+// that follows brings the four of a row together in every lane.)
 template <int O>
 __device__ __forceinline__ void lane_pair(float x, float& p, float& q) {
   const uint32_t u = __float_as_uint(x);

@@ -150,7 +150,7 @@ hipError_t launch_gather(const Dims& dm, const madakv_config& c, int li0, int nl
   // claim of GATHER_ROOM_LDS bytes of (unused) LDS holds them to three and leaves 37 KB: enough for a selection
   // workgroup over heads of up to 16K (34 KB; statistics, 50 KB, and longer heads once one of the three has left).  Eviction of 32 layers of 128 heads of 16K in one
   // call, median us: claims of 36 KB (four, 16 KB left) 4808, 41 KB 4795, 54 KB (two, 52 KB left) 4923; of 8 layers 1277,
-  // 1274, 1292.  Beside such gathers a selection took 122 us and the statistics 125 on average (alone 40 and 59), when they
+  // 1274, 1292.  Beside such gathers a selection took 122 us and the statistics 125 on average (alone 58 and 60), when they
   // were 73 and 58 KB large and the claim 36 KB 245 and 166; the gather 444 instead of 425.
   const size_t lds = leave_room ? GATHER_ROOM_LDS : 0;
   if (c.cache_fp8) {

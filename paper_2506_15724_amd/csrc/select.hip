@@ -150,10 +150,10 @@ struct SelectArgs {
   const float* psi_pool; const uint8_t* mask; const int32_t* budgets; const int64_t* kv_off; const int32_t* kv_len; int32_t* kept_idx;
   int B, H, L, W, nc, mpa_mode, keep_all, select_mode, sink_tokens, M;
   const int32_t* seg_len; const uint8_t* rowmod;   // ragged candidates (re-eviction), else null
+  int list_shift;                 // log2 of what a workgroup lists per modality (list_shift_of)
   // Phase 0 = the whole head in one workgroup.  Long heads on few heads: a workgroup per chunk; 1 = its counts, added to the
   // head's in memory, which the last one to arrive walks; 2 = its candidates of the crossing bins, added to the head's list,
   // which the last one to arrive ranks; 3 = its kept positions written behind those of the chunks before it.
-  int list_shift;                 // log2 of what a workgroup lists per modality (list_shift_of)
   char* split;                    // a record of split_stride bytes per head (SelSplit)
   long long split_stride;
 };

@@ -46,11 +46,11 @@ struct StatsArgs {
   const float* psi; const uint8_t* mask; float* psi_pool; void* stats; int32_t* n_mod;
   int B, H, L, W, nc, pool_r, pool_mode, share_mode, M;
   double theta;
+  unsigned long long* xchg; long long xchg_per_head;   // the exchange words of the scoring kernels, to be emptied (Exchange)
+  int list_shift;                                // log2 of what a workgroup lists per modality (list_shift_of)
   // Phase 0 = the whole head in one workgroup.  Long heads on few heads: a workgroup per chunk; 1 = its masses, added to the
   // head's in memory, which the last one to arrive walks; 2 = its keys of the crossing bins, added to the head's list, which
   // the last one to arrive ranks.
-  unsigned long long* xchg; long long xchg_per_head;   // the exchange words of the scoring kernels, to be emptied (Exchange)
-  int list_shift;                                // log2 of what a workgroup lists per modality (list_shift_of)
   char* split;                                   // a record of split_stride bytes per head (StatsSplit)
   long long split_stride;
 };
