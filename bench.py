@@ -408,7 +408,7 @@ def main():
                   read_profile(prof, "gather_total_us_per_eviction") / 1e3 if read_profile(prof, "gather_total_us_per_eviction") else sg_ms,
                   "duration summed over an eviction's gather launches in the committed rocprofv3 trace when present (else the call "
                   "above); in madakv_evict three of the four run beside the next group's statistics and selection kernels and "
-                  "hold 4 workgroups per compute unit; one gather over all layers with nothing beside it takes 1.49 ms "
+                  "hold 3 workgroups per compute unit; one gather over all layers with nothing beside it takes 1.49 ms "
                   "(0.72 of peak); copy ceiling 5.2-5.7 TB/s", None),
             dict(roofline, kernel="decode_attn_kernel (one call per layer)",
                  note="a plain streaming read of the same 135 MB takes 22.6-25.6 us on this machine (0.66-0.75 of peak)",
