@@ -76,7 +76,7 @@ size_t stats_split_bytes(int M, int nchunks);
 size_t select_split_bytes(int M, int nchunks);
 hipError_t launch_stats(const Dims& dm, const madakv_config& c, const float* psi, const uint8_t* mask,
                         float* psi_pool, void* stats, int32_t* n_mod, const Exchange& x, hipStream_t st,
-                        void* split_buf = nullptr, size_t split_bytes = 0);
+                        void* split_buf, size_t split_bytes, bool beside_gather);
 hipError_t launch_allocate(const Dims& dm, const madakv_config& c, int layer0, const void* stats,
                            const int32_t* n_mod, int32_t* budgets, long long* pool_state, hipStream_t st);
 hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, const int32_t* budgets,
@@ -85,7 +85,7 @@ hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, co
 hipError_t launch_select(const Dims& dm, const madakv_config& c, const float* psi_pool, const uint8_t* mask,
                          const int32_t* budgets, const int64_t* kv_off, const int32_t* kv_len, int32_t* kept_idx,
                          hipStream_t st, const int32_t* seg_len = nullptr, const uint8_t* rowmod = nullptr,
-                         void* split_buf = nullptr, size_t split_bytes = 0);
+                         void* split_buf = nullptr, size_t split_bytes = 0, bool beside_gather = false);
 // re-eviction during generation (reevict.hip, and the one-sweep scoring kernel on ragged segments)
 bool score_ragged_supported(const Dims& dm, const madakv_config& c, int longest_rows);
 size_t score_ragged_ws_bytes(const Dims& dm, const madakv_config& c, int longest_rows, long long cache_rows);

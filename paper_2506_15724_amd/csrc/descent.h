@@ -63,18 +63,19 @@ __device__ __forceinline__ T pick(const T (&x)[N], int m) {              // x[m]
   return r;
 }
 
-// Entries that a workgroup's list has per modality, log2.  Some hundredths of a head's candidates fall into the crossing bin;
-// where they do not fit, another pass over all of them is due: 2048 for heads of more than 16K candidates of two modalities (192
-// heads of 128K: statistics 92 us, selection 99, with 1024 entries 127 and 141; 112 of 32K and 224 proxy rows 29 and 32, with
-// 1024 39 and 32), else 1024 (of 16K and 224 rows 22 and 23, 23 and 24), which leaves the workgroup smaller: where it runs
-// beside a gather it has to find room on a compute unit (launch_gather).
-constexpr int LIST_SHIFT_MIN = 10, LIST_SHIFT_MAX = 11;
-inline int list_shift_of(int M, int nc) { return M == 2 && nc > 16384 ? LIST_SHIFT_MAX : LIST_SHIFT_MIN; }
+// Entries that a workgroup's list has per modality.  Some hundredths of a head's candidates fall into the crossing bin; where they
+// do not fit, another pass over all of them is due: 2048 for two modalities (192 heads of 128K: statistics 92 us, selection 99,
+// with 1024 entries 127 and 141; 112 of 32K and 224 proxy rows 29 and 32, with 1024 39 and 32; of 16K 22 and 23, with 1024 23 and 24).
+// SMALL: 1024, in a call over several layer groups for heads of up to SMALL_HEADS candidates: the workgroup has to find room on
+// a compute unit beside a gather (launch_gather).
+template <int MM, bool SMALL> constexpr int LIST_MAX = MM == 2 && !SMALL ? 2048 : 1024;
+constexpr int SMALL_HEADS = 16384;
 
 // Few lanes of a wave find something for a list now and then: they leave it in a buffer of the wave's own, which needs no
 // atomic and waits for nothing, and the buffer goes to the list once it holds a wave's worth (push per entry).  All lanes of
 // the wave take part in every call.
-constexpr int WAVE_BUF = 64 + 64;                // entries: a rest, and one of every lane
+constexpr int WAVE_BUF = 64 + 256;               // entries: a rest, and a group of four of every lane
+constexpr int WAVE_BUF_SMALL = 64 + 64;          // a rest, and one of every lane
 template <typename E>
 struct WaveBuf {
   E* buf;                                        // this wave's

@@ -449,7 +449,7 @@ static int32_t score_impl(madakv_handle* h, int32_t layer0, int32_t n,
     }
     if (e == hipSuccess)
       e = launch_stats(dg, c, psi_g, mask, pool_g, static_cast<char*>(stats) + lb * c.n_kv_heads * 8 * (size_t)c.n_modalities,
-                       g0 == 0 ? n_mod : nullptr, x, ss, h->d_split, h->split_bytes);
+                       g0 == 0 ? n_mod : nullptr, x, ss, h->d_split, h->split_bytes, false);
     if (e != hipSuccess) (void)empty_exchange(h, st);      // (at once: a graph captured before has no clear in it)
   }
   if (overlap) e = join_side(h, st, e);
@@ -540,7 +540,7 @@ int32_t madakv_select_gather(madakv_handle* h, int32_t layer0, int32_t n,
     const int bpb = blocks_per_batch(c, ng);
     e = launch_offsets(dg, c, layer0 + g0, bud_g, kv_off + heads0, kv_len + heads0, len1_of(h, layer0 + g0), h->d_state + c.batch,
                        h->d_maxlen + (size_t)(layer0 + g0) * c.batch, ws_g, make_paging(h), bpb, ss);
-    if (e == hipSuccess) e = launch_select(dg, c, pool_g, mask, bud_g, kv_off + heads0, kv_len + heads0, kept_idx, ss, nullptr, nullptr, h->d_split, h->split_bytes);
+    if (e == hipSuccess) e = launch_select(dg, c, pool_g, mask, bud_g, kv_off + heads0, kv_len + heads0, kept_idx, ss, nullptr, nullptr, h->d_split, h->split_bytes, overlap);
     if (overlap && e == hipSuccess) e = hipEventRecord(h->ev_sel[gi], h->side);
     if (overlap && e == hipSuccess) e = hipStreamWaitEvent(st, h->ev_sel[gi], 0);
     const char* kg = static_cast<const char*>(k) + heads0 * (size_t)c.ctx_len * c.head_dim * es;
@@ -614,12 +614,12 @@ int32_t madakv_evict(madakv_handle* h, int32_t layer0, int32_t n,
       if (e == hipSuccess) e = hipStreamWaitEvent(h->side, h->ev_grp[gi], 0);
       ss = h->side;
     }
-    if (e == hipSuccess) e = launch_stats(dg, c, psi_g, mask, pool_g, stats_g, g0 == 0 ? n_mod : nullptr, x, ss, h->d_split, h->split_bytes);
+    if (e == hipSuccess) e = launch_stats(dg, c, psi_g, mask, pool_g, stats_g, g0 == 0 ? n_mod : nullptr, x, ss, h->d_split, h->split_bytes, overlap);
     if (e != hipSuccess) (void)empty_exchange(h, st);      // (at once: a graph captured before has no clear in it)
     const AllocArgs alloc = alloc_args(dg, c, layer0 + g0, stats_g, n_mod, bud_g, h->d_state);
     if (e == hipSuccess) e = launch_offsets(dg, c, layer0 + g0, bud_g, kv_off + heads0, kv_len + heads0, len1_of(h, layer0 + g0), h->d_state + c.batch,
                                             h->d_maxlen + (size_t)(layer0 + g0) * c.batch, ws_g, make_paging(h), blocks_per_batch(c, ng), ss, &alloc);
-    if (e == hipSuccess) e = launch_select(dg, c, pool_g, mask, bud_g, kv_off + heads0, kv_len + heads0, kept_idx, ss, nullptr, nullptr, h->d_split, h->split_bytes);
+    if (e == hipSuccess) e = launch_select(dg, c, pool_g, mask, bud_g, kv_off + heads0, kv_len + heads0, kept_idx, ss, nullptr, nullptr, h->d_split, h->split_bytes, overlap);
     if (overlap && e == hipSuccess) e = hipEventRecord(h->ev_sel[gi], h->side);
     // the gather of the group before goes behind this group's sweeps: this group's statistics and
     // selection then run beside a gather, which leaves them room, and not beside the next sweeps

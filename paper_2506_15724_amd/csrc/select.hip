@@ -150,7 +150,6 @@ struct SelectArgs {
   const float* psi_pool; const uint8_t* mask; const int32_t* budgets; const int64_t* kv_off; const int32_t* kv_len; int32_t* kept_idx;
   int B, H, L, W, nc, mpa_mode, keep_all, select_mode, sink_tokens, M;
   const int32_t* seg_len; const uint8_t* rowmod;   // ragged candidates (re-eviction), else null
-  int list_shift;                 // log2 of what a workgroup lists per modality (list_shift_of)
   // Phase 0 = the whole head in one workgroup.  Long heads on few heads: a workgroup per chunk; 1 = its counts, added to the
   // head's in memory, which the last one to arrive walks; 2 = its candidates of the crossing bins, added to the head's list,
   // which the last one to arrive ranks; 3 = its kept positions written behind those of the chunks before it.
@@ -246,7 +245,10 @@ __device__ __forceinline__ uint32_t write_kept(const float* sc, const uint8_t* m
 }
 
 // LDS in front of the list: the counts, in whose place the waves' buffers and the ranks are when they have been walked
-__host__ __device__ constexpr int select_front(int M) { return 4 * M * (BINS + 64) > SEL_THREADS / 64 * WAVE_BUF * 8 ? 4 * M * (BINS + 64) : SEL_THREADS / 64 * WAVE_BUF * 8; }
+__host__ __device__ constexpr int select_front(int M, bool small) {
+  const int counts = 4 * M * (BINS + 64), bufs = SEL_THREADS / 64 * (small ? WAVE_BUF_SMALL : WAVE_BUF) * 8;
+  return counts > bufs ? counts : bufs;
+}
 
 // f(candidate's group, its first candidate) for this thread's groups of [i_first, i_end), the next one on its way.  WHOLE: all
 // lanes of a wave make the same trips, some with groups past the end.
@@ -261,16 +263,16 @@ __device__ __forceinline__ void for_key_groups(const float* sc, const uint8_t* m
   }
 }
 
-template <int MM, int PHASE>   // modalities the kernel is built for (2, or 4 for three and four), phase (SelectArgs)
+// modalities the kernel is built for (2, or 4 for three and four), phase (SelectArgs), one that has to fit beside a gather
+template <int MM, int PHASE, bool SMALL>
 __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM == 2 ? 8 : 4))) void select_kernel(SelectArgs a) {
   constexpr int NWAVES = SEL_THREADS / 64, WPM = NWAVES / MM;   // waves per modality
-  constexpr int phase = PHASE;
-  const int CS = MM == 2 ? a.list_shift : LIST_SHIFT_MIN, CAP = 1 << CS;
+  constexpr int phase = PHASE, CAP = LIST_MAX<MM, SMALL>;
   extern __shared__ __attribute__((aligned(16))) unsigned char select_smem[];
   const int M = MM == 2 ? 2 : a.M;
   uint32_t* cnt = reinterpret_cast<uint32_t*>(select_smem);                          // [M][BINS] counts, [M][64] of the lowest bin
   uint32_t* low = cnt + M * BINS;
-  unsigned long long* list = reinterpret_cast<unsigned long long*>(select_smem + select_front(M));   // [M][CAP] key, ~position
+  unsigned long long* list = reinterpret_cast<unsigned long long*>(select_smem + select_front(M, SMALL));   // [M][CAP] key, ~position
   uint32_t* rank = cnt;                                                              // [M][SEL_RANK_MAX] larger ones (in the place of the counts)
   __shared__ DescentRange s_range[MM];
   __shared__ uint32_t s_need[MM], s_alive[MM], s_tau[MM], s_pos[MM], s_before[MM], s_bin[MM], s_part[MM][NWAVES], s_listed[MM], s_glisted[MM], s_sure, s_flag;
@@ -431,12 +433,12 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
     }
     auto push = [&](int m, unsigned long long x) {
       const uint32_t at = atomicAdd(&s_listed[m], 1u);
-      if (at < (uint32_t)CAP) list[(m << CS) + at] = x;
+      if (at < (uint32_t)CAP) list[m * CAP + at] = x;
     };
     auto within = [&](int m, uint32_t key) { return key - s_range[m].lo <= s_range[m].hi - s_range[m].lo; };
     if (have == 0) {                               // from the scores
       // (in the place of the counts, which have been walked)
-      WaveBuf<unsigned long long> wb{reinterpret_cast<unsigned long long*>(select_smem) + wave0 * WAVE_BUF, 0u};
+      WaveBuf<unsigned long long> wb{reinterpret_cast<unsigned long long*>(select_smem) + wave0 * (SMALL ? WAVE_BUF_SMALL : WAVE_BUF), 0u};
       const auto take = [&](unsigned long long x) {
         const uint32_t m = ((uint32_t)x >> 30) ^ 3u;
         push((int)m, x ^ (m << 30));
@@ -458,8 +460,9 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
           // (a position takes 20 bits: two of the others say the modality)
           wb.put(i + q < i_end && key - lo <= sp, ((unsigned long long)key << 32) | (~(uint32_t)(i + q) ^ ((uint32_t)m << 30)));
           if (phase == 2) sure += i + q < i_end && key > pick(hi, m) ? 1u : 0u;
-          if (wb.n > 64u) wb.flush(lane, take);
+          if (SMALL && wb.n > 64u) wb.flush(lane, take);
         }
+        if (!SMALL && wb.n > 64u) wb.flush(lane, take);
       });
       wb.flush(lane, take);
       if (phase == 2) {
@@ -473,13 +476,13 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
           if (within(m, (uint32_t)(x >> 32))) push(m, x);
         }
     } else {                                       // from the list itself
-      constexpr int PT = (MM << (MM == 2 ? LIST_SHIFT_MAX : LIST_SHIFT_MIN)) / SEL_THREADS;
+      constexpr int PT = MM * CAP / SEL_THREADS;
       unsigned long long x[PT];
       bool in[PT];
 #pragma unroll
       for (int j = 0; j < PT; ++j) {
-        const int e = tid + j * SEL_THREADS, m = e >> CS;
-        in[j] = m < M && (e & (CAP - 1)) < listed(min(m, M - 1));
+        const int e = tid + j * SEL_THREADS, m = e / CAP;
+        in[j] = m < M && e % CAP < listed(min(m, M - 1));
         x[j] = in[j] ? list[e] : 0ULL;
       }
       __syncthreads();
@@ -487,7 +490,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < PT; ++j) {
-        const int m = min((tid + j * SEL_THREADS) >> CS, M - 1);
+        const int m = min((tid + j * SEL_THREADS) / CAP, M - 1);
         if (in[j] && within(m, (uint32_t)(x[j] >> 32))) push(m, x[j]);
       }
     }
@@ -503,7 +506,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       __syncthreads();
       for (int m = 0; m < M; ++m)
         for (int e = tid; e < min((int)s_listed[m], CAP); e += SEL_THREADS)
-          if (s_base[m] + e < (uint32_t)gcap) agent_store(glist + m * gcap + s_base[m] + e, list[(m << CS) + e]);
+          if (s_base[m] + e < (uint32_t)gcap) agent_store(glist + m * gcap + s_base[m] + e, list[m * CAP + e]);
       if (!arrive_last(&meet->arrived[1], gridDim.x, &s_flag)) return;
       if (tid < M) { s_glisted[tid] = s_listed[tid] = agent_load(&meet->listed[tid]); agent_store(&meet->listed[tid], 0u); }
       if (tid == 0) agent_store(&meet->arrived[1], 0u);
@@ -517,7 +520,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       alone = !there;
       if (here)
         for (int m = 0; m < M; ++m)
-          for (int e = tid; e < min((int)s_glisted[m], CAP); e += SEL_THREADS) list[(m << CS) + e] = agent_load(glist + m * gcap + e);
+          for (int e = tid; e < min((int)s_glisted[m], CAP); e += SEL_THREADS) list[m * CAP + e] = agent_load(glist + m * gcap + e);
       have = here ? 1 : there ? 2 : 0;
       __syncthreads();
       i_begin = 0; i_end = nc;                     // from here on the whole head is this workgroup's
@@ -534,10 +537,10 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
       const bool mine = m_of < M && s_alive[min(m_of, M - 1)] == 1u;
       const int n = mine ? (int)s_listed[m_of] : 0;
       for (int i0 = 0; i0 < n; i0 += 64) {
-        const unsigned long long x = list[(m_of << CS) + min(i0 + lane, n - 1)];
+        const unsigned long long x = list[m_of * CAP + min(i0 + lane, n - 1)];
         uint32_t above = 0u;
 #pragma unroll 4
-        for (int j = part; j < n; j += WPM) above += list[(m_of << CS) + j] > x ? 1u : 0u;
+        for (int j = part; j < n; j += WPM) above += list[m_of * CAP + j] > x ? 1u : 0u;
         if (i0 + lane < n) atomicAdd(&rank[m_of * SEL_RANK_MAX + i0 + lane], above);
       }
       __syncthreads();
@@ -545,7 +548,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
         const uint32_t need = s_need[m_of];
         for (int i = part * 64 + lane; i < n; i += WPM * 64) {
           const uint32_t above = rank[m_of * SEL_RANK_MAX + i];
-          const unsigned long long x = list[(m_of << CS) + i];
+          const unsigned long long x = list[m_of * CAP + i];
           if (above + 1u == need) { s_tau[m_of] = (uint32_t)(x >> 32); s_pos[m_of] = ~(uint32_t)x; }
         }
       }
@@ -568,7 +571,7 @@ __global__ __launch_bounds__(SEL_THREADS) __attribute__((amdgpu_waves_per_eu(MM 
     } else {
       for (int m = 0; m < M; ++m)
         for (int e = tid; e < (have == 1 ? listed(m) : glisted(m)); e += SEL_THREADS)
-          add(m, (uint32_t)((have == 1 ? list[(m << CS) + e] : agent_load(glist + m * gcap + e)) >> 32));
+          add(m, (uint32_t)((have == 1 ? list[m * CAP + e] : agent_load(glist + m * gcap + e)) >> 32));
     }
     __syncthreads();
   }
@@ -711,24 +714,24 @@ hipError_t launch_offsets(const Dims& dm, const madakv_config& c, int layer0, co
   return hipGetLastError();
 }
 
-template <int MM, int PHASE>
+template <int MM, int PHASE, bool SMALL = false>
 static hipError_t launch_select_t(const SelectArgs& a, dim3 grid, hipStream_t st) {
-  const size_t lds = PHASE == 3 ? 0 : select_front(a.M) + ((size_t)a.M << a.list_shift) * sizeof(unsigned long long);
-  if (lds > 48 * 1024) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<MM, PHASE>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((select_kernel<MM, PHASE>), grid, dim3(SEL_THREADS), lds, st, a);
+  const size_t lds = PHASE == 3 ? 0 : select_front(a.M, SMALL) + (size_t)a.M * LIST_MAX<MM, SMALL> * sizeof(unsigned long long);
+  if (lds > 48 * 1024) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<MM, PHASE, SMALL>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((select_kernel<MM, PHASE, SMALL>), grid, dim3(SEL_THREADS), lds, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_select(const Dims& dm, const madakv_config& c, const float* psi_pool, const uint8_t* mask,
                          const int32_t* budgets, const int64_t* kv_off, const int32_t* kv_len, int32_t* kept_idx,
-                         hipStream_t st, const int32_t* seg_len, const uint8_t* rowmod, void* split_buf, size_t split_bytes) {
+                         hipStream_t st, const int32_t* seg_len, const uint8_t* rowmod, void* split_buf, size_t split_bytes, bool beside_gather) {
   SelectArgs a;
   a.seg_len = seg_len; a.rowmod = rowmod;
   a.psi_pool = psi_pool; a.mask = mask; a.budgets = budgets; a.kv_off = kv_off; a.kv_len = kv_len; a.kept_idx = kept_idx;
   a.B = dm.B; a.H = dm.H; a.L = dm.L; a.W = dm.W; a.nc = dm.nc; a.mpa_mode = c.mpa_mode;
   a.keep_all = (c.budget >= c.ctx_len && !seg_len) ? 1 : 0;
   a.select_mode = c.select_mode; a.sink_tokens = c.sink_tokens; a.M = c.n_modalities;
-  a.split = nullptr; a.split_stride = 0; a.list_shift = list_shift_of(a.M, dm.nc);
+  a.split = nullptr; a.split_stride = 0;
   const int nchunks = split_chunks(dm);
   const dim3 whole(dm.heads), chunks(nchunks, dm.heads);
   const bool two = a.M == 2;
@@ -741,6 +744,7 @@ hipError_t launch_select(const Dims& dm, const madakv_config& c, const float* ps
     if (e == hipSuccess) e = two ? launch_select_t<2, 3>(a, chunks, st) : launch_select_t<4, 3>(a, chunks, st);
     return e;
   }
+  if (beside_gather && a.nc <= SMALL_HEADS) return two ? launch_select_t<2, 0, true>(a, whole, st) : launch_select_t<4, 0, true>(a, whole, st);
   return two ? launch_select_t<2, 0>(a, whole, st) : launch_select_t<4, 0>(a, whole, st);
 }
 

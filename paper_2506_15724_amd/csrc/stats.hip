@@ -47,7 +47,6 @@ struct StatsArgs {
   int B, H, L, W, nc, pool_r, pool_mode, share_mode, M;
   double theta;
   unsigned long long* xchg; long long xchg_per_head;   // the exchange words of the scoring kernels, to be emptied (Exchange)
-  int list_shift;                                // log2 of what a workgroup lists per modality (list_shift_of)
   // Phase 0 = the whole head in one workgroup.  Long heads on few heads: a workgroup per chunk; 1 = its masses, added to the
   // head's in memory, which the last one to arrive walks; 2 = its keys of the crossing bins, added to the head's list, which
   // the last one to arrive ranks.
@@ -176,10 +175,10 @@ __device__ __forceinline__ void pool_group_wide(const float* psi, float* pool, i
   }
 }
 
-template <int MM, int PHASE>   // modalities the kernel is built for (2, or 4 for three and four), phase (StatsArgs)
+// modalities the kernel is built for (2, or 4 for three and four), phase (StatsArgs), one that has to fit beside a gather
+template <int MM, int PHASE, bool SMALL>
 __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(MM == 2 ? 8 : 4))) void stats_kernel(StatsArgs a) {
-  constexpr int phase = PHASE;
-  const int CS = MM == 2 ? a.list_shift : LIST_SHIFT_MIN, CAP = 1 << CS;
+  constexpr int phase = PHASE, CAP = LIST_MAX<MM, SMALL>;
   const int M = MM == 2 ? 2 : a.M;
   extern __shared__ __attribute__((aligned(16))) unsigned char stats_smem[];
   unsigned long long* sum = reinterpret_cast<unsigned long long*>(stats_smem);      // [M][BINS] masses, [M][64] of the lowest bin
@@ -384,7 +383,7 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
     for (int m = 0; m < MM; ++m) { rg[m] = descent_uniform(s_range[min(m, M - 1)]); found[m] = 0u; }
     auto push = [&](int m, uint32_t key) {
       const uint32_t at = atomicAdd(&s_listed[m], 1u);
-      if (at < (uint32_t)CAP) list[(m << CS) + at] = key;
+      if (at < (uint32_t)CAP) list[m * CAP + at] = key;
     };
     if (have == 0) {                             // from the scores (what lies past the end has the key 0)
       // (in the place of the masses, which have been walked)
@@ -403,8 +402,8 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
             for (int mm = 0; mm < MM; ++mm) found[mm] += m == mm && key > hi ? 1u : 0u;
           }
           wb.put(key - lo <= hi - lo, ((unsigned long long)m << 32) | key);
-          if (wb.n > 64u) wb.flush(lane, take);
         }
+        if (wb.n > 64u) wb.flush(lane, take);
       });
       wb.flush(lane, take);
       if (MM == 2) found[0] -= found[1];
@@ -417,13 +416,13 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
         }
       if (tid < M) atomicAdd(&s_above[tid], s_gabove[tid]);
     } else {                                     // from the list itself
-      constexpr int PT = (MM << (MM == 2 ? LIST_SHIFT_MAX : LIST_SHIFT_MIN)) / STATS_THREADS;
+      constexpr int PT = MM * CAP / STATS_THREADS;
       uint32_t key[PT];
       bool in[PT];
 #pragma unroll
       for (int j = 0; j < PT; ++j) {
-        const int e = tid + j * STATS_THREADS, m = e >> CS;
-        in[j] = m < M && (e & (CAP - 1)) < listed(min(m, M - 1));
+        const int e = tid + j * STATS_THREADS, m = e / CAP;
+        in[j] = m < M && e % CAP < listed(min(m, M - 1));
         key[j] = in[j] ? list[e] : 0u;
       }
       __syncthreads();
@@ -431,7 +430,7 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < PT; ++j) {
-        const int m = min((tid + j * STATS_THREADS) >> CS, M - 1);
+        const int m = min((tid + j * STATS_THREADS) / CAP, M - 1);
         if (in[j] && key[j] - s_range[m].lo <= s_range[m].hi - s_range[m].lo) push(m, key[j]);
         else if (in[j] && key[j] > s_range[m].hi) atomicAdd(&s_above[m], 1u);
       }
@@ -455,7 +454,7 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
       __syncthreads();
       for (int m = 0; m < M; ++m)
         for (int e = tid; e < min((int)s_listed[m], CAP); e += STATS_THREADS)
-          if (s_base[m] + e < (uint32_t)gcap) agent_store(glist + m * gcap + s_base[m] + e, list[(m << CS) + e]);
+          if (s_base[m] + e < (uint32_t)gcap) agent_store(glist + m * gcap + s_base[m] + e, list[m * CAP + e]);
       if (!arrive_last(&meet->arrived[1], gridDim.x, &s_flag)) return;
       if (tid < M) {
         s_glisted[tid] = s_listed[tid] = agent_load(&meet->listed[tid]);
@@ -471,7 +470,7 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
       }
       if (here)
         for (int m = 0; m < M; ++m)
-          for (int e = tid; e < min((int)s_glisted[m], CAP); e += STATS_THREADS) list[(m << CS) + e] = agent_load(glist + m * gcap + e);
+          for (int e = tid; e < min((int)s_glisted[m], CAP); e += STATS_THREADS) list[m * CAP + e] = agent_load(glist + m * gcap + e);
       have = here ? 1 : there ? 2 : 0;
       __syncthreads();
       i_begin = 0; i_end = a.nc;                 // from here on the whole head is this workgroup's
@@ -489,11 +488,11 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
       const bool mine = m_of < M && s_alive[min(m_of, M - 1)] == 1u;
       const int n = mine ? (int)s_listed[m_of] : 0;
       for (int i0 = 0; i0 < n; i0 += 64) {
-        const uint32_t ki = list[(m_of << CS) + min(i0 + lane, n - 1)];
+        const uint32_t ki = list[m_of * CAP + min(i0 + lane, n - 1)];
         unsigned long long gt = 0ULL;
         uint32_t c = 0u;
         for (int j = part; j < n; j += WPM) {
-          const uint32_t kj = list[(m_of << CS) + j];
+          const uint32_t kj = list[m_of * CAP + j];
           gt += kj > ki ? to_fx(__uint_as_float(kj)) : 0ULL;
           c += kj > ki ? 1u : (kj == ki ? 65536u : 0u);
         }
@@ -502,7 +501,7 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
       __syncthreads();
       if (mine && part * 64 + lane < n) {        // (RANK_MAX <= 64 * WPM)
         const int i = part * 64 + lane;
-        const uint32_t key = list[(m_of << CS) + i], c = rank_cnt[m_of * RANK_MAX + i];
+        const uint32_t key = list[m_of * CAP + i], c = rank_cnt[m_of * RANK_MAX + i];
         const unsigned long long before = s_sum_gt[m_of] + rank_gt[m_of * RANK_MAX + i], target = s_target[m_of];
         if (before < target && before + to_fx(__uint_as_float(key)) * (c >> 16) >= target) {      // (all that hold this key: the same values)
           s_tau[m_of] = key; s_bincnt[m_of] = c >> 16; s_cnt_gt[m_of] = s_above[m_of] + (c & 0xffffu);
@@ -532,7 +531,7 @@ __global__ __launch_bounds__(STATS_THREADS) __attribute__((amdgpu_waves_per_eu(M
       });
     } else {
       for (int m = 0; m < M; ++m)
-        for (int e = tid; e < (have == 1 ? listed(m) : glisted(m)); e += STATS_THREADS) add(m, have == 1 ? list[(m << CS) + e] : agent_load(glist + m * gcap + e));
+        for (int e = tid; e < (have == 1 ? listed(m) : glisted(m)); e += STATS_THREADS) add(m, have == 1 ? list[m * CAP + e] : agent_load(glist + m * gcap + e));
     }
     __syncthreads();
   }
@@ -580,35 +579,36 @@ size_t stats_split_bytes(int M, int nchunks) {
 }
 size_t split_head_bytes(int M, int nchunks) { return (stats_split_bytes(M, nchunks) + select_split_bytes(M, nchunks) + 255) / 256 * 256; }
 
-template <int MM, int PHASE>
-static hipError_t launch_stats_t(const StatsArgs& a, dim3 grid, size_t lds, hipStream_t st) {
-  if (lds > 48 * 1024) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&stats_kernel<MM, PHASE>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((stats_kernel<MM, PHASE>), grid, dim3(STATS_THREADS), lds, st, a);
+template <int MM, int PHASE, bool SMALL = false>
+static hipError_t launch_stats_t(const StatsArgs& a, dim3 grid, hipStream_t st) {
+  const size_t lds = (size_t)a.M * ((BINS + 64) * sizeof(unsigned long long) + LAST_BINS * sizeof(uint32_t) + LIST_MAX<MM, SMALL> * sizeof(uint32_t));
+  if (lds > 48 * 1024) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&stats_kernel<MM, PHASE, SMALL>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((stats_kernel<MM, PHASE, SMALL>), grid, dim3(STATS_THREADS), lds, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_stats(const Dims& dm, const madakv_config& c, const float* psi, const uint8_t* mask,
                         float* psi_pool, void* stats, int32_t* n_mod, const Exchange& x, hipStream_t st,
-                        void* split_buf, size_t split_bytes) {
+                        void* split_buf, size_t split_bytes, bool beside_gather) {
   StatsArgs a;
   a.psi = psi; a.mask = mask; a.psi_pool = psi_pool; a.stats = stats; a.n_mod = n_mod;
   a.B = dm.B; a.H = dm.H; a.L = dm.L; a.W = dm.W; a.nc = dm.nc; a.pool_r = (c.pool_k - 1) / 2;
   a.xchg = x.words; a.xchg_per_head = x.per_head;
   a.pool_mode = c.pool_mode; a.share_mode = c.share_mode; a.theta = (double)c.theta;
   a.M = c.n_modalities;
-  a.split = nullptr; a.split_stride = 0; a.list_shift = list_shift_of(a.M, dm.nc);
+  a.split = nullptr; a.split_stride = 0;
   static_assert(STATS_THREADS / 64 * WAVE_BUF <= 2 * (BINS + 64 + LAST_BINS / 2), "the waves' buffers must fit the masses and counts");
-  const size_t lds = (size_t)a.M * ((BINS + 64) * sizeof(unsigned long long) + LAST_BINS * sizeof(uint32_t) + (sizeof(uint32_t) << a.list_shift));
   const int nchunks = split_chunks(dm);
   const dim3 whole(dm.heads), chunks(nchunks, dm.heads);
   if (nchunks && split_buf && split_bytes >= dm.heads * split_head_bytes(a.M, nchunks)) {
     a.split = static_cast<char*>(split_buf);
     a.split_stride = (long long)split_head_bytes(a.M, nchunks);
-    hipError_t e = a.M == 2 ? launch_stats_t<2, 1>(a, chunks, lds, st) : launch_stats_t<4, 1>(a, chunks, lds, st);
-    if (e == hipSuccess) e = a.M == 2 ? launch_stats_t<2, 2>(a, chunks, lds, st) : launch_stats_t<4, 2>(a, chunks, lds, st);
+    hipError_t e = a.M == 2 ? launch_stats_t<2, 1>(a, chunks, st) : launch_stats_t<4, 1>(a, chunks, st);
+    if (e == hipSuccess) e = a.M == 2 ? launch_stats_t<2, 2>(a, chunks, st) : launch_stats_t<4, 2>(a, chunks, st);
     return e;
   }
-  return a.M == 2 ? launch_stats_t<2, 0>(a, whole, lds, st) : launch_stats_t<4, 0>(a, whole, lds, st);
+  if (beside_gather && a.nc <= SMALL_HEADS && a.M == 2) return launch_stats_t<2, 0, true>(a, whole, st);
+  return a.M == 2 ? launch_stats_t<2, 0>(a, whole, st) : launch_stats_t<4, 0>(a, whole, st);
 }
 
 }  // namespace madakv

@@ -641,10 +641,10 @@ def test_decode_pieces_that_come_into_being(kw):
 
 
 @pytest.mark.parametrize("L,W,M", [(3000, 8, 2), (9001, 8, 3), (20000, 8, 2), (40001, 8, 2), (70001, 8, 2), (70001, 8, 3), (200001, 16, 2)])
-def test_statistics_of_crowded_bins(L, W, M):
+def test_statistics_of_crowded_bins(L, W, M, monkeypatch):
     """Scores so close together that the bin where the running mass crosses theta holds a few, hundreds (ranked, or walked once
     more), thousands (more than a workgroup's list, or than the chunk's share of the head's) or all of the candidates, equal ones
-    among them; two layers in one call and one after the other.  The rules of test_statistics_at_edges."""
+    among them; two layers in one call, one after the other and in two groups.  The rules of test_statistics_at_edges."""
     scale = [0.0, 0.001, 0.01, 0.03, 0.1, 0.4]
     H, d, nc = len(scale), 64, L - W
     g = torch.Generator().manual_seed(L + M)
@@ -664,6 +664,11 @@ def test_statistics_of_crowded_bins(L, W, M):
         torch.cuda.synchronize()
     w_1, k_1 = eng.stats_host()
     assert np.array_equal(w_g, w_1) and np.array_equal(k_g, k_1) and torch.equal(pool, eng.psi_pool)
+    monkeypatch.setenv("MADAKV_LAYER_GROUPS", "2")              # the kernels that fit beside a gather
+    eng.evict(0, 2, q, k, k, mask)
+    torch.cuda.synchronize()
+    w_1, k_1 = eng.stats_host()
+    assert np.array_equal(w_g, w_1) and np.array_equal(k_g, k_1) and torch.equal(pool, eng.psi_pool)
     for l in range(2):
         psi = eng.psi[l, 0].cpu().numpy().astype(np.float64)
         w_o, k_o, _ = O.modality_stats(psi, mh, W, 0.9, 0, M)
@@ -676,10 +681,10 @@ def test_statistics_of_crowded_bins(L, W, M):
 
 
 @pytest.mark.parametrize("L,M", [(9000, 2), (9000, 3), (20001, 2), (40001, 2), (70001, 2), (70001, 4), (200001, 2)])
-def test_selection_of_crowded_bins(L, M):
+def test_selection_of_crowded_bins(L, M, monkeypatch):
     """Kept positions, bit for bit, where the threshold is among 2 to 5000 scores of one bin (or all of them), at and around
     what is ranked at once and what a list holds, in bins of either width and next to their boundary, with ties; two layers in
-    one call and one after the other."""
+    one call, one after the other and in two groups."""
     W, d, nc = 8, 64, L - 8
     sizes = [2, 63, 65, 255, 257, 1023, 1025, 2047, 2049, 5000, nc]
     H = len(sizes)
@@ -710,6 +715,11 @@ def test_selection_of_crowded_bins(L, M):
         eng.select_gather(l, 1, k[l:l + 1], k[l:l + 1], mask, **{x: t[l:l + 1] for x, t in args.items()})
     torch.cuda.synchronize()
     used = int(off[-1, -1] + ln[-1, -1])
+    assert torch.equal(kept[:used], eng.kept_idx[:used])
+    monkeypatch.setenv("MADAKV_LAYER_GROUPS", "2")              # the kernel that fits beside a gather
+    eng.kept_idx.fill_(-1)
+    eng.select_gather(0, 2, k, k, mask, **args)
+    torch.cuda.synchronize()
     assert torch.equal(kept[:used], eng.kept_idx[:used])
     kept = kept.cpu().numpy()
     for l in range(2):
