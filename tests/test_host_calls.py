@@ -190,19 +190,18 @@ def test_where_partial_results_of_decode_go(runtime, cfg):
 @pytest.mark.parametrize("cfg", [good(n_layers=4, ctx_len=16384, budget=2048), good(n_layers=2, n_q_heads=28, n_kv_heads=4, ctx_len=8192, budget=600),
                                  good(n_layers=3, n_q_heads=12, n_kv_heads=2, window=40, ctx_len=3001, budget=600, head_dim=64)],
                          ids=lambda c: f"q{c.n_q_heads}_kv{c.n_kv_heads}_w{c.window}")
-def test_scoring_workspaces_hold_no_exchange_words(runtime, cfg):
-    """The words that workgroups exchange are the handle's; a caller's workspace is the counter, the shares of O and of psi of
-    the window attention's row blocks, the row statistics of the two-sweep kernels."""
+def test_window_workspace_holds_no_exchange_words(runtime, cfg):
+    """The words that workgroups exchange are the handle's; a caller's workspace of the window attention is the counter and the
+    row blocks' shares of O and of psi."""
     heads, rows, L, d = cfg.n_layers * cfg.batch * cfg.n_kv_heads, cfg.n_q_heads // cfg.n_kv_heads * cfg.window, cfg.ctx_len, cfg.head_dim
     up = lambda x, n: (x + n - 1) // n * n
     blocks, chunks = up(rows, 32) // 32, up(L, 512 if d == 128 else 768) // (512 if d == 128 else 768)
     window = 256 + up(heads * blocks * chunks * 32 * d * 4, 256) + (blocks * heads * L * 4 if blocks > 1 else 0)
-    score = 512 + up(heads * (L // 256 + 1) * up(rows, 32) * 8, 256)             # chunks of at least 256 keys
     scenario(runtime, f"""
         h = create(sys.argv[3])
-        a, b, n = Z(), Z(), I({cfg.n_layers})
-        assert lib.madakv_workspace_bytes(h, n, C.byref(a), None, None) == 0 and lib.madakv_window_attn_workspace_bytes(h, n, C.byref(b)) == 0
-        assert b.value <= {window} and a.value <= {score}, (a.value, {score}, b.value, {window})
+        b = Z()
+        assert lib.madakv_window_attn_workspace_bytes(h, I({cfg.n_layers}), C.byref(b)) == 0
+        assert b.value == {window}, (b.value, {window})
         """, cfg)
 
 
