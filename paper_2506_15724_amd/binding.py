@@ -280,7 +280,7 @@ class MadaKV:
             raise ValueError(f"out must hold {numel} elements of {want} (out_fp32={self.cfg.out_fp32}); got {out.numel()} of {out.dtype}")
 
     def decode_attn(self, l0, n, q, k_new, v_new, out):
-        # One call per layer and token: with 4 KV heads the kernel takes 8.3 us and this is what a token waits for.  So no
+        # One call per layer and token: with 4 KV heads the kernel takes 8 us and this is what a token waits for.  So no
         # views of the own buffers and no intermediate call: 7.0 us on the host (8.1 as decode_attn_static makes them).
         self._check_out(out, n * self._out_row)
         heads0 = l0 * self._heads

@@ -18,7 +18,7 @@
 //
 // Measured per layer call, with a merge kernel behind the attention kernel -> in one launch: 128 heads of ~2K bf16 rows,
 // 135 MB, 28.6 -> 26.8 us (the rows alone take 21.7 at the rate of a large read), 8-bit rows 18.7 -> 16.6, 4 heads of 2K rows
-// with 7 queries each 10.5 -> 8.3.  What the end of a piece costs, from the last row to the output: 0.35 us among the lanes
+// with 7 queries each 10.5 -> 8.1.  What the end of a piece costs, from the last row to the output: 0.35 us among the lanes
 // of a wave (row swaps and rotations; shuffles through LDS took 0.75), 0.4 among the waves, 0.6 for acknowledgement and
 // arrival, 0.7-1.3 for reading the pieces, 0.3 for the output.  It is instructions as much as trips to memory: a merge by
 // the whole workgroup with 8-byte accesses, polling for words not yet there instead of counting, took 3.5 us longer than
