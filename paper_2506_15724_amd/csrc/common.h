@@ -39,10 +39,9 @@ int page_table_entries(const madakv_config& c);
 
 // How the pieces a decode call cuts a head into meet (decode.hip); owned by the handle.  Their partial results are in the
 // call's workspace.
-constexpr int MEET_WAVES = 4;            // counters of a head of grouped queries (a single query head: one)
 constexpr int MEET_COUNT_STRIDE = 32;    // a counter has 128 bytes to itself
 struct Meet {
-  uint32_t* count;          // [n_layers * B * H][MEET_WAVES if G > 1][MEET_COUNT_STRIDE] arrivals, zero between calls
+  uint32_t* count;          // [n_layers * B * H][G][MEET_COUNT_STRIDE] arrivals, zero between calls
   int32_t* len1;            // [n_layers * B * H] 1 + the rows the eviction left each head, 0 before the first one
 };
 

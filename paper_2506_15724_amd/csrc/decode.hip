@@ -18,7 +18,7 @@
 //
 // Measured per layer call, with a merge kernel behind the attention kernel -> in one launch: 128 heads of ~2K bf16 rows,
 // 135 MB, 28.6 -> 26.8 us (the rows alone take 21.7 at the rate of a large read), 8-bit rows 18.7 -> 16.6, 4 heads of 2K rows
-// with 7 queries each 10.5 -> 8.1.  What the end of a piece costs, from the last row to the output: 0.35 us among the lanes
+// with 7 queries each 10.5 -> 8.8 (7.6 with the kernel as it is now).  What the end of a piece costs, from the last row to the output: 0.35 us among the lanes
 // of a wave (row swaps and rotations; shuffles through LDS took 0.75), 0.4 among the waves, 0.6 for acknowledgement and
 // arrival, 0.7-1.3 for reading the pieces, 0.3 for the output.  It is instructions as much as trips to memory: a merge by
 // the whole workgroup with 8-byte accesses, polling for words not yet there instead of counting, took 3.5 us longer than
@@ -38,6 +38,11 @@ constexpr float DNEG_BIG = -1.0e30f;
 constexpr int DEC_THREADS = 256;
 typedef __attribute__((ext_vector_type(4))) unsigned int du32x4_t;
 typedef __attribute__((ext_vector_type(2))) unsigned int du32x2_t;
+typedef __attribute__((ext_vector_type(8))) __bf16 dbf16x8_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 dbf16x2_t;
+typedef __attribute__((ext_vector_type(4))) float df32x4_t;
+typedef __attribute__((ext_vector_type(2))) float df32x2_t;
+typedef __attribute__((ext_vector_type(4))) short ds16x4_t;
 
 struct DecodeArgs {
   const void* q; const void* k_new; const void* v_new; void* k_c; void* v_c;
@@ -48,6 +53,8 @@ struct DecodeArgs {
   float* part;          // [heads][slots][G][d] partial results of the pieces of the call's heads
   float* part_ml;       // [heads][slots][G][2] their (max, sum)
   int slots;            // most pieces of a head
+  uint32_t by_heads;    // ceil(2^32 / heads), likewise, where heads * (heads + pieces) < 2^32
+  uint32_t by_chunk;    // ceil(2^32 / chunk_rows): quotients of numbers below 2^21, 0 where a head may be longer (see pieces_of)
   Meet meet;            // how they meet
   long long capacity;   // rows in k_c / v_c
   // paged cache (page_rows > 0): see struct Paging
@@ -139,9 +146,10 @@ struct RowMap {
   }
 };
 
+template <bool PAGED>
 __device__ __forceinline__ bool can_append_to(const DecodeArgs& a, long long off, int len_old) {
   // an empty segment (its budgets did not fit the cache) stays empty; contiguous segments also end at the cache's end
-  return a.has_new && len_old > 0 && (a.page_rows ? true : off + len_old < a.capacity);
+  return a.has_new && len_old > 0 && (PAGED || off + len_old < a.capacity);
 }
 
 // All threads of the workgroup.  rows [r_begin, r_end) are the workgroup's; when the appended row is
@@ -183,28 +191,33 @@ __device__ __forceinline__ int head_chunk_rows(const DecodeArgs& a, int len) {
   return ((len + a.max_chunks - 1) / a.max_chunks + 31) / 32 * 32;
 }
 
+// ceil(len / chunk_rows).  As a product: len + chunk_rows - 1 < 2^21 and chunk_rows <= 2^10, so what by_chunk is too large by
+// (below chunk_rows / 2^32) stays below 1 in units of the next quotient.
+__device__ __forceinline__ int pieces_of(const DecodeArgs& a, int len) {
+  const uint32_t x = (uint32_t)(len + a.chunk_rows - 1);
+  return a.by_chunk ? (int)__umulhi(x, a.by_chunk) : (int)(x / (uint32_t)a.chunk_rows);
+}
+
 // The head a workgroup works on.  Workgroups go to the 8 XCDs in turn; with the head as the fast grid dimension all
 // pieces of a head would meet on one XCD (128 heads), and XCDs with long heads would finish last: the pieces of a head
 // are rotated over the XCDs instead.
-__device__ __forceinline__ int piece_head() {
-  const int x = (int)blockIdx.x + (int)blockIdx.y;
-  return x < (int)gridDim.x ? x : x % (int)gridDim.x;
+__device__ __forceinline__ int piece_head(const DecodeArgs& a) {
+  const uint32_t x = blockIdx.x + blockIdx.y;
+  if (x < gridDim.x) return (int)x;
+  return (int)(x - (a.by_heads ? __umulhi(x, a.by_heads) : x / gridDim.x) * gridDim.x);
 }
 
-// The appended row in the cache's element type: written to the cache (Eq. 4) and left in LDS, K then V, for the tile it
-// belongs to.  All threads; `row` is its place in the cache.  (Kept out of the load path of the tiles: the encoding of
-// an 8-bit row, unrolled there, had made 48 KB of the grouped-query kernel.  Fetching a thread's element before the
-// head's length is known gains nothing: 27.7 against 27.4 us per call, in every workgroup for the sake of one per head.)
-template <typename T, typename CT, int D>
-__device__ __forceinline__ void stage_new_row(const DecodeArgs& a, long long hidx, long long row, CT* s_new) {
+// The appended row of the 8-bit cache, encoded: written to the cache (Eq. 4) and left in LDS, K then V, for the tile it
+// belongs to.  All threads; `row` is its place in the cache.  (Kept out of the load path of the tiles: the encoding,
+// unrolled there, had made 48 KB of the grouped-query kernel, and by the wave of the tile, in its loop, it costs a single
+// query head's calls 2%.)
+template <int D>
+__device__ __forceinline__ void stage_new_row(const DecodeArgs& a, long long hidx, long long row, uint8_t* s_new) {
   for (int e = threadIdx.x; e < 2 * D; e += (int)blockDim.x) {
     const bool is_k = e < D;
     const int c = is_k ? e : e - D;
-    const T x = (reinterpret_cast<const T*>(is_k ? a.k_new : a.v_new))[hidx * D + c];
-    CT y;
-    if constexpr (sizeof(T) == sizeof(CT)) y = __builtin_bit_cast(CT, x);
-    else y = (CT)f32_to_e4m3(bf16_bits_to_f32(x));
-    (reinterpret_cast<CT*>(is_k ? a.k_c : a.v_c))[row * D + c] = y;
+    const uint8_t y = (uint8_t)f32_to_e4m3(bf16_bits_to_f32((reinterpret_cast<const uint16_t*>(is_k ? a.k_new : a.v_new))[hidx * D + c]));
+    (reinterpret_cast<uint8_t*>(is_k ? a.k_c : a.v_c))[row * D + c] = y;
     s_new[e] = y;
   }
   __syncthreads();
@@ -250,9 +263,8 @@ __device__ __forceinline__ void merge_lanes(float& m, float& l, float (&acc)[N])
 // which the last one to arrive has replaced by the time a workgroup further back in the grid starts.
 __device__ __forceinline__ int arrivals(const DecodeArgs& a, int len1) {
   if (len1 == 0) return (int)gridDim.y;
-  return max(1, min((int)gridDim.y, (len1 - 1 + a.max_new + a.chunk_rows - 1) / a.chunk_rows));
+  return max(1, min((int)gridDim.y, pieces_of(a, len1 - 1 + a.max_new)));
 }
-
 // four neighbouring elements of the output
 template <typename T>
 __device__ __forceinline__ void store_out4(const DecodeArgs& a, long long o, float4 x, float ls) {
@@ -260,9 +272,9 @@ __device__ __forceinline__ void store_out4(const DecodeArgs& a, long long o, flo
   if (a.out_fp32 || sizeof(T) == 4) {
     *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + o) = x;
   } else {
-    const uint32_t lo = (uint32_t)f32_to_bf16_rne(x.x) | ((uint32_t)f32_to_bf16_rne(x.y) << 16);
-    const uint32_t hi = (uint32_t)f32_to_bf16_rne(x.z) | ((uint32_t)f32_to_bf16_rne(x.w) << 16);
-    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + o) = make_uint2(lo, hi);
+    const df32x2_t lo = {x.x, x.y}, hi = {x.z, x.w};                    // (to nearest even, in one instruction each)
+    const uint2 y = make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, dbf16x2_t)), __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, dbf16x2_t)));
+    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + o) = y;
   }
 }
 // Partial results go past the caches that other XCDs do not see (the sc1 bit, which is what an agent-scope atomic access
@@ -278,42 +290,47 @@ constexpr int NOWHERE = 0x7ffffff0;      // past the end of any of them: a read 
 // for itself, with counters of its own: 64 / (D / 4) query heads per wave, four elements per lane (a single query head:
 // the first wave alone, whose lanes share the pieces); a wave has its stores acknowledged, arrives, and leaves unless it is
 // the last.
-template <typename T, int D, int NW, int GT>
+// s_ml: [NW][GT] (max, sum); s_acc: a wave's results WS floats behind those of the wave before it, AR floats per query head.
+template <typename T, int D, int NW, int GT, int WS, int AR>
 __device__ __forceinline__ void finish_piece(const DecodeArgs& a, long long hidx, int chunk, int len, int rows, bool can_append, int arrive,
-                                             const float (*s_ml)[GT][2], const float (*s_acc)[GT][D]) {
-  constexpr int TL = D / 4, QW = 64 / TL, KP = GT == 1 ? QW : 1, MB = GT == 1 ? 8 : 16;   // MB: pieces in flight per lane
+                                             const float (*s_ml)[GT][2], const float* s_acc) {
+  constexpr int TL = D / 4, QW = 64 / TL;
+  constexpr bool OWN = NW >= GT;                             // a query head per wave, whose lanes share the pieces
+  constexpr int KP = OWN ? QW : 1, MB = OWN ? 8 : 16;        // MB: pieces in flight per lane
+  constexpr int WK = GT > 1 && OWN ? KP : 1;                 // (grouped queries: the waves' results, too)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (GT == 1 ? wave > 0 : wave * QW >= a.G) return;
-  const int t = lane % TL, kp = GT == 1 ? lane / TL : 0, g = GT == 1 ? 0 : wave * QW + lane / TL;
-  const bool act = GT == 1 ? kp == 0 : g < a.G;
-  const int pieces = len <= rows ? 1 : (len + rows - 1) / rows;
+  if (wave * (OWN ? 1 : QW) >= (GT == 1 ? 1 : a.G)) return;
+  const int t = lane % TL, kp = OWN ? lane / TL : 0, g = OWN ? wave : wave * QW + lane / TL;
+  const bool act = OWN ? kp == 0 : g < a.G;
+  const int pieces = len <= rows ? 1 : rows == a.chunk_rows ? pieces_of(a, len) : (len + rows - 1) / rows;
   const long long o = (hidx * a.G + g) * D + 4 * t;
   // records of a head: [slots][G][D] accumulated elements, [slots][G] (max, sum)
   const int step = a.G * D * 4, step_ml = a.G * 8;
   const __amdgpu_buffer_rsrc_t rec = agent_buffer(a.part + hidx * a.slots * a.G * D, a.slots * step);
   const __amdgpu_buffer_rsrc_t rec_ml = agent_buffer(a.part_ml + hidx * a.slots * a.G * 2, a.slots * step_ml);
-  if (chunk < pieces && act) {
-    float mx = DNEG_BIG, ls = 0.f;
-    float4 av = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (chunk < pieces && (act || WK > 1)) {
+    float mx = DNEG_BIG, ls = 0.f, av[4] = {0.f, 0.f, 0.f, 0.f};
+    const int w0 = WK > 1 ? kp * (NW / WK) : 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) mx = fmaxf(mx, s_ml[w][g][0]);
+    for (int w = 0; w < NW / WK; ++w) mx = fmaxf(mx, s_ml[w0 + w][g][0]);
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float c = weight_of(s_ml[w][g][0] - mx);
-      const float4 x = *reinterpret_cast<const float4*>(&s_acc[w][g][4 * t]);
-      ls += s_ml[w][g][1] * c;
-      av.x += x.x * c; av.y += x.y * c; av.z += x.z * c; av.w += x.w * c;
+    for (int w = 0; w < NW / WK; ++w) {
+      const float c = weight_of(s_ml[w0 + w][g][0] - mx);
+      const float4 x = *reinterpret_cast<const float4*>(s_acc + (w0 + w) * WS + g * AR + 4 * t);
+      ls += s_ml[w0 + w][g][1] * c;
+      av[0] += x.x * c; av[1] += x.y * c; av[2] += x.z * c; av[3] += x.w * c;
     }
+    if (WK > 1) merge_lanes<TL, 4>(mx, ls, av);
     if (pieces == 1) {
-      store_out4<T>(a, o, av, ls);
-    } else {
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(du32x4_t, av), rec, (g * D + 4 * t) * 4, chunk * step, AGENT);
+      if (act) store_out4<T>(a, o, make_float4(av[0], av[1], av[2], av[3]), ls);
+    } else if (act) {
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(du32x4_t, make_float4(av[0], av[1], av[2], av[3])), rec, (g * D + 4 * t) * 4, chunk * step, AGENT);
       if (t == 0) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(du32x2_t, make_float2(mx, ls)), rec_ml, g * 8, chunk * step_ml, AGENT);
     }
   }
   if (arrive > 1) {
     const long long head = a.head0 + hidx;
-    uint32_t* count = a.meet.count + (GT == 1 ? head : head * MEET_WAVES + wave) * MEET_COUNT_STRIDE;
+    uint32_t* count = a.meet.count + (GT == 1 ? head : head * a.G + wave) * MEET_COUNT_STRIDE;
     uint32_t arrived = 0u;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the wave's stores are where everybody sees them
     if (lane == 0) arrived = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -322,8 +339,8 @@ __device__ __forceinline__ void finish_piece(const DecodeArgs& a, long long hidx
     if (lane == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (pieces > 1) {
       float m = DNEG_BIG, ls = 0.f, av[4] = {0.f, 0.f, 0.f, 0.f};
-      const int gg = act || GT == 1 ? g : 0;                   // (lanes without a query head read along)
-      const int at = ((kp + gg) * D + 4 * t) * 4, at_ml = (kp + gg) * 8;       // (kp > 0: a single query head)
+      const int gg = act || OWN ? g : 0;                       // (lanes without a query head read along)
+      const int at = ((kp * a.G + gg) * D + 4 * t) * 4, at_ml = (kp * a.G + gg) * 8;
       const int left = min(pieces, a.slots);                   // (a head longer than the launch was sized for: what there is of it)
       const auto merge = [&](const float4 (&x)[MB], const float2 (&ml)[MB]) {
         float bm = m;
@@ -380,11 +397,12 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
   constexpr int D = LPR * EPL;
   __shared__ float s_ml[NW][GT][2];
   __shared__ __attribute__((aligned(16))) float s_acc[NW][GT][D];
-  __shared__ __attribute__((aligned(16))) CT s_new[2 * D];
+  constexpr bool ENCODE = sizeof(CT) != sizeof(T);
+  __shared__ __attribute__((aligned(16))) uint8_t s_new[ENCODE ? 2 * D : 16];
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane / LPR, piece = lane % LPR;
-  const long long hidx = piece_head();               // (layer, batch, kv head) of the call
+  const long long hidx = piece_head(a);               // (layer, batch, kv head) of the call
   const int chunk = blockIdx.y;                      // which piece of the head
   const int len1 = a.meet.len1[a.head0 + hidx], len_old = a.kv_len[hidx];
   const long long off = a.kv_off[hidx];
@@ -397,17 +415,18 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
     for (int e = 0; e < EPL; ++e) qf[g][e] = 0.f;
     if (g < a.G) load_floats<T, EPL>(qg + (long long)g * D + piece * EPL, qf[g]);
   }
+  asm volatile("" :: "s"(len1), "s"(len_old), "s"((int)off));          // (all three in one trip)
   const int arrive = arrivals(a, len1);
   if (chunk >= arrive) return;                       // the grid is the same for all heads (decode_plan)
   // an empty segment (its budgets did not fit the cache) stays empty: no append, output 0/0 = NaN
-  const bool can_append = can_append_to(a, off, len_old);
+  const bool can_append = can_append_to<PAGED>(a, off, len_old);
   const int len = len_old + (can_append ? 1 : 0);
   const int rows = head_chunk_rows(a, len);
   const int r_begin = chunk * rows;                  // (past the head's end: no rows, the workgroup only arrives)
   const int r_end = min(len, r_begin + rows);
   const RowMap at = make_row_map<PAGED>(a, hidx, off, len_old, can_append, r_begin, r_end);
   const bool has_fresh = can_append && len_old >= r_begin && len_old < r_end;   // uniform: the appended row is in this piece
-  if (has_fresh) stage_new_row<T, CT, D>(a, hidx, at(len_old), s_new);
+  if constexpr (ENCODE) { if (has_fresh) stage_new_row<D>(a, hidx, at(len_old), s_new); }
   // the NW waves take turns on consecutive RPI * UNROLL-row slices, so that at any moment the
   // workgroup reads one contiguous stretch of K and one of V
   constexpr int WSTEP = RPI * UNROLL;
@@ -438,13 +457,23 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
         kraw[u] = stream_load16(kc + o); vraw[u] = stream_load16(vc + o);
       }
     }
-    if (has_fresh && row0 <= len_old && len_old < row0 + WSTEP) {        // the appended row comes from LDS
+    if (has_fresh && row0 <= len_old && len_old < row0 + WSTEP) {        // the appended row (rows past it are masked)
+      uint4 knew, vnew;
+      if constexpr (ENCODE) {
+        knew = *reinterpret_cast<const uint4*>(s_new + piece * EPL);
+        vnew = *reinterpret_cast<const uint4*>(s_new + D + piece * EPL);
+      } else {
+        knew = *reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.k_new) + hidx * D + piece * EPL);
+        vnew = *reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.v_new) + hidx * D + piece * EPL);
+        if (sub == 0) {
+          const long long o = at(len_old) * D + piece * EPL;
+          *reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.k_c) + o) = knew;
+          *reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.v_c) + o) = vnew;
+        }
+      }
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u)
-        if (row0 + u * RPI + sub >= len_old) {                              // (rows past it are masked)
-          kraw[u] = *reinterpret_cast<const uint4*>(s_new + piece * EPL);
-          vraw[u] = *reinterpret_cast<const uint4*>(s_new + D + piece * EPL);
-        }
+        if (row0 + u * RPI + sub >= len_old) { kraw[u] = knew; vraw[u] = vnew; }
     }
     if (row0 + WSTEP > r_end) {                                             // what is masked contributes 0 * 0
 #pragma unroll
@@ -501,7 +530,7 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
     }
   }
   __syncthreads();
-  finish_piece<T, D, NW, GT>(a, hidx, chunk, len, rows, can_append, arrive, s_ml, s_acc);
+  finish_piece<T, D, NW, GT, GT * D, D>(a, hidx, chunk, len, rows, can_append, arrive, s_ml, &s_acc[0][0][0]);
 }
 
 // ------------------------------------------------------------------------------------
@@ -520,15 +549,17 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
 // The running max / sum live per query in the lanes of S^T; the rescale factors are fetched
 // into the O layout with four lane reads per tile.
 // A layer of a grouped-query model has few KV heads and a few MB of cache: the kernel is bound by the latencies of
-// one workgroup (start, length, rows, two contractions, merge), among them the fetching of its instructions, which are
-// cold at every launch.  So a wave has one tile in the usual piece of 128 rows, the load path appears once and the
-// appended row comes in through LDS.
+// one workgroup (start, length, rows, two contractions, merge), of which a wave's instructions, issued one per four
+// cycles, are the larger part.  So a workgroup has eight waves with one tile of 16 rows each in the usual piece of 128: half
+// of the instructions of a 32-row tile, a query head per wave in the merges, twice the loads in flight.  A tile of 16 keys
+// fills the contraction index of P.V with the hi and the lo parts of P against the same rows of V; O comes out transposed (a lane
+// has four neighbouring dims of one query: rescaled by its own factor, left in LDS in 16-byte pieces); the first tile adds
+// to nothing and rescales nothing; the appended row is fetched from k_new / v_new in place of the cache row.
+// The rows are read with ordinary loads: a K fragment takes half of a cache line, and a non-temporal load would fetch the
+// line a second time for the other half.  Per layer call, four waves of 32 rows with non-temporal loads -> this: 4 heads of
+// 2K rows, 7 queries, 8.8 -> 7.6 us (half of it the ordinary loads); 16 heads of 2K rows 11.4 -> 9.9; 32 heads of 4K rows, 4
+// queries, 14.5 -> 11.5; 2 heads of 40K rows, 6 queries, 18.4 -> 12.6.
 // ------------------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(8))) __bf16 dbf16x8_t;
-typedef __attribute__((ext_vector_type(2))) __bf16 dbf16x2_t;
-typedef __attribute__((ext_vector_type(4))) float df32x4_t;
-typedef __attribute__((ext_vector_type(2))) float df32x2_t;
-typedef __attribute__((ext_vector_type(4))) short ds16x4_t;
 typedef __attribute__((address_space(3))) ds16x4_t* lds_s16x4_ptr_t;
 
 // 4 E4M3 bytes -> 4 bf16 (exact: 3 mantissa bits fit bf16's 7), as two packed dwords
@@ -540,123 +571,129 @@ __device__ __forceinline__ du32x2_t e4m3x4_to_bf16x4(uint32_t w) {
   return o;
 }
 
+constexpr int GQA_WAVES = 8;
 template <int D, bool FP8, bool PAGED>   // FP8: the cache rows are E4M3 bytes, turned into bf16 operands on the fly
-__global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
-  using CT = typename std::conditional<FP8, uint8_t, uint16_t>::type;
-  constexpr int GT = 8;                // query heads per KV head supported (rows 8..15 of the MFMA tile are padding)
-  constexpr int NW = 4;
+__global__ __launch_bounds__(GQA_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_gqa_kernel(DecodeArgs a) {
+  constexpr int GT = 8;                // query heads per KV head supported (columns 8..15 of the MFMA tile are padding)
+  constexpr int NW = GQA_WAVES;
+  constexpr int TR = 16;               // rows of a wave's tile
   constexpr int KS = D / 32;           // MFMA steps over the head dimension
   constexpr int DB = D / 16;           // 16-column blocks of the output
   constexpr int RS = D + 16;           // bf16 elements per LDS row of the V tile (rows 8 banks apart: the transposing reads of a wave do not collide)
+  constexpr int AR = D + 4;            // floats per query head of a wave's results
   constexpr int CB = FP8 ? 1 : 2;      // bytes per cache element
   constexpr int LPR = D * CB / 16;     // lanes per row in a coalesced 16-byte load
   constexpr int VE = 16 / CB;          // V elements per lane and load
   constexpr int RPI = 64 / LPR;        // rows per load instruction
-  constexpr int VL = 32 / RPI;         // load instructions per 32-row V tile
+  constexpr int VL = TR / RPI;         // load instructions per V tile
+  constexpr int WB = TR * RS * 2 > GT * AR * 4 ? TR * RS * 2 : GT * AR * 4;        // bytes of a wave's V tile, later of its results
   __shared__ float s_ml[NW][GT][2];
-  __shared__ __attribute__((aligned(16))) uint16_t s_v[NW][32][RS];
-  __shared__ __attribute__((aligned(16))) CT s_new[2 * D];
-  // the per-wave results reuse the V tiles once every wave is through with them
-  static_assert(sizeof(float) * NW * GT * D <= sizeof(uint16_t) * NW * 32 * RS, "results must fit the V tiles");
-  float (*s_acc)[GT][D] = reinterpret_cast<float (*)[GT][D]>(&s_v[0][0][0]);
+  __shared__ __attribute__((aligned(16))) unsigned char s_wave[NW][WB];
+  __shared__ __attribute__((aligned(16))) uint8_t s_new[FP8 ? 2 * D : 16];
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j16 = lane & 15, c = lane >> 4;
-  const long long hidx = piece_head();
+  const long long hidx = piece_head(a);
   const int chunk = blockIdx.y;
   const int len1 = a.meet.len1[a.head0 + hidx], len_old = a.kv_len[hidx];
   const long long off = a.kv_off[hidx];
-  // Q as the B operand: lane (q = j16, c) holds dims [32 ks + 8 c, +8) of query q
+  // Q as the B operand: lane (q = j16, c) holds dims [32 ks + 8 c, +8) of query q (padding columns: the last query once more)
   dbf16x8_t qb[KS];
-  const uint16_t* qg = reinterpret_cast<const uint16_t*>(a.q) + hidx * a.G * D;
+  const uint16_t* qg = reinterpret_cast<const uint16_t*>(a.q) + hidx * a.G * D + min(j16, a.G - 1) * D + c * 8;
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    du32x4_t raw = {0u, 0u, 0u, 0u};
-    if (j16 < a.G) raw = *reinterpret_cast<const du32x4_t*>(qg + (long long)j16 * D + ks * 32 + c * 8);
-    qb[ks] = __builtin_bit_cast(dbf16x8_t, raw);
-  }
+  for (int ks = 0; ks < KS; ++ks) qb[ks] = __builtin_bit_cast(dbf16x8_t, *reinterpret_cast<const du32x4_t*>(qg + ks * 32));
+  asm volatile("" :: "s"(len1), "s"(len_old), "s"((int)off));             // (all three in one trip)
   const int arrive = arrivals(a, len1);
-  if (chunk >= arrive) return;
-  const bool can_append = can_append_to(a, off, len_old);
+  if (chunk >= arrive) return;                       // the grid is the same for all heads (decode_plan)
+  const bool can_append = can_append_to<PAGED>(a, off, len_old);
   const int len = len_old + (can_append ? 1 : 0);
   const int rows = head_chunk_rows(a, len);
   const int r_begin = chunk * rows;
   const int r_end = min(len, r_begin + rows);
   const RowMap at = make_row_map<PAGED>(a, hidx, off, len_old, can_append, r_begin, r_end);
   const bool has_fresh = can_append && len_old >= r_begin && len_old < r_end;   // uniform: the appended row is in this piece
-  if (has_fresh) stage_new_row<uint16_t, CT, D>(a, hidx, at(len_old), s_new);
 
   // the piece's first row (cache rows of D * CB bytes); the rows' offsets from it fit 32 bits
-  const unsigned char* kc = reinterpret_cast<const unsigned char*>(a.k_c) + (PAGED ? 0 : (off + r_begin) * (D * CB));
-  const unsigned char* vc = reinterpret_cast<const unsigned char*>(a.v_c) + (PAGED ? 0 : (off + r_begin) * (D * CB));
-
-  float m_run = DNEG_BIG, l_run = 0.f;       // for query j16 (every lane group c holds a copy of m, a share of l)
-  df32x4_t oacc[DB];                         // O[q = 4c + r][d = 16 db + j16]
-#pragma unroll
-  for (int db = 0; db < DB; ++db) oacc[db] = df32x4_t{0.f, 0.f, 0.f, 0.f};
-  uint16_t* vt = &s_v[wave][0][0];
+  unsigned char* kc = reinterpret_cast<unsigned char*>(a.k_c) + (PAGED ? 0 : (off + r_begin) * (D * CB));
+  unsigned char* vc = reinterpret_cast<unsigned char*>(a.v_c) + (PAGED ? 0 : (off + r_begin) * (D * CB));
+  const unsigned char* kn = reinterpret_cast<const unsigned char*>(a.k_new) + hidx * (D * 2);
+  const unsigned char* vn = reinterpret_cast<const unsigned char*>(a.v_new) + hidx * (D * 2);
   const int vsub = lane / LPR, vpiece = lane % LPR;
+  const auto row_at = [&](unsigned char* base, int r) { return PAGED ? base + at(r) * (D * CB) : base + (uint32_t)(r - r_begin) * (uint32_t)(D * CB); };
 
-  // K fragments and V rows of the wave's tile; rows past the end of the piece: its last row once more, masked where
-  // they are used.  (The waves of other workgroups keep the memory busy while this one computes.)
-  for (int t0 = r_begin + wave * 32; t0 < r_end; t0 += NW * 32) {
-    du32x4_t kraw[2][KS], vraw[VL];            // raw cache bytes (E4M3: 8 bytes of a K piece sit in kraw[..][..].xy)
+  // K fragments and V rows of a tile; rows past the end of the piece: its last row once more, masked where they are used.
+  // The appended row comes from k_new and v_new (8-bit rows: from LDS, encoded).
+  du32x4_t kraw[KS], vraw[VL];             // raw cache bytes (E4M3: 8 bytes of a K piece sit in .xy)
+  const auto load_tile = [&](int t) {
+    const int r = min(t + j16, r_end - 1);
+    const unsigned char* kp = row_at(kc, r);
+    if (!FP8 && has_fresh && r == len_old) kp = kn;
 #pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      const int r = min(t0 + blk * 16 + j16, r_end - 1);
-      const unsigned char* kp = PAGED ? kc + at(r) * (D * CB) : kc + (uint32_t)(r - r_begin) * (uint32_t)(D * CB);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (FP8) { const du32x2_t t2 = __builtin_nontemporal_load(reinterpret_cast<const du32x2_t*>(kp + ks * 32 + c * 8)); kraw[blk][ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
-        else kraw[blk][ks] = __builtin_nontemporal_load(reinterpret_cast<const du32x4_t*>(kp + ks * 64 + c * 16));
-      }
+    for (int ks = 0; ks < KS; ++ks) {
+      if (FP8) { const du32x2_t t2 = *reinterpret_cast<const du32x2_t*>(kp + ks * 32 + c * 8); kraw[ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
+      else kraw[ks] = *reinterpret_cast<const du32x4_t*>(kp + ks * 64 + c * 16);
     }
 #pragma unroll
     for (int i = 0; i < VL; ++i) {
-      const int r = min(t0 + i * RPI + vsub, r_end - 1);
-      const unsigned char* vp = PAGED ? vc + at(r) * (D * CB) : vc + (uint32_t)(r - r_begin) * (uint32_t)(D * CB);
-      vraw[i] = __builtin_nontemporal_load(reinterpret_cast<const du32x4_t*>(vp + vpiece * 16));
+      const int r = min(t + i * RPI + vsub, r_end - 1);
+      const unsigned char* vp = row_at(vc, r);
+      if (!FP8 && has_fresh && r == len_old) vp = vn;
+      vraw[i] = *reinterpret_cast<const du32x4_t*>(vp + vpiece * 16);
     }
-    if (has_fresh && t0 <= len_old && len_old < t0 + 32) {          // the appended row (the last of the piece) comes from LDS
+  };
+  const int first = r_begin + wave * TR;
+  if (first < r_end) load_tile(first);
+  if constexpr (FP8) { if (has_fresh) stage_new_row<D>(a, hidx, at(len_old), s_new); }       // (behind the loads)
+
+  float m_run = DNEG_BIG, l_run = 0.f;       // for query j16 (every lane group c holds a copy of m, a share of l)
+  df32x4_t oacc[DB];                         // O^T[d = 16 db + 4c + r][q = j16]
+  uint16_t* vt = reinterpret_cast<uint16_t*>(s_wave[wave]);
+  const auto tile = [&](auto is_first, int t0) {
+    constexpr bool FIRST = decltype(is_first)::value;
+    if (!FIRST) load_tile(t0);
+    if (has_fresh && t0 <= len_old && len_old < t0 + TR) {          // the appended row, the last of the piece
+      if constexpr (FP8) {
+        if (t0 + j16 >= len_old) {
 #pragma unroll
-      for (int blk = 0; blk < 2; ++blk)
-        if (t0 + blk * 16 + j16 >= len_old) {
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            if (FP8) { const du32x2_t t2 = *reinterpret_cast<const du32x2_t*>(s_new + ks * 32 + c * 8); kraw[blk][ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
-            else kraw[blk][ks] = *reinterpret_cast<const du32x4_t*>(s_new + ks * 32 + c * 8);
-          }
+          for (int ks = 0; ks < KS; ++ks) { const du32x2_t t2 = *reinterpret_cast<const du32x2_t*>(s_new + ks * 32 + c * 8); kraw[ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
         }
 #pragma unroll
-      for (int i = 0; i < VL; ++i)
-        if (t0 + i * RPI + vsub >= len_old) vraw[i] = *reinterpret_cast<const du32x4_t*>(s_new + D + vpiece * VE);
+        for (int i = 0; i < VL; ++i)
+          if (t0 + i * RPI + vsub >= len_old) vraw[i] = *reinterpret_cast<const du32x4_t*>(s_new + D + vpiece * VE);
+      } else {                                                      // on its way to the cache
+        unsigned char* kp = row_at(kc, len_old);
+        unsigned char* vp = row_at(vc, len_old);
+        if (t0 + j16 == len_old)
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<du32x4_t*>(kp + ks * 64 + c * 16) = kraw[ks];
+#pragma unroll
+        for (int i = 0; i < VL; ++i)
+          if (t0 + i * RPI + vsub == len_old) *reinterpret_cast<du32x4_t*>(vp + vpiece * 16) = vraw[i];
+      }
     }
-    // ---- S^T for the two 16-key blocks
-    float p[2][4];
+    // ---- S^T of 16 keys
+    df32x4_t sacc = df32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      du32x4_t kb = kraw[ks];
+      if (FP8) {
+        const du32x2_t c0 = e4m3x4_to_bf16x4(kraw[ks][0]), c1 = e4m3x4_to_bf16x4(kraw[ks][1]);
+        kb = du32x4_t{c0[0], c0[1], c1[0], c1[1]};
+      }
+      sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dbf16x8_t, kb), qb[ks], sacc, 0, 0, 0);
+    }
+    float p[4];
     float tmax = DNEG_BIG;
 #pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      df32x4_t sacc = df32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        du32x4_t kb = kraw[blk][ks];
-        if (FP8) {
-          const du32x2_t c0 = e4m3x4_to_bf16x4(kraw[blk][ks][0]), c1 = e4m3x4_to_bf16x4(kraw[blk][ks][1]);
-          kb = du32x4_t{c0[0], c0[1], c1[0], c1[1]};
-        }
-        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dbf16x8_t, kb), qb[ks], sacc, 0, 0, 0);
-      }
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int key = t0 + blk * 16 + 4 * c + rr;      // in S^T the lane holds keys 4c..4c+3 of the block
-        p[blk][rr] = key < r_end ? sacc[rr] * a.scale_log2 : DNEG_BIG;
-        tmax = fmaxf(tmax, p[blk][rr]);
-      }
+    for (int rr = 0; rr < 4; ++rr) {
+      const int key = t0 + 4 * c + rr;                       // in S^T the lane holds keys 4c..4c+3
+      p[rr] = key < r_end ? sacc[rr] * a.scale_log2 : DNEG_BIG;
+      tmax = fmaxf(tmax, p[rr]);
     }
     // ---- V rows parked in the wave's LDS tile
 #pragma unroll
     for (int i = 0; i < VL; ++i) {
-      if (FP8) {                                           // 16 bytes -> 16 bf16
+      if (FP8) {                                             // 16 bytes -> 16 bf16
         const du32x2_t c0 = e4m3x4_to_bf16x4(vraw[i][0]), c1 = e4m3x4_to_bf16x4(vraw[i][1]);
         const du32x2_t c2 = e4m3x4_to_bf16x4(vraw[i][2]), c3 = e4m3x4_to_bf16x4(vraw[i][3]);
         const du32x4_t b0 = {c0[0], c0[1], c1[0], c1[1]}, b1 = {c2[0], c2[1], c3[0], c3[1]};
@@ -669,70 +706,67 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_gqa_kernel(DecodeArgs a) {
     float lo_m, hi_m;
     lane_pair<16>(tmax, lo_m, hi_m); tmax = fmaxf(lo_m, hi_m);
     lane_pair<32>(tmax, lo_m, hi_m); tmax = fmaxf(lo_m, hi_m);
-    const float m_new = fmaxf(m_run, tmax);
-    const float alpha = weight_of(m_run - m_new);
-    m_run = m_new;
+    const float m_new = FIRST ? tmax : fmaxf(m_run, tmax);
     float psum = 0.f;
-    uint32_t hi[4], lo[4];                                // P as bf16 hi + lo, 8 keys per lane: the A fragment
+    uint32_t hi[2], lo[2];                                   // P as bf16 hi + lo of the lane's 4 keys: the B fragment
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const df32x2_t pv = {weight_of(p[e >> 1][(e & 1) * 2] - m_new), weight_of(p[e >> 1][(e & 1) * 2 + 1] - m_new)};
+    for (int e = 0; e < 2; ++e) {
+      const df32x2_t pv = {weight_of(p[2 * e] - m_new), weight_of(p[2 * e + 1] - m_new)};
       psum += pv[0] + pv[1];
       hi[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pv, dbf16x2_t));          // round to nearest even
       const df32x2_t rest = {pv[0] - bf16_lo(hi[e]), pv[1] - bf16_hi(hi[e])};
       lo[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, dbf16x2_t));
     }
-    l_run = l_run * alpha + psum;
-    const dbf16x8_t pa_hi = __builtin_bit_cast(dbf16x8_t, du32x4_t{hi[0], hi[1], hi[2], hi[3]});
-    const dbf16x8_t pa_lo = __builtin_bit_cast(dbf16x8_t, du32x4_t{lo[0], lo[1], lo[2], lo[3]});
-    // (the wave's first tile, its only one in a piece of 128 rows, finds nothing to rescale)
-    if (t0 >= r_begin + NW * 32) {
-      // rescale factors of the queries this lane holds in the O layout (q = 4c + r)
-      float al[4];
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) al[rr] = __shfl(alpha, (c << 4) | (4 * c + rr), 64);
+    if (FIRST) {
+      l_run = psum;
+    } else {
+      const float alpha = weight_of(m_run - m_new);
+      l_run = l_run * alpha + psum;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) oacc[db][rr] *= al[rr];
+        for (int rr = 0; rr < 4; ++rr) oacc[db][rr] *= alpha;
     }
+    m_run = m_new;
+    const dbf16x8_t pb = __builtin_bit_cast(dbf16x8_t, du32x4_t{hi[0], hi[1], lo[0], lo[1]});
     // the V tile must be complete before it is read with another lane mapping (same wave: in order)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // B fragment: for output column 16 db + j16 the 8 keys of this lane group (4c..4c+3 of either block).  A transposing
+    // A fragment: for dim 16 db + j16 the 4 keys of this lane group, twice (against the hi and the lo parts).  A transposing
     // read takes, per 16 lanes, four rows of 16 columns: lane j points at columns 4 (j & 3).. of row j >> 2 and gets
     // column j of the four rows.
     const uint16_t* vf = vt + (4 * c + (j16 >> 2)) * RS + 4 * (j16 & 3);
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
-      const ds16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)(vf + db * 16));
-      const ds16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)(vf + 16 * RS + db * 16));
-      const dbf16x8_t vb = __builtin_bit_cast(dbf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-      df32x4_t o = oacc[db];
-      o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_hi, vb, o, 0, 0, 0);
-      o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_lo, vb, o, 0, 0, 0);
-      oacc[db] = o;
+      const ds16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)(vf + db * 16));
+      const dbf16x8_t va = __builtin_bit_cast(dbf16x8_t, __builtin_shufflevector(v, v, 0, 1, 2, 3, 4, 5, 6, 7));
+      oacc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb, FIRST ? df32x4_t{0.f, 0.f, 0.f, 0.f} : oacc[db], 0, 0, 0);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-  }
-
-  // ---- per wave: total of the sums over the lane groups, then everything to LDS in [q][d] form
-  {
-    float x, y;
+  };
+  if (first < r_end) {
+    tile(std::true_type{}, first);
+#pragma unroll 1
+    for (int t0 = first + NW * TR; t0 < r_end; t0 += NW * TR) tile(std::false_type{}, t0);
+    float x, y;                                              // the sums of the lane groups
     lane_pair<16>(l_run, x, y); l_run = x + y;
     lane_pair<32>(l_run, x, y); l_run = x + y;
+  } else {
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db] = df32x4_t{0.f, 0.f, 0.f, 0.f};
   }
-  __syncthreads();                                   // all V tiles are dead: their space takes the results
-  if (c == 0 && j16 < GT) { s_ml[wave][j16][0] = m_run; s_ml[wave][j16][1] = l_run; }
-  if (c < GT / 4)                                    // (lanes of the padding rows 8..15 have nothing to leave)
+
+  // ---- per wave: everything to LDS in [q][d] form, where its V tile was
+  if (j16 < GT) {                                            // (the padding columns 8..15 have nothing to leave)
+    if (c == 0) { s_ml[wave][j16][0] = m_run; s_ml[wave][j16][1] = l_run; }
+    float* acc = reinterpret_cast<float*>(s_wave[wave]) + j16 * AR + 4 * c;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) s_acc[wave][4 * c + rr][db * 16 + j16] = oacc[db][rr];
+    for (int db = 0; db < DB; ++db) *reinterpret_cast<df32x4_t*>(acc + db * 16) = oacc[db];
+  }
   __syncthreads();
-  finish_piece<uint16_t, D, NW, GT>(a, hidx, chunk, len, rows, can_append, arrive, s_ml, s_acc);
+  finish_piece<uint16_t, D, NW, GT, WB / 4, AR>(a, hidx, chunk, len, rows, can_append, arrive, s_ml, reinterpret_cast<const float*>(s_wave));
 }
 
 // Rows per workgroup: small for a single layer (many short workgroups balance ragged heads and
@@ -762,7 +796,8 @@ DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows)
   const int worst = plan_longest(c, c.ctx_len + c.max_new_tokens);
   const int base = plan_chunk_rows(dm, c);
   p.chunk_rows = base;
-  // grouped queries, few heads: a tile of 32 rows per wave while the launch does not fill the chip with that
+  // Grouped queries, few heads: a tile of 16 rows per wave while the launch does not fill the chip with that.  (Twice as far: 2 heads
+  // of 40K rows 12.6 -> 16.1 us; four times: 32 heads of 4K rows 11.5 -> 13.4: the pieces to merge.)
   const long long typical = std::min(c.budget, c.ctx_len) + (long long)c.max_new_tokens;
   const bool short_pieces = c.dtype == MADAKV_BF16 && dm.G >= 2 && dm.heads <= 512 && dm.heads * typical <= 256LL * 128 * 2;
   if (short_pieces) p.chunk_rows = 128;
@@ -800,7 +835,7 @@ static hipError_t launch_decode_t(const Dims& dm, DecodeArgs& a, int grid_chunks
   // of 256 75 and 70, but 1024 heads of 512 45.6 and 47.6.  8-bit rows, of which a lane has twice the elements, take four always:
   // 128 heads of 16K rows 89.3 us with either at 128 dims, 50.6 and 52.9 at 64 (64 heads of 32K: 92.8 and 90.4, 50.4 and 48.0).
   constexpr int LONG_ROWS = sizeof(CT) == 1 ? 4 : 8;
-  if (sizeof(T) == 2 && dm.G >= 2) hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED>), grid, block, 0, st, a);   // grouped queries in bf16: the MFMA kernel
+    if (sizeof(T) == 2 && dm.G >= 2) hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED>), grid, dim3(GQA_WAVES * 64), 0, st, a);   // grouped queries in bf16: the MFMA kernel
   else if (dm.G == 1 && a.chunk_rows > 512) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, LONG_ROWS, 4, PAGED>), grid, block, 0, st, a);
   else if (dm.G == 1) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, 4, 4, PAGED>), grid, block, 0, st, a);
   else if constexpr (sizeof(T) == 4) {
@@ -830,6 +865,8 @@ hipError_t launch_decode(const Dims& dm, const madakv_config& c, const void* q, 
   DecodePlan p = decode_plan(dm, c, longest_rows);
   a.B = dm.B; a.H = dm.H; a.G = dm.G; a.chunk_rows = p.chunk_rows; a.max_chunks = p.max_chunks;
   a.slots = p.grid_chunks;
+  a.by_heads = dm.heads > 1 && (long long)dm.heads * (dm.heads + p.grid_chunks) < (1ll << 32) ? (uint32_t)(((1ull << 32) + dm.heads - 1) / dm.heads) : 0u;
+  a.by_chunk = plan_longest(c, c.ctx_len + c.max_new_tokens) + (long long)c.max_new_tokens + a.chunk_rows < (1 << 21) ? (uint32_t)(((1ull << 32) + a.chunk_rows - 1) / a.chunk_rows) : 0u;
   a.part = reinterpret_cast<float*>(ws); a.part_ml = a.part + (long long)dm.heads * a.slots * dm.G * dm.d;
   a.out_fp32 = c.out_fp32; a.has_new = (k_new != nullptr) ? 1 : 0;
   const float scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)dm.d);

@@ -243,7 +243,7 @@ hipError_t join_side(madakv_handle* h, hipStream_t st, hipError_t e) {
 
 constexpr size_t NO_WORKSPACE = ~(size_t)0;
 // The handle's device memory but for d_split, in one allocation that starts with what has to be zero: the carry state, the
-// page table, the counters and lengths of decode's pieces (132 bytes per head, 516 with grouped queries).  Then the exchange words of the scoring
+// page table, the counters and lengths of decode's pieces (4 bytes per head, 128 per query head).  Then the exchange words of the scoring
 // kernels, and the partial results of one madakv_decode_attn_static call, whatever layers it is over.
 hipError_t create_memory(madakv_handle* h) {
   const madakv_config& c = h->cfg;
@@ -253,7 +253,7 @@ hipError_t create_memory(madakv_handle* h) {
   const size_t heads = (size_t)c.n_layers * c.batch * c.n_kv_heads, G = c.n_q_heads / c.n_kv_heads;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t table = up(sizeof(long long) * 3 * c.batch), count = table + up(sizeof(int32_t) * heads * page_table_entries(c));
-  const size_t len = count + heads * (G > 1 ? MEET_WAVES : 1) * MEET_COUNT_STRIDE * sizeof(uint32_t), xchg = len + up(heads * sizeof(int32_t));
+  const size_t len = count + heads * G * MEET_COUNT_STRIDE * sizeof(uint32_t), xchg = len + up(heads * sizeof(int32_t));
   h->xchg_words = xchg_layer_words(c, make_dims(c, 1));
   const size_t xbytes = c.n_layers * h->xchg_words * sizeof(unsigned long long), scratch = xchg + up(xbytes);
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&h->d_state), scratch + h->scratch_bytes);

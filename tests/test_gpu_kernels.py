@@ -134,6 +134,15 @@ def test_decode_pieces(kw, lens, out_fp32):
     eng.close()
 
 
+@pytest.mark.parametrize("Hq,H", [(2, 1), (9, 3), (28, 4), (16, 2)])
+@pytest.mark.parametrize("kw", [dict(head_dim=128), dict(head_dim=64), dict(head_dim=128, cache_fp8=1), dict(head_dim=64, cache_fp8=1)])
+def test_decode_of_grouped_queries_at_tile_edges(Hq, H, kw):
+    """Heads whose last tile of 16 rows, last wave and last piece of 128 rows are full, hold one row or are one row short, the
+    appended row the first, the last or alone in them: against 64-bit attention over the same rows (the bound of
+    test_decode_pieces)."""
+    test_decode_pieces(dict(n_q_heads=Hq, n_kv_heads=H, batch=4, ctx_len=2000, budget=300, **kw), [15, 16, 17, 126, 127, 128, 143, 144, 255, 256, 257, 1][:4 * H], 1)
+
+
 @pytest.mark.parametrize("L,W,M,pool_k,avg", [
     (9, 8, 2, 7, 0), (13, 8, 2, 3, 1), (200, 5, 2, 7, 1), (4096 + 8, 8, 2, 7, 0), (4097 + 8, 8, 3, 5, 0), (16383 + 8, 8, 2, 7, 0),
     (16384 + 8, 8, 4, 1, 0), (16385 + 8, 8, 2, 9, 0), (20483 + 1, 1, 2, 7, 0), (70001, 8, 2, 7, 0), (70001, 8, 3, 5, 1)])
