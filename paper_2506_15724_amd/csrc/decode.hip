@@ -297,7 +297,7 @@ __device__ __forceinline__ void finish_piece(const DecodeArgs& a, long long hidx
   constexpr int TL = D / 4, QW = 64 / TL;
   constexpr bool OWN = NW >= GT;                             // a query head per wave, whose lanes share the pieces
   constexpr int KP = OWN ? QW : 1, MB = OWN ? 8 : 16;        // MB: pieces in flight per lane
-  constexpr int WK = GT > 1 && OWN ? KP : 1;                 // (grouped queries: the waves' results, too)
+  constexpr int WK = OWN && (GT > 1 || NW == 8) ? KP : 1;    // and, of more than a few waves, their results
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wave * (OWN ? 1 : QW) >= (GT == 1 ? 1 : a.G)) return;
   const int t = lane % TL, kp = OWN ? lane / TL : 0, g = OWN ? wave : wave * QW + lane / TL;
@@ -789,17 +789,27 @@ static int plan_longest(const madakv_config& c, int longest_rows) { return std::
 // whatever hcc_rho is, 128 heads of which 8 hold half of the rows, 512 on average, took 21.3 us instead of 14.7, 512 heads of 256,
 // 16 with half of the rows, 34 instead of 21.  Neither depends on what the host knows of the
 // longest head, so that a call's result does not either; only the grid, at most max_chunks pieces, shrinks when it is known.
-constexpr int SHORT_PIECES = 2000;             // most 128-row pieces of a launch: what the static scratch holds of 8 queries x 128 dims
+constexpr int SHORT_PIECES = 2000;             // most 128-row pieces of a launch (or two per head): what the static scratch holds of 8 queries x 128 dims
 static_assert((size_t)SHORT_PIECES * 8 * (128 + 2) * sizeof(float) <= MADAKV_STATIC_SCRATCH_BYTES, "short pieces must fit the static scratch");
 DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows) {
   DecodePlan p;
   const int worst = plan_longest(c, c.ctx_len + c.max_new_tokens);
   const int base = plan_chunk_rows(dm, c);
   p.chunk_rows = base;
-  // Grouped queries, few heads: a tile of 16 rows per wave while the launch does not fill the chip with that.  (Twice as far: 2 heads
-  // of 40K rows 12.6 -> 16.1 us; four times: 32 heads of 4K rows 11.5 -> 13.4: the pieces to merge.)
   const long long typical = std::min(c.budget, c.ctx_len) + (long long)c.max_new_tokens;
-  const bool short_pieces = c.dtype == MADAKV_BF16 && dm.G >= 2 && dm.heads <= 512 && dm.heads * typical <= 256LL * 128 * 2;
+  // A launch that does not fill the chip with it: pieces of 128 rows, one trip of all waves to memory each, where a piece of 256 is
+  // two (grouped queries) to four trips one behind the other.
+  // Grouped queries up to 64K rows in all.  (Twice as far: 2 heads of 40K rows 12.6 -> 16.1 us; four times: 32 heads of 4K rows
+  // 11.5 -> 13.4: the pieces to merge.)  Single ones, us per call (device), 256-row pieces -> these: 32 heads of 200 rows 6.0 -> 5.0,
+  // of 500 7.2 -> 6.3, of 1K 8.6 -> 7.0, of 2K 10.2 -> 9.5, 16 of 2.5K 8.7 -> 8.5, 20 of 1K fp32 rows 11.2 -> 8.5.  Rows of less
+  // than 256 bytes, of which a piece of 256 takes no more trips, lose: 20 heads of 400 8-bit rows 5.1 -> 5.3.  Heads of few
+  // pieces gain up to twice as many rows in all: 128 of 500 rows 9.9 -> 9.8, 128 calls over 128 of 900 2643 -> 2627 us; over 80 of
+  // 1.5K they lose, 2401 -> 2658.  Heads of hardly more than one such piece keep the longer ones, which they fill alone (32 of 120
+  // rows: 4.2 us either way).
+  const long long rows = dm.heads * typical;
+  const int row_bytes = dm.d * (c.cache_fp8 ? 1 : c.dtype == MADAKV_BF16 ? 2 : 4);
+  const bool short_pieces = dm.heads <= 512 && (dm.G >= 2 ? c.dtype == MADAKV_BF16 && rows <= 65536
+                                                           : row_bytes >= 256 && typical > 160 && rows <= (typical <= 768 ? 131072 : 65536));
   if (short_pieces) p.chunk_rows = 128;
   long long want = std::max<long long>((std::max(2, c.hcc_rho) * typical + p.chunk_rows - 1) / p.chunk_rows, 512 / dm.heads);
   if (short_pieces) want = std::min<long long>(want, SHORT_PIECES / dm.heads);
@@ -836,6 +846,9 @@ static hipError_t launch_decode_t(const Dims& dm, DecodeArgs& a, int grid_chunks
   // 128 heads of 16K rows 89.3 us with either at 128 dims, 50.6 and 52.9 at 64 (64 heads of 32K: 92.8 and 90.4, 50.4 and 48.0).
   constexpr int LONG_ROWS = sizeof(CT) == 1 ? 4 : 8;
     if (sizeof(T) == 2 && dm.G >= 2) hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED>), grid, dim3(GQA_WAVES * 64), 0, st, a);   // grouped queries in bf16: the MFMA kernel
+  else if (LPR >= 16 && dm.G == 1 && a.chunk_rows == 128) {          // eight waves, a piece in one trip
+    if constexpr (LPR >= 16) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, LPR / 4, 8, PAGED>), grid, dim3(512), 0, st, a);
+  }
   else if (dm.G == 1 && a.chunk_rows > 512) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, LONG_ROWS, 4, PAGED>), grid, block, 0, st, a);
   else if (dm.G == 1) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, 4, 4, PAGED>), grid, block, 0, st, a);
   else if constexpr (sizeof(T) == 4) {

@@ -82,6 +82,11 @@ def test_fp32_scores(kw, monkeypatch):
     (dict(n_q_heads=12, n_kv_heads=2, head_dim=128, ctx_len=5000, budget=1000, cache_fp8=1), [1700, 159]),
     (dict(n_q_heads=3, n_kv_heads=1, head_dim=128, ctx_len=12000, budget=11000, dtype="fp32"), [10999]),
     (dict(n_q_heads=2, n_kv_heads=2, head_dim=64, ctx_len=400, budget=300, dtype="fp32"), [299, 255]),
+    # single queries, little to read: pieces of 128 rows in one trip (by the bytes of a row), heads at their edges and longer than all of them
+    (dict(batch=2, n_q_heads=5, n_kv_heads=5, head_dim=128, ctx_len=3000, budget=700), [127, 128, 129, 255, 256, 0, 1, 2990]),
+    (dict(batch=2, n_q_heads=5, n_kv_heads=5, head_dim=64, ctx_len=3000, budget=700), [126, 127, 128, 31, 32, 0, 1, 2990]),
+    (dict(batch=2, n_q_heads=5, n_kv_heads=5, head_dim=64, ctx_len=3000, budget=700, cache_fp8=1), [126, 127, 128, 63, 64, 0, 1, 2990]),
+    (dict(batch=2, n_q_heads=5, n_kv_heads=5, head_dim=128, ctx_len=3000, budget=700, dtype="fp32"), [126, 127, 128, 15, 16, 0, 1, 2990]),
     # long pieces (768 rows): eight rows in flight
     (dict(batch=4, n_q_heads=64, n_kv_heads=64, head_dim=64, ctx_len=7000, budget=6200), [6190, 769, 768, 767, 1]),
 ], ids=lambda x: f"q{x['n_q_heads']}_kv{x['n_kv_heads']}_d{x['head_dim']}_L{x['ctx_len']}_{x.get('dtype', 'bf16')}" if isinstance(x, dict) else "")
