@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 namespace madakv {
 
@@ -23,6 +24,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) int i32x4_t;
 
 constexpr float NEG_BIG = -1.0e30f;
 constexpr int SCORE_THREADS = 256;
@@ -111,28 +113,30 @@ __device__ __forceinline__ float half_reduce(float x) {
   return x;
 }
 
-// The same sums, in the same order, of 16 values: at each step a lane goes on with half of its values and takes what its
-// partner had of them; lane i of a half-wave gets the sum of x[i & 15].  (Half the instructions of 16 single
+// The same, in the same order, of 16 values: at each step a lane goes on with half of its values and takes what its
+// partner had of them; lane i of a half-wave gets the result of x[i & 15].  (Half the instructions of 16 single
 // reductions, one wide store instead of 16.)
+template <int OP>   // 0 = max, 1 = sum
 __device__ __forceinline__ float half_fold(const float (&x)[16], int lane) {
 #define MADAKV_DPP(v, ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xF, 0xF, true))
+  const auto both = [](float x, float y) { return OP ? x + y : fmaxf(x, y); };
   float a[8], b[4], c[2];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) { const bool o = lane & 1; const float keep = o ? x[2 * k + 1] : x[2 * k], give = o ? x[2 * k] : x[2 * k + 1]; a[k] = keep + MADAKV_DPP(give, 0xB1); }   // lane ^ 1
+  for (int k = 0; k < 8; ++k) { const bool o = lane & 1; const float keep = o ? x[2 * k + 1] : x[2 * k], give = o ? x[2 * k] : x[2 * k + 1]; a[k] = both(keep, MADAKV_DPP(give, 0xB1)); }   // lane ^ 1
 #pragma unroll
-  for (int k = 0; k < 4; ++k) { const bool o = lane & 2; const float keep = o ? a[2 * k + 1] : a[2 * k], give = o ? a[2 * k] : a[2 * k + 1]; b[k] = keep + MADAKV_DPP(give, 0x4E); }   // lane ^ 2
+  for (int k = 0; k < 4; ++k) { const bool o = lane & 2; const float keep = o ? a[2 * k + 1] : a[2 * k], give = o ? a[2 * k] : a[2 * k + 1]; b[k] = both(keep, MADAKV_DPP(give, 0x4E)); }   // lane ^ 2
 #pragma unroll
   for (int k = 0; k < 2; ++k) {                                                     // lane ^ 4: mirrored in 8, then in 4
     const bool o = lane & 4;
     const float keep = o ? b[2 * k + 1] : b[2 * k], give = o ? b[2 * k] : b[2 * k + 1];
     const float m = MADAKV_DPP(give, 0x141);
-    c[k] = keep + MADAKV_DPP(m, 0x1B);
+    c[k] = both(keep, MADAKV_DPP(m, 0x1B));
   }
   const bool o = lane & 8;
   const float keep = o ? c[1] : c[0], give = o ? c[0] : c[1];
-  const float d = keep + MADAKV_DPP(give, 0x128);                                   // lane ^ 8: rotated by 8 in 16
+  const float d = both(keep, MADAKV_DPP(give, 0x128));                                   // lane ^ 8: rotated by 8 in 16
 #undef MADAKV_DPP
-  return d + __shfl_xor(d, 16, 64);                                                 // the two 16-lane rows of the half
+  return both(d, __shfl_xor(d, 16, 64));                                                 // the two 16-lane rows of the half
 }
 
 template <int D, int NRB, int PASS>
@@ -665,8 +669,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
 
 // ------------------------------------------------------------------------------------
 // One sweep over K (bf16 and 8-bit keys in at most two row blocks, G*W <= 64; fp32 in blocks of 64 rows).  The logits of a workgroup's
-// keys fit in its registers: a wave keeps the D tiles of its NS subtiles (NS * NRB * 16 floats
-// per lane) instead of reducing them on the fly.  After its last subtile a workgroup knows the
+// keys, or their softmax terms against a reference, fit in its registers: a wave keeps the D tiles of its NS subtiles (NS * NRB * 16
+// floats per lane) instead of reducing them on the fly.  After its last subtile a workgroup knows the
 // (max, sum) of every proxy row over its own keys; the workgroups of a head exchange these
 // through memory, every one merges all of them in the same fixed order, and the column sums
 // come out of the registers: K is read once and multiplied once.
@@ -755,7 +759,8 @@ __device__ __forceinline__ void score_head_stats_alone(const ScoreArgs& a, int L
 // After a workgroup has left the (max, sum) of every proxy row over its own keys in part[4 waves][mpad][2]
 // (LDS, behind a barrier): the head-wide exchange described above, in two halves.  post_row_stats
 // publishes this workgroup's words and waits for nobody; collect_row_stats gathers the head's words and
-// leaves offs[r] = max + log2(sum) over all keys of the head (log2 domain; +inf for padding rows).
+// leaves offs[r] = max + log2(sum) over all keys of the head (log2 domain; +inf for padding rows), and, if asked, max and
+// 1 / sum (0 for padding rows) in norm[2 r], norm[2 r + 1], unless a workgroup had to go its own way (*s_fail).
 // All threads call both; work that needs nobody else's statistics can sit between them.  The caller
 // adds the barrier after collect_row_stats.
 __device__ __forceinline__ void post_row_stats(const ScoreArgs& a, int head, int slot, int fs, const float* part) {   // slot: the chunk, or a word of the group level
@@ -811,14 +816,18 @@ constexpr int XCHG_GROUP = 16;       // chunks per group when the exchange has t
 
 template <int D, int KIND = K_BF16>
 __device__ __forceinline__ void collect_row_stats(const ScoreArgs& a, int head, int split, int fs, int Lh, int Mh, int rowbase,
-                                                  const uint16_t* kg, const uint16_t* qs, const float* part, float* offs, float* pm, int* s_fail) {
+                                                  const uint16_t* kg, const uint16_t* qs, const float* part, float* offs, float* norm, float* pm, int* s_fail) {
   const int tid = threadIdx.x;
   const int nparts = SCORE_THREADS / a.mpad;
+  const auto leave = [&](float m, float l) {
+    offs[tid] = (tid < Mh) ? m + log2f(l) : __builtin_inff();
+    if (norm) { norm[2 * tid] = m; norm[2 * tid + 1] = (tid < Mh) ? 1.f / l : 0.f; }
+  };
   if (fs == 1) {
     if (tid < a.mpad) {
       float m = NEG_BIG, l = 0.f;
       for (int w = 0; w < 4; ++w) merge_ml(m, l, part[(w * a.mpad + tid) * 2], part[(w * a.mpad + tid) * 2 + 1]);
-      offs[tid] = (tid < Mh) ? m + log2f(l) : __builtin_inff();
+      leave(m, l);
     }
     return;
   }
@@ -852,15 +861,15 @@ __device__ __forceinline__ void collect_row_stats(const ScoreArgs& a, int head, 
   } else if (tid < a.mpad) {
     float mm = NEG_BIG, ll = 0.f;
     for (int q = 0; q < nparts; ++q) merge_ml(mm, ll, pm[(q * a.mpad + tid) * 2], pm[(q * a.mpad + tid) * 2 + 1]);
-    offs[tid] = (tid < Mh) ? mm + log2f(ll) : __builtin_inff();
+    leave(mm, ll);
   }
 }
 
 template <int D, int KIND = K_BF16>
 __device__ __forceinline__ void exchange_row_stats(const ScoreArgs& a, int head, int split, int fs, int Lh, int Mh, int rowbase,
-                                                   const uint16_t* kg, const uint16_t* qs, const float* part, float* offs, float* pm, int* s_fail) {
+                                                   const uint16_t* kg, const uint16_t* qs, const float* part, float* offs, float* norm, float* pm, int* s_fail) {
   post_row_stats(a, head, split, fs, part);
-  collect_row_stats<D, KIND>(a, head, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, pm, s_fail);
+  collect_row_stats<D, KIND>(a, head, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, norm, pm, s_fail);
 }
 
 #ifndef MADAKV_FUSED_NS1      // tuning constants of the one-sweep kernel (measured on MI355X)
@@ -876,6 +885,14 @@ __device__ __forceinline__ void exchange_row_stats(const ScoreArgs& a, int head,
 // products and sums throughout, no conversion).  The plain FMA kernels they replace were bound by their loads (every lane
 // walked a row of its own, one uncoalesced dword at a time): one layer of 8 heads x 1024 keys x 16 rows took 117 + 124 us in
 // two sweeps, 17 us here (+ 2 us for the exchange words), most of it the latencies of one pass and the instruction stream.
+// Between a workgroup's last key and its scores stand the row statistics, the exchange and the column sums, and all workgroups
+// of a head go through them at about the same time, so the memory is idle meanwhile: with the logits in registers, two exp2 per
+// logit and 32 or 64 row reductions of ten steps one behind the other.  With the softmax terms themselves there (below) it is additions,
+// two folds and one product per logit, the exp2 (one) and everything else under the loads.  Score and statistics calls before /
+// after, us: 32 heads of 128K keys, 32 rows 255 / 228, 64 rows 358 / 326, 64 rows and 64 dims 290 / 246; 32 of 32K 83 / 77; 128 of
+// 16K 119 / 113.  (The polling is not what costs: one lane of a row polling for all changes nothing, nor does
+// starting the heads one after the other.)  A row's whole sum over the wave's keys beyond which its terms are not used (2^100, so that no product overflows):
+constexpr float LATE_SUM = 0x1p100f;
 template <int D, int NRB, int NS, int KIND = K_BF16>
 __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(KIND == K_F32 && D == 128 ? 1 : MADAKV_FUSED_WPE, KIND == K_F32 && D == 128 ? 1 : MADAKV_FUSED_WPE))) void score_fused_kernel(ScoreArgs a) {
   constexpr bool F8 = KIND == K_E4M3, F32 = KIND == K_F32;
@@ -892,7 +909,10 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
   float* part = reinterpret_cast<float*>(kt_all + 4 * 32 * RS);           // [4 waves][mpad][2]
   float* offs = part + 4 * a.mpad * 2;                                    // [mpad]
   float* pm = offs + a.mpad;                                              // [256 / mpad parts][mpad][2]
-  __shared__ int s_fail;
+  float* refs = pm + 512;                                                 // [4 waves][mpad]
+  float* norm = refs + 4 * a.mpad;                                        // [mpad][2]
+  int* last = reinterpret_cast<int*>(norm + 2 * a.mpad);                  // [mpad] last key of the chunk that the row sees
+  __shared__ int s_fail, s_late;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int bx = blockIdx.x;                  // (the parked chunks first: split is set below, once fs is known)
@@ -916,20 +936,21 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
   const int chunk0 = split * CK;
   const int chunk1 = min(Lh, chunk0 + CK);
   uint16_t* kt = kt_all + (size_t)wave * 32 * RS;
-  if (tid == 0) s_fail = 0;
+  float* ref = refs + wave * a.mpad;
+  if (tid == 0) s_fail = s_late = 0;
 
   // subtile `it` of this wave: keys chunk0 + (it * 4 + wave) * 32 ...; PF subtiles in flight
   constexpr int CPR = F8 ? PPR / 2 : PPR;      // 16-byte pieces per cached row
   constexpr int LPSK = F8 ? LPS / 2 : LPS;     // loads per lane and subtile
   u32x4_t pre[PF][LPSK];
+  const int lrow = lane / CPR, lpiece = lane % CPR;     // of the lane's first load; the next is 64 / CPR rows further
 #define MADAKV_FUSED_LOAD(SET, IT)                                                               \
   {                                                                                              \
-    const int lt0 = chunk0 + ((IT) * 4 + wave) * 32;                                             \
+    const int lt0 = chunk0 + ((IT) * 4 + wave) * 32 + lrow;                                      \
     _Pragma("unroll") for (int i = 0; i < LPSK; ++i) {                                           \
-      const int idx = i * 64 + lane;                                                             \
-      const int lkey = min(lt0 + idx / CPR, Lh - 1); /* past the end: a valid row, masked later */ \
+      const int lkey = min(lt0 + i * (64 / CPR), Lh - 1); /* past the end: a valid row, masked later */ \
       pre[SET][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(                 \
-          reinterpret_cast<const unsigned char*>(kg) + ((long long)lkey * CPR + (idx % CPR)) * 16)); \
+          reinterpret_cast<const unsigned char*>(kg) + (uint32_t)(lkey * CPR + lpiece) * 16u));  \
     }                                                                                            \
   }
 #pragma unroll
@@ -943,141 +964,241 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
     if (F32 || r < Mh) val = *reinterpret_cast<const uint4*>(qg + (long long)(F32 ? min(r, Mh - 1) : r) * RU + c * 8);
     *reinterpret_cast<uint4*>(qs + r * RS + c * 8) = val;
   }
+  if (tid < a.mpad) last[tid] = tid < Mh ? min(Lh - a.W + (rowbase + tid) % a.W, chunk1 - 1) : -1;
   __syncthreads();
 
   const int half = lane >> 5, col = lane & 31;
   const int first_masked = Lh - a.W + 1;      // keys below this are visible to every proxy row
   bf16x8_t areg[KS];                           // one row block: its Q fragments stay in registers
 #pragma unroll
-  for (int ks = 0; ks < (F32 ? 0 : KS); ++ks)
+  for (int ks = 0; ks < (F32 || NRB > 1 ? 0 : KS); ++ks)
     areg[ks] = *reinterpret_cast<const bf16x8_t*>(qs + col * RS + half * (D / 2) + ks * 8);
 
-  float lg[NS][NRB][16];                       // scaled logits (log2 domain); masked entries hold NEG_BIG
+  // (padding rows need no mask: their offset is +inf)
+  const auto mask = [&](float (&x)[16], int b, int it, float none) __attribute__((always_inline)) {
+    const int t0 = chunk0 + (it * 4 + wave) * 32, key = t0 + col;
+    if (t0 + 32 <= first_masked && t0 + 32 <= chunk1) return;
 #pragma unroll
-  for (int it = 0; it < NS; ++it) {
+    for (int c = 0; c < 4; ++c) {
+      const i32x4_t to = *reinterpret_cast<const i32x4_t*>(last + b * 32 + half * 4 + c * 8);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[c * 4 + e] = key <= to[e] ? x[c * 4 + e] : none;
+    }
+  };
+  // a subtile's keys from their registers to the wave's tile
+  const auto park = [&](const u32x4_t (&keys)[LPSK]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < LPSK; ++i) {
-      const int idx = i * 64 + lane;
+      uint16_t* kw = kt + lrow * RS + lpiece * (F8 ? 16 : 8) + i * (64 / CPR) * RS;
       if (F8) {                                   // 16 bytes of a row -> 16 bf16
-        const u32x4_t raw = pre[it % PF][i];
+        const u32x4_t raw = keys[i];
         const u32x2_t c0 = e4m3x4_as_bf16x4(raw[0]), c1 = e4m3x4_as_bf16x4(raw[1]), c2 = e4m3x4_as_bf16x4(raw[2]), c3 = e4m3x4_as_bf16x4(raw[3]);
-        *reinterpret_cast<u32x4_t*>(kt + (idx / CPR) * RS + (idx % CPR) * 16) = u32x4_t{c0[0], c0[1], c1[0], c1[1]};
-        *reinterpret_cast<u32x4_t*>(kt + (idx / CPR) * RS + (idx % CPR) * 16 + 8) = u32x4_t{c2[0], c2[1], c3[0], c3[1]};
+        *reinterpret_cast<u32x4_t*>(kw) = u32x4_t{c0[0], c0[1], c1[0], c1[1]};
+        *reinterpret_cast<u32x4_t*>(kw + 8) = u32x4_t{c2[0], c2[1], c3[0], c3[1]};
       } else {
-        *reinterpret_cast<u32x4_t*>(kt + (idx / PPR) * RS + (idx % PPR) * 8) = pre[it % PF][i];
+        *reinterpret_cast<u32x4_t*>(kw) = keys[i];
       }
     }
-    if (it + PF < NS) MADAKV_FUSED_LOAD(it % PF, it + PF)
+  };
+  const auto contract = [&](f32x16_t (&acc)[NRB]) __attribute__((always_inline)) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int t0 = chunk0 + (it * 4 + wave) * 32;
-    const int key = t0 + col;
-    const bool tail = (t0 + 32 > first_masked) || (t0 + 32 > chunk1);     // (padding rows need no mask: their offset is +inf)
     const uint16_t* krow = kt + col * RS + half * (RU / 2);
-    bf16x8_t bfrag[KS];
+    const uint16_t* qrow = qs + col * RS + half * (RU / 2);
 #pragma unroll
-    for (int ks = 0; ks < (F32 ? 0 : KS); ++ks) bfrag[ks] = *reinterpret_cast<const bf16x8_t*>(krow + ks * 8);
-    if (!F32) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    }
+    for (int b = 0; b < NRB; ++b) acc[b] = f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (F32) {                                    // step s contracts dims s and D/2 + s: a lane's operands are consecutive floats
 #pragma unroll
-    for (int b = 0; b < NRB; ++b) {
-      f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      const uint16_t* qrow = qs + (b * 32 + col) * RS + half * (RU / 2);
-      if (F32) {                                // step s contracts dims s and D/2 + s: a lane's operands are consecutive floats
+      for (int b = 0; b < NRB; ++b) {
 #pragma unroll 4
         for (int c = 0; c < D / 8; ++c) {
-          const f32x4_t qv = *reinterpret_cast<const f32x4_t*>(qrow + c * 8), kv = *reinterpret_cast<const f32x4_t*>(krow + c * 8);
+          const f32x4_t qv = *reinterpret_cast<const f32x4_t*>(qrow + b * 32 * RS + c * 8), kv = *reinterpret_cast<const f32x4_t*>(krow + c * 8);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qv[e], kv[e], acc, 0, 0, 0);
-        }
-      }
-#pragma unroll
-      for (int ks = 0; ks < (F32 ? 0 : KS); ++ks) {
-        const bf16x8_t afrag = (NRB == 1) ? areg[ks] : *reinterpret_cast<const bf16x8_t*>(qrow + ks * 8);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag, bfrag[ks], acc, 0, 0, 0);
-      }
-      if (!tail) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) lg[it][b][j] = acc[j] * a.scale_log2;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int row = b * 32 + (j >> 2) * 8 + half * 4 + (j & 3);
-          const int pos = Lh - a.W + ((rowbase + row) % a.W);
-          const bool valid = (key < chunk1) && (key <= pos) && (row < Mh);
-          lg[it][b][j] = valid ? acc[j] * a.scale_log2 : NEG_BIG;
+          for (int e = 0; e < 4; ++e) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(qv[e], kv[e], acc[b], 0, 0, 0);
         }
       }
     }
-    if (F32) {                                  // (the operands were read row block by row block: only now is the tile free)
+    if (NRB == 1) {
+      bf16x8_t bfrag[KS];
+#pragma unroll
+      for (int ks = 0; ks < (F32 ? 0 : KS); ++ks) bfrag[ks] = *reinterpret_cast<const bf16x8_t*>(krow + ks * 8);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
-    }
-  }
-#undef MADAKV_FUSED_LOAD
-
-  // ---- (max, sum) of every row over this workgroup's keys: lanes, then waves (fixed order)
 #pragma unroll
-  for (int b = 0; b < NRB; ++b) {
+      for (int ks = 0; ks < (F32 ? 0 : KS); ++ks) acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(areg[ks], bfrag[ks], acc[0], 0, 0, 0);
+    } else {                                      // (a key fragment at a time: all of them would spill)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      float mx = lg[0][b][j];
-      if (F32) mx = fmaxf(mx, NEG_BIG);         // (a row whose logits here are all -Inf: against NEG_BIG its sum is 0)
+      for (int ks = 0; ks < (F32 ? 0 : KS); ++ks) {
+        const bf16x8_t bfrag = *reinterpret_cast<const bf16x8_t*>(krow + ks * 8);
 #pragma unroll
-      for (int it = 1; it < NS; ++it) mx = fmaxf(mx, lg[it][b][j]);
-      const float m = half_reduce<0>(mx);
-      float sm = 0.f;
-#pragma unroll
-      for (int it = 0; it < NS; ++it) sm += fast_exp2(lg[it][b][j] - m);   // masked entries against a real maximum: 0
-      const float l = half_reduce<1>(sm);
-      if (col == 0) {
-        const int row = b * 32 + (j >> 2) * 8 + half * 4 + (j & 3);
-        part[(wave * a.mpad + row) * 2] = m;
-        part[(wave * a.mpad + row) * 2 + 1] = l;
+        for (int b = 0; b < NRB; ++b)
+          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(qrow + b * 32 * RS + ks * 8), bfrag, acc[b], 0, 0, 0);
       }
     }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");                // (the tile is free)
+    __builtin_amdgcn_wave_barrier();
+  };
+
+  float* psi = (a.rb_count > 1 ? a.psi_part + (hv % a.rb_count) * a.psi_part_stride : a.psi) + base;
+  const auto store = [&](int it, float colsum) __attribute__((always_inline)) {
+    colsum += __shfl_xor(colsum, 32, 64);
+    const int key = chunk0 + (it * 4 + wave) * 32 + col;
+    if (half == 0 && key < chunk1) __builtin_nontemporal_store(colsum, psi + key);
+  };
+  // What stays in registers of a (row, key) pair is its softmax term against the wave's reference of the row, the
+  // largest logit of the wave's first subtile (a whole number, so that nothing is rounded but the difference).  The
+  // terms are formed under the loads of the keys that follow; behind the last subtile the row sums are additions and the column
+  // sums products with one factor per row and wave.
+  // In a workgroup in which a row's terms pass LATE_SUM or are no numbers, and in the parked chunks: the logits themselves, and
+  // all row maxima and two exp2 per logit between the last key and the scores.
+  float x[NS][NRB][16];
+  const auto sweep = [&](auto terms_t) __attribute__((always_inline)) {
+    constexpr bool T = decltype(terms_t)::value;
+    if (!T) {
+#pragma unroll
+      for (int it = 0; it < PF; ++it) MADAKV_FUSED_LOAD(it, it)
+    }
+#pragma unroll
+    for (int it = 0; it < NS; ++it) {
+      park(pre[it % PF]);
+      if (it + PF < NS) MADAKV_FUSED_LOAD(it % PF, it + PF)
+      f32x16_t acc[NRB];
+      contract(acc);
+#pragma unroll
+      for (int b = 0; b < NRB; ++b) {
+        if (!T) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) x[it][b][j] = acc[b][j] * a.scale_log2;
+          mask(x[it][b], b, it, NEG_BIG);
+          continue;
+        }
+        if (it == 0) {
+          float lg[16];
+#pragma unroll
+          for (int j = 0; j < 16; ++j) lg[j] = acc[b][j] * a.scale_log2;
+          mask(lg, b, it, NEG_BIG);
+          const float mx = half_fold<0>(lg, lane);
+          if (col < 16) ref[b * 32 + half * 4 + (col >> 2) * 8 + (col & 3)] = mx == NEG_BIG ? 0.f : floorf(mx);
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const f32x4_t m = *reinterpret_cast<const f32x4_t*>(ref + b * 32 + half * 4 + c * 8);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[it][b][c * 4 + e] = fast_exp2(fmaf(acc[b][c * 4 + e], a.scale_log2, -m[e]));
+        }
+        mask(x[it][b], b, it, 0.f);
+      }
+    }
+  };
+  bool terms = !parked;
+  if (terms) {
+    sweep(std::true_type{});
+    // ---- (reference, sum) of every row over this workgroup's keys: lanes, then waves (fixed order)
+#pragma unroll
+    for (int b = 0; b < NRB; ++b) {
+      float sum[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        sum[j] = x[0][b][j];
+#pragma unroll
+        for (int it = 1; it < NS; ++it) sum[j] += x[it][b][j];
+      }
+      const float l = half_fold<1>(sum, lane);
+      if (!(l <= LATE_SUM)) s_late = 1;         // (NaN too)
+      if (col < 16) {
+        const int row = b * 32 + (col >> 2) * 8 + half * 4 + (col & 3);
+        const int e = l > 0.f ? __builtin_amdgcn_frexp_expf(l) : 0;
+        part[(wave * a.mpad + row) * 2] = l > 0.f ? ref[row] + (float)e : NEG_BIG;
+        part[(wave * a.mpad + row) * 2 + 1] = ldexpf(l, -e);
+      }
+    }
+    __syncthreads();
+    terms = s_late == 0;                        // the same in the whole workgroup
   }
-  __syncthreads();
-  if (parked) {
-    // its statistics as a word of the group level (behind the groups' own), its logits to memory; nobody is waited for
-    post_row_stats(a, hv, fs + (a.xgroups - a.nstrag) + (split - fs), fs, part);
-    float* pk = a.park + ((long long)hv * a.nstrag + (split - fs)) * (NS * NRB * 16 * SCORE_THREADS);
+  if (!terms) {
+    sweep(std::false_type{});
+    // ---- (max, sum) the same way
 #pragma unroll
-    for (int it = 0; it < NS; ++it)
+    for (int b = 0; b < NRB; ++b) {
 #pragma unroll
-      for (int b = 0; b < NRB; ++b)
+      for (int j = 0; j < 16; ++j) {
+        float mx = x[0][b][j];
+        if (F32) mx = fmaxf(mx, NEG_BIG);       // (a row whose logits here are all -Inf: against NEG_BIG its sum is 0)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) __builtin_nontemporal_store(lg[it][b][j], pk + ((it * NRB + b) * 16 + j) * SCORE_THREADS + tid);
-    return;
+        for (int it = 1; it < NS; ++it) mx = fmaxf(mx, x[it][b][j]);
+        const float m = half_reduce<0>(mx);
+        float sm = 0.f;
+#pragma unroll
+        for (int it = 0; it < NS; ++it) sm += fast_exp2(x[it][b][j] - m);   // masked entries against a real maximum: 0
+        const float l = half_reduce<1>(sm);
+        if (col == 0) {
+          const int row = b * 32 + (j >> 2) * 8 + half * 4 + (j & 3);
+          part[(wave * a.mpad + row) * 2] = m;
+          part[(wave * a.mpad + row) * 2 + 1] = l;
+        }
+      }
+    }
+    __syncthreads();
+    if (parked) {
+      // its statistics as a word of the group level (behind the groups' own), its logits to memory; nobody is waited for
+      post_row_stats(a, hv, fs + (a.xgroups - a.nstrag) + (split - fs), fs, part);
+      float* pk = a.park + ((long long)hv * a.nstrag + (split - fs)) * (NS * NRB * 16 * SCORE_THREADS);
+#pragma unroll
+      for (int it = 0; it < NS; ++it)
+#pragma unroll
+        for (int b = 0; b < NRB; ++b)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) __builtin_nontemporal_store(x[it][b][j], pk + ((it * NRB + b) * 16 + j) * SCORE_THREADS + tid);
+      return;
+    }
   }
-  exchange_row_stats<D, KIND>(a, hv, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, pm, &s_fail);
+  exchange_row_stats<D, KIND>(a, hv, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, norm, pm, &s_fail);
   __syncthreads();
   if (a.offs_out && split == 0 && tid < a.mpad) a.offs_out[(long long)hv * a.mpad + tid] = offs[tid];
 
   // ---- column sums from the registers
-  float off_r[NRB][16];
-#pragma unroll
-  for (int b = 0; b < NRB; ++b)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) off_r[b][j] = offs[b * 32 + (j >> 2) * 8 + half * 4 + (j & 3)];
-#pragma unroll
-  for (int it = 0; it < NS; ++it) {
-    float colsum = 0.f;
+  const auto column_sums = [&](const float* per_row, auto entry) __attribute__((always_inline)) {
+    float f[NRB][16];
 #pragma unroll
     for (int b = 0; b < NRB; ++b)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) colsum += fast_exp2(lg[it][b][j] - off_r[b][j]);
-    colsum += __shfl_xor(colsum, 32, 64);
-    const int key = chunk0 + (it * 4 + wave) * 32 + col;
-    if (half == 0 && key < chunk1) __builtin_nontemporal_store(colsum, (a.rb_count > 1 ? a.psi_part + (hv % a.rb_count) * a.psi_part_stride : a.psi) + (base + key));
+      for (int j = 0; j < 16; ++j) f[b][j] = per_row[b * 32 + (j >> 2) * 8 + half * 4 + (j & 3)];
+#pragma unroll
+    for (int it = 0; it < NS; ++it) {
+      float colsum = 0.f;
+#pragma unroll
+      for (int b = 0; b < NRB; ++b)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) colsum = entry(colsum, x[it][b][j], f[b][j]);
+      store(it, colsum);
+    }
+  };
+  if (!terms) {
+    column_sums(offs, [](float sum, float lg, float off) { return sum + fast_exp2(lg - off); });
+    return;
   }
+  // a row's factor, exp2(reference - max) / sum (a wave has not more than 64 rows; a row that sees none of the wave's keys has
+  // a reference of 0 and no terms)
+  const int r = min(lane, a.mpad - 1);
+  const float rel = fminf(ref[r] - (s_fail ? offs[r] : norm[2 * r]), 0.f), inv = s_fail ? 1.f : norm[2 * r + 1];
+  // Where the wave's reference is far below the head's maximum, the factor alone would flush to zero and its product
+  // with a large term would not: two factors then.
+  const bool small = __any(rel < -100.f && inv > 0.f);
+  if (lane < a.mpad) ref[lane] = small ? fast_exp2(0.5f * rel) * sqrtf(inv) : fast_exp2(rel) * inv;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  if (__builtin_expect(small, 0)) column_sums(ref, [](float sum, float p, float f) { return fmaf(p * f, f, sum); });
+  else column_sums(ref, [](float sum, float p, float f) { return fmaf(p, f, sum); });
 }
+#undef MADAKV_FUSED_LOAD
 
 // The parked chunks' column sums, from their logits and the heads' row offsets: the arithmetic (and its order) of the
-// kernel's own last step.  Grid (parked chunk, head).
+// kernel's own last step on logits.  Grid (parked chunk, head).
 template <int NRB, int NS>
 __global__ __launch_bounds__(SCORE_THREADS) void score_fused_finish_kernel(ScoreArgs a) {
   constexpr int CK = 4 * NS * 32;
@@ -1299,7 +1420,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2
 #undef MADAKV_WIN_PARK
 
   // ---- the head-wide statistics (by now the other workgroups have normally posted theirs)
-  collect_row_stats<D>(a, hv, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, pm, &s_fail);
+  collect_row_stats<D>(a, hv, split, fs, Lh, Mh, rowbase, kg, qs, part, offs, nullptr, pm, &s_fail);
   __syncthreads();
   if (split == 0 && wa.lse && tid < Mh) wa.lse[(lb * a.H + kvh) * (long long)a.G * a.W + rowbase + tid] = offs[tid] * 0.6931471805599453f;
   const float mxw = part[(wave * 32 + col) * 2];           // the wave's own row maximum again
@@ -1312,7 +1433,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(2
     float cs[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) cs[j] = lg[it][j] * rs;
-    const float sum = half_fold(cs, lane);                 // over the 32 rows: psi of the key that this lane (of the first 16) has
+    const float sum = half_fold<1>(cs, lane);                 // over the 32 rows: psi of the key that this lane (of the first 16) has
     const int key = t0 + 8 * ((lane & 15) >> 2) + 4 * half + (lane & 3);
     // (more than 32 proxy rows: the block's share of psi, added to the other blocks' in block order afterwards)
     float* psi_dst = a.rb_count > 1 ? a.psi_part + (hv % a.rb_count) * a.psi_part_stride : a.psi;
@@ -1845,7 +1966,7 @@ __global__ __launch_bounds__(256) void score_blocks_sum_kernel(const float* part
 template <int D, int NRB, int NS, int KIND>
 static void launch_fused_kernel(const ScoreArgs& a, dim3 grid, hipStream_t st) {
   constexpr int RS = (KIND == K_F32 ? 2 * D : D) + 8;
-  const size_t lds = ((size_t)a.mpad + 4 * 32) * RS * 2 + ((size_t)4 * a.mpad * 2 + a.mpad + 512) * sizeof(float);
+  const size_t lds = ((size_t)a.mpad + 4 * 32) * RS * 2 + ((size_t)4 * a.mpad * 3 + 4 * a.mpad + 512) * sizeof(float);
   if (lds > 48 * 1024)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_fused_kernel<D, NRB, NS, KIND>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL((score_fused_kernel<D, NRB, NS, KIND>), grid, dim3(SCORE_THREADS), lds, st, a);

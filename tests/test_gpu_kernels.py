@@ -280,6 +280,37 @@ def softmax_rows(q, k, W, kv_head):
     return torch.softmax(x, -1), torch.logsumexp(x, -1)
 
 
+@pytest.mark.parametrize("top,base", [(-105, 0), (0, 0), (-105, -300)], ids=["far_below", "above", "all_low"])
+@pytest.mark.parametrize("dtype,H,W,d,L", [("bf16", 2, 32, 128, 4100), ("bf16", 2, 64, 128, 3900), ("bf16", 2, 17, 64, 3000),
+                                            ("bf16", 2, 64, 64, 2500), ("fp32", 2, 16, 64, 2048), ("fp32", 2, 40, 128, 1500)])
+def test_scores_far_from_a_waves_first_keys(dtype, H, W, d, L, top, base):
+    """Keys whose logits are up to 2^95, or 2^200, times those of the first keys that their wave sees, while the row's normaliser is
+    2^200 times those: the terms' factor alone would flush to zero, or the terms pass what they are kept for.  Or
+    all that 2^300 lower, where a row that sees none of a wave's keys has nothing to be scaled up.  Logits are at most 500 (log2),
+    rounded to 2^-24 of that a few times: 1e-4 relative; 1e-3 is allowed, down to the smallest normal numbers."""
+    g = torch.Generator().manual_seed(L + W)
+    want = torch.empty(H, L).uniform_(-195, top, generator=g)                # a key's logit, log2
+    want[:, :1024] = 0.
+    want[:, (torch.arange(L) >= 1024) & (torch.arange(L) % 1024 < 128)] = -200.
+    if W > 32:                                   # (768 keys per chunk)
+        want[:, (torch.arange(L) >= 768) & (torch.arange(L) % 768 < 128)] = -200.
+    q, k = 0.25 * torch.randn(1, 1, H, W, d, generator=g), 0.5 * torch.randn(1, 1, H, L, d, generator=g)
+    q[..., 0] = 4.
+    k[0, 0, :, :, 0] = (want + base) * (d ** 0.5 / (4. * 1.4427))
+    q, k = (t.to(DEV, torch.bfloat16 if dtype == "bf16" else torch.float32) for t in (q, k))
+    mask = torch.randint(0, 2, (1, L), generator=g).to(torch.uint8).to(DEV)
+    eng = MB.MadaKV(n_layers=1, batch=1, n_q_heads=H, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=W + L // 4, dtype=dtype,
+                    pool_k=1, out_fp32=1, device=DEV)
+    say(f"scores far from a wave's first keys {dtype} H={H} W={W} d={d} L={L} top={top} base={base}")
+    eng.score(0, 1, q, k, mask)
+    torch.cuda.synchronize()
+    for h in range(H):
+        ref = softmax_rows(q[0, 0], k[0, 0], W, h)[0].sum(0)
+        err = (eng.psi[0, 0, h].cpu().double() - ref).abs()
+        assert (err <= 1e-3 * ref + 2.0 ** -125 * W).all(), float((err / ref).max())
+    eng.close()
+
+
 @pytest.mark.parametrize("Hq,H,W,d,L,where", [
     (3, 3, 17, 64, 600, [5]), (3, 3, 32, 64, 1100, range(0, 512)), (5, 1, 9, 128, 1100, [31, 32, 700]), (5, 1, 9, 128, 1100, range(512, 1024)),
     (7, 1, 10, 64, 900, [0, 600]), (2, 2, 16, 64, 400, range(0, 128))],
