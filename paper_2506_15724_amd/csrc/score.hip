@@ -339,8 +339,8 @@ _Pragma("unroll") \
 // ------------------------------------------------------------------------------------
 // More than 64 proxy rows (grouped queries: G*W up to 256), the same two sweeps.  The arithmetic per
 // key grows with the rows and is what bounds these kernels (one exp2 per logit and sweep on the vector
-// unit; the contraction is a fraction of that), so the layout serves the vector unit: wave w owns
-// proxy rows [32 NRB w, 32 NRB (w + 1)) for all keys of the workgroup's chunk and keeps their Q
+// unit; the contraction is a fraction of that), so the layout serves the vector unit: a wave owns
+// one or two blocks of 32 proxy rows for all keys of the workgroup's chunk and keeps their Q
 // fragments in registers; the waves share the keys.  Sweep 1 needs no merge among the waves (a row's
 // statistics over the chunk are complete in its wave) and multiplies the other way round, S^T = K Q^T:
 // a lane then holds one row against 16 keys, the running (max, sum) of a row is one register pair and
@@ -397,7 +397,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
   const int ntiles = (chunk1 - chunk0 + DMA_TK - 1) / DMA_TK;
   const int half = lane >> 5, col = lane & 31;
   const int MB = a.mpad / 32;
-  const int rb0 = wave * NRB;                  // first row block of this wave
+  // Row blocks of this wave: `role` and, with two per wave, role + NW.  Where the rows leave the second of some waves empty (160
+  // rows: five blocks for four waves) it is left out, and the roles go round from workgroup to workgroup: wave w of all
+  // workgroups of a compute unit is on the same SIMD, and the light ones would help only that.  (Score and
+  // statistics calls over 32K keys: 64 heads of 160 rows 341 -> 305 us, 56 of 192 rows 343 -> 332, 112 of 224 rows 628 -> 608; a branch
+  // per block instead of two pieces of code is 5% slower than that.)
+  const int role = NRB == 1 ? wave : __builtin_amdgcn_readfirstlane((wave + (int)(blockIdx.x + blockIdx.y)) % NW);
+  const bool second = NRB == 2 && (role + NW) * 32 < a.M;
   const int first_masked = a.L - a.W + 1;      // keys below this are visible to every proxy row
 
   // sweep 2: the rows' offsets (ordinary LDS traffic, so before the first key is on its way)
@@ -423,7 +429,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
   for (int b = 0; b < NRB; ++b)
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      const int row = (rb0 + b) * 32 + (j >> 2) * 8 + half * 4 + (j & 3);     // (a block past the last: rows that count for nothing)
+      const int row = (role + b * NW) * 32 + (j >> 2) * 8 + half * 4 + (j & 3);     // (a block past the last: rows that count for nothing)
       if (PASS == 2) st_m[b][j] = row < a.mpad ? offs[row] : __builtin_inff();
     }
 #pragma unroll
@@ -456,7 +462,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
   bf16x8_t areg[NRB][KS];
 #pragma unroll
   for (int b = 0; b < NRB; ++b) {
-    const int row = (rb0 + b) * 32 + col;
+    const int row = (role + b * NW) * 32 + col;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       uint4 val = make_uint4(0, 0, 0, 0);
@@ -493,15 +499,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
     // Sweep 2's vector arithmetic runs on the BS logits a lane holds of every row after the contractions of BS
     // subtiles.  In a tail tile (it holds keys that some proxy row must not see: the last W - 1 keys of the head,
     // keys past the chunk's end) such logits become NEG_BIG, in both sweeps.
-#define MADAKV_DMA_VECTOR(TAIL)                                                                      \
-    _Pragma("unroll") for (int b = 0; b < NRB; ++b) {                                                \
+#define MADAKV_DMA_VECTOR(TAIL, NB)                                                                  \
+    _Pragma("unroll") for (int b = 0; b < (NB); ++b) {                                               \
       _Pragma("unroll") for (int j = 0; j < 16; ++j) {                                               \
         float x[BS];                                                                                 \
         _Pragma("unroll") for (int u = 0; u < BS; ++u) {                                             \
           x[u] = acc[u][b][j];                                                                       \
           if (TAIL) {                                                                                \
             const int key = chunk0 + t * DMA_TK + (s0 + u) * 32 + col;                               \
-            const int row = (rb0 + b) * 32 + (j >> 2) * 8 + half * 4 + (j & 3);                      \
+            const int row = (role + b * NW) * 32 + (j >> 2) * 8 + half * 4 + (j & 3);                      \
             const int pos = a.L - a.W + (row % a.W);                                                 \
             const bool valid = (key < chunk1) && (key <= pos) && (row < a.M);                        \
             x[u] = valid ? x[u] : NEG_BIG;                                                           \
@@ -516,13 +522,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
     // The running maximum stays in accumulator units (scale > 0).  A row that has seen no key yet holds NEG_BIG and
     // a meaningless, finite sum, which the first real key (and any merge with real statistics) multiplies by
     // exp2(-huge) = 0.
-#define MADAKV_DMA_ROWS(TAIL)                                                                        \
-    _Pragma("unroll") for (int b = 0; b < NRB; ++b) {                                                \
+#define MADAKV_DMA_ROWS(TAIL, NB)                                                                    \
+    _Pragma("unroll") for (int b = 0; b < (NB); ++b) {                                               \
       f32x16_t xt = f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; \
       _Pragma("unroll") for (int ks = 0; ks < KS; ++ks)                                              \
         xt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfrag[0][ks], areg[b][ks], xt, 0, 0, 0);        \
       if (TAIL) {                                                                                    \
-        const int row = (rb0 + b) * 32 + col;                                                        \
+        const int row = (role + b * NW) * 32 + col;                                                        \
         const int pos = a.L - a.W + (row % a.W);                                                     \
         _Pragma("unroll") for (int j = 0; j < 16; ++j) {                                             \
           const int key = chunk0 + t * DMA_TK + s0 * 32 + 8 * (j >> 2) + 4 * half + (j & 3);         \
@@ -586,9 +592,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
       // code, so that the second row block's contraction can be issued between the first block's vector
       // instructions (a wave issues in order: what follows a matrix instruction that waits for its predecessor
       // waits with it).
-#define MADAKV_DMA_CONTRACT                                                                          \
+#define MADAKV_DMA_CONTRACT(NB)                                                                      \
       if (BS == 1) {                                                                                 \
-        _Pragma("unroll") for (int b = 0; b < NRB; ++b) {                                            \
+        _Pragma("unroll") for (int b = 0; b < (NB); ++b) {                                           \
           acc[0][b] = f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; \
           _Pragma("unroll") for (int ks = 0; ks < KS; ++ks)                                          \
             acc[0][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(areg[b][ks], bfrag[0][ks], acc[0][b], 0, 0, 0); \
@@ -597,13 +603,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
       if (PASS == 1) {
         static_assert(PASS == 2 || BS == 1, "sweep 1 takes one subtile at a time");
         (void)acc;
-        if (tail) { MADAKV_DMA_ROWS(true) } else { MADAKV_DMA_ROWS(false) }
-      } else if (tail) {
-        MADAKV_DMA_CONTRACT
-        MADAKV_DMA_VECTOR(true)
+        if (tail) { MADAKV_DMA_ROWS(true, NRB) } else if (second) { MADAKV_DMA_ROWS(false, NRB) } else { MADAKV_DMA_ROWS(false, 1) }
+      } else if (tail) {                         // (empty blocks count for nothing: offsets of +inf)
+        MADAKV_DMA_CONTRACT(NRB)
+        MADAKV_DMA_VECTOR(true, NRB)
+      } else if (NRB == 2 && !second) {
+        MADAKV_DMA_CONTRACT(1)
+        MADAKV_DMA_VECTOR(false, 1)
       } else {
-        MADAKV_DMA_CONTRACT
-        MADAKV_DMA_VECTOR(false)
+        MADAKV_DMA_CONTRACT(NRB)
+        MADAKV_DMA_VECTOR(false, NRB)
         if (BS == 1 && NRB == 2 && PASS == 2 && KS == 8) {
           // the order asked of the compiler: the first block's eight matrix instructions, then each of the second
           // block's followed by four plain and two exp2 instructions of the first block's arithmetic
@@ -621,7 +630,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
 #pragma unroll
         for (int u = 0; u < BS; ++u) {
           const float cs = colsum[u] + __shfl_xor(colsum[u], 32, 64);
-          const uint32_t dst = red_lds + (uint32_t)((((t & 1) * NW + wave) * DMA_TK + (s0 + u) * 32 + col) * 4);
+          const uint32_t dst = red_lds + (uint32_t)((((t & 1) * NW + role) * DMA_TK + (s0 + u) * 32 + col) * 4);
           if (half == 0) asm volatile("ds_write_b32 %0, %1" :: "v"(dst), "v"(cs) : "memory");
         }
       }
@@ -659,8 +668,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PASS ==
         l = row_l[b] * fast_exp2((row_m[b] - mx) * a.scale_log2) + l2 * fast_exp2((m2 - mx) * a.scale_log2);
         m = mx * a.scale_log2;
       }
-      if (rb0 + b < MB && half == 0) {
-        const int row = (rb0 + b) * 32 + col;
+      if (role + b * NW < MB && half == 0) {
+        const int row = (role + b * NW) * 32 + col;
         rs[row * 2] = m; rs[row * 2 + 1] = l;
       }
     }

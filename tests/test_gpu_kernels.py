@@ -280,6 +280,21 @@ def softmax_rows(q, k, W, kv_head):
     return torch.softmax(x, -1), torch.logsumexp(x, -1)
 
 
+@pytest.mark.parametrize("G,W,d,L", [(3, 43, 128, 700), (4, 40, 128, 4100), (7, 23, 64, 2100), (6, 32, 128, 64), (3, 64, 64, 1500),
+                                      (7, 32, 128, 3000), (5, 45, 128, 1030)], ids=lambda x: str(x))
+def test_scores_where_waves_own_one_or_two_row_blocks(G, W, d, L):
+    """Five to eight blocks of 32 proxy rows for four waves (129, 160, 161, 192, 224 and 225 rows), whose second block is left out where
+    it is empty, in chunks that start the round of the waves anywhere.  The tolerance of every psi check (1e-3)."""
+    wl = workload("row_blocks", n_q_heads=3 * G, n_kv_heads=3, head_dim=d, window=W, ctx_len=max(L, W + 24), budget=W + 16)
+    q, k, v, mask, masks = PU.make_inputs(wl, DEV)
+    eng = engine(wl)
+    say(f"row blocks {G * W} rows d={d} L={wl.ctx_len}")
+    eng.score(0, 1, q, k, mask)
+    torch.cuda.synchronize()
+    assert check_psi(eng, wl, q, k) < 1e-4
+    eng.close()
+
+
 @pytest.mark.parametrize("top,base", [(-105, 0), (0, 0), (-105, -300)], ids=["far_below", "above", "all_low"])
 @pytest.mark.parametrize("dtype,H,W,d,L", [("bf16", 2, 32, 128, 4100), ("bf16", 2, 64, 128, 3900), ("bf16", 2, 17, 64, 3000),
                                             ("bf16", 2, 64, 64, 2500), ("fp32", 2, 16, 64, 2048), ("fp32", 2, 40, 128, 1500)])
