@@ -1193,7 +1193,8 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
   // a row's factor, exp2(reference - max) / sum (a wave has not more than 64 rows; a row that sees none of the wave's keys has
   // a reference of 0 and no terms)
   const int r = min(lane, a.mpad - 1);
-  const float rel = fminf(ref[r] - (s_fail ? offs[r] : norm[2 * r]), 0.f), inv = s_fail ? 1.f : norm[2 * r + 1];
+  const float dist = ref[r] - (s_fail ? offs[r] : norm[2 * r]), inv = s_fail ? 1.f : norm[2 * r + 1];
+  const float rel = dist > 0.f ? 0.f : dist;                 // (a normaliser that is no number stays one: fminf would lose it)
   // Where the wave's reference is far below the head's maximum, the factor alone would flush to zero and its product
   // with a large term would not: two factors then.
   const bool small = __any(rel < -100.f && inv > 0.f);

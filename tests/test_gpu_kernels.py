@@ -326,6 +326,32 @@ def test_scores_far_from_a_waves_first_keys(dtype, H, W, d, L, top, base):
     eng.close()
 
 
+@pytest.mark.parametrize("dtype,H,W,d,L", [("bf16", 4, 32, 128, 4100), ("bf16", 4, 64, 64, 3900), ("fp32", 4, 16, 64, 2048)])
+@pytest.mark.parametrize("spin", [None, "1"])
+def test_scores_of_a_head_with_a_key_that_is_no_number(dtype, H, W, d, L, spin, monkeypatch):
+    """Every proxy row sees the key, so no score of its head is a number, in whichever chunk and also where a workgroup stopped
+    waiting and went its own way; the other heads' scores are as ever."""
+    g = torch.Generator().manual_seed(L)
+    q, k = torch.randn(1, 1, H, W, d, generator=g), torch.randn(1, 1, H, L, d, generator=g)
+    k[0, 0, 0, L - W - 3, 5], k[0, 0, 2, 7, 0] = float("nan"), float("nan")
+    mask = torch.randint(0, 2, (1, L), generator=g).to(torch.uint8).to(DEV)
+    q, k = (t.to(DEV, torch.bfloat16 if dtype == "bf16" else torch.float32) for t in (q, k))
+    eng = MB.MadaKV(n_layers=1, batch=1, n_q_heads=H, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=W + L // 4, dtype=dtype,
+                    pool_k=1, out_fp32=1, device=DEV)
+    if spin:
+        monkeypatch.setenv("MADAKV_SCORE_SPIN_LIMIT", spin)          # workgroups that find a word missing go their own way
+    eng.score_ws.zero_()
+    say(f"a key that is no number {dtype} H={H} W={W} d={d} L={L} spin={spin}")
+    eng.score(0, 1, q, k, mask)
+    torch.cuda.synchronize()
+    say(f"{int(eng.score_ws[:4].view(torch.int32)[0])} workgroups went their own way")
+    assert torch.isnan(eng.psi[0, 0, 0::2]).all()
+    for h in range(1, H, 2):
+        nbad, worst = PU.psi_close(eng.psi[0, 0, h].cpu().numpy()[None], softmax_rows(q[0, 0], k[0, 0], W, h)[0].sum(0).numpy()[None], 1, W, L)
+        assert nbad == 0, (nbad, worst)
+    eng.close()
+
+
 @pytest.mark.parametrize("Hq,H,W,d,L,where", [
     (3, 3, 17, 64, 600, [5]), (3, 3, 32, 64, 1100, range(0, 512)), (5, 1, 9, 128, 1100, [31, 32, 700]), (5, 1, 9, 128, 1100, range(512, 1024)),
     (7, 1, 10, 64, 900, [0, 600]), (2, 2, 16, 64, 400, range(0, 128))],
