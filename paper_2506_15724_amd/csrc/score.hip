@@ -900,8 +900,10 @@ __device__ __forceinline__ void exchange_row_stats(const ScoreArgs& a, int head,
 // two folds and one product per logit, the exp2 (one) and everything else under the loads.  Score and statistics calls before /
 // after, us: 32 heads of 128K keys, 32 rows 255 / 228, 64 rows 358 / 326, 64 rows and 64 dims 290 / 246; 32 of 32K 83 / 77; 128 of
 // 16K 119 / 113.  (The polling is not what costs: one lane of a row polling for all changes nothing, nor does
-// starting the heads one after the other.)  A row's whole sum over the wave's keys beyond which its terms are not used (2^100, so that no product overflows):
-constexpr float LATE_SUM = 0x1p100f;
+// starting the heads one after the other.)  A row's terms are not used beyond
+// - 2^100 of their whole sum over the wave's keys, so that no product overflows;
+// - a reference of 2^23, so that reference + exponent is exact (logits of 2^30 and more gave zeros and NaN without this).
+constexpr float LATE_SUM = 0x1p100f, LATE_REF = 0x1p23f;
 template <int D, int NRB, int NS, int KIND = K_BF16>
 __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(KIND == K_F32 && D == 128 ? 1 : MADAKV_FUSED_WPE, KIND == K_F32 && D == 128 ? 1 : MADAKV_FUSED_WPE))) void score_fused_kernel(ScoreArgs a) {
   constexpr bool F8 = KIND == K_E4M3, F32 = KIND == K_F32;
@@ -1059,7 +1061,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
   // largest logit of the wave's first subtile (a whole number, so that nothing is rounded but the difference).  The
   // terms are formed under the loads of the keys that follow; behind the last subtile the row sums are additions and the column
   // sums products with one factor per row and wave.
-  // In a workgroup in which a row's terms pass LATE_SUM or are no numbers, and in the parked chunks: the logits themselves, and
+  // In a workgroup in which a row's terms pass LATE_SUM, its reference LATE_REF or are no numbers, and in the parked chunks: the logits themselves, and
   // all row maxima and two exp2 per logit between the last key and the scores.
   float x[NS][NRB][16];
   const auto sweep = [&](auto terms_t) __attribute__((always_inline)) {
@@ -1117,11 +1119,12 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
         for (int it = 1; it < NS; ++it) sum[j] += x[it][b][j];
       }
       const float l = half_fold<1>(sum, lane);
-      if (!(l <= LATE_SUM)) s_late = 1;         // (NaN too)
       if (col < 16) {
         const int row = b * 32 + (col >> 2) * 8 + half * 4 + (col & 3);
+        const float rf = ref[row];
+        if (!(l <= LATE_SUM) || fabsf(rf) > LATE_REF) s_late = 1;         // (NaN too)
         const int e = l > 0.f ? __builtin_amdgcn_frexp_expf(l) : 0;
-        part[(wave * a.mpad + row) * 2] = l > 0.f ? ref[row] + (float)e : NEG_BIG;
+        part[(wave * a.mpad + row) * 2] = l > 0.f ? rf + (float)e : NEG_BIG;
         part[(wave * a.mpad + row) * 2 + 1] = ldexpf(l, -e);
       }
     }

@@ -326,6 +326,36 @@ def test_scores_far_from_a_waves_first_keys(dtype, H, W, d, L, top, base):
     eng.close()
 
 
+@pytest.mark.parametrize("Hq,H,W,d,L,dtype", [(2, 2, 16, 64, 700, "bf16"), (2, 2, 40, 128, 3000, "bf16"), (2, 2, 16, 128, 2100, "bf16"),
+                                              (3, 1, 16, 64, 500, "fp32"), (2, 2, 16, 128, 9000, "fp32"), (1, 1, 16, 64, 17000, "fp32")], ids=lambda x: str(x))
+@pytest.mark.parametrize("log2", [11, 20, 23, 24, 26, 30, 40])
+def test_scores_of_large_logits(Hq, H, W, d, L, dtype, log2):
+    """Logits of +-2^11 to 2^40, of which fp32 holds a short fraction or none: a quarter of the keys have the one, the others the
+    other, so every proxy row pays the same to each of the visible keys that have the larger one and nothing to the rest.  A logit and a
+    row's max + log2(sum) are rounded by half a unit of their last place, 2^(log2 - 24), a score by that many times ln 2 in all.  Beyond 2^23 the sum of a row
+    is lost in that; the keys with the larger logit still score above the others."""
+    g = torch.Generator().manual_seed(L)
+    sign = torch.where(torch.rand(H, L, generator=g) < 0.25, 1., -1.)
+    sign[:, 512:640] = sign[:, L - W:] = -1.                                          # (waves whose first keys have the smaller one alone)
+    a = (2.0 ** log2 / (2.1 * d ** 0.5)) ** 0.5
+    q, k = torch.full((1, 1, Hq, W, d), a), 1.3 * a * sign[None, None, :, :, None].expand(1, 1, H, L, d)
+    q, k = (t.contiguous().to(DEV, torch.bfloat16 if dtype == "bf16" else torch.float32) for t in (q, k))
+    q[:, :, 0] *= -1.                                                                 # (a head whose large logits are the others')
+    mask = torch.randint(0, 2, (1, L), generator=g).to(torch.uint8).to(DEV)
+    eng = MB.MadaKV(n_layers=1, batch=1, n_q_heads=Hq, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=W + L // 4, dtype=dtype,
+                    pool_k=1, out_fp32=1, device=DEV)
+    say(f"logits of 2^{log2} {dtype} {Hq}/{H} W={W} d={d} L={L}")
+    eng.score(0, 1, q, k, mask)
+    torch.cuda.synchronize()
+    for h in range(H):
+        psi, ref = eng.psi[0, 0, h].cpu().double(), softmax_rows(q[0, 0], k[0, 0], W, h)[0].sum(0)
+        assert torch.isfinite(psi).all() and (psi[ref > 1e-9] > 0).all() and (psi[ref <= 1e-9] == 0).all()
+        if log2 <= 23:
+            err = (psi - ref).abs()
+            assert (err <= (1e-5 + 0.7 * 2.0 ** (log2 - 24)) * ref).all(), float((err / ref.clamp_min(1e-30)).max())
+    eng.close()
+
+
 @pytest.mark.parametrize("dtype,H,W,d,L", [("bf16", 4, 32, 128, 4100), ("bf16", 4, 64, 64, 3900), ("fp32", 4, 16, 64, 2048)])
 @pytest.mark.parametrize("spin", [None, "1"])
 def test_scores_of_a_head_with_a_key_that_is_no_number(dtype, H, W, d, L, spin, monkeypatch):
