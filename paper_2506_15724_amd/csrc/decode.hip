@@ -538,27 +538,30 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(DecodeArgs a) {
 // that the G query heads of a KV head cost no more vector instructions than one.
 //   S^T[key][q] = K_tile . Q^T     A = 16 keys x 32 dims read straight from the cache rows
 //                                  (a lane takes 16 bytes of "its" key), B = Q, kept in registers
-//   O[q][d]    += P . V_tile       contraction over 32 keys.  In S^T a lane holds 4 keys of each
-//                                  16-key block for its query; the contraction index is numbered
-//                                  so that exactly those 8 keys are the lane's A fragment of P
-//                                  (no cross-lane movement); V needs the matching rows per output
-//                                  column: transposing LDS reads (four rows of 16 columns per 16
+//   O^T[d][q]  += V_tile^T . P^T   contraction over 16 keys, twice: in S^T a lane holds 4 keys for
+//                                  its query; as bf16 hi and lo parts, which keep fp32-level accuracy,
+//                                  they are the lane's 8 entries of the B fragment (no cross-lane
+//                                  movement), against the same 4 rows of V in both halves of the A
+//                                  fragment: transposing LDS reads (four rows of 16 columns per 16
 //                                  lanes) of a wave-private LDS tile that the V rows were written to
 //                                  with coalesced 16-byte loads.
-// P goes through the MFMA as bf16 hi + lo parts (two MFMAs), which keeps fp32-level accuracy.
-// The running max / sum live per query in the lanes of S^T; the rescale factors are fetched
-// into the O layout with four lane reads per tile.
+// The running max / sum live per query in the lanes of S^T, and so do the four neighbouring dims of one query that a
+// lane has of O^T: rescaled by its own factor, left in LDS in 16-byte pieces.
 // A layer of a grouped-query model has few KV heads and a few MB of cache: the kernel is bound by the latencies of
 // one workgroup (start, length, rows, two contractions, merge), of which a wave's instructions, issued one per four
 // cycles, are the larger part.  So a workgroup has eight waves with one tile of 16 rows each in the usual piece of 128: half
-// of the instructions of a 32-row tile, a query head per wave in the merges, twice the loads in flight.  A tile of 16 keys
-// fills the contraction index of P.V with the hi and the lo parts of P against the same rows of V; O comes out transposed (a lane
-// has four neighbouring dims of one query: rescaled by its own factor, left in LDS in 16-byte pieces); the first tile adds
+// of the instructions of a 32-row tile, a query head per wave in the merges, twice the loads in flight; the first tile adds
 // to nothing and rescales nothing; the appended row is fetched from k_new / v_new in place of the cache row.
 // The rows are read with ordinary loads: a K fragment takes half of a cache line, and a non-temporal load would fetch the
-// line a second time for the other half.  Per layer call, four waves of 32 rows with non-temporal loads -> this: 4 heads of
-// 2K rows, 7 queries, 8.8 -> 7.6 us (half of it the ordinary loads); 16 heads of 2K rows 11.4 -> 9.9; 32 heads of 4K rows, 4
-// queries, 14.5 -> 11.5; 2 heads of 40K rows, 6 queries, 18.4 -> 12.6.
+// line a second time for the other half.  Per layer call, four waves of 32 rows with non-temporal loads in a layout of O[q][d] -> this: 4
+// heads of 2K rows, 7 queries, 8.8 -> 7.6 us (half of it the ordinary loads); 16 heads of 2K rows 11.4 -> 9.9; 32 heads of 4K rows, 4
+// queries, 14.5 -> 11.5; 2 heads of 40K rows, 6 queries, 18.4 -> 12.6.  Launches that fill the chip: 64 heads of 8K rows 67 -> 62, 256 of 2K
+// 71 -> 68, 128 of 16K 218 -> 218, 1024 of 2K 220 -> 217; 8-bit rows, 1024 heads of 1K, 84 -> 69.
+// Rows of 64 dims have half the bytes for the same instructions per tile: with many of them in a launch it is four waves of 32-row
+// tiles (the maxima, factors and rescaling once per 32 rows), in more workgroups at a time, and non-temporal loads of V, of which
+// an instruction takes whole lines.  Old layout / eight waves of 16 rows / this, us: 64 heads of 4K rows 22.3 / 23.9 / 18.3, of 16K 64 / 68 / 54,
+// 1024 of 2K 114 / 126 / 92; 8-bit rows, 128 heads of 4K 27 / 32 / 21, 1024 of 2K 78 / 83 / 58.  In pieces of 128 rows it is better from
+// 256 heads on: 256 of 200 rows 8.9 / 11.1 / 8.7, 512 of 80 9.5 / 10.5 / 8.7, but 128 of 400 9.4 / 8.9 / 9.2, 4 of 2K 7.9 / 6.6 / 7.4.
 // ------------------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) ds16x4_t* lds_s16x4_ptr_t;
 
@@ -571,12 +574,10 @@ __device__ __forceinline__ du32x2_t e4m3x4_to_bf16x4(uint32_t w) {
   return o;
 }
 
-constexpr int GQA_WAVES = 8;
-template <int D, bool FP8, bool PAGED>   // FP8: the cache rows are E4M3 bytes, turned into bf16 operands on the fly
-__global__ __launch_bounds__(GQA_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_gqa_kernel(DecodeArgs a) {
+template <int D, bool FP8, bool PAGED, int NW, int NB>   // FP8: the cache rows are E4M3 bytes, turned into bf16 operands on the fly; NW waves of tiles of 16 NB rows
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 5 : 4, NB > 1 ? 5 : 4))) void decode_gqa_kernel(DecodeArgs a) {
   constexpr int GT = 8;                // query heads per KV head supported (columns 8..15 of the MFMA tile are padding)
-  constexpr int NW = GQA_WAVES;
-  constexpr int TR = 16;               // rows of a wave's tile
+  constexpr int TR = 16 * NB;          // rows of a wave's tile
   constexpr int KS = D / 32;           // MFMA steps over the head dimension
   constexpr int DB = D / 16;           // 16-column blocks of the output
   constexpr int RS = D + 16;           // bf16 elements per LDS row of the V tile (rows 8 banks apart: the transposing reads of a wave do not collide)
@@ -623,22 +624,26 @@ __global__ __launch_bounds__(GQA_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
 
   // K fragments and V rows of a tile; rows past the end of the piece: its last row once more, masked where they are used.
   // The appended row comes from k_new and v_new (8-bit rows: from LDS, encoded).
-  du32x4_t kraw[KS], vraw[VL];             // raw cache bytes (E4M3: 8 bytes of a K piece sit in .xy)
+  du32x4_t kraw[NB][KS], vraw[VL];         // raw cache bytes (E4M3: 8 bytes of a K piece sit in .xy)
   const auto load_tile = [&](int t) {
-    const int r = min(t + j16, r_end - 1);
-    const unsigned char* kp = row_at(kc, r);
-    if (!FP8 && has_fresh && r == len_old) kp = kn;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (FP8) { const du32x2_t t2 = *reinterpret_cast<const du32x2_t*>(kp + ks * 32 + c * 8); kraw[ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
-      else kraw[ks] = *reinterpret_cast<const du32x4_t*>(kp + ks * 64 + c * 16);
+    for (int nb = 0; nb < NB; ++nb) {
+      const int r = min(t + nb * 16 + j16, r_end - 1);
+      const unsigned char* kp = row_at(kc, r);
+      if (!FP8 && has_fresh && r == len_old) kp = kn;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (FP8) { const du32x2_t t2 = *reinterpret_cast<const du32x2_t*>(kp + ks * 32 + c * 8); kraw[nb][ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
+        else kraw[nb][ks] = *reinterpret_cast<const du32x4_t*>(kp + ks * 64 + c * 16);
+      }
     }
 #pragma unroll
     for (int i = 0; i < VL; ++i) {
       const int r = min(t + i * RPI + vsub, r_end - 1);
       const unsigned char* vp = row_at(vc, r);
       if (!FP8 && has_fresh && r == len_old) vp = vn;
-      vraw[i] = *reinterpret_cast<const du32x4_t*>(vp + vpiece * 16);
+      const du32x4_t* at16 = reinterpret_cast<const du32x4_t*>(vp + vpiece * 16);
+      vraw[i] = NB > 1 ? __builtin_nontemporal_load(at16) : *at16;
     }
   };
   const int first = r_begin + wave * TR;
@@ -653,42 +658,49 @@ __global__ __launch_bounds__(GQA_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     if (!FIRST) load_tile(t0);
     if (has_fresh && t0 <= len_old && len_old < t0 + TR) {          // the appended row, the last of the piece
       if constexpr (FP8) {
-        if (t0 + j16 >= len_old) {
 #pragma unroll
-          for (int ks = 0; ks < KS; ++ks) { const du32x2_t t2 = *reinterpret_cast<const du32x2_t*>(s_new + ks * 32 + c * 8); kraw[ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
-        }
+        for (int nb = 0; nb < NB; ++nb)
+          if (t0 + nb * 16 + j16 >= len_old) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) { const du32x2_t t2 = *reinterpret_cast<const du32x2_t*>(s_new + ks * 32 + c * 8); kraw[nb][ks] = du32x4_t{t2[0], t2[1], 0u, 0u}; }
+          }
 #pragma unroll
         for (int i = 0; i < VL; ++i)
           if (t0 + i * RPI + vsub >= len_old) vraw[i] = *reinterpret_cast<const du32x4_t*>(s_new + D + vpiece * VE);
       } else {                                                      // on its way to the cache
         unsigned char* kp = row_at(kc, len_old);
         unsigned char* vp = row_at(vc, len_old);
-        if (t0 + j16 == len_old)
 #pragma unroll
-          for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<du32x4_t*>(kp + ks * 64 + c * 16) = kraw[ks];
+        for (int nb = 0; nb < NB; ++nb)
+          if (t0 + nb * 16 + j16 == len_old)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<du32x4_t*>(kp + ks * 64 + c * 16) = kraw[nb][ks];
 #pragma unroll
         for (int i = 0; i < VL; ++i)
           if (t0 + i * RPI + vsub == len_old) *reinterpret_cast<du32x4_t*>(vp + vpiece * 16) = vraw[i];
       }
     }
-    // ---- S^T of 16 keys
-    df32x4_t sacc = df32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      du32x4_t kb = kraw[ks];
-      if (FP8) {
-        const du32x2_t c0 = e4m3x4_to_bf16x4(kraw[ks][0]), c1 = e4m3x4_to_bf16x4(kraw[ks][1]);
-        kb = du32x4_t{c0[0], c0[1], c1[0], c1[1]};
-      }
-      sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dbf16x8_t, kb), qb[ks], sacc, 0, 0, 0);
-    }
-    float p[4];
+    // ---- S^T of the tile's keys, 16 at a time
+    float p[NB][4];
     float tmax = DNEG_BIG;
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int key = t0 + 4 * c + rr;                       // in S^T the lane holds keys 4c..4c+3
-      p[rr] = key < r_end ? sacc[rr] * a.scale_log2 : DNEG_BIG;
-      tmax = fmaxf(tmax, p[rr]);
+    for (int nb = 0; nb < NB; ++nb) {
+      df32x4_t sacc = df32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        du32x4_t kb = kraw[nb][ks];
+        if (FP8) {
+          const du32x2_t c0 = e4m3x4_to_bf16x4(kraw[nb][ks][0]), c1 = e4m3x4_to_bf16x4(kraw[nb][ks][1]);
+          kb = du32x4_t{c0[0], c0[1], c1[0], c1[1]};
+        }
+        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dbf16x8_t, kb), qb[ks], sacc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        const int key = t0 + nb * 16 + 4 * c + rr;           // in S^T the lane holds keys 4c..4c+3
+        p[nb][rr] = key < r_end ? sacc[rr] * a.scale_log2 : DNEG_BIG;
+        tmax = fmaxf(tmax, p[nb][rr]);
+      }
     }
     // ---- V rows parked in the wave's LDS tile
 #pragma unroll
@@ -708,14 +720,19 @@ __global__ __launch_bounds__(GQA_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     lane_pair<32>(tmax, lo_m, hi_m); tmax = fmaxf(lo_m, hi_m);
     const float m_new = FIRST ? tmax : fmaxf(m_run, tmax);
     float psum = 0.f;
-    uint32_t hi[2], lo[2];                                   // P as bf16 hi + lo of the lane's 4 keys: the B fragment
+    dbf16x8_t pb[NB];                                        // P as bf16 hi + lo of the lane's 4 keys: the B fragment
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const df32x2_t pv = {weight_of(p[2 * e] - m_new), weight_of(p[2 * e + 1] - m_new)};
-      psum += pv[0] + pv[1];
-      hi[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pv, dbf16x2_t));          // round to nearest even
-      const df32x2_t rest = {pv[0] - bf16_lo(hi[e]), pv[1] - bf16_hi(hi[e])};
-      lo[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, dbf16x2_t));
+    for (int nb = 0; nb < NB; ++nb) {
+      uint32_t hi[2], lo[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const df32x2_t pv = {weight_of(p[nb][2 * e] - m_new), weight_of(p[nb][2 * e + 1] - m_new)};
+        psum += pv[0] + pv[1];
+        hi[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pv, dbf16x2_t));          // round to nearest even
+        const df32x2_t rest = {pv[0] - bf16_lo(hi[e]), pv[1] - bf16_hi(hi[e])};
+        lo[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, dbf16x2_t));
+      }
+      pb[nb] = __builtin_bit_cast(dbf16x8_t, du32x4_t{hi[0], hi[1], lo[0], lo[1]});
     }
     if (FIRST) {
       l_run = psum;
@@ -728,7 +745,6 @@ __global__ __launch_bounds__(GQA_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         for (int rr = 0; rr < 4; ++rr) oacc[db][rr] *= alpha;
     }
     m_run = m_new;
-    const dbf16x8_t pb = __builtin_bit_cast(dbf16x8_t, du32x4_t{hi[0], hi[1], lo[0], lo[1]});
     // the V tile must be complete before it is read with another lane mapping (same wave: in order)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -739,9 +755,12 @@ __global__ __launch_bounds__(GQA_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     const uint16_t* vf = vt + (4 * c + (j16 >> 2)) * RS + 4 * (j16 & 3);
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
-      const ds16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)(vf + db * 16));
-      const dbf16x8_t va = __builtin_bit_cast(dbf16x8_t, __builtin_shufflevector(v, v, 0, 1, 2, 3, 4, 5, 6, 7));
-      oacc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb, FIRST ? df32x4_t{0.f, 0.f, 0.f, 0.f} : oacc[db], 0, 0, 0);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const ds16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)(vf + nb * 16 * RS + db * 16));
+        const dbf16x8_t va = __builtin_bit_cast(dbf16x8_t, __builtin_shufflevector(v, v, 0, 1, 2, 3, 4, 5, 6, 7));
+        oacc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[nb], FIRST && nb == 0 ? df32x4_t{0.f, 0.f, 0.f, 0.f} : oacc[db], 0, 0, 0);
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -845,7 +864,13 @@ static hipError_t launch_decode_t(const Dims& dm, DecodeArgs& a, int grid_chunks
   // of 256 75 and 70, but 1024 heads of 512 45.6 and 47.6.  8-bit rows, of which a lane has twice the elements, take four always:
   // 128 heads of 16K rows 89.3 us with either at 128 dims, 50.6 and 52.9 at 64 (64 heads of 32K: 92.8 and 90.4, 50.4 and 48.0).
   constexpr int LONG_ROWS = sizeof(CT) == 1 ? 4 : 8;
-    if (sizeof(T) == 2 && dm.G >= 2) hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED>), grid, dim3(GQA_WAVES * 64), 0, st, a);   // grouped queries in bf16: the MFMA kernel
+  if (sizeof(T) == 2 && dm.G >= 2) {                                 // grouped queries in bf16: the MFMA kernel
+    if constexpr (D == 64) if (a.chunk_rows > 128 || dm.heads > 128) {
+      hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED, 4, 2>), grid, dim3(256), 0, st, a);
+      return hipGetLastError();
+    }
+    hipLaunchKernelGGL((decode_gqa_kernel<D, sizeof(CT) == 1, PAGED, 8, 1>), grid, dim3(512), 0, st, a);
+  }
   else if (LPR >= 16 && dm.G == 1 && a.chunk_rows == 128) {          // eight waves, a piece in one trip
     if constexpr (LPR >= 16) hipLaunchKernelGGL((decode_attn_kernel<T, CT, LPR, 1, LPR / 4, 8, PAGED>), grid, dim3(512), 0, st, a);
   }

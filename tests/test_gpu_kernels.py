@@ -80,6 +80,11 @@ def test_fp32_scores(kw, monkeypatch):
     (dict(n_q_heads=28, n_kv_heads=4, head_dim=128, ctx_len=9000, budget=2000), [6001, 128, 127, 129]),
     (dict(n_q_heads=8, n_kv_heads=1, head_dim=64, ctx_len=9000, budget=4500), [4499]),
     (dict(n_q_heads=12, n_kv_heads=2, head_dim=128, ctx_len=5000, budget=1000, cache_fp8=1), [1700, 159]),
+    # grouped queries of 64 dims in large launches: tiles of 32 rows, in longer pieces and, with many heads, in those of 128
+    (dict(batch=2, n_q_heads=64, n_kv_heads=8, head_dim=64, ctx_len=9000, budget=4300), [8000, 511, 512, 513, 543, 544, 545, 31, 32, 33, 0, 1]),
+    (dict(batch=2, n_q_heads=56, n_kv_heads=8, head_dim=64, ctx_len=9000, budget=4300, cache_fp8=1), [8000, 511, 512, 513, 543, 544, 545, 31, 32, 33, 0, 1]),
+    (dict(batch=4, n_q_heads=128, n_kv_heads=64, head_dim=64, ctx_len=2000, budget=200), [1500, 127, 128, 129, 159, 160, 161, 31, 32, 33, 0, 1]),
+    (dict(batch=4, n_q_heads=192, n_kv_heads=64, head_dim=64, ctx_len=2000, budget=200, cache_fp8=1), [1500, 127, 128, 129, 159, 160, 161, 31, 32, 33, 0, 1]),
     (dict(n_q_heads=3, n_kv_heads=1, head_dim=128, ctx_len=12000, budget=11000, dtype="fp32"), [10999]),
     (dict(n_q_heads=2, n_kv_heads=2, head_dim=64, ctx_len=400, budget=300, dtype="fp32"), [299, 255]),
     # single queries, little to read: pieces of 128 rows in one trip (by the bytes of a row), heads at their edges and longer than all of them
@@ -596,6 +601,8 @@ def test_decode_static_cuts_heads_like_the_workspace_call(kw, lens):
     (dict(n_q_heads=14, n_kv_heads=2, head_dim=128, ctx_len=2000, budget=400, page_rows=64), [128, 640]),       # grouped queries: pieces of 128 rows
     (dict(n_q_heads=8, n_kv_heads=1, head_dim=64, ctx_len=2000, budget=400, page_rows=16, cache_fp8=1), [255]),
     (dict(n_q_heads=8, n_kv_heads=4, head_dim=128, ctx_len=9000, budget=6000, page_rows=256, hcc_rho=16), [8000, 512, 1, 256 + 128]),
+    (dict(n_q_heads=64, n_kv_heads=16, head_dim=64, ctx_len=9000, budget=4300, page_rows=64), [8000, 512, 511, 256, 240, 32, 16] + [40] * 9),     # 64 dims: tiles of 32 rows
+    (dict(n_q_heads=32, n_kv_heads=16, head_dim=64, ctx_len=9000, budget=4300, page_rows=16, cache_fp8=1), [8000, 512, 511, 256, 240, 32, 16] + [40] * 9),
     (dict(n_q_heads=4, n_kv_heads=4, head_dim=128, ctx_len=2000, budget=400, page_rows=32, cache_fp8=1), [256, 255, 512, 33]),
     (dict(n_q_heads=6, n_kv_heads=2, head_dim=128, ctx_len=1500, budget=600, page_rows=16, dtype="fp32"), [512, 271]),
 ], ids=lambda x: f"q{x['n_q_heads']}_kv{x['n_kv_heads']}_d{x['head_dim']}_P{x['page_rows']}_{x.get('dtype', 'bf16')}" if isinstance(x, dict) else "")
