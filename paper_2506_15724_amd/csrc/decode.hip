@@ -808,7 +808,7 @@ static int plan_longest(const madakv_config& c, int longest_rows) { return std::
 // whatever hcc_rho is, 128 heads of which 8 hold half of the rows, 512 on average, took 21.3 us instead of 14.7, 512 heads of 256,
 // 16 with half of the rows, 34 instead of 21.  Neither depends on what the host knows of the
 // longest head, so that a call's result does not either; only the grid, at most max_chunks pieces, shrinks when it is known.
-constexpr int SHORT_PIECES = 2000;             // most 128-row pieces of a launch (or two per head): what the static scratch holds of 8 queries x 128 dims
+constexpr int SHORT_PIECES = 2000;             // most 128-row pieces of a launch: what the static scratch holds of 8 queries x 128 dims
 static_assert((size_t)SHORT_PIECES * 8 * (128 + 2) * sizeof(float) <= MADAKV_STATIC_SCRATCH_BYTES, "short pieces must fit the static scratch");
 DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows) {
   DecodePlan p;
@@ -819,16 +819,19 @@ DecodePlan decode_plan(const Dims& dm, const madakv_config& c, int longest_rows)
   // A launch that does not fill the chip with it: pieces of 128 rows, one trip of all waves to memory each, where a piece of 256 is
   // two (grouped queries) to four trips one behind the other.
   // Grouped queries up to 64K rows in all.  (Twice as far: 2 heads of 40K rows 12.6 -> 16.1 us; four times: 32 heads of 4K rows
-  // 11.5 -> 13.4: the pieces to merge.)  Single ones, us per call (device), 256-row pieces -> these: 32 heads of 200 rows 6.0 -> 5.0,
-  // of 500 7.2 -> 6.3, of 1K 8.6 -> 7.0, of 2K 10.2 -> 9.5, 16 of 2.5K 8.7 -> 8.5, 20 of 1K fp32 rows 11.2 -> 8.5.  Rows of less
-  // than 256 bytes, of which a piece of 256 takes no more trips, lose: 20 heads of 400 8-bit rows 5.1 -> 5.3.  Heads of few
-  // pieces gain up to twice as many rows in all: 128 of 500 rows 9.9 -> 9.8, 128 calls over 128 of 900 2643 -> 2627 us; over 80 of
-  // 1.5K they lose, 2401 -> 2658.  Heads of hardly more than one such piece keep the longer ones, which they fill alone (32 of 120
-  // rows: 4.2 us either way).
+  // 11.5 -> 13.4: the pieces to merge.)
+  // Single ones on up to 128 heads, up to 64K rows in all while a head has few pieces to merge, fewer with more of them.  Us per call
+  // (device), 256-row pieces / these: 8 heads of 300 rows 6.9 / 6.3, of 2K 9.1 / 7.8, of 4K 10.0 / 9.7, 32 of 600 9.2 / 7.6, of 1.5K 10.8 / 10.4,
+  // of 1.7K fp32 rows 16.9 / 15.4, 64 of 300 9.4 / 8.0, of 700 10.7 / 10.3, 96 of 600 11.9 / 11.9, 128 of 200 9.5 / 8.5, of 450 11.6 / 11.8
+  // (paged, of 400 12.6 / 11.6).  Beyond: 8 heads of 6K 11.4 / 11.6, 16 of 3K 11.0 / 11.0, of 4K 12.4 / 13.0, 32 of 2K 11.9 / 12.4, 64 of 1K 12.0 / 12.3;
+  // more heads fill the chip with 256-row pieces: 192 of 300 rows 11.9 / 12.5, 256 of 200 10.9 / 11.4, 512 of 130 12.0 / 14.0.  Rows of less
+  // than 256 bytes, of which a piece of 256 takes no more trips, lose: 20 heads of 400 8-bit rows 5.1 / 5.3.  Heads of hardly more
+  // than one such piece keep the longer ones, which they fill alone: 32 of 140 rows and room 5.8 / 6.4, of 150 6.5 / 6.6, of 175 7.1 / 6.7.
   const long long rows = dm.heads * typical;
   const int row_bytes = dm.d * (c.cache_fp8 ? 1 : c.dtype == MADAKV_BF16 ? 2 : 4);
-  const bool short_pieces = dm.heads <= 512 && (dm.G >= 2 ? c.dtype == MADAKV_BF16 && rows <= 65536
-                                                           : row_bytes >= 256 && typical > 160 && rows <= (typical <= 768 ? 131072 : 65536));
+  const long long most = typical <= 160 ? 0 : typical <= 1024 ? 65536 : typical <= 2048 ? 57344 : typical <= 4096 ? 32768 : 0;
+  const bool short_pieces = dm.G >= 2 ? dm.heads <= 512 && c.dtype == MADAKV_BF16 && rows <= 65536
+                                      : dm.heads <= 128 && row_bytes >= 256 && rows <= most;
   if (short_pieces) p.chunk_rows = 128;
   long long want = std::max<long long>((std::max(2, c.hcc_rho) * typical + p.chunk_rows - 1) / p.chunk_rows, 512 / dm.heads);
   if (short_pieces) want = std::min<long long>(want, SHORT_PIECES / dm.heads);

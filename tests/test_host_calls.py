@@ -226,3 +226,39 @@ def test_per_head_kernels_fit_beside_a_gather(runtime, cfg):
         left = unit - unit // claim * claim
         assert max(lds["select"]) + 2048 <= left and max(lds["stats"]) + 2048 <= left + claim, (lds, left)
         """, cfg)
+
+
+SHORT, USUAL = "decode_attn_kernelIttLi16ELi1ELi4ELi8E", "decode_attn_kernelIttLi16ELi1ELi4ELi4E"          # eight waves, pieces of 128 rows; four
+TILES16, TILES32 = "Li8ELi1EE", "Li4ELi2EE"
+
+
+@pytest.mark.parametrize("heads,rows,want", [(32, 160, USUAL), (32, 161, SHORT), (64, 1024, SHORT), (64, 1025, USUAL), (28, 2048, SHORT), (29, 2048, USUAL),
+                                             (15, 2049, SHORT), (16, 2049, USUAL), (8, 4096, SHORT), (8, 4097, USUAL), (128, 200, SHORT), (129, 200, USUAL),
+                                             (512, 200, USUAL)])
+def test_single_queries_take_short_pieces_up_to(runtime, heads, rows, want):
+    """Where pieces of 128 rows are the faster ones for heads of one query: by the heads of a launch, their rows and the rows of all."""
+    scenario(runtime, f"""
+        h = create(sys.argv[3])
+        b = Z()
+        assert lib.madakv_workspace_bytes(h, I(1), None, None, C.byref(b)) == 0
+        log()
+        assert lib.madakv_decode_attn(h, I(0), I(1), *[P(T().p) for _ in range(8)], P(T(b.value).p), b, P(0)) == 0
+        (x,) = [x for x in log() if x.kind == "launch"]
+        assert {want!r} in str(x), x
+        """, good(n_layers=1, batch=heads, n_q_heads=1, n_kv_heads=1, ctx_len=9000, budget=rows - 2, max_new_tokens=2, hcc_rho=2))
+
+
+@pytest.mark.parametrize("d,heads,rows,want", [(64, 32, 2048, TILES16), (64, 32, 2049, TILES32), (64, 128, 400, TILES16), (64, 129, 400, TILES32), (64, 512, 128, TILES32),
+                                               (128, 512, 128, TILES16), (128, 64, 8192, TILES16)])
+@pytest.mark.parametrize("fp8", [0, 1])
+def test_grouped_queries_take_tiles_of(runtime, d, heads, rows, want, fp8):
+    """Tiles of 32 rows for heads of 64 dims in longer pieces than 128 rows or on more than 128 heads, of 16 rows otherwise."""
+    scenario(runtime, f"""
+        h = create(sys.argv[3])
+        b = Z()
+        assert lib.madakv_workspace_bytes(h, I(1), None, None, C.byref(b)) == 0
+        log()
+        assert lib.madakv_decode_attn(h, I(0), I(1), *[P(T().p) for _ in range(8)], P(T(b.value).p), b, P(0)) == 0
+        (x,) = [x for x in log() if x.kind == "launch"]
+        assert "decode_gqa_kernel" in str(x) and {want!r} in str(x), x
+        """, good(n_layers=1, batch=heads, n_q_heads=4, n_kv_heads=1, head_dim=d, ctx_len=9000, budget=rows - 2, max_new_tokens=2, hcc_rho=2, cache_fp8=fp8))
