@@ -900,10 +900,11 @@ __device__ __forceinline__ void exchange_row_stats(const ScoreArgs& a, int head,
 // two folds and one product per logit, the exp2 (one) and everything else under the loads.  Score and statistics calls before /
 // after, us: 32 heads of 128K keys, 32 rows 255 / 228, 64 rows 358 / 326, 64 rows and 64 dims 290 / 246; 32 of 32K 83 / 77; 128 of
 // 16K 119 / 113.  (The polling is not what costs: one lane of a row polling for all changes nothing, nor does
-// starting the heads one after the other.)  A row's terms are not used beyond
-// - 2^100 of their whole sum over the wave's keys, so that no product overflows;
-// - a reference of 2^23, so that reference + exponent is exact (logits of 2^30 and more gave zeros and NaN without this).
-constexpr float LATE_SUM = 0x1p100f, LATE_REF = 0x1p23f;
+// starting the heads one after the other.)  A row's terms are not used where
+// - their sum over the wave's keys is no number, or beyond 2^120;
+// - its reference is beyond 2^23, so that reference + exponent is exact (logits of 2^30 and more gave zeros and NaN without this).
+// A term of more than 2^100 gives its row another reference (see the kernel).
+constexpr float FAR_TERM = 0x1p100f, LATE_SUM = 0x1p120f, LATE_REF = 0x1p23f;
 template <int D, int NRB, int NS, int KIND = K_BF16>
 __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(KIND == K_F32 && D == 128 ? 1 : MADAKV_FUSED_WPE, KIND == K_F32 && D == 128 ? 1 : MADAKV_FUSED_WPE))) void score_fused_kernel(ScoreArgs a) {
   constexpr bool F8 = KIND == K_E4M3, F32 = KIND == K_F32;
@@ -923,6 +924,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
   float* refs = pm + 512;                                                 // [4 waves][mpad]
   float* norm = refs + 4 * a.mpad;                                        // [mpad][2]
   int* last = reinterpret_cast<int*>(norm + 2 * a.mpad);                  // [mpad] last key of the chunk that the row sees
+  int* drops = last + a.mpad;                                             // [4 waves][NS][mpad]
   __shared__ int s_fail, s_late;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -948,6 +950,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
   const int chunk1 = min(Lh, chunk0 + CK);
   uint16_t* kt = kt_all + (size_t)wave * 32 * RS;
   float* ref = refs + wave * a.mpad;
+  int* drop = drops + wave * NS * a.mpad;
   if (tid == 0) s_fail = s_late = 0;
 
   // subtile `it` of this wave: keys chunk0 + (it * 4 + wave) * 32 ...; PF subtiles in flight
@@ -1061,9 +1064,72 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
   // largest logit of the wave's first subtile (a whole number, so that nothing is rounded but the difference).  The
   // terms are formed under the loads of the keys that follow; behind the last subtile the row sums are additions and the column
   // sums products with one factor per row and wave.
-  // In a workgroup in which a row's terms pass LATE_SUM, its reference LATE_REF or are no numbers, and in the parked chunks: the logits themselves, and
-  // all row maxima and two exp2 per logit between the last key and the scores.
+  // A subtile with a term beyond FAR_TERM gives its block's rows their largest logit so far as a reference; by how much the terms before it
+  // are too large, an exponent, goes to LDS and into them behind the last subtile.  (A second sweep over the workgroup's keys with the logits
+  // instead, which all workgroups of the head wait for, is what such keys had cost: queries four times as long as those of the workloads put a
+  // wave's first keys that far below others in 20 to 60% of the workgroups.  Us per call with logits in registers / with that second sweep / now: 128
+  // heads of 16K keys, 32 rows, all workgroups 128 / 210 / 127, 32 of 128K, 64 rows, all 354 / 530 / 362, 64 fp32 heads of 4K, long queries 37.0 / 41.7 /
+  // 36.6.  The check itself costs nothing, 64 dims even gain by it, 60 -> 56 (112 heads of 8K, 40 rows).  The scaling in the branch, one check of
+  // both blocks, or contractions in full there spilled 40 to 190 registers in the ordinary path of two blocks of 128 dims: 341 -> 356-400 us.)
+  // In a workgroup in which a row's terms or reference pass their limits (above), and in the parked chunks: the logits themselves,
+  // and all row maxima and two exp2 per logit between the last key and the scores.
   float x[NS][NRB][16];
+  bool moved = false;                             // a reference did
+  const auto settle = [&]() __attribute__((always_inline)) {             // (what the wave's lanes leave each other in LDS)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  const auto form = [&](const f32x16_t& acc, int b, int it) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const f32x4_t m = *reinterpret_cast<const f32x4_t*>(ref + b * 32 + half * 4 + c * 8);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[it][b][c * 4 + e] = fast_exp2(fmaf(acc[c * 4 + e], a.scale_log2, -m[e]));
+    }
+    mask(x[it][b], b, it, 0.f);
+  };
+  // a block of the subtile that is still in the wave's tile once more
+  const auto again = [&](int b) __attribute__((always_inline)) {
+    const uint16_t* krow = kt + col * RS + half * (RU / 2);
+    const uint16_t* qrow = qs + (b * 32 + col) * RS + half * (RU / 2);
+    f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int c = 0; c < (F32 ? D / 8 : KS); ++c) {
+      if (F32) {
+        const f32x4_t qv = *reinterpret_cast<const f32x4_t*>(qrow + c * 8), kv = *reinterpret_cast<const f32x4_t*>(krow + c * 8);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qv[e], kv[e], acc, 0, 0, 0);
+      } else {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(qrow + c * 8), *reinterpret_cast<const bf16x8_t*>(krow + c * 8), acc, 0, 0, 0);
+      }
+    }
+    settle();
+    return acc;
+  };
+  const int frow = half * 4 + (col >> 2) * 8 + (col & 3);                // the row of a block whose fold this lane (of the first 16) gets
+  const auto move = [&](int b, int it) __attribute__((always_inline)) {
+    if (!moved)
+      for (int e = lane; e < NS * a.mpad; e += 64) drop[e] = 0;
+    moved = true;
+    settle();
+    {
+      const f32x16_t acc = again(b);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[it][b][j] = acc[j] * a.scale_log2;
+    }
+    mask(x[it][b], b, it, NEG_BIG);
+    const float mx = half_fold<0>(x[it][b], lane);
+    if (col < 16) {
+      const float old = ref[b * 32 + frow], now = fmaxf(old, floorf(mx));
+      const int up = (int)fminf(now - old, 1e6f);
+      ref[b * 32 + frow] = now;
+#pragma unroll 1
+      for (int i = 0; i < it; ++i) drop[i * a.mpad + b * 32 + frow] += up;
+    }
+    settle();
+    form(again(b), b, it);
+  };
   const auto sweep = [&](auto terms_t) __attribute__((always_inline)) {
     constexpr bool T = decltype(terms_t)::value;
     if (!T) {
@@ -1090,24 +1156,34 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
           for (int j = 0; j < 16; ++j) lg[j] = acc[b][j] * a.scale_log2;
           mask(lg, b, it, NEG_BIG);
           const float mx = half_fold<0>(lg, lane);
-          if (col < 16) ref[b * 32 + half * 4 + (col >> 2) * 8 + (col & 3)] = mx == NEG_BIG ? 0.f : floorf(mx);
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+          if (col < 16) ref[b * 32 + frow] = mx == NEG_BIG ? 0.f : floorf(mx);
+          settle();
         }
+        form(acc[b], b, it);
+        if (it > 0) {
+          float top = x[it][b][0];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const f32x4_t m = *reinterpret_cast<const f32x4_t*>(ref + b * 32 + half * 4 + c * 8);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[it][b][c * 4 + e] = fast_exp2(fmaf(acc[b][c * 4 + e], a.scale_log2, -m[e]));
+          for (int j = 1; j < 16; ++j) top = fmaxf(top, x[it][b][j]);
+          if (__builtin_expect(__any(!(top <= FAR_TERM)), 0)) move(b, it);
         }
-        mask(x[it][b], b, it, 0.f);
       }
     }
   };
   bool terms = !parked;
   if (terms) {
     sweep(std::true_type{});
+    if (__builtin_expect(moved, 0)) {
+#pragma unroll
+      for (int it = 0; it + 1 < NS; ++it)
+#pragma unroll
+        for (int b = 0; b < NRB; ++b)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const i32x4_t n = *reinterpret_cast<const i32x4_t*>(drop + it * a.mpad + b * 32 + half * 4 + c * 8);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[it][b][c * 4 + e] = ldexpf(x[it][b][c * 4 + e], -n[e]);
+          }
+    }
     // ---- (reference, sum) of every row over this workgroup's keys: lanes, then waves (fixed order)
 #pragma unroll
     for (int b = 0; b < NRB; ++b) {
@@ -1979,7 +2055,7 @@ __global__ __launch_bounds__(256) void score_blocks_sum_kernel(const float* part
 template <int D, int NRB, int NS, int KIND>
 static void launch_fused_kernel(const ScoreArgs& a, dim3 grid, hipStream_t st) {
   constexpr int RS = (KIND == K_F32 ? 2 * D : D) + 8;
-  const size_t lds = ((size_t)a.mpad + 4 * 32) * RS * 2 + ((size_t)4 * a.mpad * 3 + 4 * a.mpad + 512) * sizeof(float);
+  const size_t lds = ((size_t)a.mpad + 4 * 32) * RS * 2 + ((size_t)4 * a.mpad * 3 + 4 * a.mpad + 512 + (size_t)4 * NS * a.mpad) * sizeof(float);
   if (lds > 48 * 1024)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_fused_kernel<D, NRB, NS, KIND>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL((score_fused_kernel<D, NRB, NS, KIND>), grid, dim3(SCORE_THREADS), lds, st, a);

@@ -331,6 +331,70 @@ def test_scores_far_from_a_waves_first_keys(dtype, H, W, d, L, top, base):
     eng.close()
 
 
+def logits_by_chunk(shape, L, chunk, top, base, g):
+    """Logits (log2) for keys in chunks of `chunk`: 0 in the first chunk, then by turns a chunk whose waves' first keys (its first 128) are
+    at -200 and whose others are anywhere up to `top`, and one of ordinary keys.  All of them `base` lower.  top = "steps": chunks whose first
+    keys are at -130, the next up to -35 and the others up to 0, and where those that follow are another 130 higher."""
+    i = torch.arange(L)
+    if top == "steps":
+        most = torch.tensor([0., 95., 130., 130., 260., 260., 260., 260.])[i % chunk // 128]
+        want = torch.rand(*shape, L, generator=g) * most - (260. if chunk > 512 else 130.)
+    else:
+        want = torch.empty(*shape, L).uniform_(-195, top, generator=g)
+        want[..., i % chunk < 128] = -200.
+    ordinary = i // chunk % 2 == 0
+    want[..., ordinary] = torch.empty(*shape, int(ordinary.sum())).uniform_(-20, 0, generator=g)
+    want[..., :chunk] = 0.
+    return want + base
+
+
+@pytest.mark.parametrize("top,base", [(-105, 0), (0, 0), (-105, -300), ("steps", 0)], ids=["far_below", "above", "all_low", "steps"])
+@pytest.mark.parametrize("dtype,H,W,d,L,chunk", [("fp32", 2, 16, 64, 9000, 256), ("fp32", 2, 40, 128, 9000, 256), ("fp32", 1, 40, 64, 17000, 512),
+                                                  ("fp32", 1, 16, 128, 17000, 512), ("bf16", 1, 64, 64, 131072, 768), ("bf16", 1, 20, 128, 70000, 1024),
+                                                  ("bf16", 2, 40, 128, 5000, 768), ("bf16", 3, 32, 64, 6000, 1024)])
+def test_scores_far_from_a_waves_first_keys_by_chunk(dtype, H, W, d, L, chunk, top, base):
+    """As above, for fp32 in the longer chunks (2 and 4 subtiles per wave), where some keys of a wave are not among its first, and for heads
+    of more than 64 chunks, in whose exchange of two levels workgroups of both kinds meet (and, with 171 chunks, the one that
+    only leaves its logits)."""
+    g = torch.Generator().manual_seed(L + W)
+    q, k = 0.25 * torch.randn(1, 1, H, W, d, generator=g), 0.5 * torch.randn(1, 1, H, L, d, generator=g)
+    q[..., 0] = 4.
+    k[0, 0, :, :, 0] = logits_by_chunk((H,), L, chunk, top, base, g) * (d ** 0.5 / (4. * 1.4427))
+    q, k = (t.to(DEV, torch.bfloat16 if dtype == "bf16" else torch.float32) for t in (q, k))
+    mask = torch.randint(0, 2, (1, L), generator=g).to(torch.uint8).to(DEV)
+    eng = MB.MadaKV(n_layers=1, batch=1, n_q_heads=H, n_kv_heads=H, head_dim=d, ctx_len=L, window=W, budget=W + L // 4, dtype=dtype,
+                    pool_k=1, out_fp32=1, device=DEV)
+    say(f"scores by chunk {dtype} H={H} W={W} d={d} L={L} top={top} base={base}")
+    eng.score(0, 1, q, k, mask)
+    torch.cuda.synchronize()
+    for h in range(H):
+        ref = softmax_rows(q[0, 0], k[0, 0], W, h)[0].sum(0)
+        err = (eng.psi[0, 0, h].cpu().double() - ref).abs()
+        assert (err <= 1e-3 * ref + 2.0 ** -125 * W).all(), float((err / ref).max())
+    eng.close()
+
+
+@pytest.mark.parametrize("W,L,chunk", [(32, 16384, 1024), (64, 65536, 768)])
+def test_time_of_scores_does_not_depend_on_where_the_large_ones_are(W, L, chunk):
+    """Keys far above those that their wave sees first: 1.05 times the time of ordinary ones (1.6 and 1.5 with a second pass over them)."""
+    H, us = 32, {}
+    q, mask = torch.randn(1, 1, H, W, 128, device=DEV, dtype=torch.bfloat16), torch.zeros(1, L, dtype=torch.uint8, device=DEV)
+    q[..., 0] = 16.
+    k = torch.randn(1, 1, H, L, 128, device=DEV, dtype=torch.bfloat16)
+    eng = MB.MadaKV(n_layers=1, batch=1, n_q_heads=H, n_kv_heads=H, head_dim=128, ctx_len=L, window=W, budget=2048, device=DEV)
+    for far in (0, 1):
+        k[..., 0] = torch.where(torch.arange(L, device=DEV) % chunk < 128, -200. * far * 128 ** 0.5 / (16. * 1.4427), 0.)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(22)]
+        for e in ev:
+            eng.score(0, 1, q, k, mask)
+            e.record()
+        torch.cuda.synchronize()
+        us[far] = sorted(a.elapsed_time(b) for a, b in zip(ev[1:], ev[2:]))[10] * 1e3
+    eng.close()
+    say(f"scores of {H} heads of {L} keys, {W} rows: {us[0]:.0f} us, large ones far from the first {us[1]:.0f} us")
+    assert us[1] < 1.3 * us[0]
+
+
 @pytest.mark.parametrize("Hq,H,W,d,L,dtype", [(2, 2, 16, 64, 700, "bf16"), (2, 2, 40, 128, 3000, "bf16"), (2, 2, 16, 128, 2100, "bf16"),
                                               (3, 1, 16, 64, 500, "fp32"), (2, 2, 16, 128, 9000, "fp32"), (1, 1, 16, 64, 17000, "fp32")], ids=lambda x: str(x))
 @pytest.mark.parametrize("log2", [11, 20, 23, 24, 26, 30, 40])
@@ -629,6 +693,35 @@ def test_decode_pieces_paged(kw, lens):
         ref = torch.softmax(q.view(H, Hq // H, d)[h].cpu().double() @ k.T / d ** 0.5, -1) @ v
         assert float((outs[0].view(H, Hq // H, d)[h].cpu().double() - ref).abs().max()) < 1e-4          # (the bound of test_decode_pieces)
     flat.close(); paged.close()
+
+
+@pytest.mark.parametrize("top,base", [(-105, 0), (0, 0), (-105, -300), ("steps", 0)], ids=["far_below", "above", "all_low", "steps"])
+@pytest.mark.parametrize("G,W,d,fp8", [(2, 16, 128, 1), (8, 8, 64, 1), (4, 16, 128, 1), (4, 24, 64, 1), (8, 16, 128, 1), (3, 7, 64, 0), (4, 24, 128, 0)])
+def test_reeviction_scores_far_from_a_waves_first_keys(G, W, d, fp8, top, base):
+    """test_scores_far_from_a_waves_first_keys_by_chunk on the ragged rows of a reduced cache, of 8 bits and of 16, with up to 64 proxy rows and with
+    more (blocks of 64).  The reference reads what the cache holds."""
+    lens = [3000, 1100, 200, 40]
+    eng, args = evicted_engine(lens, n_q_heads=4 * G, n_kv_heads=4, head_dim=d, ctx_len=3200, budget=1200, window=W, cache_fp8=fp8)
+    g = torch.Generator().manual_seed(G * W + d)
+    q = 0.25 * torch.randn(1, 1, 4 * G, W, d, generator=g)
+    q[..., 0] = 16.                                    # (so that a key's element is one of 8 bits)
+    q = q.to(torch.bfloat16)
+    off, keys = eng.kv_off.view(-1).tolist(), []
+    for h, n in enumerate(lens):
+        k = 0.5 * torch.randn(n, d, generator=g)
+        k[:, 0] = logits_by_chunk((), n, 1024 if G * W <= 32 else 768, top, base, g) * (d ** 0.5 / (16. * 1.4427))
+        k = k.to(torch.float8_e4m3fn if fp8 else torch.bfloat16)
+        eng.k_c[off[h]:off[h] + n] = (k.view(torch.uint8) if fp8 else k).to(DEV)
+        keys.append(k.double())
+    say(f"re-eviction scores G={G} W={W} d={d} fp8={fp8} top={top} base={base}")
+    eng.reevict(0, 1, q.to(DEV), torch.zeros(1, args["ctx_len"], dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    psi = eng.reevict_ws[:eng.capacity * 4].view(torch.float32).cpu().double()
+    for h, n in enumerate(lens):
+        ref = softmax_rows(q[0, 0, h * G:(h + 1) * G], keys[h][None], W, 0)[0].sum(0)
+        err = (psi[off[h]:off[h] + n] - ref).abs()
+        assert (err <= 1e-3 * ref + 2.0 ** -125 * G * W).all(), (h, float((err / ref).max()))
+    eng.close()
 
 
 @pytest.mark.parametrize("kw", [dict(head_dim=128), dict(head_dim=64, n_q_heads=8), dict(head_dim=128, cache_fp8=1), dict(head_dim=64, page_rows=16)],
