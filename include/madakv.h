@@ -40,8 +40,9 @@
  *     found there leave all outputs untouched.
  *   - The handle belongs to the HIP device that was current in madakv_create; that device must
  *     be current in every later call on it.  It owns device memory: carry state (layer recurrence, cache
- *     cursors), per head of the model up to 516 bytes in which decode's pieces count themselves, the words in which the
- *     scoring kernels exchange row statistics (per head up to about 1 byte per key of the prompt with G * W <= 64, up to 4.3
+ *     cursors), per KV head of the model 128 bytes per query head that it serves and 4 more (at most 1028) in which
+ *     decode's pieces count themselves, the words in which the scoring kernels exchange row statistics
+ *     (per head up to about 1 byte per key of the prompt with G * W <= 64, up to 4.3
  *     beyond, or less than 1 MB in all), up to MADAKV_STATIC_SCRATCH_BYTES for madakv_decode_attn_static, with a paged cache
  *     its page table, and for contexts of four or more 16384-token chunks on at most 128 heads per layer 25 to 72 KB per
  *     chunk of up to 128 heads for the lists and histograms that the per-head statistics and selection kernels share

@@ -154,7 +154,7 @@ def test_where_partial_results_of_decode_go(runtime, cfg):
     heads = cfg.n_layers * cfg.batch * cfg.n_kv_heads
     G = cfg.n_q_heads // cfg.n_kv_heads
     per_key = 1.1 if G * cfg.window <= 64 else 4.4
-    most = (8 << 20) + (1 << 20) + int(heads * (516 + per_key * cfg.ctx_len))
+    most = (8 << 20) + 4096 + heads * (128 * G + 4) + max(1 << 20, int(heads * per_key * cfg.ctx_len))
     if cfg.page_rows:
         most += heads * 4 * (2 + (cfg.ctx_len + cfg.max_new_tokens) // cfg.page_rows)
     scenario(runtime, f"""
