@@ -669,6 +669,10 @@ def test_decode_static_cuts_heads_like_the_workspace_call(kw, lens):
     (dict(n_q_heads=32, n_kv_heads=16, head_dim=64, ctx_len=9000, budget=4300, page_rows=16, cache_fp8=1), [8000, 512, 511, 256, 240, 32, 16] + [40] * 9),
     (dict(n_q_heads=4, n_kv_heads=4, head_dim=128, ctx_len=2000, budget=400, page_rows=32, cache_fp8=1), [256, 255, 512, 33]),
     (dict(n_q_heads=6, n_kv_heads=2, head_dim=128, ctx_len=1500, budget=600, page_rows=16, dtype="fp32"), [512, 271]),
+    # single queries, little to read: pieces of 128 rows in one trip, the last head longer than all of them
+    (dict(n_q_heads=4, n_kv_heads=4, head_dim=128, ctx_len=2000, budget=400, page_rows=16), [128, 127, 256, 1060]),
+    (dict(n_q_heads=4, n_kv_heads=4, head_dim=64, ctx_len=2000, budget=400, page_rows=64, dtype="fp32"), [128, 127, 256, 1060]),
+    (dict(n_q_heads=4, n_kv_heads=4, head_dim=128, ctx_len=2000, budget=400, page_rows=16, dtype="fp32"), [128, 127, 256, 1060]),
 ], ids=lambda x: f"q{x['n_q_heads']}_kv{x['n_kv_heads']}_d{x['head_dim']}_P{x['page_rows']}_{x.get('dtype', 'bf16')}" if isinstance(x, dict) else "")
 def test_decode_pieces_paged(kw, lens):
     """The kernels' paged forms at the edges of pieces, tiles and pages, the appended row being the first of a piece and of a
