@@ -1064,13 +1064,14 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
   // largest logit of the wave's first subtile (a whole number, so that nothing is rounded but the difference).  The
   // terms are formed under the loads of the keys that follow; behind the last subtile the row sums are additions and the column
   // sums products with one factor per row and wave.
-  // A subtile with a term beyond FAR_TERM gives its block's rows their largest logit so far as a reference; by how much the terms before it
-  // are too large, an exponent, goes to LDS and into them behind the last subtile.  (A second sweep over the workgroup's keys with the logits
+  // A subtile with a term beyond FAR_TERM gives the rows their largest logit so far as a reference; by how much the terms before it are
+  // too large, an exponent, goes to LDS and into them behind the last subtile.  (A second sweep over the workgroup's keys with the logits
   // instead, which all workgroups of the head wait for, is what such keys had cost: queries four times as long as those of the workloads put a
   // wave's first keys that far below others in 20 to 60% of the workgroups.  Us per call with logits in registers / with that second sweep / now: 128
-  // heads of 16K keys, 32 rows, all workgroups 128 / 210 / 127, 32 of 128K, 64 rows, all 354 / 530 / 362, 64 fp32 heads of 4K, long queries 37.0 / 41.7 /
-  // 36.6.  The check itself costs nothing, 64 dims even gain by it, 60 -> 56 (112 heads of 8K, 40 rows).  The scaling in the branch, one check of
-  // both blocks, or contractions in full there spilled 40 to 190 registers in the ordinary path of two blocks of 128 dims: 341 -> 356-400 us.)
+  // heads of 16K keys, 32 rows, all workgroups 128 / 210 / 125, 32 of 128K, 64 rows, all 354 / 530 / 360, 64 fp32 heads of 4K, long queries 37.0 / 41.7 /
+  // 36.7.  The check costs nothing that runs do not differ by, 64 dims gain, 60 -> 57 (112 heads of 8K, 40 rows); one per block instead costs two
+  // blocks of 128 dims 2-3%.  The scaling in the branch itself, the logits of both blocks before the terms of either, or unrolled
+  // contractions there spilled 40 to 190 registers in the ordinary path of two blocks of 128 dims: 341 -> 356-400 us.)
   // In a workgroup in which a row's terms or reference pass their limits (above), and in the parked chunks: the logits themselves,
   // and all row maxima and two exp2 per logit between the last key and the scores.
   float x[NS][NRB][16];
@@ -1142,6 +1143,7 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
       if (it + PF < NS) MADAKV_FUSED_LOAD(it % PF, it + PF)
       f32x16_t acc[NRB];
       contract(acc);
+      uint32_t top = 0u;
 #pragma unroll
       for (int b = 0; b < NRB; ++b) {
         if (!T) {
@@ -1160,11 +1162,13 @@ __global__ __launch_bounds__(SCORE_THREADS) __attribute__((amdgpu_waves_per_eu(K
           settle();
         }
         form(acc[b], b, it);
-        if (it > 0) {
-          float top = x[it][b][0];
+        if (it > 0) {                             // (no term is negative: the largest has the largest bits)
 #pragma unroll
-          for (int j = 1; j < 16; ++j) top = fmaxf(top, x[it][b][j]);
-          if (__builtin_expect(__any(!(top <= FAR_TERM)), 0)) move(b, it);
+          for (int j = 0; j < 16; ++j) top = max(top, __float_as_uint(x[it][b][j]));
+          if (b == NRB - 1 && __builtin_expect(__any(top > __float_as_uint(FAR_TERM)), 0)) {
+#pragma unroll
+            for (int o = 0; o < NRB; ++o) move(o, it);
+          }
         }
       }
     }
